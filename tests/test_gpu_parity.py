@@ -390,6 +390,19 @@ def test_groupnorm_matches_oracle(B, Bn, T, C):
     assert rel_err(ref, ref_s) > 10 * BF16_TOL          # the activation is visible at this tolerance
 
 
+# slabs of whole rows: more rows than threads, several slabs a workgroup, a last one that is partly empty; channel counts that
+# are no multiple of 8 (2-channel accesses); more groups than threads of a row; the largest row
+@pytest.mark.parametrize("Bn,T,C,groups", [(1, 1, 64, 32), (3, 27, 320, 32), (1, 5000, 320, 32), (2, 1537, 960, 32), (1, 300, 36, 3), (2, 130, 100, 50),
+                                           (1, 40, 2048, 1024), (1, 2100, 2046, 33)])
+def test_groupnorm_slabs_match_oracle(B, Bn, T, C, groups):
+    r = rng(T + C + groups)
+    x = G.bf16_round((r.standard_normal((Bn, T, C)) * 1.5 + r.standard_normal((Bn, 1, C)) * 2).astype(np.float32))
+    g = G.bf16_round((1 + 0.1 * r.standard_normal(C)).astype(np.float32))
+    b = G.bf16_round((0.1 * r.standard_normal(C)).astype(np.float32))
+    y = B.groupnorm_fwd(dev(x, B), dev(g, B), dev(b, B), groups=groups)
+    assert rel_err(host(y), O.groupnorm(x, g, b, groups=groups)) <= BF16_TOL
+
+
 # ------------------------------------------------------------ spatial_transformer_fwd
 def run_stack(B, cfg, seed=0):
     p = G.make_stack_inputs(cfg, seed)
