@@ -29,10 +29,10 @@ __device__ __forceinline__ void nt_store4(float* p, float4 v) {
 // These kernels stream: what limits them is how well HBM copes with the mix of requests in
 // flight, and past a point more wavefronts per CU make that worse (more streams interleaved per
 // channel).  The copies back therefore ask for dynamic LDS that no kernel touches, only to cap
-// the workgroups per CU (160 KB of LDS per CU) at six: +5 % on the 310-matrix sweep.  The patch
-// pass is capped by its registers at four workgroups per CU, which is where it runs best (a cap
-// of three cost 4 % once the undo record went out first; two cost 15 %).
-constexpr int UNPATCH_THROTTLE_LDS = 24 * 1024;
+// the workgroups per CU (160 KB of LDS per CU) at four, sixteen wavefronts: a sweep's copy back and
+// next patch take 2690 us together, 2735 with three or six workgroups, 2755 with eight.  The patch passes are held to eight wavefronts per CU by registers and LDS,
+// which is where they run best.
+constexpr int UNPATCH_THROTTLE_LDS = 40 * 1024;
 
 struct PatchPlanEntry {
     sd_patch_desc d;       // 48 bytes
@@ -43,8 +43,6 @@ struct PatchPlanEntry {
 static_assert(sizeof(sd_patch_desc) == 48, "descriptor layout");
 static_assert(sizeof(PatchPlanEntry) == 64, "plan entry layout");
 
-// workgroup tile: PT_WAVES wavefronts side by side, 32 rows x 128 columns each (two waves
-// per workgroup measured ~4 % faster than four or one on the 310-matrix sweep)
 struct PatchMultiEntry {
     sd_patch_multi_desc d;
     int64_t tile_begin;
@@ -53,11 +51,13 @@ struct PatchMultiEntry {
 };
 static_assert(sizeof(PatchMultiEntry) % 8 == 0, "plan entry layout");
 
-constexpr int PT_WAVES = 2;
-constexpr int PT_ROWS = 32, PT_COLS = 128 * PT_WAVES;
-constexpr int PT_THREADS = 64 * PT_WAVES;
+// workgroup tile: 2 x 2 wavefronts of 32 rows x 128 columns each
+constexpr int PT_WR = 2, PT_WC = 2;
+constexpr int PT_ROWS = 32 * PT_WR, PT_COLS = 128 * PT_WC;
+constexpr int PT_THREADS = 64 * PT_WR * PT_WC;
 
-__device__ __forceinline__ int find_entry(const PatchPlanEntry* __restrict__ plan, int n, int64_t tile) {
+template <typename Entry>
+__device__ __forceinline__ int find_entry(const Entry* __restrict__ plan, int n, int64_t tile) {
     int lo = 0, hi = n - 1;   // last entry with tile_begin <= tile
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -66,332 +66,168 @@ __device__ __forceinline__ int find_entry(const PatchPlanEntry* __restrict__ pla
     return lo;
 }
 
-// k pairs per batch of fragment loads in the rank-32 path.  Measured on the 310-matrix sweep:
-// 8 beats 16 (all fragments up front) by 1 % with one adapter and by 10 % with two, and beats 4
-// and 2; requesting a batch while the batch before it multiplies (double registers) lost.
-constexpr int FRAG_KP = 8;
-// acc[j][v] += sum_k B[row(v)][k] * A[k][col + j] for one adapter on a full tile (all 32 rows
-// and 128 columns inside the matrix, in % 4 == 0): lane l32 supplies B row r0 + l32 and the
-// four A columns col..col+3, k pair (2 kp + hi) per MFMA.
-__device__ __forceinline__ void delta_full(const float* __restrict__ A, const float* __restrict__ B, int r, int in, int r0,
-                                           int col, int l32, int hi, f32x16 (&acc)[4]) {
-    const float* bp = B + (size_t)(r0 + l32) * r + hi;
-    const float* ap = A + (size_t)hi * in + col;
-    const int kp_n = r >> 1;
-    if (r == 32) {
-        // the common rank: the A and B fragments (they come out of L2) are requested in two
-        // batches of FRAG_KP k pairs, 32 MFMAs behind each
-#pragma unroll 1
-        for (int k0 = 0; k0 < 16; k0 += FRAG_KP) {
-            float bv[FRAG_KP];
-            float4 av[FRAG_KP];
-#pragma unroll
-            for (int kp = 0; kp < FRAG_KP; ++kp) bv[kp] = bp[2 * (k0 + kp)];
-#pragma unroll
-            for (int kp = 0; kp < FRAG_KP; ++kp) av[kp] = *reinterpret_cast<const float4*>(ap + (size_t)(2 * (k0 + kp)) * in);
-#pragma unroll
-            for (int kp = 0; kp < FRAG_KP; ++kp) {
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[kp], av[kp].x, acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[kp], av[kp].y, acc[1], 0, 0, 0);
-                acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[kp], av[kp].z, acc[2], 0, 0, 0);
-                acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[kp], av[kp].w, acc[3], 0, 0, 0);
-            }
-        }
-    } else {
-#pragma unroll 4
-        for (int kp = 0; kp < kp_n; ++kp) {
-            const float bv = bp[2 * kp];
-            const float4 av = *reinterpret_cast<const float4*>(ap + (size_t)(2 * kp) * in);
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av.x, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av.y, acc[1], 0, 0, 0);
-            acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av.z, acc[2], 0, 0, 0);
-            acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av.w, acc[3], 0, 0, 0);
-        }
-    }
-    if (r & 1) {   // odd rank: last k pairs with a zero
-        const int kk = r - 1;
-        const float bv = hi ? 0.f : B[(size_t)(r0 + l32) * r + kk];
-        float4 av = {0.f, 0.f, 0.f, 0.f};
-        if (!hi) av = *reinterpret_cast<const float4*>(A + (size_t)kk * in + col);
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av.x, acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av.y, acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av.z, acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av.w, acc[3], 0, 0, 0);
-    }
+// ---------------------------------------------------------------------------------------
+// The product's operands come through LDS.  A wavefront that fetches its own A and B fragments
+// from L2 pays a round trip per batch of them, on top of the matrix-core time that it issues in
+// order; with ranks of 16 and 64 on one matrix those trips were two thirds of the pass.  Here the
+// workgroup's A columns and B rows of PT_RC ranks at a time go straight from global memory into a
+// ring of LDS stages, all but one of them requested before the W tile itself, shared by the
+// workgroup's wavefronts, and refilled while the chunks in between multiply: any rank that is
+// a multiple of 4 runs without a round trip between its first and its last MFMA.
+//
+// Measured on the 310-matrix sweep (830 M elements), before and after, and the floor at the 6.0 TB/s
+// that the copy back reaches: one adapter of rank 32 1739 -> 1715 us (1680), of rank 64 2514 -> 2020,
+// of rank 128 4274 -> 2607; two of rank 32 with the bf16 copy 2492 -> 2045 (1980).  60 matrices of
+// 1280 x 1280 under ranks 16 and 64: 356 -> 300 us (230).
+// One adapter: three stages and two workgroups per CU; a third one costs ranks up to 32 4 % (more
+// streams per HBM channel) though it gains rank 64 10 %.  Several: two stages, which leaves room for
+// the third workgroup, 5 to 9 % faster at the matrix-core time of two adapters.
+// ---------------------------------------------------------------------------------------
+constexpr int PT_RC = 16;
+constexpr int PT_A_CHUNKS = PT_RC * PT_COLS / 4;    // 16-byte chunks of a stage: A rows [rank][PT_COLS] ...
+constexpr int PT_B_CHUNKS = PT_ROWS * PT_RC / 4;    // ... then B rows [row][PT_RC], chunks of a row XOR-swizzled
+constexpr int PT_STAGE_CHUNKS = PT_A_CHUNKS + PT_B_CHUNKS;
+constexpr int PT_NW = PT_WR * PT_WC;
+constexpr int PT_LOADS = PT_STAGE_CHUNKS / 64 / PT_NW;   // direct-to-LDS loads of a wavefront per stage
+static_assert(PT_RC == 16 && PT_COLS == 256 && PT_STAGE_CHUNKS % (64 * PT_NW) == 0 && PT_A_CHUNKS % (64 * PT_NW) == 0, "stage layout");
+
+// where lanes point whose chunk lies past the rank or the matrix
+__device__ __attribute__((aligned(256))) uint32_t g_patch_zeros[64];
+
+// one direct global -> LDS load: each lane fetches 16 bytes, the 64 pieces land contiguously at LDS
+// byte address lds_base (wave-uniform); completion is tracked with vmcnt and a barrier
+__device__ __forceinline__ void patch_dma16(const void* gptr, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory", "m0");
+}
+template <int N>
+__device__ __forceinline__ void patch_wait_vmcnt() {
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// the same product on a ragged tile: every access guarded and scalar
-__device__ __forceinline__ void delta_ragged(const float* __restrict__ A, const float* __restrict__ B, int r, int out, int in,
-                                             int r0, int col, int l32, int hi, f32x16 (&acc)[4]) {
-    const int brow = r0 + l32;
-    const int kp_n = (r + 1) >> 1;
-#pragma unroll 1
-    for (int kp = 0; kp < kp_n; ++kp) {
-        const int kk = 2 * kp + hi;
-        const bool kv = kk < r;
-        const float bv = (kv && brow < out) ? B[(size_t)brow * r + kk] : 0.f;
-        float av[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) av[j] = (kv && col + j < in) ? A[(size_t)kk * in + col + j] : 0.f;
-        acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av[0], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av[1], acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av[2], acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av[3], acc[3], 0, 0, 0);
-    }
-}
+// one matrix's adapters, in application order
+struct PatchAdapters {
+    const float* const* A;
+    const float* const* B;
+    const int32_t* r;
+    const float* scale;
+    int n;
+};
 
-__global__ __launch_bounds__(PT_THREADS, 2) void lora_patch_kernel(const PatchPlanEntry* __restrict__ plan, int n) {
-    const int64_t tile = blockIdx.x;
-    const PatchPlanEntry& E = plan[find_entry(plan, n, tile)];
-    const int out = E.d.out, in = E.d.in, r = E.d.r;
-    const float scale = E.d.scale;
-    float* __restrict__ W = E.d.W;
-    float* __restrict__ U = E.d.undo;
-    const float* __restrict__ A = E.d.A;
-    const float* __restrict__ B = E.d.B;
-    const int local = (int)(tile - E.tile_begin);
-    const int tc = local % E.tiles_c, tr = local / E.tiles_c;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// A workgroup tile under the adapters of its matrix: W_i = fl32(W_{i-1} + fl32(scale_i * (B_i A_i))),
+// undo <- W_0, W <- W_n, serving <- bf16(W_n).  For in and every rank multiples of 4 (a lane's four
+// columns are inside the matrix or outside together).  Wavefronts and lanes outside the matrix load
+// and multiply with the others and store nothing.
+// Lane l of a wavefront holds columns c0 + 4 * (l % 32) + {0..3} of 16 rows; with the 32x32x2 MFMA
+// the upper half-wavefront supplies ranks 4 .. 7 of every 8, the lower half ranks 0 .. 3, so that one
+// 16-byte LDS read holds a lane's B values of 8 ranks.
+template <int PT_STAGES>
+__device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restrict__ Und, uint16_t* __restrict__ S, int out, int in,
+                                           const PatchAdapters& ad, int tr, int tc, u32x4* const lds) {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
-    const int r0 = tr * PT_ROWS;
-    const int c0 = tc * PT_COLS + wave * 128;
-    if (c0 >= in) return;
+    const int row_wg = tr * PT_ROWS, col_wg = tc * PT_COLS;
+    const int r0 = row_wg + (wave / PT_WC) * 32, c0 = col_wg + (wave % PT_WC) * 128;
     const int col = c0 + 4 * l32;
-    const bool full = (r0 + 32 <= out) && (c0 + 128 <= in) && ((in & 3) == 0);
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds + wave * 1024;
+
+    // ---- operand chunks: (adapter, first rank), walked by the loads a few ahead of the MFMAs
+    int ia = 0, ik = 0;            // next chunk to request
+    auto issue = [&](int slot) {
+        const int r = ad.r[ia];
+        const float* const A = ad.A[ia];
+        const float* const B = ad.B[ia];
+        const uint32_t dst = lds_base + slot * (PT_STAGE_CHUNKS * 16);
+#pragma unroll
+        for (int j = 0; j < PT_LOADS; ++j) {
+            const void* src;
+            if (j < PT_A_CHUNKS / 64 / PT_NW) {          // one rank's 256 columns
+                const int k = ik + j * PT_NW + wave;
+                const int c = col_wg + lane * 4;
+                src = (k < r && c < in) ? (const void*)(A + (size_t)k * in + c) : (const void*)g_patch_zeros;
+            } else {                                     // 16 rows of B
+                const int row = ((j - PT_A_CHUNKS / 64 / PT_NW) * PT_NW + wave) * 16 + (lane >> 2);
+                const int k = ik + (((lane & 3) ^ ((row >> 2) & 3)) << 2);
+                src = (k < r && row_wg + row < out) ? (const void*)(B + (size_t)(row_wg + row) * r + k) : (const void*)g_patch_zeros;
+            }
+            patch_dma16(src, dst + j * (PT_NW * 1024));
+        }
+        ik += PT_RC;
+        if (ik >= r) { ik = 0; ++ia; }
+    };
+    int total = 0;                 // chunks in all
+    for (int a = 0; a < ad.n; ++a) total += (ad.r[a] + PT_RC - 1) / PT_RC;
+#pragma unroll
+    for (int s = 0; s < PT_STAGES - 1; ++s)
+        if (s < total) issue(s);
+
+    // ---- W, undo and serving addresses: the row of register v lies 8 * (v / 4) + v % 4 rows below
+    // the lane's first, a wave-uniform distance; one 32-bit byte offset per lane serves all arrays
+    // (the caller checked that the matrix has fewer than 2^30 elements)
+    const uint32_t woff = (uint32_t)(((size_t)(r0 + 4 * hi) * in + col) * 4);
+    auto row_of = [&](int v) { return 8 * (v >> 2) + (v & 3); };
+    auto row_bytes = [&](int v) -> size_t { return (size_t)row_of(v) * in * 4; };
+    const bool full = r0 + 32 <= out && c0 + 128 <= in;     // uniform: no lane of this wavefront is outside
+    const bool col_in = col < in;
+    float4 w[16];
+    if (full) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) w[v] = NT_LOAD4(reinterpret_cast<const float*>(reinterpret_cast<const char*>(W) + row_bytes(v) + woff));
+        // W's old bits go out first, as one burst of stores, before any adapter's product
+#pragma unroll
+        for (int v = 0; v < 16; ++v) NT_STORE4(reinterpret_cast<float*>(reinterpret_cast<char*>(Und) + row_bytes(v) + woff), w[v]);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            w[v] = float4{0.f, 0.f, 0.f, 0.f};
+            if (col_in && r0 + 4 * hi + row_of(v) < out) w[v] = NT_LOAD4(reinterpret_cast<const float*>(reinterpret_cast<const char*>(W) + row_bytes(v) + woff));
+        }
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (col_in && r0 + 4 * hi + row_of(v) < out) NT_STORE4(reinterpret_cast<float*>(reinterpret_cast<char*>(Und) + row_bytes(v) + woff), w[v]);
+        patch_wait_vmcnt<0>();
+    }
+    // From here on this wavefront's loads of the first PT_STAGES - 1 chunks have landed: they are older
+    // than the W tile, whose values the undo stores have just taken, and loads retire in order.
 
     f32x16 acc[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-
-    if (full) {
-        float4 w[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-            w[v] = NT_LOAD4(W + (size_t)row * in + col);
+    int ma = 0, mk = 0, slot = 0;  // adapter and first rank of the chunk being multiplied, its ring slot
+    const int brow = (wave / PT_WC) * 32 + l32;
+#pragma unroll 1
+    for (int c = 0; c < total; ++c) {
+        static_assert(PT_STAGES == 2 || PT_STAGES == 3, "at most one chunk is in flight behind the one waited for");
+        if (c >= PT_STAGES - 1) {
+            if (PT_STAGES == 3 && c + 1 < total) patch_wait_vmcnt<(PT_STAGES - 2) * PT_LOADS>();
+            else patch_wait_vmcnt<0>();
         }
-        // the undo record needs nothing but W: it goes out as one burst of stores before the
-        // rank-r product, whose MFMAs then run under those stores (a little faster than with the
-        // undo and result stores interleaved afterwards)
+        __syncthreads();           // every wavefront's part of the chunk is in LDS, and the slot before it is free
+        if (c + PT_STAGES - 1 < total) issue(slot == 0 ? PT_STAGES - 1 : slot - 1);
+        const u32x4* const la = lds + slot * PT_STAGE_CHUNKS;
+        const u32x4* const lb = la + PT_A_CHUNKS;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-            NT_STORE4(U + (size_t)row * in + col, w[v]);
-        }
-        delta_full(A, B, r, in, r0, col, l32, hi, acc);
+        for (int u = 0; u < PT_RC / 8; ++u) {
+            const float4 bv = __builtin_bit_cast(float4, lb[brow * 4 + ((2 * u + hi) ^ ((brow >> 2) & 3))]);
+            float4 av[4];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-            const size_t idx = (size_t)row * in + col;
-            float4 o;
-            o.x = __fadd_rn(w[v].x, __fmul_rn(scale, acc[0][v]));
-            o.y = __fadd_rn(w[v].y, __fmul_rn(scale, acc[1][v]));
-            o.z = __fadd_rn(w[v].z, __fmul_rn(scale, acc[2][v]));
-            o.w = __fadd_rn(w[v].w, __fmul_rn(scale, acc[3][v]));
-            NT_STORE4(W + idx, o);
-        }
-    } else {
-        // ragged tile: same arithmetic, every access guarded and scalar
-        delta_ragged(A, B, r, out, in, r0, col, l32, hi, acc);
+            for (int kp = 0; kp < 4; ++kp) av[kp] = __builtin_bit_cast(float4, la[(8 * u + 4 * hi + kp) * (PT_COLS / 4) + (wave % PT_WC) * 32 + l32]);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-            if (row >= out) continue;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (col + j >= in) continue;
-                const size_t idx = (size_t)row * in + col + j;
-                const float wv = W[idx];
-                U[idx] = wv;
-                W[idx] = __fadd_rn(wv, __fmul_rn(scale, acc[j][v]));
+            for (int kp = 0; kp < 4; ++kp) {
+                const float b = reinterpret_cast<const float*>(&bv)[kp];
+                acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, av[kp].x, acc[0], 0, 0, 0);
+                acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, av[kp].y, acc[1], 0, 0, 0);
+                acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, av[kp].z, acc[2], 0, 0, 0);
+                acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(b, av[kp].w, acc[3], 0, 0, 0);
             }
+            __builtin_amdgcn_sched_barrier(0);
         }
-    }
-}
-
-__device__ __forceinline__ int find_entry_multi(const PatchMultiEntry* __restrict__ plan, int n, int64_t tile) {
-    int lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (plan[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
-    }
-    return lo;
-}
-
-// Several adapters on one matrix in one pass over W (one or two LoRAs per request is the norm,
-// Section 3.1; each is merged as in Section 4.2): the tile's W values stay in registers while
-// the adapters are applied one after the other, W_i = fl32(W_{i-1} + fl32(scale_i * (B_i A_i))),
-// so the result equals successive single patches bit for bit at one third of their traffic for
-// two adapters.  Optionally also writes the bf16 copy of W' that the bf16 GEMMs read.
-//
-// CB: 32-column MFMA blocks per wavefront, interleaved so that lane l holds CB adjacent columns
-// (c0 + CB * (l % 32) + {0 .. CB-1}) of 16 rows.  A workgroup covers 32 rows x 256 columns with
-// 8 / CB wavefronts.  The second adapter doubles the matrix-core time of a tile (64 fp32 MFMAs of
-// 64 clocks per adapter and 32 x 128 elements) while its traffic stays the same, and a wavefront
-// that multiplies has nothing in flight.  CB = 2 keeps a tile in half the registers (W 32,
-// accumulators 32), so four wavefronts fit a SIMD instead of two: measured 15 % slower on the
-// 310-matrix sweep (8-byte accesses, more streams per channel), so CB = 4 is what is launched; what
-// did help is the pipelined path below.
-template <int CB>
-struct PatchVec;
-template <>
-struct PatchVec<4> { typedef float4 type; };
-template <>
-struct PatchVec<2> { typedef float2 type; };
-template <int CB>
-__device__ __forceinline__ float& pv_at(typename PatchVec<CB>::type& v, int j) { return reinterpret_cast<float*>(&v)[j]; }
-
-template <int CB>
-__device__ __forceinline__ typename PatchVec<CB>::type nt_loadv(const float* p) {
-    typedef float nt_vec __attribute__((ext_vector_type(CB)));
-    nt_vec t = __builtin_nontemporal_load(reinterpret_cast<const nt_vec*>(p));
-    typename PatchVec<CB>::type r;
-#pragma unroll
-    for (int j = 0; j < CB; ++j) reinterpret_cast<float*>(&r)[j] = t[j];
-    return r;
-}
-template <int CB>
-__device__ __forceinline__ void nt_storev(float* p, const typename PatchVec<CB>::type& v) {
-    typedef float nt_vec __attribute__((ext_vector_type(CB)));
-    nt_vec t;
-#pragma unroll
-    for (int j = 0; j < CB; ++j) t[j] = reinterpret_cast<const float*>(&v)[j];
-    __builtin_nontemporal_store(t, reinterpret_cast<nt_vec*>(p));
-}
-
-// delta_full for CB column blocks: acc[j][v] += sum_k B[row(v)][k] * A[k][col + j]
-template <int CB>
-__device__ __forceinline__ void delta_full_cb(const float* __restrict__ A, const float* __restrict__ B, int r, int in, int r0,
-                                              int col, int l32, int hi, f32x16 (&acc)[CB]) {
-    typedef typename PatchVec<CB>::type vec;
-    const float* bp = B + (size_t)(r0 + l32) * r + hi;
-    const float* ap = A + (size_t)hi * in + col;
-    const int kp_n = r >> 1;
-    int kp0 = 0;
-    // batches of FRAG_KP k pairs: fragments requested together, their MFMAs behind them
-#pragma unroll 1
-    for (; kp0 + FRAG_KP <= kp_n; kp0 += FRAG_KP) {
-        float bv[FRAG_KP];
-        vec av[FRAG_KP];
-#pragma unroll
-        for (int kp = 0; kp < FRAG_KP; ++kp) bv[kp] = bp[2 * (kp0 + kp)];
-#pragma unroll
-        for (int kp = 0; kp < FRAG_KP; ++kp) av[kp] = *reinterpret_cast<const vec*>(ap + (size_t)(2 * (kp0 + kp)) * in);
-#pragma unroll
-        for (int kp = 0; kp < FRAG_KP; ++kp)
-#pragma unroll
-            for (int j = 0; j < CB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv[kp], pv_at<CB>(av[kp], j), acc[j], 0, 0, 0);
-    }
-#pragma unroll 1
-    for (; kp0 < kp_n; ++kp0) {
-        const float bv = bp[2 * kp0];
-        vec av = *reinterpret_cast<const vec*>(ap + (size_t)(2 * kp0) * in);
-#pragma unroll
-        for (int j = 0; j < CB; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, pv_at<CB>(av, j), acc[j], 0, 0, 0);
-    }
-    if (r & 1) {   // odd rank: last k with a zero partner
-        const int kk = r - 1;
-        const float bv = hi ? 0.f : B[(size_t)(r0 + l32) * r + kk];
-#pragma unroll
-        for (int j = 0; j < CB; ++j) {
-            const float a = hi ? 0.f : A[(size_t)kk * in + col + j];
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, a, acc[j], 0, 0, 0);
-        }
-    }
-}
-
-template <int CB>
-__device__ __forceinline__ void delta_ragged_cb(const float* __restrict__ A, const float* __restrict__ B, int r, int out, int in,
-                                                int r0, int col, int l32, int hi, f32x16 (&acc)[CB]) {
-    const int brow = r0 + l32;
-    const int kp_n = (r + 1) >> 1;
-#pragma unroll 1
-    for (int kp = 0; kp < kp_n; ++kp) {
-        const int kk = 2 * kp + hi;
-        const bool kv = kk < r;
-        const float bv = (kv && brow < out) ? B[(size_t)brow * r + kk] : 0.f;
-#pragma unroll
-        for (int j = 0; j < CB; ++j) {
-            const float a = (kv && col + j < in) ? A[(size_t)kk * in + col + j] : 0.f;
-            acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, a, acc[j], 0, 0, 0);
-        }
-    }
-}
-
-// A full tile under NA adapters of rank 32, the common case, as one straight line.  What a
-// wavefront spends per tile is a chain of round trips: with the fragments of a batch requested
-// only after the MFMAs of the batch before have been issued (a wavefront issues its 32x32x2 fp32
-// MFMAs one per 64 clocks, in order), every batch pays an L2 round trip on top of its matrix
-// time, and a second adapter adds all of its own.  Here the k pairs form units of PIPE_KP, the
-// fragments of unit u + PIPE_DEPTH are requested before the MFMAs of unit u, across adapter
-// boundaries, and the first units are requested ahead of the W tile itself.  Same MFMAs in the
-// same order on the same operands as the plain loop: same bits.
-// (measured on the 310-matrix sweep with two adapters: 2.77 ms with the plain loop, 2.55 ms with
-// units of 4 k pairs two units ahead; three units ahead spills and loses; where W's undo stores
-// sit among the first units makes no difference)
-constexpr int PIPE_KP = 4, PIPE_DEPTH = 2;
-template <int NA>
-__device__ __forceinline__ void patch_tile_rank32(const PatchMultiEntry& E, int in, int r0, int col, int l32, int hi) {
-    constexpr int UPA = 16 / PIPE_KP;            // units per adapter
-    constexpr int U = NA * UPA, SLOTS = PIPE_DEPTH + 1;
-    float* __restrict__ W = E.d.W;
-    float* __restrict__ Und = E.d.undo;
-    uint16_t* __restrict__ S = E.d.serving;
-    float bvb[SLOTS][PIPE_KP];
-    float4 avb[SLOTS][PIPE_KP];
-    // addresses as a wave-uniform base (adapter, k pair: scalar arithmetic) plus one 32-bit byte
-    // offset per lane for all of B's fragments and one for all of A's
-    const uint32_t boff = (uint32_t)(((r0 + l32) * 32 + hi) * 4);
-    const uint32_t aoff = (uint32_t)(((size_t)hi * in + col) * 4);
-    auto issue = [&](int u, int slot) {
-        const int a = u / UPA, k0 = (u % UPA) * PIPE_KP;
-        const char* bbase = reinterpret_cast<const char*>(E.d.B[a]);
-        const char* abase = reinterpret_cast<const char*>(E.d.A[a]);
-#pragma unroll
-        for (int kp = 0; kp < PIPE_KP; ++kp) bvb[slot][kp] = *reinterpret_cast<const float*>(bbase + 8 * (k0 + kp) + boff);
-#pragma unroll
-        for (int kp = 0; kp < PIPE_KP; ++kp)
-            avb[slot][kp] = *reinterpret_cast<const float4*>(abase + (size_t)(2 * (k0 + kp)) * in * 4 + aoff);
-    };
-#pragma unroll
-    for (int u = 0; u < PIPE_DEPTH && u < U; ++u) issue(u, u);
-    // W, undo and serving addresses likewise: the row of register v lies d(v) = 8 * (v / 4) + v % 4
-    // rows below the lane's first, a wave-uniform distance; one 32-bit byte offset per lane serves
-    // all three arrays (the caller checked that the matrix has fewer than 2^30 elements)
-    const uint32_t woff = (uint32_t)(((size_t)(r0 + 4 * hi) * in + col) * 4);
-    auto row_bytes = [&](int v) -> size_t { return (size_t)(8 * (v >> 2) + (v & 3)) * in * 4; };
-    float4 w[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) w[v] = NT_LOAD4(reinterpret_cast<const float*>(reinterpret_cast<const char*>(W) + row_bytes(v) + woff));
-    // W's old bits go out first, as one burst of stores, before any adapter's product
-#pragma unroll
-    for (int v = 0; v < 16; ++v) NT_STORE4(reinterpret_cast<float*>(reinterpret_cast<char*>(Und) + row_bytes(v) + woff), w[v]);
-    f32x16 acc[4];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        if (u % UPA == 0) {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-        }
-        // (the scheduler is kept from hoisting every unit's requests to the top, which would need
-        // registers for all of them at once)
-        __builtin_amdgcn_sched_barrier(0);
-        if (u + PIPE_DEPTH < U) issue(u + PIPE_DEPTH, (u + PIPE_DEPTH) % SLOTS);
-        __builtin_amdgcn_sched_barrier(0);
-        const int slot = u % SLOTS;
-#pragma unroll
-        for (int kp = 0; kp < PIPE_KP; ++kp) {
-            acc[0] = __builtin_amdgcn_mfma_f32_32x32x2f32(bvb[slot][kp], avb[slot][kp].x, acc[0], 0, 0, 0);
-            acc[1] = __builtin_amdgcn_mfma_f32_32x32x2f32(bvb[slot][kp], avb[slot][kp].y, acc[1], 0, 0, 0);
-            acc[2] = __builtin_amdgcn_mfma_f32_32x32x2f32(bvb[slot][kp], avb[slot][kp].z, acc[2], 0, 0, 0);
-            acc[3] = __builtin_amdgcn_mfma_f32_32x32x2f32(bvb[slot][kp], avb[slot][kp].w, acc[3], 0, 0, 0);
-        }
-        if (u % UPA == UPA - 1) {
-            const float scale = E.d.scale[u / UPA];
+        slot = slot + 1 == PT_STAGES ? 0 : slot + 1;
+        mk += PT_RC;
+        if (mk >= ad.r[ma]) {      // the adapter's last chunk
+            const float scale = ad.scale[ma];
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 w[v].x = __fadd_rn(w[v].x, __fmul_rn(scale, acc[0][v]));
@@ -399,133 +235,125 @@ __device__ __forceinline__ void patch_tile_rank32(const PatchMultiEntry& E, int 
                 w[v].z = __fadd_rn(w[v].z, __fmul_rn(scale, acc[2][v]));
                 w[v].w = __fadd_rn(w[v].w, __fmul_rn(scale, acc[3][v]));
             }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+            mk = 0;
+            ++ma;
         }
     }
-    // (the offset is laundered so that the sixteen row addresses are formed again here instead of
-    // being carried, or spilled, through the adapters' products)
+    // (the offset is laundered so that the row addresses are formed again here instead of being
+    // carried, or spilled, through the adapters' products)
     uint32_t woff2 = woff;
     asm volatile("" : "+v"(woff2));
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        NT_STORE4(reinterpret_cast<float*>(reinterpret_cast<char*>(W) + row_bytes(v) + woff2), w[v]);
-        if (S) {
-            bf16x4 o = {(__bf16)w[v].x, (__bf16)w[v].y, (__bf16)w[v].z, (__bf16)w[v].w};
-            *reinterpret_cast<bf16x4*>(reinterpret_cast<char*>(S) + row_bytes(v) / 2 + woff2 / 2) = o;
+        if (full || (col_in && r0 + 4 * hi + row_of(v) < out)) {
+            NT_STORE4(reinterpret_cast<float*>(reinterpret_cast<char*>(W) + row_bytes(v) + woff2), w[v]);
+            if (S) {
+                bf16x4 o = {(__bf16)w[v].x, (__bf16)w[v].y, (__bf16)w[v].z, (__bf16)w[v].w};
+                *reinterpret_cast<bf16x4*>(reinterpret_cast<char*>(S) + row_bytes(v) / 2 + woff2 / 2) = o;
+            }
         }
     }
 }
 
-template <int CB>
-__global__ __launch_bounds__(64 * 8 / CB, CB == 2 ? 4 : 2) void lora_patch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
-    typedef typename PatchVec<CB>::type vec;
-    const int64_t tile = blockIdx.x;
-    const PatchMultiEntry& E = plan[find_entry_multi(plan, n, tile)];
-    const int out = E.d.out, in = E.d.in, na = E.d.n_adapters;
-    float* __restrict__ W = E.d.W;
-    float* __restrict__ U = E.d.undo;
-    uint16_t* __restrict__ S = E.d.serving;
-    const int local = (int)(tile - E.tile_begin);
-    const int tc = local % E.tiles_c, tr = local / E.tiles_c;
+// The same for any in and rank (and matrices of 2^30 elements or more): every access guarded, one
+// element at a time.
+__device__ __forceinline__ void patch_tile_any(float* __restrict__ W, float* __restrict__ Und, uint16_t* __restrict__ S, int out, int in,
+                                               const PatchAdapters& ad, int tr, int tc) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, hi = lane >> 5;
-    const int r0 = tr * PT_ROWS;
-    const int c0 = tc * PT_COLS + wave * (32 * CB);
-    if (c0 >= in) return;
-    const int col = c0 + CB * l32;
-    const bool full = (r0 + 32 <= out) && (c0 + 32 * CB <= in) && ((in & 3) == 0);
-    if constexpr (CB == 4) {
-        bool all32 = full && (int64_t)out * in < (int64_t(1) << 30);
+    const int r0 = tr * PT_ROWS + (wave / PT_WC) * 32;
+    const int col = tc * PT_COLS + (wave % PT_WC) * 128 + 4 * l32;
+    float w[16][4];
 #pragma unroll
-        for (int a = 0; a < SD_PATCH_MAX_ADAPTERS; ++a) all32 = all32 && (a >= na || E.d.r[a] == 32);
-        // (one or two adapters, the production norm; with three or four the straight line would
-        // need more registers than two wavefronts per SIMD leave, and the plain loop below serves)
-        if (all32 && na == 1) { patch_tile_rank32<1>(E, in, r0, col, l32, hi); return; }
-        if (all32 && na == 2) { patch_tile_rank32<2>(E, in, r0, col, l32, hi); return; }
-    }
-    f32x16 acc[CB];
-    if (full) {
-        vec w[16];
+    for (int v = 0; v < 16; ++v) {
+        const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-            w[v] = nt_loadv<CB>(W + (size_t)row * in + col);
-        }
-        // W's old bits go out first, as one burst of stores, before any adapter's product
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-            nt_storev<CB>(U + (size_t)row * in + col, w[v]);
-        }
-#pragma unroll 1
-        for (int a = 0; a < na; ++a) {
-#pragma unroll
-            for (int j = 0; j < CB; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-            delta_full_cb<CB>(E.d.A[a], E.d.B[a], E.d.r[a], in, r0, col, l32, hi, acc);
-            const float scale = E.d.scale[a];
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-#pragma unroll
-                for (int j = 0; j < CB; ++j) pv_at<CB>(w[v], j) = __fadd_rn(pv_at<CB>(w[v], j), __fmul_rn(scale, acc[j][v]));
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-            const size_t idx = (size_t)row * in + col;
-            nt_storev<CB>(W + idx, w[v]);
-            if (S) {
-                typedef __bf16 bvec __attribute__((ext_vector_type(CB)));
-                bvec o;
-#pragma unroll
-                for (int j = 0; j < CB; ++j) o[j] = (__bf16)pv_at<CB>(w[v], j);
-                *reinterpret_cast<bvec*>(S + idx) = o;
-            }
-        }
-    } else {
-        float wv[16][CB];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-#pragma unroll
-            for (int j = 0; j < CB; ++j) {
-                const bool ok = row < out && col + j < in;
-                wv[v][j] = ok ? W[(size_t)row * in + col + j] : 0.f;
-                if (ok) U[(size_t)row * in + col + j] = wv[v][j];
-            }
-        }
-#pragma unroll 1
-        for (int a = 0; a < na; ++a) {
-#pragma unroll
-            for (int j = 0; j < CB; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
-            delta_ragged_cb<CB>(E.d.A[a], E.d.B[a], E.d.r[a], out, in, r0, col, l32, hi, acc);
-            const float scale = E.d.scale[a];
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-#pragma unroll
-                for (int j = 0; j < CB; ++j) wv[v][j] = __fadd_rn(wv[v][j], __fmul_rn(scale, acc[j][v]));
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
-            if (row >= out) continue;
-#pragma unroll
-            for (int j = 0; j < CB; ++j) {
-                if (col + j >= in) continue;
-                const size_t idx = (size_t)row * in + col + j;
-                W[idx] = wv[v][j];
-                if (S) S[idx] = __builtin_bit_cast(uint16_t, (__bf16)wv[v][j]);
-            }
+        for (int j = 0; j < 4; ++j) {
+            const bool ok = row < out && col + j < in;
+            w[v][j] = ok ? W[(size_t)row * in + col + j] : 0.f;
+            if (ok) Und[(size_t)row * in + col + j] = w[v][j];
         }
     }
+    const int brow = r0 + l32;
+#pragma unroll 1
+    for (int a = 0; a < ad.n; ++a) {
+        f32x16 acc[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
+        const float* const A = ad.A[a];
+        const float* const B = ad.B[a];
+        const int r = ad.r[a];
+#pragma unroll 1
+        for (int kp = 0; kp < 4 * ((r + 7) >> 3); ++kp) {
+            const int kk = (kp >> 2) * 8 + 4 * hi + (kp & 3);   // same pairs of ranks as above: same bits
+            const bool kv = kk < r;
+            const float bv = (kv && brow < out) ? B[(size_t)brow * r + kk] : 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const float av = (kv && col + j < in) ? A[(size_t)kk * in + col + j] : 0.f;
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av, acc[j], 0, 0, 0);
+            }
+        }
+        const float scale = ad.scale[a];
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) w[v][j] = __fadd_rn(w[v][j], __fmul_rn(scale, acc[j][v]));
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (row >= out || col + j >= in) continue;
+            const size_t idx = (size_t)row * in + col + j;
+            W[idx] = w[v][j];
+            if (S) S[idx] = __builtin_bit_cast(uint16_t, (__bf16)w[v][j]);
+        }
+    }
+}
+
+template <int PT_STAGES>
+__device__ __forceinline__ void patch_matrix_tile(float* W, float* Und, uint16_t* S, int out, int in, const PatchAdapters& ad, int local, int tiles_c,
+                                                  u32x4* const lds) {
+    const int tc = local % tiles_c, tr = local / tiles_c;
+    bool quads = (in & 3) == 0 && (int64_t)out * in < (int64_t(1) << 30);
+    for (int a = 0; a < ad.n; ++a) quads = quads && (ad.r[a] & 3) == 0;
+    if (quads) patch_tile<PT_STAGES>(W, Und, S, out, in, ad, tr, tc, lds);
+    else patch_tile_any(W, Und, S, out, in, ad, tr, tc);
+}
+
+__global__ __launch_bounds__(PT_THREADS, 2) void lora_patch_kernel(const PatchPlanEntry* __restrict__ plan, int n) {
+    __shared__ u32x4 lds[3 * PT_STAGE_CHUNKS];
+    const int64_t tile = blockIdx.x;
+    const PatchPlanEntry& E = plan[find_entry(plan, n, tile)];
+    const PatchAdapters ad = {&E.d.A, &E.d.B, &E.d.r, &E.d.scale, 1};
+    patch_matrix_tile<3>(E.d.W, E.d.undo, nullptr, E.d.out, E.d.in, ad, (int)(tile - E.tile_begin), E.tiles_c, lds);
+}
+
+// Several adapters on one matrix in one pass over W (one or two LoRAs per request is the norm,
+// Section 3.1; each is merged as in Section 4.2): the tile's W values stay in registers while
+// the adapters are applied one after the other, so the result equals successive single patches bit
+// for bit at one third of their traffic for two adapters.  Optionally also writes the bf16 copy of
+// W' that the bf16 GEMMs read.
+__global__ __launch_bounds__(PT_THREADS, 3) void lora_patch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
+    __shared__ u32x4 lds[2 * PT_STAGE_CHUNKS];
+    const int64_t tile = blockIdx.x;
+    const PatchMultiEntry& E = plan[find_entry(plan, n, tile)];
+    const PatchAdapters ad = {E.d.A, E.d.B, E.d.r, E.d.scale, E.d.n_adapters};
+    patch_matrix_tile<2>(E.d.W, E.d.undo, E.d.serving, E.d.out, E.d.in, ad, (int)(tile - E.tile_begin), E.tiles_c, lds);
 }
 
 // W <- undo (flat linear copy), and the serving copy follows it: bf16(undo)
 __global__ __launch_bounds__(PT_THREADS) void lora_unpatch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
     const int64_t tile = blockIdx.x;
-    const PatchMultiEntry& E = plan[find_entry_multi(plan, n, tile)];
+    const PatchMultiEntry& E = plan[find_entry(plan, n, tile)];
     float* __restrict__ W = E.d.W;
     const float* __restrict__ U = E.d.undo;
     uint16_t* __restrict__ S = E.d.serving;
@@ -670,9 +498,8 @@ static int patch_multi_launch(bool undo, const void* plan_dev, int32_t n, int64_
     SD_REQUIRE(total_tiles < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch: %lld tiles exceed one grid", (long long)total_tiles);
     const PatchMultiEntry* plan = static_cast<const PatchMultiEntry*>(plan_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    // (the multi-adapter patch kernel is held to fewer waves by its registers already)
     if (undo) hipLaunchKernelGGL(lora_unpatch_multi_kernel, dim3((unsigned)total_tiles), dim3(PT_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
-    else hipLaunchKernelGGL((lora_patch_multi_kernel<4>), dim3((unsigned)total_tiles), dim3(PT_THREADS), 0, s, plan, n);
+    else hipLaunchKernelGGL(lora_patch_multi_kernel, dim3((unsigned)total_tiles), dim3(PT_THREADS), 0, s, plan, n);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }

@@ -501,6 +501,30 @@ def test_patch_small_ragged_and_roundtrip(B):
     assert sub.tobytes() != mats[3]["W"].tobytes()
 
 
+# one, two, three and more chunks of 16 ranks, chunks that are partly past the rank; tiles of 64 x 256 with rows, columns or
+# whole wavefronts outside the matrix
+@pytest.mark.parametrize("out,in_", [(64, 256), (65, 260), (31, 132), (128, 508)])
+@pytest.mark.parametrize("ranks", [(4,), (12,), (16,), (20,), (36,), (64,), (128,), (4, 52), (64, 16), (48, 8, 32)])
+def test_patch_rank_chunks(B, out, in_, ranks):
+    import torch
+    r = rng(out + in_ + sum(ranks))
+    W = (0.02 * r.standard_normal((out, in_))).astype(np.float32)
+    ads = [((0.02 * r.standard_normal((rk, in_))).astype(np.float32), (0.02 * r.standard_normal((out, rk))).astype(np.float32), sc)
+           for rk, sc in zip(ranks, (1.0, 0.5, -2.0))]
+    ref = O.lora_patch_multi(W, ads)[0]
+    d = [(torch.from_numpy(A).cuda(), torch.from_numpy(Bm).cuda(), sc) for A, Bm, sc in ads]
+    Wm, Ws = torch.from_numpy(W).cuda(), torch.from_numpy(W).cuda()
+    undo = torch.empty_like(Wm)
+    plan = B.PatchMultiPlan([(Wm, undo, torch.empty(Wm.shape, dtype=torch.bfloat16, device="cuda"), d)])
+    B.lora_patch_multi(plan)
+    for A, Bm, sc in d:
+        B.lora_patch(B.PatchPlan([(Ws, A, Bm, torch.empty_like(Ws), sc)]))
+    assert rel_err(Wm.cpu().numpy(), ref) <= PATCH_TOL
+    assert torch.equal(Wm, Ws) and undo.cpu().numpy().tobytes() == W.tobytes()
+    B.lora_unpatch_multi(plan)
+    assert Wm.cpu().numpy().tobytes() == W.tobytes()
+
+
 def test_patch_exact_integers(B):
     r = rng(9)
     W = r.integers(-8, 9, (256, 384)).astype(np.float32)
