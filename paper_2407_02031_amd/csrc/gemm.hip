@@ -14,8 +14,13 @@
 // Pipeline: operand tiles go global -> LDS directly (wave-wide 1 KB loads of 16-byte
 // chunks, XOR-swizzled so the 32 rows one MFMA operand read touches fall in distinct
 // banks) into a ring of STAGES tiles, STAGES-1 of them in flight ahead of the one being
-// multiplied; inside a tile the operand fragments of k-step kk+1 are read from LDS while
-// the MFMAs of k-step kk run.  The epilogue stages 32-row x 64-column pieces of a wave's
+// multiplied; the operand fragments of k-step kk+1 are read from LDS while the MFMAs of k-step
+// kk run, across the edge of two tiles too, and a tile's loads are dealt between the MFMAs of a
+// step.  What bounds it: the L2 -> LDS operand stream, 100-125 GB/s per CU with all of them at it
+// (a stream alone: 145 with few CUs), then the MFMAs, whose rate under load is 1.6 PFLOP/s; the
+// two overlap only as far as no wavefront waits to issue a load.  8192x4096x4096, 128x128 tiles,
+// eight wavefronts, three loads a burst after each barrier 271 us, dealt 248; 2048x1280x5120 + 64
+// at one 128x128 tile per CU 51 and 41.  The epilogue stages 32-row x 64-column pieces of a wave's
 // accumulators through LDS so that global stores (and residual loads) are 16-byte rows.
 #include "common.hpp"
 
@@ -125,10 +130,9 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
     constexpr int LPT = NBLK / NW;             // direct-to-LDS loads per wave (= per lane) per tile
     constexpr int STAGE = (BM + BN) * CPR;     // 16-byte chunks per stage
     static_assert(BK == 64 || BK == 32, "BK");
-    constexpr int DIST = STAGES - 1;           // tiles in flight ahead of the one being multiplied
     static_assert(NBLK % NW == 0, "tile/waves mismatch");
     static_assert(!GEGLU || (NI % 2 == 0), "GEGLU needs value/gate column-block pairs per wave");
-    static_assert(DIST >= 1 && DIST <= 4, "ring depth");
+    static_assert(STAGES >= 2 && STAGES <= 5, "ring depth");
 
     // ---- which tile of the problem ----
     const int local = tile - P.tile_begin;
@@ -267,75 +271,109 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
 
-    // one BK-deep tile out of ring stage `st`; fragments of k-step kk+1 are fetched while
-    // the MFMAs of k-step kk execute
-    auto compute = [&](int st) {
+    // operand fragments of two k-steps: the one being multiplied and the next, which is read
+    // from LDS meanwhile, also across the edge between two tiles (KK is even: the first k-step
+    // of every tile uses set 0)
+    bf16x8 af[2][MI], bfr[2][NI];
+    auto fetch = [&](int st, int kk, int fs) {
         const u32x4* la = lds + st * STAGE;
         const u32x4* lb = la + BM * CPR;
-        bf16x8 af[2][MI], bfr[2][NI];
-        auto fetch = [&](int kk, int fs) {
 #pragma unroll
-            for (int mi = 0; mi < MI; ++mi) {
-                const int r = wm + mi * 32 + l32;
-                af[fs][mi] = __builtin_bit_cast(bf16x8, la[r * CPR + swz<CPR>(r, kk * 2 + hi)]);
-            }
+        for (int mi = 0; mi < MI; ++mi) {
+            const int r = wm + mi * 32 + l32;
+            af[fs][mi] = __builtin_bit_cast(bf16x8, la[r * CPR + swz<CPR>(r, kk * 2 + hi)]);
+        }
 #pragma unroll
-            for (int ni = 0; ni < NI; ++ni) {
-                const int r = wn + ni * 32 + l32;
-                bfr[fs][ni] = __builtin_bit_cast(bf16x8, lb[r * CPR + swz<CPR>(r, kk * 2 + hi)]);
-            }
-        };
-        fetch(0, 0);
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-            if (kk + 1 < KK) fetch(kk + 1, (kk + 1) & 1);
-            // keep the reads of k-step kk+1 ahead of the MFMAs of k-step kk: left alone, the
-            // scheduler sinks them to just before their use and exposes the LDS latency
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int mi = 0; mi < MI; ++mi)
-#pragma unroll
-                for (int ni = 0; ni < NI; ++ni)
-                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk & 1][mi], bfr[kk & 1][ni], acc[mi][ni], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
+        for (int ni = 0; ni < NI; ++ni) {
+            const int r = wn + ni * 32 + l32;
+            bfr[fs][ni] = __builtin_bit_cast(bf16x8, lb[r * CPR + swz<CPR>(r, kk * 2 + hi)]);
         }
     };
-
-    // ---- prologue: the first DIST tiles in flight
+    // MFMAs of one k-step out of fragment set `fs`, with loads [j0, j1) of a tile dealt between them
+    // (`load(j)` issues one): a wavefront issues in order, and a burst of loads would hold up its
+    // MFMAs until the address unit has taken the last one, at 16 clocks apiece for the whole CU
+    auto multiply = [&](int fs, auto load, int j0, int j1) {
+        // keep the reads of the next k-step ahead of the MFMAs of this one: left alone, the
+        // scheduler sinks them to just before their use and exposes the LDS latency
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int d = 0; d < DIST; ++d)
+        for (int i = 0; i < MI * NI; ++i) {
+            const int mi = i / NI, ni = i % NI;
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[fs][mi], bfr[fs][ni], acc[mi][ni], 0, 0, 0);
+            const int a = j0 + (j1 - j0) * i / (MI * NI), b = j0 + (j1 - j0) * (i + 1) / (MI * NI);
+            if (a < b) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int j = a; j < b; ++j) load(j);
+            if (a < b) __builtin_amdgcn_sched_barrier(0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto no_load = [](int) {};
+
+    // ---- prologue: the first STAGES tiles in flight, the first fragments of tile 0 read
+#pragma unroll
+    for (int d = 0; d < STAGES; ++d)
         if (d < nkt) issue_tile(d, d);
     if (!dep_ready) dep_ready = __all(f_early >= P.wait_need);
-
-    // ---- main loop.  Step t: wait until this wave's loads of tile t have landed (loads of
-    // newer tiles may stay in flight), barrier (every wave's part of tile t is in LDS and
-    // every wave is done reading the stage of tile t-1), refill that stage with tile t+DIST,
-    // multiply tile t.  The steady-state loop has no conditionals; the last DIST steps run
-    // in a second loop with the shrinking wait counts.
-    int st = 0;                         // stage of tile t
-    int sf = DIST;                      // stage to refill (= stage of tile t-1)
-    int t = 0;
-#pragma unroll 1
-    for (; t + DIST < nkt; ++t) {
-        wait_vmcnt<(DIST - 1) * LPT>();
-        __syncthreads();
-        issue_tile(t + DIST, sf);
-        compute(st);
-        sf = st;
-        st = st + 1 == STAGES ? 0 : st + 1;
+    auto wait_tiles = [&](int newer) {   // `newer` tiles (at most STAGES - 1) may stay in flight
+        if (STAGES >= 5 && newer >= 4) wait_vmcnt<4 * LPT>();
+        else if (STAGES >= 4 && newer >= 3) wait_vmcnt<3 * LPT>();
+        else if (STAGES >= 3 && newer >= 2) wait_vmcnt<2 * LPT>();
+        else if (newer >= 1) wait_vmcnt<LPT>();
+        else wait_vmcnt<0>();
+    };
+    wait_tiles(nkt - 1 < STAGES - 1 ? nkt - 1 : STAGES - 1);
+    __syncthreads();
+    fetch(0, 0, 0);
+#pragma unroll
+    for (int kk = 0; kk + 1 < KK; ++kk) {
+        fetch(0, kk + 1, (kk + 1) & 1);
+        multiply(kk & 1, no_load, 0, 0);
     }
+
+    // ---- main loop.  A step starts at the edge between tile t and tile t+1, before the MFMAs of
+    // tile t's last k-step: its fragments are in registers, so once this wave's loads of tile t+1
+    // have landed (newer ones may stay in flight) one barrier says both that tile t+1 is whole and
+    // that the stage of tile t is free.  That stage is refilled with tile t+STAGES, its loads dealt
+    // over the step, while the last k-step of tile t and all but the last of tile t+1 are multiplied.
+    int st = 0;                         // stage of tile t
+    int t = 0;
+    const int nfull = GUARD ? K0 / BK : nk0;   // whole tiles of K segment 0
+#pragma unroll 1
+    for (; t + STAGES < nfull; ++t) {
+        wait_vmcnt<(STAGES - 2) * LPT>();
+        __syncthreads();
+        const int sn = st + 1 == STAGES ? 0 : st + 1;
+        const uint16_t* const pb = pb0 + (t + STAGES) * BK;
+        const uint16_t* const qb = qb0 + (t + STAGES) * BK;
+        const uint32_t sbase = wave_base + (uint32_t)st * (STAGE * 16);
+        auto load = [&](int j) { dma16_so<false>(j < JP ? pb : qb, off0[j], sbase + (uint32_t)j * (NW * 1024)); };
+        fetch(sn, 0, 0);
+        multiply(1, load, 0, LPT / KK);
+#pragma unroll
+        for (int kk = 0; kk + 1 < KK; ++kk) {
+            fetch(sn, kk + 1, (kk + 1) & 1);
+            multiply(kk & 1, load, (kk + 1) * LPT / KK, (kk + 2) * LPT / KK);
+        }
+        st = sn;
+    }
+    // the same for the tiles around and behind the end of segment 0, and for the last ones, which
+    // have nothing left to load and shrinking wait counts
 #pragma unroll 1
     for (; t + 1 < nkt; ++t) {
-        const int newer = nkt - 1 - t;  // tiles issued after tile t
-        if (DIST >= 4 && newer >= 3) wait_vmcnt<3 * LPT>();
-        else if (DIST >= 3 && newer >= 2) wait_vmcnt<2 * LPT>();
-        else wait_vmcnt<LPT>();
+        wait_tiles(nkt - 2 - t < STAGES - 2 ? nkt - 2 - t : STAGES - 2);
         __syncthreads();
-        compute(st);
-        st = st + 1 == STAGES ? 0 : st + 1;
+        const int sn = st + 1 == STAGES ? 0 : st + 1;
+        fetch(sn, 0, 0);
+        if (t + STAGES < nkt) issue_tile(t + STAGES, st);
+        multiply(1, no_load, 0, 0);
+#pragma unroll
+        for (int kk = 0; kk + 1 < KK; ++kk) {
+            fetch(sn, kk + 1, (kk + 1) & 1);
+            multiply(kk & 1, no_load, 0, 0);
+        }
+        st = sn;
     }
-    wait_vmcnt<0>();
-    __syncthreads();
 
     // ---- epilogue geometry.  Accumulator layout of the 32x32 MFMA: lane holds column l32 and
     // rows 8*(v/4) + 4*hi + (v%4), v = 0..15.  Each wave stages a 32-row x CCOLS-column piece at
@@ -387,7 +425,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
             if (GEGLU) bg_raw[nj] = bias[q + P.geglu_F];
         }
     }
-    compute(st);
+    multiply(1, no_load, 0, 0);
     __syncthreads();   // ring reads done before the epilogue reuses LDS
 
     // ---- epilogue
@@ -631,7 +669,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, (gemm_min_waves<BM, BN, BK, WGM, WG
     for (int i = blockIdx.x * (64 * NW) + threadIdx.x; i < zero_n; i += (int)grid * (64 * NW)) zero_ptr[i] = 0;
     if constexpr (BN > DOWN_BN) {
         if (P.signal) {
-            gemm_tile<BM, DOWN_BN, BK, WGM, WGN, down_stages<BM, BN, BK, STAGES>(), false, GUARD, false>(P, tile, lds);
+            gemm_tile<BM, DOWN_BN, BK, WGM * WGN / 2, 2, down_stages<BM, BN, BK, STAGES>(), false, GUARD, false>(P, tile, lds);
             return;
         }
     }
@@ -668,10 +706,9 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     bool geglu = false;   // a GEGLU group: GEGLU problems plus, possibly, the plain down-projections they wait for
     for (int i = 0; i < g.n; ++i) geglu = geglu || g.p[i].geglu_F > 0;
     bool guard = false;
-    int maxN = 0, maxK = 0;
-    long t128 = 0;        // workgroup tiles at 128x128
-    long t256 = 0;        // workgroup tiles of 256 rows x 128 output columns
-    long t64 = 0;         // workgroup tiles of 64 rows x 128 columns, down-projections aside
+    int maxN = 0;
+    double depth = 0;     // K, summed over those tiles
+    long t128 = 0, t256 = 0;   // workgroup tiles of 128 and 256 rows x 128 output columns, down-projections aside
     bool res32 = false;   // some problem adds an fp32 residual: take the kernel that prefetches it
     int n_main = 0;       // problems that are not down-projections
     for (int i = 0; i < g.n; ++i) {
@@ -698,10 +735,9 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
         if (P.Mp == 0 || P.N == 0) continue;
         if ((P.K0 & 63) || (P.K1 & 63)) guard = true;
         if (P.N > maxN) maxN = P.N;
-        if (P.K0 > maxK) maxK = P.K0;
-        t128 += (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
+        if (!P.signal) t128 += (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
         if (!P.signal) t256 += (long)((P.Mp + 255) / 256) * ((P.N + 127) / 128);
-        if (!P.signal) t64 += (long)((P.Mp + 63) / 64) * ((P.N + 127) / 128);
+        if (!P.signal) depth += (double)((P.Mp + 127) / 128) * ((P.N + 127) / 128) * P.K0;
     }
     // drop empty problems
     int w = 0;
@@ -709,43 +745,56 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
         if (g.p[i].Mp > 0 && g.p[i].N > 0) { if (w != i) g.p[w] = g.p[i]; ++w; }
     g.n = w;
     if (w == 0) return SD_OK;
-    // Tile choice, from timing whole transformer-block steps with each variant on one machine.
-    // What pays is wavefronts in flight per CU, not operand reuse: these GEMMs wait on the
-    // L2 -> LDS operand stream and on their own prologues and epilogues, and 256x128, 128x160
-    // (one exact round) and 3-stage variants all lost.  Launches of fewer than 1024 tiles at
-    // 128x128 (everything in the block except the feed-forward in-projection) run 64x128 tiles,
-    // 4 waves, 48 KB of LDS, three workgroups per CU; larger ones run 128x128 tiles with 8 waves
-    // of 32x64, two workgroups per CU.  Down-projections (N = rank <= 64): 64x64 tiles, 5-stage
-    // ring.
-    // (a GEGLU group never takes this one: its tiles need the value / gate pairing, which the
-    // 64x128 body below provides for any F)
+    // Tile choice.  What a tile costs per 64 deep step is its operand bytes (a CU takes in 100-125 GB/s
+    // from L2 whatever the ring depth) or its MFMAs, whichever is longer, and the launch takes as long
+    // as its most loaded CU; so: the largest tiles that still give every CU the same number of them.
+    // Times below are single projections of rank 64, us, measured on one machine.
+    const double meanK = t128 ? depth / t128 : 0;
+    // Down-projections (N = rank <= 64) alone: 64x64 tiles, 5-stage ring.  (A GEGLU group never takes
+    // this one: its tiles need the value / gate pairing, which the bodies below provide for any F.)
     if (maxN <= 64 && !geglu) return launch_cfg<64, 64, 64, 2, 2, 5, false, false>(g, guard, stream);
-    // ... except long-K launches (the feed-forward out-projection, K = 4C) that still give every CU
-    // a 128x128 tile: over 40 k-steps the operand bytes per FLOP decide, not the ramps
-    if (t128 < 1024 && !(maxK >= 2048 && t128 >= 256)) {
-        // at most two workgroups per CU anyway (2048 tokens): a third ring stage in the LDS the
-        // third workgroup would have used, -3 to -10 % per launch
-        if (t64 <= 512) {
+    if (t128 < 512) {
+        // at most one 128x128 tile per CU, and most CUs have one: that tile with a deep ring, one
+        // workgroup per CU (2048x1280x5120: 42.0, 53.7 with 64x128 tiles, of which 64 CUs get two)
+        if (t128 > 128 && t128 <= 256) {
+            if (geglu) return launch_cfg<128, 128, 64, 4, 2, 4, true, false>(g, guard, stream);
+            if (res32) return launch_cfg<128, 128, 64, 4, 2, 4, false, true>(g, guard, stream);
+            return launch_cfg<128, 128, 64, 4, 2, 4, false, false>(g, guard, stream);
+        }
+        // more than that, but at most one of 256x128 per CU, and no short K loop: those
+        // (8192x640x2560: 41.1, 48.2 with 128x128 tiles; 4757x1280x1280: 26.4, 33.1 with 64x128;
+        // at K = 640 the ramps of the larger tile lose: 24.1 against 21.0)
+        if (!geglu && t128 > 256 && t256 <= 256 && meanK >= 1024) {
+            if (res32) return launch_cfg<256, 128, 64, 4, 2, 3, false, true>(g, guard, stream);
+            return launch_cfg<256, 128, 64, 4, 2, 3, false, false>(g, guard, stream);
+        }
+        // few tiles: 64x128 spreads them over more CUs, two workgroups on a CU at most: three ring stages
+        if (t128 <= 128) {
             if (geglu) return launch_cfg<64, 128, 64, 2, 2, 3, true, false>(g, guard, stream);
             if (res32) return launch_cfg<64, 128, 64, 2, 2, 3, false, true>(g, guard, stream);
             return launch_cfg<64, 128, 64, 2, 2, 3, false, false>(g, guard, stream);
         }
-        if (geglu) return launch_cfg<64, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
-        if (res32) return launch_cfg<64, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
-        return launch_cfg<64, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
+        // up to three on a CU where the K loop is short or 128x128 tiles would leave most CUs with one
+        // and some with two (8192x640x640: 17.3, 18.3 with 128x128; 988x10240x1280 GEGLU: 35.7, 39.2)
+        if (t128 > 256 && (meanK < 1024 || t128 <= 384)) {
+            if (geglu) return launch_cfg<64, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
+            if (res32) return launch_cfg<64, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
+            return launch_cfg<64, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
+        }
     }
     // The feed-forward in-projection at 8192 tokens: 256x256 tiles (128 output columns after GEGLU)
     // of eight 64x128 wavefronts, one workgroup per CU, when that still gives every CU two rounds
-    // or more.  Half the operand bytes per FLOP from L2 and from LDS; measured 5 % faster per launch
-    // than 128x128 in spite of the last, partly empty round (640 tiles on 256 CUs).
+    // or more.  Half the operand bytes per FLOP from L2 and from LDS.
     if (geglu && t256 >= 512) return launch_cfg<256, 256, 64, 4, 2, 2, true, false>(g, guard, stream);
     // One large plain projection with a long K loop (no launch of the transformer block: the
-    // 8192 x 4096 x 4096 yardstick runs at 1.18 PFLOP/s this way, 1.04 at 128x128).  Not for grouped
+    // 8192 x 4096 x 4096 yardstick takes 224, 248 at 128x128).  Not for grouped
     // launches: the q/k/v group with its short text-context problems loses a third.
-    if (!geglu && !res32 && n_main == 1 && t256 >= 512 && maxK >= 2048) return launch_cfg<256, 256, 64, 4, 2, 2, false, false>(g, guard, stream);
-    if (geglu) return launch_cfg<128, 128, 64, 4, 2, 2, true, false>(g, guard, stream);
-    if (res32) return launch_cfg<128, 128, 64, 4, 2, 2, false, true>(g, guard, stream);
-    return launch_cfg<128, 128, 64, 4, 2, 2, false, false>(g, guard, stream);
+    if (!geglu && !res32 && n_main == 1 && t256 >= 512 && meanK >= 2048) return launch_cfg<256, 256, 64, 4, 2, 2, false, false>(g, guard, stream);
+    // 128x128 tiles of four 64x64 wavefronts, two workgroups per CU (2048x10240x1280 GEGLU: 66.9, 75.3
+    // with 64x128, 68.3 with eight 32x64 wavefronts; 4757x1280x1280: 25.9, 33.1, 26.9)
+    if (geglu) return launch_cfg<128, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
+    if (res32) return launch_cfg<128, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
+    return launch_cfg<128, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
 }
 
 __global__ void clear_flags_kernel(int32_t* p, int n) {
