@@ -188,6 +188,44 @@ static int run_projections(const ProjCall* calls, int n, hipStream_t stream, int
     int rc;
     auto problems_of = [](const ProjCall& c) { return c.M <= 0 ? 0 : (c.p->r > 0 ? 2 : 1); };
     auto flags_of = [](const ProjCall& c) { return (c.M > 0 && c.p->r > 0) ? ((size_t)c.M + 63) / 64 : (size_t)0; };
+    // adapters inside the tiles, where that kernel takes the whole group
+    int live = 0;
+    bool in_tile = true;
+    for (int i = 0; i < n; ++i) {
+        if (calls[i].M <= 0) continue;
+        ++live;
+        in_tile = in_tile && !calls[i].o.transposed && live <= GEMM_MAX_PROBLEMS;
+    }
+    if (in_tile && live) {
+        for (int i = 0; i < n; ++i)
+            if (calls[i].M > 0) {
+                if ((rc = push_main(g, stream, calls[i]))) return rc;
+                GemmProblem& P = g.p[g.n - 1];
+                P.p1 = calls[i].p->A;
+                P.ldp1 = calls[i].K;
+                P.t_scale = calls[i].p->scale;
+            }
+        const bool flags_clean = dep && dep->f[0] && !dep->pending;
+        if (gemm16_takes(g, flags_clean)) {
+            timing_mark(tag, 0, stream);
+            rc = launch_gemm16(g, flags_clean, stream);
+            timing_mark(tag, 1, stream);
+            return rc;
+        }
+        memset(&g, 0, sizeof(g));
+    }
+    if (n == 1 && calls[0].M > 0 && calls[0].o.geglu_F > 0) {
+        if ((rc = push_main(g, stream, calls[0]))) return rc;
+        if (gemm_geglu_takes(g.p[0])) {
+            timing_mark(tag, 0, stream);
+            const ProjCall& c = calls[0];
+            if (c.p->r > 0 && (rc = launch_down(c.x, c.ldx, c.p->A, c.p->scale, c.tbuf, c.M, c.K, c.p->r, stream))) return rc;
+            rc = launch_gemm_geglu(g, stream);
+            timing_mark(tag, 1, stream);
+            return rc;
+        }
+        memset(&g, 0, sizeof(g));
+    }
     bool fuse = g_fuse_projections && dep && dep->f[0];
     if (fuse) {
         bool any_down = false;

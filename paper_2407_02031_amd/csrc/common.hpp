@@ -133,6 +133,10 @@ struct GemmProblem {
     const int32_t* wait;
     int32_t wait_need;                         // filled by the launcher
     int32_t wait_cols;
+    // The in-tile form of an adapter (launch_gemm16): p1 is A [K1, K0], q1 is B, and the tile forms
+    // t = t_scale * x A^T by itself.
+    float t_scale;
+    int32_t unused;
 };
 
 constexpr int GEMM_MAX_PROBLEMS = 16;
@@ -149,6 +153,15 @@ struct GemmGroup {
 // Launch every problem of `g` in one grid.  Problems must all be GEGLU or all plain; signalling
 // problems come first and every problem that waits on one is in the same group.
 int launch_gemm_group(GemmGroup& g, hipStream_t stream);
+// The same for groups that gemm16_takes: plain projections with the adapter in the tile.
+// flags_clean: cleared dependency flags are at hand for the general kernel.
+bool gemm16_takes(const GemmGroup& g, bool flags_clean);
+int launch_gemm16(GemmGroup& g, bool flags_clean, hipStream_t stream);
+// t = scale * x A^T (x [M, K], A [r, K], t bf16 [M, r]) by itself, in the time of a short launch; K % 64 == 0
+int launch_down(const uint16_t* x, int64_t ldx, const uint16_t* A, float scale, uint16_t* t, int M, int K, int r, hipStream_t stream);
+// One GEGLU projection that gemm_geglu_takes; its down-projection, if any, has been computed.
+bool gemm_geglu_takes(const GemmProblem& P);
+int launch_gemm_geglu(GemmGroup& g, hipStream_t stream);
 // n zeros at p (the flags of the first dependent launch of a call)
 int launch_clear_flags(int32_t* p, int n, hipStream_t stream);
 // number of tiles, since the library was loaded, that gave up waiting for a flag (0 unless the

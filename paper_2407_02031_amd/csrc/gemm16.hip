@@ -1,0 +1,437 @@
+// Projections whose tiles cover the chip in whole rounds: bf16 MFMA GEMM with 16-granular tiles
+// and the adapter's down-projection computed inside the tile.
+//
+// What bounds it: at the block's sizes one projection is one or two tiles per CU, so its time is
+// that of the most loaded CU: launch, first loads, the K loop at the rate a CU takes operands in
+// from L2 (100-125 GB/s) or multiplies them, and the stores.  Tiles of 128x160, 64x160 and 64x80 give
+// all 256 CUs the same work where powers of two do not (8192x640 and 2048x1280 are 256 tiles of
+// 128x160 and 64x160).
+//
+// A tile's wavefronts split its K as well as its rows and columns (WGK groups each multiply every
+// WGK-th 32 deep k-step of a 64 deep stage): larger wavefront tiles, so fewer LDS reads per MFMA,
+// with two wavefronts per SIMD all the same.  The groups' sums are added through LDS at the end.
+//
+// LoRA: the tile carries the r rows of A as further columns of its product, t = x A^T, and when
+// the K loop is done adds (scale t) B^T out of LDS.  Every column tile of a row block repeats
+// that, which is cheaper at these sizes than a producer tile, its stores and the wait for them;
+// t is rounded to bf16 as if it had been stored.
+//
+// The MFMA is issued with the weight rows as its first operand: a lane then holds four
+// consecutive output columns of one row, and bias, residual and store need no staging.
+#include "gemm_dma.hpp"
+
+namespace sd {
+
+template <int BM, int BN, int WGM, int WGN, int WGK, int NRB>
+struct Tile16 {
+    static constexpr int NW = WGM * WGN * WGK;
+    static constexpr int MI = BM / WGM / 16, NI = BN / WGN / 16;   // 16x16 blocks of a wavefront
+    static constexpr int RN = NRB * 16 * WGN;                      // rows of A in a stage
+    static constexpr int ROWS = BM + BN + RN;
+    static constexpr int NBLK = ROWS / 8;                          // 1 KB blocks (8 rows of 128 bytes) of a stage
+    static constexpr int LPT = (NBLK + NW - 1) / NW;               // loads per wavefront and stage
+    static constexpr int STAGE_CH = ROWS * 8;                      // 16-byte chunks of a stage
+    // as many stages as 160 KB hold, five at most; two workgroups per CU if three stages leave room for that
+    static constexpr int FIT = 160 * 1024 / (ROWS * 128);
+    static constexpr int STAGES = FIT >= 6 ? 3 : (FIT > 5 ? 5 : FIT);
+    static constexpr int EXCH = WGK > 1 ? NW * (MI / 2) * NI * 64 : 0;   // chunks of the exchange of the groups' sums
+    static constexpr int LDS_CH = STAGES * STAGE_CH > EXCH ? STAGES * STAGE_CH : EXCH;
+    static_assert(WGK == 1 || WGK == 2, "a stage has two 32 deep k-steps");
+    static_assert(STAGES >= 3, "ring");
+    static_assert(WGK == 1 || MI % 2 == 0, "the groups share the epilogue by row blocks");
+    static_assert(BM * RN * 4 <= STAGE_CH * 16, "the exchange of t fits a stage");
+};
+
+template <int V> struct IntC { static constexpr int v = V; };
+
+template <int BM, int BN, int WGM, int WGN, int WGK, int NRB>
+__global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const GemmGroup g) {
+    using T = Tile16<BM, BN, WGM, WGN, WGK, NRB>;
+    constexpr int NW = T::NW, MI = T::MI, NI = T::NI, RN = T::RN, LPT = T::LPT, STAGES = T::STAGES, STAGE = T::STAGE_CH, NBLK = T::NBLK;
+    constexpr int PH = 2 / WGK;             // k-steps of a stage that this wavefront multiplies
+    __shared__ u32x4 lds[T::LDS_CH];
+
+    GemmProblem P;
+    int tile, zero_n;
+    int32_t* zero_ptr;
+    if (!gemm_pick_tile(g, tile, P, zero_n, zero_ptr)) return;
+    const int local = tile - P.tile_begin;
+    const int band_tiles = 8 * P.tiles_n;
+    const int band = local / band_tiles, rem = local - band * band_tiles;
+    const int band_rows = min(8, P.tiles_m - band * 8);
+    const int tn = rem / band_rows, tm = band * 8 + rem % band_rows;
+    const int m0 = tm * BM, n0 = tn * BN;
+    const int Mp = P.Mp, N = P.N, r = NRB ? P.K1 : 0;
+    const int nk0 = P.K0 / 64, nkt = nk0 + (r ? 1 : 0);
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l16 = lane & 15, quad = lane >> 4;
+    const int wk = wave / (WGM * WGN), wmn = wave % (WGM * WGN);
+    const int wm = (wmn / WGN) * (BM / WGM), wn = (wmn % WGN) * (BN / WGN), wr = (wmn % WGN) * (NRB * 16);
+
+    // ---- loader.  Load j of wavefront w fills 1 KB block j * NW + w of a stage (x rows, W rows, A rows);
+    // where NW does not divide the blocks, the last wavefronts load the last block once more.
+    uint32_t off[LPT];            // byte offset of this lane's chunk from its operand's first row
+    uint32_t offb[LPT];           // ... in the tile of B (P.q1), or past what it holds: NONE
+    const char* base[LPT];
+    int dst[LPT];
+    constexpr uint32_t NONE = 0xffffffffu;
+#pragma unroll
+    for (int j = 0; j < LPT; ++j) {
+        const int blk = min(j * NW + wave, NBLK - 1);
+        dst[j] = blk * 1024;
+        const int row = blk * 8 + (lane >> 3);
+        const int c = swz<8>(row, lane & 7);
+        offb[j] = NONE;
+        if (blk < BM / 8) {
+            const int m = min(m0 + row, Mp - 1) - m0;
+            off[j] = (uint32_t)((m * P.ldp0 + c * 8) * 2);
+            base[j] = reinterpret_cast<const char*>(P.p0 + (int64_t)m0 * P.ldp0);
+        } else if (NRB == 0 || blk < (BM + BN) / 8) {
+            const int n = min(n0 + row - BM, N - 1) - n0;
+            off[j] = (uint32_t)((n * P.ldq0 + c * 8) * 2);
+            base[j] = reinterpret_cast<const char*>(P.q0 + (int64_t)n0 * P.ldq0);
+            if (NRB && c * 8 < r) offb[j] = (uint32_t)((n * P.ldq1 + c * 8) * 2);
+        } else {
+            // (a projection without adapter in a launch that has some: rows of W, and nothing done with the product)
+            const int a = r ? min(row - BM - BN, r - 1) : 0;
+            off[j] = (uint32_t)((a * (r ? P.ldp1 : 0) + c * 8) * 2);
+            base[j] = reinterpret_cast<const char*>(r ? P.p1 : P.q0);
+        }
+    }
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+    auto load = [&](int t, int stg, int j) {
+        dma16_so<false>(base[j] + (int64_t)t * 128, off[j], lds_base + (uint32_t)(stg * (STAGE * 16) + dst[j]));
+    };
+    // the tile of B: every lane has an address of its own, chunks past its r columns (and the other
+    // operands' blocks) read zeros; as many loads as any stage, so that the wait counts hold
+    auto load_b = [&](int stg, int j) {
+        const char* src = reinterpret_cast<const char*>(P.q1 + (int64_t)n0 * P.ldq1) + offb[j];
+        src = offb[j] != NONE ? src : reinterpret_cast<const char*>(g_gemm_zeros);
+        dma16<false>(src, lds_base + (uint32_t)(stg * (STAGE * 16) + dst[j]));
+    };
+    auto issue = [&](int t, int stg) {
+        if (NRB == 0 || t < nk0) {
+#pragma unroll
+            for (int j = 0; j < LPT; ++j) load(t, stg, j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < LPT; ++j) load_b(stg, j);
+        }
+    };
+
+    f32x4 acc[MI][NI], acct[MI][NRB ? NRB : 1];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ri = 0; ri < NRB; ++ri) acct[mi][ri] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    bf16x8 xf[2][MI], wf[2][NI], rf[2][NRB ? NRB : 1];
+    // rows that are 16 apart share the swizzle: one LDS address per k-step, the rest are offsets
+    const int lrow = l16 * 8, lsw = (l16 >> 1) & 7;
+    auto fetch = [&](int st, int kk, int fs, bool down) {
+        const u32x4* const s = lds + (st * STAGE + lrow + ((kk * 4 + quad) ^ lsw));
+        const u32x4* const sx = s + wm * 8;
+        const u32x4* const sw = s + (BM + wn) * 8;
+        const u32x4* const sr = s + (BM + BN + wr) * 8;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) xf[fs][mi] = __builtin_bit_cast(bf16x8, sx[mi * 128]);
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) wf[fs][ni] = __builtin_bit_cast(bf16x8, sw[ni * 128]);
+        if (down)
+#pragma unroll
+            for (int ri = 0; ri < NRB; ++ri) rf[fs][ri] = __builtin_bit_cast(bf16x8, sr[ri * 128]);
+    };
+    // one k-step, loads [j0, j1) dealt between its MFMAs
+    auto multiply = [&](int fs, bool down, auto ld, int j0, int j1) {
+        constexpr int NT = NI + NRB;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < MI * NT; ++i) {
+            const int mi = i % MI, ni = i / MI;
+            if (ni < NI)
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[fs][ni], xf[fs][mi], acc[mi][ni], 0, 0, 0);
+            else if (down)
+                acct[mi][ni - NI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rf[fs][ni - NI], xf[fs][mi], acct[mi][ni - NI], 0, 0, 0);
+            const int a = j0 + (j1 - j0) * i / (MI * NT), b = j0 + (j1 - j0) * (i + 1) / (MI * NT);
+            if (a < b) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = a; j < b; ++j) ld(j);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto no_load = [](int) {};
+    auto wait_tiles = [&](int newer) {
+        if (STAGES >= 5 && newer >= 4) wait_vmcnt<4 * LPT>();
+        else if (STAGES >= 4 && newer >= 3) wait_vmcnt<3 * LPT>();
+        else if (newer >= 2) wait_vmcnt<2 * LPT>();
+        else if (newer >= 1) wait_vmcnt<LPT>();
+        else wait_vmcnt<0>();
+    };
+
+    // ---- prologue
+#pragma unroll
+    for (int d = 0; d < STAGES; ++d)
+        if (d < nkt) issue(d, d);
+    wait_tiles(min(nkt - 1, STAGES - 1));
+    __syncthreads();
+    fetch(0, wk, 0, true);
+    if (PH == 2) {
+        fetch(0, 1, 1, true);
+        multiply(0, true, no_load, 0, 0);
+    }
+
+    // ---- K loop.  A step's edge lies before the MFMAs of tile t's last k-step, whose fragments are in
+    // registers: when this wavefront's loads of tile t+1 have landed, one barrier says that tile t+1
+    // is whole and the stage of tile t free; that is refilled with tile t+STAGES, its loads dealt over
+    // the step's MFMAs, and the first fragments of tile t+1 are read meanwhile.  With one k-step per
+    // stage the two fragment sets take turns from step to step.
+    int st = 0, t = 0;
+    auto step = [&](auto par, auto full) {
+        constexpr int FS = PH == 2 ? 1 : decltype(par)::v;
+        if (decltype(full)::v) wait_vmcnt<(STAGES - 2) * LPT>();
+        else wait_tiles(min(nkt - 2 - t, STAGES - 2));
+        __syncthreads();
+        const int sn = st + 1 == STAGES ? 0 : st + 1;
+        fetch(sn, wk, FS ^ 1, true);
+        if (decltype(full)::v) {
+            auto ld = [&](int j) { load(t + STAGES, st, j); };
+            multiply(FS, true, ld, 0, LPT / PH);
+            if (PH == 2) {
+                fetch(sn, 1, 1, true);
+                multiply(0, true, ld, LPT / PH, LPT);
+            }
+        } else {
+            if (t + STAGES < nkt) issue(t + STAGES, st);
+            multiply(FS, true, no_load, 0, 0);
+            if (PH == 2) {
+                fetch(sn, 1, 1, true);
+                multiply(0, true, no_load, 0, 0);
+            }
+        }
+        st = sn;
+        ++t;
+    };
+    // (an odd number of steps: one ahead of the pairs, and its fragments moved to the first set)
+    if ((nk0 - 1) & 1) {
+        step(IntC<0>(), IntC<0>());
+        if (PH == 1) {
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) xf[0][mi] = xf[1][mi];
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) wf[0][ni] = wf[1][ni];
+#pragma unroll
+            for (int ri = 0; ri < NRB; ++ri) rf[0][ri] = rf[1][ri];
+        }
+    }
+#pragma unroll 1
+    while (t + 1 + STAGES < nk0) {
+        step(IntC<0>(), IntC<1>());
+        step(IntC<1>(), IntC<1>());
+    }
+#pragma unroll 1
+    while (t + 1 < nk0) {
+        step(IntC<0>(), IntC<0>());
+        step(IntC<1>(), IntC<0>());
+    }
+
+    // residual rows of the blocks this wavefront will store, requested before the last MFMAs
+    constexpr int ME = WGK == 2 ? MI / 2 : MI;   // row blocks this wavefront finishes
+    const int mfirst = WGK == 2 ? wk * ME : 0;
+    f32x4 res[ME][NI];
+    const int mrow = m0 + wm + mfirst * 16 + l16, ncol = n0 + wn + quad * 4;
+#pragma unroll
+    for (int mi = 0; mi < ME; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            res[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+            const int m = mrow + mi * 16, n = ncol + ni * 16;
+            if (P.res && m < Mp && n < N) {
+                if (P.res_f32) {
+                    res[mi][ni] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(P.res) + (int64_t)m * P.ldr + n);
+                } else {
+                    const u32x2 v = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(P.res) + (int64_t)m * P.ldr + n);
+                    res[mi][ni] = __builtin_bit_cast(f32x4, u32x4{v[0], v[1], 0u, 0u});   // raw: widened where it is used
+                }
+            }
+        }
+    u32x2 bias[NI];
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        bias[ni] = u32x2{0u, 0u};
+        if (P.bias && ncol + ni * 16 < N) bias[ni] = *reinterpret_cast<const u32x2*>(P.bias + ncol + ni * 16);
+    }
+    multiply(PH == 2 ? 1 : 0, true, no_load, 0, 0);
+
+    // ---- adapter: t = x A^T is whole (over the K groups) after this, rounded to bf16, and becomes the
+    // x part of the stage that holds B
+    if (NRB && r) {
+        wait_vmcnt<0>();
+        __syncthreads();                    // the tile of B has landed; every fragment of the last tile is in registers
+        const int sb = st + 1 == STAGES ? 0 : st + 1;
+        f32x4* const xch = reinterpret_cast<f32x4*>(lds + st * STAGE) + wmn * (MI * NRB * 64) + lane;
+        if (WGK == 2) {
+            if (wk == 1)
+#pragma unroll
+                for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                    for (int ri = 0; ri < NRB; ++ri) xch[(mi * NRB + ri) * 64] = acct[mi][ri];
+            __syncthreads();
+        }
+        if (wk == 0) {
+            uint16_t* const tb = reinterpret_cast<uint16_t*>(lds + sb * STAGE);
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int ri = 0; ri < NRB; ++ri) {
+                    f32x4 v = acct[mi][ri];
+                    if (WGK == 2) v += xch[(mi * NRB + ri) * 64];
+                    const int row = wm + mi * 16 + l16, col = wr + ri * 16 + quad * 4;
+                    bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = (__bf16)(col + e < r ? v[e] * P.t_scale : 0.f);
+                    *reinterpret_cast<bf16x4*>(tb + row * 64 + swz<8>(row, col >> 3) * 8 + (col & 4)) = o;
+                }
+        }
+        // (a rank of at most RN: what lies between its columns and the 64 of the stage was loaded as zeros)
+        __syncthreads();
+        fetch(sb, wk, 0, false);
+        multiply(0, false, no_load, 0, 0);
+        if (PH == 2) {
+            fetch(sb, 1, 0, false);
+            multiply(0, false, no_load, 0, 0);
+        }
+    }
+
+    // ---- sums of the K groups: each gives the other the half of the row blocks it does not finish
+    f32x4 fin[ME][NI];
+    if (WGK == 2) {
+        __syncthreads();
+        f32x4* const ex = reinterpret_cast<f32x4*>(lds) + lane;
+        constexpr int PER = ME * NI * 64;
+#pragma unroll
+        for (int mi = 0; mi < ME; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                ex[wave * PER + (mi * NI + ni) * 64] = wk ? acc[mi][ni] : acc[ME + mi][ni];
+                fin[mi][ni] = wk ? acc[ME + mi][ni] : acc[mi][ni];
+            }
+        __syncthreads();
+        const int other = wmn + (wk ? 0 : WGM * WGN);
+#pragma unroll
+        for (int mi = 0; mi < ME; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) fin[mi][ni] += ex[other * PER + (mi * NI + ni) * 64];
+    } else {
+#pragma unroll
+        for (int mi = 0; mi < ME; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) fin[mi][ni] = acc[mi][ni];
+    }
+
+    // ---- bias, residual, store
+    const float alpha = P.alpha;
+#pragma unroll
+    for (int mi = 0; mi < ME; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) {
+            const int m = mrow + mi * 16, n = ncol + ni * 16;
+            f32x4 v = fin[mi][ni];
+            v[0] = alpha * v[0] + bf16lo_to_f32(bias[ni][0]);
+            v[1] = alpha * v[1] + bf16hi_to_f32(bias[ni][0]);
+            v[2] = alpha * v[2] + bf16lo_to_f32(bias[ni][1]);
+            v[3] = alpha * v[3] + bf16hi_to_f32(bias[ni][1]);
+            if (P.res) {
+                if (P.res_f32) {
+                    v += res[mi][ni];
+                } else {
+                    const u32x4 w = __builtin_bit_cast(u32x4, res[mi][ni]);
+                    v[0] += bf16lo_to_f32(w[0]); v[1] += bf16hi_to_f32(w[0]);
+                    v[2] += bf16lo_to_f32(w[1]); v[3] += bf16hi_to_f32(w[1]);
+                }
+            }
+            if (m < Mp && n < N) {
+                if (P.y_f32) {
+                    *reinterpret_cast<f32x4*>(static_cast<float*>(P.y) + (int64_t)m * P.ldy + n) = v;
+                } else {
+                    bf16x4 o;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
+                    *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(P.y) + (int64_t)m * P.ldy + n) = o;
+                }
+            }
+        }
+}
+
+template <int BM, int BN, int WGM, int WGN, int WGK, int NRB>
+static int launch16(GemmGroup& g, hipStream_t stream) {
+    int total = 0;
+    g.n_lead = 0;
+    g.zero_n = 0;
+    for (int i = 0; i < g.n; ++i) {
+        GemmProblem& P = g.p[i];
+        P.tiles_m = (P.Mp + BM - 1) / BM;
+        P.tiles_n = (P.N + BN - 1) / BN;
+        P.tile_begin = total;
+        g.first_tile[i] = total;
+        total += P.tiles_m * P.tiles_n;
+    }
+    g.total_tiles = total;
+    if (total == 0) return SD_OK;
+    hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB>), dim3((total + 7) & ~7), dim3(64 * WGM * WGN * WGK), 0, stream, g);
+    SD_HIP_CHECK(hipGetLastError());
+    return SD_OK;
+}
+template <int BM, int BN, int WGM, int WGN, int WGK>
+static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
+    if (rmax == 0) return launch16<BM, BN, WGM, WGN, WGK, 0>(g, stream);
+    if (rmax <= 16 * WGN) return launch16<BM, BN, WGM, WGN, WGK, 1>(g, stream);
+    if (rmax <= 32 * WGN) return launch16<BM, BN, WGM, WGN, WGK, 2>(g, stream);
+    return launch16<BM, BN, WGM, WGN, WGK, 64 / 16 / WGN>(g, stream);
+}
+
+// Which tile, or 0 for the general kernel (any K, rank, layout and alignment; four columns are one access here): the largest of the three with which the group is one round that
+// uses more than half the CUs (64x80: any number, two workgroups fit a CU).  An adapter costs the tile its
+// A rows in every step: cheaper than a producer tile only while those are few, or while the flags that a
+// producer needs would have to be cleared by a launch of their own (flags_clean false: +3.5 us).  us, general
+// kernel with clean flags / here: 8192x640x640 14.0 / 13.0, + 64: 17.9 / 19.8; 7904x640x2560 35.8 / 31.9;
+// 2048x1280x1280 13.0 / 11.9, + 64: 16.7 / 18.0; 988x1280x1280 + 16: 12.2 / 10.6; 988x1280x5120 28.8 / 26.9;
+// 1000x640x640 + 32: 9.4 / 8.4; 512x320x320 + 8: 8.2 / 7.7; 154x1280x2048 + 64: 10.2 / 14.7.
+static int tile16(const GemmGroup& g, bool flags_clean) {
+    long big = 0, mid = 0, small = 0;
+    int rmax = 0, kmax = 0;
+    for (int i = 0; i < g.n; ++i) {
+        const GemmProblem& P = g.p[i];
+        if (P.geglu_F > 0 || P.bias_on_rows || P.K0 % 64 || P.K1 > 64 || P.N % 4 || P.ldy % 4 || (P.res && P.ldr % 4) || P.Mp <= 0 || P.N <= 0 ||
+            (uintptr_t)P.bias % 8 || (uintptr_t)P.y % (P.y_f32 ? 16 : 8) || (uintptr_t)P.res % (P.res_f32 ? 16 : 8) ||
+            P.ldp0 * 512 >= (1ll << 31) || P.ldq0 * 512 >= (1ll << 31))
+            return 0;
+        big += (long)((P.Mp + 127) / 128) * ((P.N + 159) / 160);
+        mid += (long)((P.Mp + 63) / 64) * ((P.N + 159) / 160);
+        small += (long)((P.Mp + 63) / 64) * ((P.N + 79) / 80);
+        rmax = P.K1 > rmax ? P.K1 : rmax;
+        kmax = P.K0 > kmax ? P.K0 : kmax;
+    }
+    if (rmax > 0 && kmax >= 2048) return 0;
+    const int tile = big <= 256 && big > 128 ? 3 : mid <= 256 && mid > 128 ? 2 : small <= 256 ? 1 : 0;
+    if (rmax > 0 && flags_clean && (tile != 1 || rmax > 32)) return 0;
+    return tile;
+}
+bool gemm16_takes(const GemmGroup& g, bool flags_clean) { return tile16(g, flags_clean) > 0; }
+int launch_gemm16(GemmGroup& g, bool flags_clean, hipStream_t stream) {
+    int rmax = 0;
+    for (int i = 0; i < g.n; ++i) rmax = g.p[i].K1 > rmax ? g.p[i].K1 : rmax;
+    switch (tile16(g, flags_clean)) {
+    case 3: return launch16r<128, 160, 4, 2, 1>(g, rmax, stream);
+    case 2: return launch16r<64, 160, 2, 2, 2>(g, rmax, stream);
+    default: return launch16r<64, 80, 2, 1, 2>(g, rmax, stream);
+    }
+}
+
+}  // namespace sd

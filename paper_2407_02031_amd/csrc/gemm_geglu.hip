@@ -1,0 +1,308 @@
+// The feed-forward in-projection, y = value * gelu(gate) of x W^T (+ adapter) with W [2F, K], in
+// tiles of 160 output columns (320 rows of W) and 256 or 128 rows.
+//
+// What bounds it: the MFMAs of the most loaded CU.  The block's widths (2F = 5120 and 10240) are
+// whole multiples of 320 columns, and its token counts make a whole number of rounds over 256 CUs
+// of such tiles (8192x5120: two, 2048x10240: one) where 256x256 tiles need 2.5 and 1.25, that is
+// three and two.  One workgroup per CU, eight wavefronts of 64x160 (or 32x160): seven operand
+// fragments per ten MFMAs, 142 (or 91) FLOP per byte from L2.
+//
+// Two stages of 64 deep operand tiles fill the LDS, so a stage is refilled as soon as the last
+// fragments of its tile are in registers, one load behind each of the next MFMAs, and has the
+// rest of the step to arrive.
+//
+// The MFMA takes the rows of W first: a lane holds one row of x and 16 rows of W.  The rows of a
+// 32-row block of W in LDS are dealt so that these are the value and the gate rows of eight
+// consecutive output columns: GEGLU is done in the lane, and it stores 16 bytes.
+#include "gemm_dma.hpp"
+
+namespace sd {
+
+constexpr int GG_BN = 320, GG_OUT = 160, GG_NI = 5, GG_NW = 8;
+
+// MI: 32-row blocks of x per wavefront; four wavefronts by rows, two by columns
+template <int MI>
+__global__ __launch_bounds__(512, 2) void gemm_geglu_kernel(const GemmGroup g) {
+    constexpr int BM = MI * 128, NI = GG_NI, NW = GG_NW;
+    constexpr int ROWS = BM + GG_BN, STAGE = ROWS * 8;         // 16-byte chunks of a stage
+    constexpr int LPT = ROWS / 8 / NW, JP = BM / 8 / NW;       // loads per wavefront and stage, and those of x among them
+    static_assert(ROWS % (8 * NW) == 0 && BM % (8 * NW) == 0, "whole loads");
+    __shared__ u32x4 lds[2 * STAGE];
+
+    GemmProblem P;
+    int tile, zero_n;
+    int32_t* zero_ptr;
+    if (!gemm_pick_tile(g, tile, P, zero_n, zero_ptr)) return;
+    const int local = tile - P.tile_begin;
+    const int band_tiles = 8 * P.tiles_n;
+    const int band = local / band_tiles, rem = local - band * band_tiles;
+    const int band_rows = min(8, P.tiles_m - band * 8);
+    const int tn = rem / band_rows, tm = band * 8 + rem % band_rows;
+    const int m0 = tm * BM, n0 = tn * GG_OUT;
+    const int Mp = P.Mp, F = P.N, r = P.K1;
+    const int nk0 = P.K0 / 64, nkt = nk0 + (r + 63) / 64;
+
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hi = lane >> 5;
+    const int wm = (wave >> 1) * (MI * 32), wn = (wave & 1) * (GG_BN / 2);
+
+    // row of W behind row j of the tile: in a block of 32 rows, row 16 a + 8 g + 4 h + e is the value
+    // (g = 0) or gate row of output column 8 h + 4 a + e
+    auto wrow = [&](int j) {
+        const int col = min(n0 + (j >> 5) * 16 + ((j >> 2) & 1) * 8 + ((j >> 4) & 1) * 4 + (j & 3), F - 1);
+        return col + ((j >> 3) & 1) * F;
+    };
+    // load j of wavefront w fills block j * NW + w of a stage: the rows of x first, then those of W
+    auto row_of = [&](int j) { return (j * NW + wave) * 8 + (lane >> 3); };
+    uint32_t off[LPT];
+#pragma unroll
+    for (int j = 0; j < LPT; ++j) {
+        const int row = row_of(j), c = swz<8>(row, lane & 7);
+        if (j < JP) off[j] = (uint32_t)(((min(m0 + row, Mp - 1) - m0) * P.ldp0 + c * 8) * 2);
+        else off[j] = (uint32_t)((wrow(row - BM) * P.ldq0 + c * 8) * 2);
+    }
+    const uint16_t* const pb0 = P.p0 + (int64_t)m0 * P.ldp0;
+    const uint32_t wave_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds + (uint32_t)wave * 1024;
+    auto load = [&](int t, int stg, int j) {
+        dma16_so<false>((j < JP ? pb0 : P.q0) + t * 64, off[j], wave_base + (uint32_t)(stg * (STAGE * 16) + j * (NW * 1024)));
+    };
+    // tile of the adapter's segment: t [M, r] and B [2F, r]; chunks past r read zeros
+    auto load1 = [&](int t, int stg, int j) {
+        const int row = row_of(j), c = swz<8>(row, lane & 7), k = (t - nk0) * 64 + c * 8;
+        const uint16_t* src = j < JP ? P.p1 + (int64_t)min(m0 + row, Mp - 1) * P.ldp1 : P.q1 + (int64_t)wrow(row - BM) * P.ldq1;
+        dma16<false>(k < r ? reinterpret_cast<const void*>(src + k) : reinterpret_cast<const void*>(g_gemm_zeros),
+                     wave_base + (uint32_t)(stg * (STAGE * 16) + j * (NW * 1024)));
+    };
+    auto issue = [&](int t, int stg) {
+        if (t < nk0) {
+#pragma unroll
+            for (int j = 0; j < LPT; ++j) load(t, stg, j);
+        } else {
+#pragma unroll
+            for (int j = 0; j < LPT; ++j) load1(t, stg, j);
+        }
+    };
+
+    f32x16 acc[MI][NI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+    bf16x8 xf[2][MI], wf[2][NI];
+    const int lrow = l32 * 8, lsw = (l32 >> 1) & 7;
+    auto fetch = [&](int st, int kk, int fs) {
+        const u32x4* const s = lds + (st * STAGE + lrow + ((kk * 2 + hi) ^ lsw));
+        const u32x4* const sx = s + wm * 8;
+        const u32x4* const sw = s + (BM + wn) * 8;
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) xf[fs][mi] = __builtin_bit_cast(bf16x8, sx[mi * 256]);
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) wf[fs][ni] = __builtin_bit_cast(bf16x8, sw[ni * 256]);
+    };
+    auto multiply = [&](int fs, auto ld, int j0, int j1) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < MI * NI; ++i) {
+            const int mi = i % MI, ni = i / MI;
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[fs][ni], xf[fs][mi], acc[mi][ni], 0, 0, 0);
+            const int a = j0 + (j1 - j0) * i / (MI * NI), b = j0 + (j1 - j0) * (i + 1) / (MI * NI);
+            if (a < b) {
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = a; j < b; ++j) ld(j);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto no_load = [](int) {};
+    auto head = [&](int st) {       // all k-steps of a tile but the last
+#pragma unroll
+        for (int kk = 0; kk < 3; ++kk) {
+            fetch(st, kk + 1, (kk + 1) & 1);
+            multiply(kk & 1, no_load, 0, 0);
+        }
+    };
+
+    issue(0, 0);
+    if (nkt > 1) issue(1, 1);
+    if (nkt > 1) wait_vmcnt<LPT>();
+    else wait_vmcnt<0>();
+    __syncthreads();
+    fetch(0, 0, 0);
+    head(0);
+
+    // a step: the edge between tiles t and t+1, before the MFMAs of tile t's last k-step (whose
+    // fragments are in registers); the stage of tile t takes tile t+2
+    int t = 0;
+#pragma unroll 1
+    for (; t + 2 < nk0; ++t) {
+        const int st = t & 1, sn = st ^ 1;
+        wait_vmcnt<0>();
+        __syncthreads();
+        auto ld = [&](int j) { load(t + 2, st, j); };
+        fetch(sn, 0, 0);
+        multiply(1, ld, 0, MI == 2 ? LPT : 5);
+        fetch(sn, 1, 1);
+        multiply(0, ld, MI == 2 ? LPT : 5, LPT);
+        fetch(sn, 2, 0);
+        multiply(1, no_load, 0, 0);
+        fetch(sn, 3, 1);
+        multiply(0, no_load, 0, 0);
+    }
+#pragma unroll 1
+    for (; t + 1 < nkt; ++t) {
+        const int st = t & 1, sn = st ^ 1;
+        wait_vmcnt<0>();
+        __syncthreads();
+        fetch(sn, 0, 0);
+        if (t + 2 < nkt) issue(t + 2, st);
+        multiply(1, no_load, 0, 0);
+        head(sn);
+    }
+    multiply(1, no_load, 0, 0);
+
+    // ---- bias, GEGLU, store
+    const float alpha = P.alpha;
+    const uint16_t* const bias = P.bias;
+#pragma unroll
+    for (int ni = 0; ni < NI; ++ni) {
+        const int n = n0 + (wn >> 1) + ni * 16 + hi * 8;
+        if (n >= F) continue;       // F is a multiple of 8
+        float bv[8], bg[8];
+        u32x4 b0 = {0u, 0u, 0u, 0u}, b1 = {0u, 0u, 0u, 0u};
+        if (bias) {
+            b0 = *reinterpret_cast<const u32x4*>(bias + n);
+            b1 = *reinterpret_cast<const u32x4*>(bias + F + n);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            bv[e] = e & 1 ? bf16hi_to_f32(b0[e >> 1]) : bf16lo_to_f32(b0[e >> 1]);
+            bg[e] = e & 1 ? bf16hi_to_f32(b1[e >> 1]) : bf16lo_to_f32(b1[e >> 1]);
+        }
+#pragma unroll
+        for (int mi = 0; mi < MI; ++mi) {
+            const int m = m0 + wm + mi * 32 + l32;
+            bf16x8 o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int v = (e >> 2) * 8 + (e & 3);
+                o[e] = (__bf16)((alpha * acc[mi][ni][v] + bv[e]) * gelu_erf(alpha * acc[mi][ni][v + 4] + bg[e]));
+            }
+            if (m < Mp) *reinterpret_cast<bf16x8*>(static_cast<uint16_t*>(P.y) + (int64_t)m * P.ldy + n) = o;
+        }
+    }
+}
+
+// ---- the adapter's down-projection in front of it: 32 rows x 64 columns per workgroup, so that a few
+// thousand rows still reach every CU; two column wavefronts' worth of K halves.  Bound by latency (one
+// load round trip per 640 of K): two stages of 320 in flight, no tile of any other kind waits for it.
+constexpr int DN_BM = 32, DN_BN = 64, DN_KB = 5;               // rows, columns, 64 deep blocks per stage
+__global__ __launch_bounds__(512, 2) void down_kernel(const uint16_t* __restrict__ x, int64_t ldx, const uint16_t* __restrict__ A, float scale,
+                                                      uint16_t* __restrict__ t, int M, int K, int r) {
+    constexpr int ROWS = DN_BM + DN_BN, BLK = ROWS * 8;        // 16-byte chunks of a 64 deep block
+    constexpr int NL = ROWS / 8 * DN_KB, LPT = (NL + 7) / 8;   // 1 KB loads of a stage, and per wavefront
+    constexpr int STAGE = BLK * DN_KB;
+    __shared__ u32x4 lds[2 * STAGE];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, quad = lane >> 4;
+    const int m0 = blockIdx.x * DN_BM, c0 = blockIdx.y * DN_BN;
+    const int nb = K / 64, ns = (nb + DN_KB - 1) / DN_KB;
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
+    auto issue = [&](int s, int stg) {
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+            const int l = min(j * 8 + wave, NL - 1);           // the last load once more where 8 does not divide them
+            const int kb = l / (ROWS / 8), row = (l % (ROWS / 8)) * 8 + (lane >> 3);
+            const int k = min(s * DN_KB + kb, nb - 1) * 64 + swz<8>(row, lane & 7) * 8;
+            const uint16_t* const src = row < DN_BM ? x + (int64_t)min(m0 + row, M - 1) * ldx : A + (int64_t)min(c0 + row - DN_BM, r - 1) * K;
+            dma16<false>(src + k, base + (uint32_t)(stg * (STAGE * 16) + l * 1024));
+        }
+    };
+    issue(0, 0);
+    if (ns > 1) issue(1, 1);
+    const int col = (wave & 3) * 16, wk = wave >> 2;
+    f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+    const int lsw = (l16 >> 1) & 7;
+#pragma unroll 1
+    for (int s = 0; s < ns; ++s) {
+        if (s + 1 < ns) wait_vmcnt<LPT>();
+        else wait_vmcnt<0>();
+        __syncthreads();
+#pragma unroll
+        for (int kb = 0; kb < DN_KB; ++kb)
+            if (s * DN_KB + kb < nb) {
+                const u32x4* const b = lds + (s & 1) * STAGE + kb * BLK + l16 * 8 + ((wk * 4 + quad) ^ lsw);
+                const bf16x8 a = __builtin_bit_cast(bf16x8, b[(DN_BM + col) * 8]);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+                    acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, b[i * 128]), acc[i], 0, 0, 0);
+            }
+        __syncthreads();
+        if (s + 2 < ns) issue(s + 2, s & 1);
+    }
+    f32x4* const ex = reinterpret_cast<f32x4*>(lds);
+    if (wk == 1) {
+        ex[((wave & 3) * 2 + 0) * 64 + lane] = acc[0];
+        ex[((wave & 3) * 2 + 1) * 64 + lane] = acc[1];
+    }
+    __syncthreads();
+    if (wk == 0) {
+        const int c = c0 + col + quad * 4;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const f32x4 v = acc[i] + ex[(wave * 2 + i) * 64 + lane];
+            const int m = m0 + i * 16 + l16;
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (__bf16)(v[e] * scale);
+            if (m < M && c < r) *reinterpret_cast<bf16x4*>(t + (int64_t)m * r + c) = o;    // r is a multiple of 8
+        }
+    }
+}
+int launch_down(const uint16_t* x, int64_t ldx, const uint16_t* A, float scale, uint16_t* t, int M, int K, int r, hipStream_t stream) {
+    hipLaunchKernelGGL(down_kernel, dim3((M + DN_BM - 1) / DN_BM, (r + DN_BN - 1) / DN_BN), dim3(512), 0, stream, x, ldx, A, scale, t, M, K, r);
+    SD_HIP_CHECK(hipGetLastError());
+    return SD_OK;
+}
+
+template <int MI>
+static int launch_geglu_mi(GemmGroup& g, hipStream_t stream) {
+    GemmProblem& P = g.p[0];
+    P.tiles_m = (P.Mp + MI * 128 - 1) / (MI * 128);
+    P.tiles_n = (P.N + GG_OUT - 1) / GG_OUT;
+    P.tile_begin = g.first_tile[0] = 0;
+    g.n_lead = 0;
+    g.total_tiles = P.tiles_m * P.tiles_n;
+    hipLaunchKernelGGL((gemm_geglu_kernel<MI>), dim3((g.total_tiles + 7) & ~7), dim3(512), 0, stream, g);
+    SD_HIP_CHECK(hipGetLastError());
+    return SD_OK;
+}
+// Rows per tile, or 0: the smaller tiles of the general kernel.  Estimates in us, fitted to launches of 4
+// to 21 steps on one machine: a round of 256 tiles takes 6 + 2.1 per step with 256 rows and 5.6 + 1.12
+// with 128; the general kernel's 64x128 tiles (64 output columns) 6 + 0.33 per step and tile on the
+// most loaded CU.  (7904x5120x640: 72 general, 59.7 with 256 rows, 71.7 with 128; 988x10240x1280: 37.1,
+// 41.6, 30.6; 512x2560x320 + 8: 11.1, 25.7, 19.2.)
+static int geglu_rows(const GemmProblem& P) {
+    const double steps = P.K0 / 64 + (P.K1 + 63) / 64;
+    auto tiles = [&](int rows, int cols) { return (double)((P.Mp + rows - 1) / rows) * ((P.N + cols - 1) / cols); };
+    auto rounds = [&](double n) { return (double)(long)((n + 255) / 256); };
+    const double by256 = rounds(tiles(256, GG_OUT)) * (6.0 + 2.1 * steps);
+    const double by128 = rounds(tiles(128, GG_OUT)) * (5.6 + 1.12 * steps);
+    const double down = P.K1 ? 5.0 : 0.0;   // a launch of its own, where the general kernel hides it
+    const double general = 6.0 + 0.33 * steps * rounds(tiles(64, 64));
+    if (general <= by256 + down && general <= by128 + down) return 0;
+    return by256 < by128 ? 256 : 128;
+}
+bool gemm_geglu_takes(const GemmProblem& P) {
+    return P.geglu_F == P.N && P.N > 0 && P.Mp > 0 && P.K0 % 64 == 0 && P.N % 8 == 0 && P.ldy % 8 == 0 && !P.y_f32 && !P.res && !P.bias_on_rows && aligned16(P.bias) && aligned16(P.y) &&
+           P.ldp0 * 512 < (1ll << 31) && P.ldq0 * 4 * P.N < (1ll << 32) && geglu_rows(P) > 0;
+}
+int launch_gemm_geglu(GemmGroup& g, hipStream_t stream) {
+    return geglu_rows(g.p[0]) == 256 ? launch_geglu_mi<2>(g, stream) : launch_geglu_mi<1>(g, stream);
+}
+
+}  // namespace sd

@@ -185,6 +185,40 @@ def test_lora_linear_large_plain_projection(B, M, N, K, rank):
     assert B.gemm_dep_timeouts() == 0
 
 
+# one round of 128x160, 64x160 or 64x80 tiles: K of one, two, three and many 64 deep steps (both parities, rings that never fill), ragged
+# rows and columns, ranks with 1, 2 or 4 column blocks of A and none, an fp32 or bf16 residual, bias or none
+@pytest.mark.parametrize("M,K,N,rank,f32", [(1, 64, 8, 8, False), (63, 128, 84, 24, True), (130, 192, 80, 64, False), (333, 320, 324, 0, True), (512, 320, 320, 8, True),
+                                            (988, 1280, 1280, 16, False), (1000, 640, 1284, 0, False), (1990, 704, 1280, 64, False), (2048, 256, 1280, 0, True),
+                                            (5000, 128, 640, 0, False), (8192, 640, 640, 40, True), (8190, 64, 640, 0, True), (154, 2048, 1280, 0, False)])
+def test_lora_linear_one_round_of_tiles(B, M, K, N, rank, f32):
+    import torch
+    r = rng(M + K + N)
+    p = mkproj(r, N, K, rank, bias=M % 2 == 0, scale=0.7)
+    x = G.bf16_round(r.standard_normal((M, K)).astype(np.float32))
+    res = G.bf16_round(r.standard_normal((M, N)).astype(np.float32))
+    upd = O.lora_linear(x, p["W"], p["b"], p["A"], p["B"], p["scale"])
+    resd = torch.from_numpy(res).cuda() if f32 else dev(res, B)
+    y = B.lora_linear_fwd(dev(x, B), B.Proj.from_numpy(p), residual=resd, out_dtype=torch.float32 if f32 else torch.bfloat16)
+    # a bf16 y rounds the sum: its unit in the last place is relative to the sum, not to the update
+    assert rel_err(host(y), upd + res) <= BF16_TOL
+    if f32:
+        assert rel_err(host(y) - res, upd) <= BF16_TOL
+
+
+# tiles of 256 and 128 rows x 160 output columns: ragged rows and columns, one, two, three and more steps, the adapter's segment of less
+# and more than 64 columns, its down-projection with one and two column tiles and one to four stages of 320
+@pytest.mark.parametrize("M,C,F,rank", [(6300, 64, 1288, 0), (8192, 128, 2560, 8), (4000, 192, 2568, 0), (1000, 640, 5120, 72), (988, 1280, 5120, 0), (2047, 1280, 5120, 64)])
+def test_lora_linear_geglu_wide_tiles(B, M, C, F, rank):
+    r = rng(M + F + rank)
+    p = mkproj(r, 2 * F, C, rank, bias=rank != 8, scale=0.6, w_std=0.05)
+    x = G.bf16_round(r.standard_normal((M, C)).astype(np.float32))
+    y = B.lora_linear_fwd(dev(x, B), B.Proj.from_numpy(p), epilogue=B.SD_EPI_GEGLU)
+    assert y.shape == (M, F)
+    rows = np.unique(np.concatenate([np.arange(0, M, 97), np.arange(max(0, M - 40), M), np.arange(96, 160), np.arange(250, 262)]))
+    ref = O.geglu(O.lora_linear(x[rows], p["W"], p["b"], p["A"], p["B"], p["scale"]))
+    assert rel_err(host(y)[rows], ref) <= BF16_TOL
+
+
 # ---------------------------------------------------------------------- attention_fwd
 def vt_layout(v, B):
     """[Bn, Tk, C] -> the transposed, per-sample padded layout [C, Bn * Tkp]."""
