@@ -136,8 +136,15 @@ struct GemmProblem {
     // The in-tile form of an adapter (launch_gemm16): p1 is A [K1, K0], q1 is B, and the tile forms
     // t = t_scale * x A^T by itself.
     float t_scale;
-    int32_t unused;
+    int32_t readers;                           // filled by the launcher: tiles that wait for one row block
+    // nonce != 0: signal and wait are records of DEP_RECORD bytes per row-tile index that need not be
+    // zero when the launch starts (a random number says that a producer of this launch wrote them) and
+    // hold no such number any more when it ends; at most two column tiles of producers, wait_cols 0.
+    uint64_t nonce;
 };
+// one record: a 64-bit word for each of the producer's column tiles, then the 32-bit count of tiles that
+// have seen them all
+constexpr int DEP_RECORD = 32;
 
 constexpr int GEMM_MAX_PROBLEMS = 16;
 struct GemmGroup {

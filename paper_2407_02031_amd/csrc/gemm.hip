@@ -98,13 +98,17 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
     // have run on another XCD.
     const int32_t* const wflag = K1 ? P.wait : nullptr;
     const int32_t* fptr = nullptr;
-    int f_early = 0;
-    if (wflag) {
+    // with a nonce: the record of this row block, lane l looks at the word of column tile l
+    const uint64_t* const rec = wflag && P.nonce ? reinterpret_cast<const uint64_t*>(wflag) + tm * (DEP_RECORD / 8) : nullptr;
+    bool f_early = true;
+    if (rec) {
+        f_early = __hip_atomic_load(rec + min(lane, P.wait_need - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == P.nonce;
+    } else if (wflag) {
         const int lo = P.wait_cols ? n0 : m0;
         const int hi = P.wait_cols ? min(n0 + BN_OUT, N) : min(m0 + BM, Mp);
         const int f0 = lo / BM, f1 = (hi - 1) / BM;
         fptr = wflag + f0 + min(lane, f1 - f0);
-        f_early = __hip_atomic_load(fptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        f_early = __hip_atomic_load(fptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= P.wait_need;
     }
 
     // Q-operand (weight) row of tile row j.  GEGLU: 32-row blocks alternate value / gate
@@ -175,8 +179,9 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
             // the producer's tiles were dispatched before this one and wait for nothing, so
             // this ends; the bound is there so that it ends even if that reasoning is wrong
             for (int spins = 0;; ++spins) {
-                const int v = __hip_atomic_load(fptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (__all(v >= P.wait_need)) break;
+                const bool seen = rec ? __hip_atomic_load(rec + min(lane, P.wait_need - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == P.nonce
+                                      : __hip_atomic_load(fptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= P.wait_need;
+                if (__all(seen)) break;
                 if (spins >= DEP_SPIN_LIMIT) {
                     if (tid == 0) atomicAdd(&g_gemm_dep_timeouts, 1ull);
                     timed_out = true;
@@ -256,7 +261,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
 #pragma unroll
     for (int d = 0; d < STAGES; ++d)
         if (d < nkt) issue_tile(d, d);
-    if (!dep_ready) dep_ready = __all(f_early >= P.wait_need);
+    if (!dep_ready) dep_ready = __all(f_early);
     auto wait_tiles = [&](int newer) {   // `newer` tiles (at most STAGES - 1) may stay in flight
         if (STAGES >= 5 && newer >= 4) wait_vmcnt<4 * LPT>();
         else if (STAGES >= 4 && newer >= 3) wait_vmcnt<3 * LPT>();
@@ -369,6 +374,11 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
     }
     multiply(1, no_load, 0, 0);
     __syncthreads();   // ring reads done before the epilogue reuses LDS
+    // a record's last reader takes the nonce out again: a replay of this launch finds none.  (Every wavefront
+    // of the tile has seen the words by now; the count was zeroed before the first of them was written.)
+    int32_t* const seen_by = rec ? reinterpret_cast<int32_t*>(const_cast<uint64_t*>(rec) + 2) : nullptr;
+    int readers_before = -1;
+    if (rec && tid == 0) readers_before = __hip_atomic_fetch_add(seen_by, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
     // ---- epilogue
     float* stage = reinterpret_cast<float*>(lds) + wave * 32 * EPI_STRIDE;
@@ -535,9 +545,20 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
             __builtin_amdgcn_wave_barrier();
         }
     }
+    if (rec && tid == 0 && readers_before == P.readers - 1) {
+        __hip_atomic_store(const_cast<uint64_t*>(rec), (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(const_cast<uint64_t*>(rec) + 1, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     // ---- tell the tiles that wait for this one: every wave's stores have completed at device
-    // scope (vmcnt counts a device-scope store until it is visible there), then one flag add
-    if (sig) {
+    // scope (vmcnt counts a device-scope store until it is visible there), then one flag add, or
+    // the nonce in this column tile's word (the first one's writer zeroes the readers' count before)
+    if (sig && P.nonce) {
+        uint64_t* const w = reinterpret_cast<uint64_t*>(sig) + tm * (DEP_RECORD / 8);
+        if (tid == 0 && tn == 0) __hip_atomic_store(reinterpret_cast<int32_t*>(w + 2), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wait_vmcnt<0>();
+        __syncthreads();
+        if (tid == 0) __hip_atomic_store(w + tn, P.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else if (sig) {
         wait_vmcnt<0>();
         __syncthreads();
         if (tid == 0) __hip_atomic_fetch_add(sig + tm, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -574,6 +595,7 @@ static int launch_cfg(GemmGroup& g, bool guard, hipStream_t stream) {
         P.tiles_m = (P.Mp + BM - 1) / BM;
         P.tiles_n = P.signal ? (P.N + (BN < DOWN_BN ? BN : DOWN_BN) - 1) / (BN < DOWN_BN ? BN : DOWN_BN) : (P.N + BN_OUT - 1) / BN_OUT;
         P.tile_begin = total;
+        P.readers = P.tiles_n;
         g.first_tile[i] = total;
         total += P.tiles_m * P.tiles_n;
         if (P.signal) g.n_lead = total;
@@ -595,6 +617,7 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     for (int i = 0; i < g.n; ++i) geglu = geglu || g.p[i].geglu_F > 0;
     bool guard = false;
     int maxN = 0;
+    long lead = 0;        // down-projection tiles of 128 rows: workgroups too, ahead of the others
     double depth = 0;     // K, summed over those tiles
     long t128 = 0, t256 = 0;   // workgroup tiles of 128 and 256 rows x 128 output columns, down-projections aside
     bool res32 = false;   // some problem adds an fp32 residual: take the kernel that prefetches it
@@ -619,12 +642,15 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
             SD_REQUIRE(!P.y_f32 && !P.res && !P.wait && P.N % 4 == 0 && P.ldy % 4 == 0 && P.geglu_F == 0, SD_EINVAL,
                        "gemm problem %d: a signalling problem stores plain bf16 rows", i);
         }
+        SD_REQUIRE(!P.nonce || (P.signal ? P.N <= 2 * DOWN_BN : (P.wait && !P.wait_cols && P.K1 <= 2 * DOWN_BN)), SD_EINVAL,
+                   "gemm problem %d: what a dependency record does not hold", i);
         SD_REQUIRE(!P.wait || (P.K1 > 0 && g.p[0].signal), SD_EINVAL, "gemm problem %d waits but the group has no producer", i);
         if (P.Mp == 0 || P.N == 0) continue;
         if ((P.K0 & 63) || (P.K1 & 63)) guard = true;
         if (P.N > maxN) maxN = P.N;
         if (!P.signal) t128 += (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
         if (!P.signal) t256 += (long)((P.Mp + 255) / 256) * ((P.N + 127) / 128);
+        if (P.signal) lead += (long)((P.Mp + 127) / 128) * ((P.N + DOWN_BN - 1) / DOWN_BN);
         if (!P.signal) depth += (double)((P.Mp + 127) / 128) * ((P.N + 127) / 128) * P.K0;
     }
     // drop empty problems
@@ -644,7 +670,7 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     if (t128 < 512) {
         // at most one 128x128 tile per CU, and most CUs have one: that tile with a deep ring, one
         // workgroup per CU (2048x1280x5120: 42.0, 53.7 with 64x128 tiles, of which 64 CUs get two)
-        if (t128 > 128 && t128 <= 256) {
+        if (t128 > 128 && t128 + lead <= 256) {
             if (geglu) return launch_cfg<128, 128, 64, 4, 2, 4, true, false>(g, guard, stream);
             if (res32) return launch_cfg<128, 128, 64, 4, 2, 4, false, true>(g, guard, stream);
             return launch_cfg<128, 128, 64, 4, 2, 4, false, false>(g, guard, stream);
@@ -652,7 +678,7 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
         // more than that, but at most one of 256x128 per CU, and no short K loop: those
         // (8192x640x2560: 41.1, 48.2 with 128x128 tiles; 4757x1280x1280: 26.4, 33.1 with 64x128;
         // at K = 640 the ramps of the larger tile lose: 24.1 against 21.0)
-        if (!geglu && t128 > 256 && t256 <= 256 && meanK >= 1024) {
+        if (!geglu && t128 > 256 && t256 + lead <= 256 && meanK >= 1024) {
             if (res32) return launch_cfg<256, 128, 64, 4, 2, 3, false, true>(g, guard, stream);
             return launch_cfg<256, 128, 64, 4, 2, 3, false, false>(g, guard, stream);
         }

@@ -69,7 +69,7 @@ typedef uint32_t u32x16u __attribute__((ext_vector_type(16), aligned(4)));
 typedef uint32_t u32x8u __attribute__((ext_vector_type(8), aligned(4)));
 typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2u __attribute__((ext_vector_type(2), aligned(4)));
-struct alignas(8) ProblemWords { uint32_t w[46]; };
+struct alignas(8) ProblemWords { uint32_t w[48]; };
 static_assert(offsetof(GemmGroup, p) == 88 && offsetof(GemmGroup, first_tile) == 24 && offsetof(GemmGroup, zero_ptr) == 16 &&
               offsetof(GemmGroup, n_lead) == 8 && offsetof(GemmGroup, zero_n) == 12, "header layout");
 static_assert(sizeof(GemmProblem) == sizeof(ProblemWords), "problem record size");
@@ -113,7 +113,7 @@ __device__ __forceinline__ bool gemm_pick_tile(const GemmGroup& g, int& tile, Ge
     u32x16u rb = *reinterpret_cast<const u32x16u*>(pw + 16);
     u32x8u rc = *reinterpret_cast<const u32x8u*>(pw + 32);
     u32x4u rd = *reinterpret_cast<const u32x4u*>(pw + 40);
-    u32x2u re = *reinterpret_cast<const u32x2u*>(pw + 44);
+    u32x4u re = *reinterpret_cast<const u32x4u*>(pw + 44);
     asm volatile("" : "+s"(ra), "+s"(rb), "+s"(rc), "+s"(rd), "+s"(re));
     ProblemWords words;
 #pragma unroll
@@ -121,9 +121,7 @@ __device__ __forceinline__ bool gemm_pick_tile(const GemmGroup& g, int& tile, Ge
 #pragma unroll
     for (int i = 0; i < 8; ++i) words.w[32 + i] = rc[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) words.w[40 + i] = rd[i];
-    words.w[44] = re[0];
-    words.w[45] = re[1];
+    for (int i = 0; i < 4; ++i) { words.w[40 + i] = rd[i]; words.w[44 + i] = re[i]; }
     P = __builtin_bit_cast(GemmProblem, words);
     return true;
 }

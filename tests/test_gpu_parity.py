@@ -520,6 +520,60 @@ def patch_roundtrip(B, mats):
     return patched, restored
 
 
+# dependency records that the launch finds as it may: all ones, what another call left, what the launch's own replay left.  One and two
+# column tiles of producers, several launches' worth of segments, row blocks that are not full
+@pytest.mark.parametrize("lengths,ranks", [((4096, 2100, 2990), (16, 128, 72)), ((700,) * 12, (64, 8, 128, 24) * 3), ((9000,), (64,))])
+def test_multi_lora_workspace_contents_do_not_matter(B, lengths, ranks):
+    import torch
+    r = rng(sum(lengths))
+    K, N, M = 128, 640, sum(lengths)
+    W = G.bf16_round((0.05 * r.standard_normal((N, K))).astype(np.float32))
+    offsets = [sum(lengths[:i]) for i in range(len(lengths) + 1)]
+    ws = torch.full((B.lib().sd_multi_lora_linear_workspace_bytes(M, max(ranks)),), 255, dtype=torch.uint8, device="cuda")
+    x = torch.empty((M, K), dtype=torch.bfloat16, device="cuda")
+    A = [torch.empty((k, K), dtype=torch.bfloat16, device="cuda") for k in ranks]
+    Bm = [torch.empty((N, k), dtype=torch.bfloat16, device="cuda") for k in ranks]
+    out = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+
+    def draw():
+        arrays = [G.bf16_round((s * r.standard_normal(t.shape)).astype(np.float32)) for t, s in [(x, 1.0)] + [(t, 0.3) for t in A] + [(t, 0.1) for t in Bm]]
+        for t, a in zip([x] + A + Bm, arrays):
+            t.copy_(dev(a, B))
+        return arrays[0], arrays[1:1 + len(ranks)], arrays[1 + len(ranks):]
+
+    def call():
+        B.multi_lora_linear_fwd(x, dev_W, None, A, Bm, [0.5] * len(ranks), offsets, list(range(len(ranks))), out=out, ws=ws)
+
+    def check(arrays):
+        xs, As, Bs = arrays
+        got = host(out)
+        for i, (a, b) in enumerate(zip(As, Bs)):
+            rows = slice(offsets[i], offsets[i + 1])
+            ref = O.lora_linear(xs[rows], W, None, a, b, 0.5)
+            assert rel_err(got[rows], ref) <= BF16_TOL
+            assert rel_err(O.linear(xs[rows], W, None), ref) > 3 * BF16_TOL     # a stale or missing adapter term would be seen
+
+    dev_W = dev(W, B)
+    arrays = draw()
+    call()
+    check(arrays)
+    arrays = draw()
+    call()
+    check(arrays)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        call()
+    for _ in range(3):
+        arrays = draw()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        check(arrays)
+    assert B.gemm_dep_timeouts() == 0
+
+
 def test_patch_small_ragged_and_roundtrip(B):
     groups = ((2, 300, 200), (1, 128, 128), (1, 33, 1027), (3, 640, 640), (1, 1, 4))
     mats = G.make_patch_inputs(groups, r=32, alpha=16.0, seed=5)
