@@ -80,7 +80,8 @@ __device__ __forceinline__ void store_queries(const f32x16 (&o)[2], float l, uin
 // (-m split into three bf16 terms, exact to fp32) on the query side, so the accumulator holds
 // s - m and the vector ALU only exponentiates.  Without PRE one FMA per score does both.
 // MEASURE: the maximum of every key tile is measured before its exponentials are formed and the
-// reference moves whenever a tile's maximum exceeds it by 2^8.  PRE tries without first.  What
+// reference moves whenever a tile's maximum exceeds it by 2^8.  With TRY (prescaled keys, and long
+// ranges of plain ones) the kernel tries without first.  What
 // the reference maximum is for is range, not accuracy: p = 2^(s - m) is formed, rounded and
 // accumulated in floating point, whose relative precision does not depend on magnitude, so any m
 // gives the same result as long as nothing overflows and the row sum does not vanish.  The first
@@ -106,7 +107,6 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
                                                int Tq, int Tk, int Tkp, int heads, int qtiles, float c,
                                                int nfull, int nsplit, float* __restrict__ parts, int32_t* __restrict__ arrived,
                                                lds_u32x4* const ldsK, lds_u32x4* const ldsV, lds_i32* const wg_redo, const int tid, const int bid) {
-    static_assert(PRE || MEASURE, "only prescaled keys have the unmeasured form");
     constexpr int QB = 1;             // 32-query blocks per wavefront
     constexpr int BQ = 4 * 32 * QB;
 
@@ -531,7 +531,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     return false;
 }
 
-template <bool PRE>
+template <bool PRE, bool TRY>
 __global__ __launch_bounds__(256, 3) void attention_kernel(const uint16_t* __restrict__ q, int64_t ldq,
                                                         const uint16_t* __restrict__ k, int64_t ldk,
                                                         const uint16_t* __restrict__ vt, int64_t ldvt,
@@ -540,29 +540,27 @@ __global__ __launch_bounds__(256, 3) void attention_kernel(const uint16_t* __res
                                                         int nfull, int nsplit, float* __restrict__ parts, int32_t* __restrict__ arrived) {
     __shared__ u32x4 ldsK[2 * 64 * 8];
     __shared__ u32x4 ldsV[3 * 64 * 8];
-    __shared__ int32_t wg_redo;         // PRE: some wavefront's unmeasured attempt overflowed
+    __shared__ int32_t wg_redo;         // some wavefront's unmeasured attempt overflowed
     lds_u32x4* const lk = (lds_u32x4*)ldsK;
     lds_u32x4* const lv = (lds_u32x4*)ldsV;
     lds_i32* const redo = (lds_i32*)&wg_redo;
-    if constexpr (PRE) {
-        if (threadIdx.x == 0) *redo = 0;    // (ordered before its first use by the key loop's barriers)
-        if (attention_body<true, false>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk, lv, redo,
-                                        (int)threadIdx.x, (int)blockIdx.x)) {
-            // Second attempt, in the measured form, for inputs whose scores climb by more than 2^100
-            // over a key range.  Its inputs pass through empty assembly statements so that it shares
-            // no value with the first attempt: nothing of it may stay in registers through the first
-            // attempt's key loop and tail.
-            int tid2 = threadIdx.x, bid2 = blockIdx.x;
-            const uint16_t *q2 = q, *k2 = k, *vt2 = vt;
-            uint16_t* out2 = out;
-            lds_u32x4 *lk2 = lk, *lv2 = lv;
-            asm volatile("" : "+v"(tid2), "+s"(bid2), "+s"(q2), "+s"(k2), "+s"(vt2), "+s"(out2), "+s"(lk2), "+s"(lv2));
-            (void)attention_body<true, true>(q2, ldq, k2, ldk, vt2, ldvt, out2, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk2, lv2,
-                                             redo, tid2, bid2);
-        }
-    } else {
-        (void)attention_body<false, true>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk, lv, redo,
-                                          (int)threadIdx.x, (int)blockIdx.x);
+    if (TRY && threadIdx.x == 0) *redo = 0;    // (ordered before its first use by the key loop's barriers)
+    if (!TRY) {
+        (void)attention_body<PRE, true>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk, lv, redo,
+                                        (int)threadIdx.x, (int)blockIdx.x);
+    } else if (attention_body<PRE, false>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk, lv, redo,
+                                   (int)threadIdx.x, (int)blockIdx.x)) {
+        // Second attempt, in the measured form, for inputs whose scores climb by more than 2^100
+        // over a key range.  Its inputs pass through empty assembly statements so that it shares
+        // no value with the first attempt: nothing of it may stay in registers through the first
+        // attempt's key loop and tail.
+        int tid2 = threadIdx.x, bid2 = blockIdx.x;
+        const uint16_t *q2 = q, *k2 = k, *vt2 = vt;
+        uint16_t* out2 = out;
+        lds_u32x4 *lk2 = lk, *lv2 = lv;
+        asm volatile("" : "+v"(tid2), "+s"(bid2), "+s"(q2), "+s"(k2), "+s"(vt2), "+s"(out2), "+s"(lk2), "+s"(lv2));
+        (void)attention_body<PRE, true>(q2, ldq, k2, ldk, vt2, ldvt, out2, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk2, lv2,
+                                        redo, tid2, bid2);
     }
 }
 
@@ -636,12 +634,18 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     if (nsplit > 0 && !(scratch && scratch_bytes >= need && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0)) nsplit = 0;
     const int nfull = (int)tiles - nsplit;
     if (nsplit > arrived_n) arrived = nullptr;   // not enough counters: the halves are merged by the second kernel
-    if (k_prescaled)
-        hipLaunchKernelGGL((attention_kernel<true>), dim3((unsigned)(nfull + 2 * nsplit)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out,
-                           ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived);
-    else
-        hipLaunchKernelGGL((attention_kernel<false>), dim3((unsigned)(nfull + 2 * nsplit)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out,
-                           ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived);
+    // The unmeasured attempt saves a maximum per score tile and costs its check and the registers that the second
+    // attempt's code takes from it.  Against measuring every tile: prescaled keys 84 us for 90 at 4096 keys, and
+    // ahead at 77 too (a 32 x 32 stack 2690 for 2760); plain keys 355 for 372 at 8 x 3929 x 10 heads, 116 for 123 at
+    // 8 x 1434 x 20, 22.7 for 22.9 at 2 x 1330 x 10, but 59.7 for 57.6 at 8 x 988 x 20.
+    const int nt = (Tk + 63) / 64;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(nfull + 2 * nsplit)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
+                           qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived);
+    };
+    if (k_prescaled) go(attention_kernel<true, true>);
+    else if (nt >= 20) go(attention_kernel<false, true>);
+    else go(attention_kernel<false, false>);
     SD_HIP_CHECK(hipGetLastError());
     *cut_tiles = arrived ? 0 : nsplit;
     return SD_OK;

@@ -617,7 +617,7 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     for (int i = 0; i < g.n; ++i) geglu = geglu || g.p[i].geglu_F > 0;
     bool guard = false;
     int maxN = 0;
-    long lead = 0;        // down-projection tiles of 128 rows: workgroups too, ahead of the others
+    double lead = 0;      // down-projection tiles of 128 rows: workgroups too, ahead of the others
     double depth = 0;     // K, summed over those tiles
     long t128 = 0, t256 = 0;   // workgroup tiles of 128 and 256 rows x 128 output columns, down-projections aside
     bool res32 = false;   // some problem adds an fp32 residual: take the kernel that prefetches it
@@ -650,7 +650,7 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
         if (P.N > maxN) maxN = P.N;
         if (!P.signal) t128 += (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
         if (!P.signal) t256 += (long)((P.Mp + 255) / 256) * ((P.N + 127) / 128);
-        if (P.signal) lead += (long)((P.Mp + 127) / 128) * ((P.N + DOWN_BN - 1) / DOWN_BN);
+        if (P.signal) lead += (double)((P.Mp + 127) / 128) * ((P.N + DOWN_BN - 1) / DOWN_BN);
         if (!P.signal) depth += (double)((P.Mp + 127) / 128) * ((P.N + 127) / 128) * P.K0;
     }
     // drop empty problems
@@ -678,7 +678,7 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
         // more than that, but at most one of 256x128 per CU, and no short K loop: those
         // (8192x640x2560: 41.1, 48.2 with 128x128 tiles; 4757x1280x1280: 26.4, 33.1 with 64x128;
         // at K = 640 the ramps of the larger tile lose: 24.1 against 21.0)
-        if (!geglu && t128 > 256 && t256 + lead <= 256 && meanK >= 1024) {
+        if (!geglu && t128 > 256 && t256 + lead / 2 <= 256 && meanK >= 1024) {
             if (res32) return launch_cfg<256, 128, 64, 4, 2, 3, false, true>(g, guard, stream);
             return launch_cfg<256, 128, 64, 4, 2, 3, false, false>(g, guard, stream);
         }
@@ -688,9 +688,9 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
             if (res32) return launch_cfg<64, 128, 64, 2, 2, 3, false, true>(g, guard, stream);
             return launch_cfg<64, 128, 64, 2, 2, 3, false, false>(g, guard, stream);
         }
-        // up to three on a CU where the K loop is short or 128x128 tiles would leave most CUs with one
-        // and some with two (8192x640x640: 17.3, 18.3 with 128x128; 988x10240x1280 GEGLU: 35.7, 39.2)
-        if (t128 > 256 && (meanK < 1024 || t128 <= 384)) {
+        // up to three on a CU where the K loop is short, or GEGLU's epilogue long and 128x128 tiles would leave
+        // most CUs with one and some with two (8192x640x640: 17.3, 18.3 with 128x128; 988x10240x1280 GEGLU: 35.7, 39.2)
+        if (t128 > 256 && (meanK < 1024 || (geglu && t128 <= 384))) {
             if (geglu) return launch_cfg<64, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
             if (res32) return launch_cfg<64, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
             return launch_cfg<64, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
