@@ -221,13 +221,16 @@ static int run_projections(const ProjCall* calls, int n, hipStream_t stream, int
     for (int i = 0; i < n; ++i) {
         if (calls[i].M <= 0) continue;
         ++live;
-        in_tile = in_tile && !calls[i].o.transposed && live <= GEMM_MAX_PROBLEMS;
+        in_tile = in_tile && live <= GEMM_MAX_PROBLEMS;
     }
     if (in_tile && live) {
         for (int i = 0; i < n; ++i)
             if (calls[i].M > 0) {
-                if ((rc = push_main(g, stream, calls[i]))) return rc;
+                ProjCall c = calls[i];
+                c.o.transposed = false;
+                if ((rc = push_main(g, stream, c))) return rc;
                 GemmProblem& P = g.p[g.n - 1];
+                if (calls[i].o.transposed) P.bias_on_rows = 2;
                 P.p1 = calls[i].p->A;
                 P.ldp1 = calls[i].K;
                 P.t_scale = calls[i].p->scale;

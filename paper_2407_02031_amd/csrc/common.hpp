@@ -121,7 +121,7 @@ struct GemmProblem {
     int32_t geglu_F;                           // > 0: Q has 2F rows (value, gate); N == F
     int32_t y_f32;                             // output dtype: 1 fp32, 0 bf16
     int32_t res_f32;                           // residual dtype (an fp32 stream may be added into a bf16 output)
-    int32_t bias_on_rows;
+    int32_t bias_on_rows;                      // 1: bias per row; 2 (launch_gemm16): per column, and y is stored transposed, y[n * ldy + m]
     float alpha;
     int32_t tile_begin, tiles_m, tiles_n;      // filled by the launcher
     // Dependencies inside one launch (a down-projection and the base GEMM that reads it as its

@@ -357,7 +357,11 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
                 }
             }
             if (m < Mp && n < N) {
-                if (P.y_f32) {
+                if (P.bias_on_rows == 2) {      // transposed: 16 rows of x are 32 contiguous bytes
+                    uint16_t* const yt = static_cast<uint16_t*>(P.y) + (int64_t)n * P.ldy + m;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) yt[e * P.ldy] = __builtin_bit_cast(uint16_t, (__bf16)v[e]);
+                } else if (P.y_f32) {
                     *reinterpret_cast<f32x4*>(static_cast<float*>(P.y) + (int64_t)m * P.ldy + n) = v;
                 } else {
                     bf16x4 o;
@@ -402,14 +406,16 @@ static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
 // producer needs would have to be cleared by a launch of their own (flags_clean false: +3.5 us).  us, general
 // kernel with clean flags / here: 8192x640x640 14.0 / 13.0, + 64: 17.9 / 19.8; 7904x640x2560 35.8 / 31.9;
 // 2048x1280x1280 13.0 / 11.9, + 64: 16.7 / 18.0; 988x1280x1280 + 16: 12.2 / 10.6; 988x1280x5120 28.8 / 26.9;
-// 1000x640x640 + 32: 9.4 / 8.4; 512x320x320 + 8: 8.2 / 7.7; 154x1280x2048 + 64: 10.2 / 14.7.
+// 1000x640x640 + 32: 9.4 / 8.4; 512x320x320 + 8: 8.2 / 7.7; 154x1280x2048 + 64: 10.2 / 14.7;
+// the q, k, v and text key / value group of 988 tokens of 1280 channels + 16
+// 37.6 / 27.6, of 2 x 256 of 320 + 8 20.4 / 13.9 (values stored transposed).
 static int tile16(const GemmGroup& g, bool flags_clean) {
     long big = 0, mid = 0, small = 0;
     int rmax = 0, kmax = 0;
     for (int i = 0; i < g.n; ++i) {
         const GemmProblem& P = g.p[i];
-        if (P.geglu_F > 0 || P.bias_on_rows || P.K0 % 64 || P.K1 > 64 || P.N % 4 || P.ldy % 4 || (P.res && P.ldr % 4) || P.Mp <= 0 || P.N <= 0 ||
-            (uintptr_t)P.bias % 8 || (uintptr_t)P.y % (P.y_f32 ? 16 : 8) || (uintptr_t)P.res % (P.res_f32 ? 16 : 8) ||
+        if (P.geglu_F > 0 || P.bias_on_rows == 1 || P.K0 % 64 || P.K1 > 64 || P.N % 4 || (P.bias_on_rows == 2 ? P.y_f32 || P.res : P.ldy % 4) || (P.res && P.ldr % 4) || P.Mp <= 0 || P.N <= 0 ||
+            (uintptr_t)P.bias % 8 || (uintptr_t)P.y % (P.bias_on_rows == 2 ? 2 : P.y_f32 ? 16 : 8) || (uintptr_t)P.res % (P.res_f32 ? 16 : 8) ||
             P.ldp0 * 512 >= (1ll << 31) || P.ldq0 * 512 >= (1ll << 31))
             return 0;
         big += (long)((P.Mp + 127) / 128) * ((P.N + 159) / 160);
@@ -418,9 +424,9 @@ static int tile16(const GemmGroup& g, bool flags_clean) {
         rmax = P.K1 > rmax ? P.K1 : rmax;
         kmax = P.K0 > kmax ? P.K0 : kmax;
     }
-    if (rmax > 0 && kmax >= 2048) return 0;
+    if (rmax > 0 && kmax >= 2048 && g.n == 1) return 0;
     const int tile = big <= 256 && big > 128 ? 3 : mid <= 256 && mid > 128 ? 2 : small <= 256 ? 1 : 0;
-    if (rmax > 0 && flags_clean && (tile != 1 || rmax > 32)) return 0;
+    if (rmax > 0 && flags_clean && (rmax > 32 || !(tile == 1 || (tile == 3 && g.n > 1)))) return 0;
     return tile;
 }
 bool gemm16_takes(const GemmGroup& g, bool flags_clean) { return tile16(g, flags_clean) > 0; }

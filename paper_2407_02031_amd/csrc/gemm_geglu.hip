@@ -283,8 +283,8 @@ static int launch_geglu_mi(GemmGroup& g, hipStream_t stream) {
 }
 // Rows per tile, or 0: the smaller tiles of the general kernel.  Estimates in us, fitted to launches of 4
 // to 21 steps on one machine: a round of 256 tiles takes 6 + 2.1 per step with 256 rows and 5.6 + 1.12
-// with 128; the general kernel's 64x128 tiles (64 output columns) 6 + 0.33 per step and tile on the
-// most loaded CU.  (7904x5120x640: 72 general, 59.7 with 256 rows, 71.7 with 128; 988x10240x1280: 37.1,
+// with 128; the general kernel's 64x128 tiles (64 output columns), or the larger ones that it
+// prefers, 6 + 0.30 per step and 64x128 tile on the most loaded CU.  (7904x5120x640: 72 general, 59.7 with 256 rows, 71.7 with 128; 988x10240x1280: 37.1,
 // 41.6, 30.6; 512x2560x320 + 8: 11.1, 25.7, 19.2.)
 static int geglu_rows(const GemmProblem& P) {
     const double steps = P.K0 / 64 + (P.K1 + 63) / 64;
@@ -293,7 +293,7 @@ static int geglu_rows(const GemmProblem& P) {
     const double by256 = rounds(tiles(256, GG_OUT)) * (6.0 + 2.1 * steps);
     const double by128 = rounds(tiles(128, GG_OUT)) * (5.6 + 1.12 * steps);
     const double down = P.K1 ? 5.0 : 0.0;   // a launch of its own, where the general kernel hides it
-    const double general = 6.0 + 0.33 * steps * rounds(tiles(64, 64));
+    const double general = 6.0 + 0.30 * steps * rounds(tiles(64, 64));
     if (general <= by256 + down && general <= by128 + down) return 0;
     return by256 < by128 ? 256 : 128;
 }

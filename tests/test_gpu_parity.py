@@ -365,6 +365,19 @@ def test_attn_block_ragged_sizes(B, Bn, T, Tc, C, heads, rank):
     assert B.gemm_dep_timeouts() == 0
 
 
+# self-attention whose q, k and transposed v are one round of 128x160 tiles (token counts off every tile, adapters or none) or of 64x80
+@pytest.mark.parametrize("Bn,T,C,rank", [(2, 700, 640, 16), (1, 1003, 640, 0), (2, 261, 320, 24)])
+def test_attn_block_projections_in_one_round(B, Bn, T, C, rank):
+    import torch
+    r = rng(T + C)
+    ps = [mkproj(r, C, C, rank, bias=i == 3, scale=0.5) for i in range(4)]
+    g, b = G.bf16_round((1 + 0.02 * r.standard_normal(C)).astype(np.float32)), G.bf16_round((0.02 * r.standard_normal(C)).astype(np.float32))
+    x = r.standard_normal((Bn, T, C)).astype(np.float32)
+    y = B.attn_block_fwd(torch.from_numpy(x).cuda(), None, dev(g, B), dev(b, B), *[B.Proj.from_numpy(p) for p in ps], C // 64)
+    ref = O.attn_sublayer(x, None, g, b, *ps, C // 64)
+    assert rel_err(host(y) - x, ref - x) <= BF16_TOL
+
+
 @pytest.mark.parametrize("T,Tc", [(256, 128), (200, 77)])
 def test_attn_block_with_biased_q_k_v(B, T, Tc):
     """A projection record may carry a bias whatever its role.  With one on k the keys cannot leave
