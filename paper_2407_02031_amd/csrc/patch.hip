@@ -36,9 +36,9 @@ constexpr int UNPATCH_THROTTLE_LDS = 40 * 1024;
 
 struct PatchPlanEntry {
     sd_patch_desc d;       // 48 bytes
-    int64_t tile_begin;    // first workgroup tile of this matrix
-    int32_t tiles_c;       // column tiles (128 wide)
-    int32_t ntiles;        // workgroup tiles of this matrix
+    int64_t tile_begin;    // first tile of this matrix
+    int32_t tiles_c;       // tiles side by side
+    int32_t ntiles;        // tiles of this matrix
 };
 static_assert(sizeof(sd_patch_desc) == 48, "descriptor layout");
 static_assert(sizeof(PatchPlanEntry) == 64, "plan entry layout");
@@ -56,13 +56,23 @@ constexpr int PT_WR = 2, PT_WC = 2;
 constexpr int PT_ROWS = 32 * PT_WR, PT_COLS = 128 * PT_WC;
 constexpr int PT_THREADS = 64 * PT_WR * PT_WC;
 
+// A plan counts tiles of PLAN_ROWS x PT_COLS; a workgroup takes two of them, one above the other where
+// there is a pair.  Matrix i has the workgroups from first_workgroup(i) on, half its tiles rounded up,
+// and at most one before matrix i + 1 that finds nothing to do.
+constexpr int PLAN_ROWS = 32;
+static_assert(PT_ROWS == 2 * PLAN_ROWS, "two tiles of the plan per workgroup");
+__host__ __device__ __forceinline__ int64_t workgroups_before(int64_t tile_begin, int i) { return (tile_begin + i + 1) >> 1; }
+
+// the matrix of workgroup wg and, in `local`, its number among that matrix's `count` workgroups
 template <typename Entry>
-__device__ __forceinline__ int find_entry(const Entry* __restrict__ plan, int n, int64_t tile) {
-    int lo = 0, hi = n - 1;   // last entry with tile_begin <= tile
+__device__ __forceinline__ int find_entry(const Entry* __restrict__ plan, int n, int64_t wg, int& local, int& count) {
+    int lo = 0, hi = n - 1;   // last entry that begins at or before wg
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (plan[mid].tile_begin <= tile) lo = mid; else hi = mid - 1;
+        if (workgroups_before(plan[mid].tile_begin, mid) <= wg) lo = mid; else hi = mid - 1;
     }
+    local = (int)(wg - workgroups_before(plan[lo].tile_begin, lo));
+    count = (plan[lo].ntiles + 1) >> 1;
     return lo;
 }
 
@@ -322,19 +332,30 @@ __device__ __forceinline__ void patch_tile_any(float* __restrict__ W, float* __r
 template <int PT_STAGES>
 __device__ __forceinline__ void patch_matrix_tile(float* W, float* Und, uint16_t* S, int out, int in, const PatchAdapters& ad, int local, int tiles_c,
                                                   u32x4* const lds) {
-    const int tc = local % tiles_c, tr = local / tiles_c;
     bool quads = (in & 3) == 0 && (int64_t)out * in < (int64_t(1) << 30);
     for (int a = 0; a < ad.n; ++a) quads = quads && (ad.r[a] & 3) == 0;
-    if (quads) patch_tile<PT_STAGES>(W, Und, S, out, in, ad, tr, tc, lds);
-    else patch_tile_any(W, Und, S, out, in, ad, tr, tc);
+    // pairs of the plan's tiles, then, under an odd number of tile rows, the last row two side by side
+    const int tile_rows = (out + PLAN_ROWS - 1) / PLAN_ROWS, pairs = tiles_c * (tile_rows >> 1);
+    int tr = local / tiles_c, tc = local % tiles_c, end = tc + 1;
+    if (local >= pairs) {
+        tr = tile_rows >> 1;
+        tc = 2 * (local - pairs);
+        end = min(tc + 2, tiles_c);
+    }
+    for (; tc < end; ++tc) {
+        if (quads) patch_tile<PT_STAGES>(W, Und, S, out, in, ad, tr, tc, lds);
+        else patch_tile_any(W, Und, S, out, in, ad, tr, tc);
+        if (tc + 1 < end) __syncthreads();      // the next tile's loads reuse the ring
+    }
 }
 
 __global__ __launch_bounds__(PT_THREADS, 2) void lora_patch_kernel(const PatchPlanEntry* __restrict__ plan, int n) {
     __shared__ u32x4 lds[3 * PT_STAGE_CHUNKS];
-    const int64_t tile = blockIdx.x;
-    const PatchPlanEntry& E = plan[find_entry(plan, n, tile)];
+    int local, count;
+    const PatchPlanEntry& E = plan[find_entry(plan, n, blockIdx.x, local, count)];
+    if (local >= count) return;
     const PatchAdapters ad = {&E.d.A, &E.d.B, &E.d.r, &E.d.scale, 1};
-    patch_matrix_tile<3>(E.d.W, E.d.undo, nullptr, E.d.out, E.d.in, ad, (int)(tile - E.tile_begin), E.tiles_c, lds);
+    patch_matrix_tile<3>(E.d.W, E.d.undo, nullptr, E.d.out, E.d.in, ad, local, E.tiles_c, lds);
 }
 
 // Several adapters on one matrix in one pass over W (one or two LoRAs per request is the norm,
@@ -344,23 +365,25 @@ __global__ __launch_bounds__(PT_THREADS, 2) void lora_patch_kernel(const PatchPl
 // W' that the bf16 GEMMs read.
 __global__ __launch_bounds__(PT_THREADS, 3) void lora_patch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
     __shared__ u32x4 lds[2 * PT_STAGE_CHUNKS];
-    const int64_t tile = blockIdx.x;
-    const PatchMultiEntry& E = plan[find_entry(plan, n, tile)];
+    int local, count;
+    const PatchMultiEntry& E = plan[find_entry(plan, n, blockIdx.x, local, count)];
+    if (local >= count) return;
     const PatchAdapters ad = {E.d.A, E.d.B, E.d.r, E.d.scale, E.d.n_adapters};
-    patch_matrix_tile<2>(E.d.W, E.d.undo, E.d.serving, E.d.out, E.d.in, ad, (int)(tile - E.tile_begin), E.tiles_c, lds);
+    patch_matrix_tile<2>(E.d.W, E.d.undo, E.d.serving, E.d.out, E.d.in, ad, local, E.tiles_c, lds);
 }
 
 // W <- undo (flat linear copy), and the serving copy follows it: bf16(undo)
 __global__ __launch_bounds__(PT_THREADS) void lora_unpatch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
-    const int64_t tile = blockIdx.x;
-    const PatchMultiEntry& E = plan[find_entry(plan, n, tile)];
+    int local, count;
+    const PatchMultiEntry& E = plan[find_entry(plan, n, blockIdx.x, local, count)];
+    if (local >= count) return;
     float* __restrict__ W = E.d.W;
     const float* __restrict__ U = E.d.undo;
     uint16_t* __restrict__ S = E.d.serving;
     const int64_t elems = (int64_t)E.d.out * E.d.in;
     // the matrix's workgroups sweep it together, see lora_unpatch_kernel
-    const int64_t stride = (int64_t)E.ntiles * PT_THREADS * 4;
-    int64_t i = ((tile - E.tile_begin) * PT_THREADS + threadIdx.x) * 4;
+    const int64_t stride = (int64_t)count * PT_THREADS * 4;
+    int64_t i = ((int64_t)local * PT_THREADS + threadIdx.x) * 4;
 #pragma unroll 4
     for (; i + 4 <= elems; i += stride) {
         const float4 v = NT_LOAD4(U + i);
@@ -382,13 +405,14 @@ __global__ __launch_bounds__(PT_THREADS) void lora_unpatch_multi_kernel(const Pa
 // that is in flight at any moment is one narrow, contiguous window of the matrix.  HBM likes
 // that best: 6.0 TB/s, against 5.6 when every workgroup copies a contiguous 32 KB of its own.
 __global__ __launch_bounds__(PT_THREADS) void lora_unpatch_kernel(const PatchPlanEntry* __restrict__ plan, int n) {
-    const int64_t tile = blockIdx.x;
-    const PatchPlanEntry& E = plan[find_entry(plan, n, tile)];
+    int local, count;
+    const PatchPlanEntry& E = plan[find_entry(plan, n, blockIdx.x, local, count)];
+    if (local >= count) return;
     float* __restrict__ W = E.d.W;
     const float* __restrict__ U = E.d.undo;
     const int64_t elems = (int64_t)E.d.out * E.d.in;
-    const int64_t stride = (int64_t)E.ntiles * PT_THREADS * 4;
-    int64_t i = ((tile - E.tile_begin) * PT_THREADS + threadIdx.x) * 4;
+    const int64_t stride = (int64_t)count * PT_THREADS * 4;
+    int64_t i = ((int64_t)local * PT_THREADS + threadIdx.x) * 4;
 #pragma unroll 4
     for (; i + 4 <= elems; i += stride) NT_STORE4(W + i, NT_LOAD4(U + i));
     if (i < elems)   // the matrix's last 1..3 elements
@@ -422,7 +446,7 @@ extern "C" int sd_patch_plan_build(const sd_patch_desc* descs, int32_t n, void* 
         plan[i].d = d;
         plan[i].tile_begin = total;
         plan[i].tiles_c = (d.in + PT_COLS - 1) / PT_COLS;
-        const int64_t nt = (int64_t)plan[i].tiles_c * ((d.out + PT_ROWS - 1) / PT_ROWS);
+        const int64_t nt = (int64_t)plan[i].tiles_c * ((d.out + PLAN_ROWS - 1) / PLAN_ROWS);
         SD_REQUIRE(nt < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch desc %d: too many tiles", i);
         plan[i].ntiles = (int32_t)nt;
         total += nt;
@@ -439,8 +463,8 @@ static int patch_launch(bool undo, const void* plan_dev, int32_t n, int64_t tota
     SD_REQUIRE(total_tiles < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch: %lld tiles exceed one grid", (long long)total_tiles);
     const PatchPlanEntry* plan = static_cast<const PatchPlanEntry*>(plan_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (undo) hipLaunchKernelGGL(lora_unpatch_kernel, dim3((unsigned)total_tiles), dim3(PT_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
-    else hipLaunchKernelGGL(lora_patch_kernel, dim3((unsigned)total_tiles), dim3(PT_THREADS), 0, s, plan, n);
+    if (undo) hipLaunchKernelGGL(lora_unpatch_kernel, dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(PT_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
+    else hipLaunchKernelGGL(lora_patch_kernel, dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(PT_THREADS), 0, s, plan, n);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }
@@ -481,7 +505,7 @@ extern "C" int sd_patch_multi_plan_build(const sd_patch_multi_desc* descs, int32
         plan[i].d = d;
         plan[i].tile_begin = total;
         plan[i].tiles_c = (d.in + PT_COLS - 1) / PT_COLS;
-        const int64_t nt = (int64_t)plan[i].tiles_c * ((d.out + PT_ROWS - 1) / PT_ROWS);
+        const int64_t nt = (int64_t)plan[i].tiles_c * ((d.out + PLAN_ROWS - 1) / PLAN_ROWS);
         SD_REQUIRE(nt < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch desc %d: too many tiles", i);
         plan[i].ntiles = (int32_t)nt;
         total += nt;
@@ -498,8 +522,8 @@ static int patch_multi_launch(bool undo, const void* plan_dev, int32_t n, int64_
     SD_REQUIRE(total_tiles < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch: %lld tiles exceed one grid", (long long)total_tiles);
     const PatchMultiEntry* plan = static_cast<const PatchMultiEntry*>(plan_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (undo) hipLaunchKernelGGL(lora_unpatch_multi_kernel, dim3((unsigned)total_tiles), dim3(PT_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
-    else hipLaunchKernelGGL(lora_patch_multi_kernel, dim3((unsigned)total_tiles), dim3(PT_THREADS), 0, s, plan, n);
+    if (undo) hipLaunchKernelGGL(lora_unpatch_multi_kernel, dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(PT_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
+    else hipLaunchKernelGGL(lora_patch_multi_kernel, dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(PT_THREADS), 0, s, plan, n);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }
