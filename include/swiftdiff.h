@@ -102,7 +102,8 @@ const char* sd_last_error(void);
 int32_t sd_version(void);
 /* Self-check of the projection launches.  Section 2's LoRA projection runs as one launch: the
  * tiles of the down-projection t = scale * x A^T come first in the grid, and a tile of the base
- * GEMM waits, behind a bounded spin, for the rows of t it reads.
+ * GEMM waits, behind a bounded spin, for the rows of t it reads.  (Where the tiles form t by
+ * themselves, or a short launch in front does, nothing waits.)
  *   Forward progress rests on two things: (i) the down-projection tiles are the lowest-numbered
  *   workgroups of the launch and the hardware dispatches workgroups in index order on every XCD,
  *   so each of them is running or done before any tile can wait for it, and they wait for
