@@ -86,9 +86,9 @@ __device__ __forceinline__ int find_entry(const Entry* __restrict__ plan, int n,
 // a multiple of 4 runs without a round trip between its first and its last MFMA.
 //
 // Measured on the 310-matrix sweep (830 M elements), before and after: one adapter of rank 32 1755 ->
-// 1810 us (1680 at the 6.0 TB/s that the copy back reaches), of rank 64 about 2500 -> 2100, of rank 128
-// 4270 -> 2700; two of rank 32 with the bf16 copy 2550 -> 2327 (1980).  60 matrices of 1280 x 1280 under
-// ranks 16 and 64, on and off: 549 -> 458.  (The loop over a workgroup's possible second tile costs 4 to
+// 1810 us (1680 at the 6.0 TB/s that the copy back reaches), two of rank 32 with the bf16 copy 2550 ->
+// 2327 (1980).  A quarter of them under rank 64, on and off: 874 -> 809; a ninth under rank 128: 505 ->
+// 422; 60 matrices of 1280 x 1280 under ranks 16 and 64, on and off: 549 -> 458.  (The loop over a workgroup's possible second tile costs 4 to
 // 10 % of that in spilled scalars; a second copy of the tile's code costs more.)
 // One adapter: three stages and two workgroups per CU; a third one costs ranks up to 32 4 % (more
 // streams per HBM channel) though it gains rank 64 10 %.  Several: two stages, which leaves room for
