@@ -88,8 +88,8 @@ __device__ __forceinline__ void store_queries(const f32x16 (&o)[2], float l, uin
 // attempt therefore measures only a segment's first tile (m becomes a score that occurs: the row
 // sum is >= 1 from then on) and its last (which may be masked); in between the exponentials are
 // formed against that fixed reference with no maximum pass at all.  At the end every lane looks at
-// its row sum and accumulator: if anything is not finite, some score lay 2^100 or more above the
-// first tile's; a workgroup in which any wavefront saw that returns true without storing
+// its row sum and accumulator: if anything is not finite or close to it, some score lay 2^100 or more
+// above the first tile's; a workgroup in which any wavefront saw that returns true without storing
 // anything, and its caller runs the segment again in the measured form.
 // nsplit == 0: workgroup i takes tile i.  Otherwise the grid holds nfull whole tiles and
 // 2 * nsplit half tiles (both multiples of 8), dealt so that each XCD, and in dispatch order
@@ -464,13 +464,15 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     accumulate_o(vslot, pf);
 
     if (!MEASURE) {
-        // did the attempt stay in range?  (a row sum of +inf, or NaN anywhere, says no)
+        // did the attempt stay in range?  (a row sum of +inf, or NaN anywhere, says no.)  The limit leaves room for
+        // what the tail adds up: two half-wavefronts' sums, of two halves of a cut tile, must stay finite, and the
+        // reciprocal of their sum a normal number.
         float mag = l[0];
 #pragma unroll
         for (int db = 0; db < 2; ++db)
 #pragma unroll
             for (int v = 0; v < 16; ++v) mag += fabsf(o[0][db][v]);
-        const bool bad = __builtin_amdgcn_ballot_w64(!(mag <= 3.0e38f)) != 0ull;
+        const bool bad = __builtin_amdgcn_ballot_w64(!(mag <= 1.0e37f)) != 0ull;
         if (bad && lane == 0) *wg_redo = 1;
         __syncthreads();             // (which also ends every wavefront's LDS reads of this attempt)
         if (__builtin_expect(*wg_redo != 0, 0)) return true;

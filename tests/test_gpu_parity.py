@@ -299,6 +299,25 @@ def test_attention_large_scores_in_alternate_key_octets(B):
     assert rel_err(got2, ref2) <= BF16_TOL
 
 
+# Row sums just under the top of the fp32 range: one key of each half-wavefront's octets scores 2^127.3 above the first key
+# tile, so either half's sum is finite and their sum is not.  (1217 keys and more take the attempt without maxima; the values
+# are small, so that the accumulators stay in range.)  Whole tiles, and tiles whose halves are merged.
+@pytest.mark.parametrize("Bn,Tq,Tk,heads", [(1, 200, 1300, 1), (1, 200, 400, 1), (1, 4096, 1220, 20)])
+def test_attention_row_sums_at_the_top_of_the_range(B, Bn, Tq, Tk, heads):
+    r = rng(Tk)
+    C = heads * 64
+    q = np.full((Bn, Tq, C), 4.0, np.float32)
+    k = np.zeros((Bn, Tk, C), np.float32)
+    k[:, [300, 308]] = np.tile(np.repeat(np.array([2.75, 2.765625], np.float32), 32), heads)
+    score = float(q[0, 0, :64] @ k[0, 300, :64]) / 8.0 * 1.4426950408889634
+    assert 127.0 < score < 127.6 and 2.0 * 2.0 ** score > 3.41e38
+    v = G.bf16_round((1e-3 * r.standard_normal((Bn, Tk, C))).astype(np.float32))
+    got = host(B.attention_fwd(dev(q, B), dev(k, B), vt_layout(v, B), heads))
+    ref = (v[:, 300:301].astype(np.float64) + v[:, 308:309]) / 2 + np.zeros_like(q)     # every other key weighs 2^-127
+    assert np.abs(O.attention(q[:, :1], k, v, heads) - ref[:, :1]).max() <= 1e-9
+    assert rel_err(got, ref) <= BF16_TOL
+
+
 # ------------------------------------------------------- attn_block_fwd / ff_block_fwd
 def small_cfg(**kw):
     base = dict(name="t", Bn=2, T=200, C=128, heads=2, depth=1, r=8, alpha=4.0, lora_ff=True, Tc=77, Dc=256,
