@@ -82,14 +82,15 @@ __device__ __forceinline__ int find_entry(const Entry* __restrict__ plan, int n,
 // order; with ranks of 16 and 64 on one matrix those trips were two thirds of the pass.  Here the
 // workgroup's A columns and B rows of PT_RC ranks at a time go straight from global memory into a
 // ring of LDS stages, all but one of them requested before the W tile itself, shared by the
-// workgroup's wavefronts, and refilled while the chunks in between multiply: any rank that is
-// a multiple of 4 runs without a round trip between its first and its last MFMA.
+// workgroup's wavefronts, and refilled while the chunks in between multiply: no rank has a round
+// trip between its first and its last MFMA.
 //
 // Measured on the 310-matrix sweep (830 M elements), before and after: one adapter of rank 32 1755 ->
 // 1810 us (1680 at the 6.0 TB/s that the copy back reaches), two of rank 32 with the bf16 copy 2550 ->
 // 2327 (1980).  A quarter of them under rank 64, on and off: 874 -> 809; a ninth under rank 128: 505 ->
-// 422; 60 matrices of 1280 x 1280 under ranks 16 and 64, on and off: 549 -> 458.  (The loop over a workgroup's possible second tile costs 4 to
-// 10 % of that in spilled scalars; a second copy of the tile's code costs more.)
+// 422; 60 matrices of 1280 x 1280 under ranks 16 and 64, on and off: 549 -> 423.  Scalars are the scarce
+// resource: bounds and row addresses are formed where they are used and not carried through the products or
+// around the loop over a workgroup's possible second tile (spilled, they cost 6 to 10 %).
 // One adapter: three stages and two workgroups per CU; a third one costs ranks up to 32 4 % (more
 // streams per HBM channel) though it gains rank 64 10 %.  Several: two stages, which leaves room for
 // the third workgroup, 5 to 9 % faster at the matrix-core time of two adapters.
@@ -99,8 +100,9 @@ constexpr int PT_A_CHUNKS = PT_RC * PT_COLS / 4;    // 16-byte chunks of a stage
 constexpr int PT_B_CHUNKS = PT_ROWS * PT_RC / 4;    // ... then B rows [row][PT_RC], chunks of a row XOR-swizzled
 constexpr int PT_STAGE_CHUNKS = PT_A_CHUNKS + PT_B_CHUNKS;
 constexpr int PT_NW = PT_WR * PT_WC;
-constexpr int PT_LOADS = PT_STAGE_CHUNKS / 64 / PT_NW;   // direct-to-LDS loads of a wavefront per stage
-static_assert(PT_RC == 16 && PT_COLS == 256 && PT_STAGE_CHUNKS % (64 * PT_NW) == 0 && PT_A_CHUNKS % (64 * PT_NW) == 0, "stage layout");
+// direct-to-LDS loads of a wavefront per stage: of A, and one of B or, where its rows are not 16-byte aligned, four
+constexpr int PT_A_LOADS = PT_A_CHUNKS / 64 / PT_NW, PT_LOADS = PT_A_LOADS + 1;
+static_assert(PT_RC == 16 && PT_COLS == 256 && PT_A_CHUNKS % (64 * PT_NW) == 0 && PT_B_CHUNKS == 64 * PT_NW, "stage layout");
 
 // where lanes point whose chunk lies past the rank or the matrix
 __device__ __attribute__((aligned(256))) uint32_t g_patch_zeros[64];
@@ -109,6 +111,10 @@ __device__ __attribute__((aligned(256))) uint32_t g_patch_zeros[64];
 // byte address lds_base (wave-uniform); completion is tracked with vmcnt and a barrier
 __device__ __forceinline__ void patch_dma16(const void* gptr, uint32_t lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory", "m0");
+}
+// ... each lane 4 bytes, 256 in all
+__device__ __forceinline__ void patch_dma4(const void* gptr, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(gptr) : "memory", "m0");
 }
 template <int N>
 __device__ __forceinline__ void patch_wait_vmcnt() {
@@ -125,9 +131,10 @@ struct PatchAdapters {
 };
 
 // A workgroup tile under the adapters of its matrix: W_i = fl32(W_{i-1} + fl32(scale_i * (B_i A_i))),
-// undo <- W_0, W <- W_n, serving <- bf16(W_n).  For in and every rank multiples of 4 (a lane's four
-// columns are inside the matrix or outside together).  Wavefronts and lanes outside the matrix load
-// and multiply with the others and store nothing.
+// undo <- W_0, W <- W_n, serving <- bf16(W_n).  For in a multiple of 4 (a lane's four columns are inside
+// the matrix or outside together) and any rank: a B whose rows are not 16-byte aligned comes in 4 bytes
+// at a time (60 matrices of 1280 x 1280 under rank 33: 234 us, 615 with every access one element).
+// Wavefronts and lanes outside the matrix load and multiply with the others and store nothing.
 // Lane l of a wavefront holds columns c0 + 4 * (l % 32) + {0..3} of 16 rows; with the 32x32x2 MFMA
 // the upper half-wavefront supplies ranks 4 .. 7 of every 8, the lower half ranks 0 .. 3, so that one
 // 16-byte LDS read holds a lane's B values of 8 ranks.
@@ -144,27 +151,34 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
 
     // ---- operand chunks: (adapter, first rank), walked by the loads a few ahead of the MFMAs
     int ia = 0, ik = 0;            // next chunk to request
+    int r = ad.r[0];
+    const float* A = ad.A[0];
+    const float* B = ad.B[0];
     auto issue = [&](int slot) {
-        const int r = ad.r[ia];
-        const float* const A = ad.A[ia];
-        const float* const B = ad.B[ia];
         const uint32_t dst = lds_base + slot * (PT_STAGE_CHUNKS * 16);
 #pragma unroll
-        for (int j = 0; j < PT_LOADS; ++j) {
-            const void* src;
-            if (j < PT_A_CHUNKS / 64 / PT_NW) {          // one rank's 256 columns
-                const int k = ik + j * PT_NW + wave;
-                const int c = col_wg + lane * 4;
-                src = (k < r && c < in) ? (const void*)(A + (size_t)k * in + c) : (const void*)g_patch_zeros;
-            } else {                                     // 16 rows of B
-                const int row = ((j - PT_A_CHUNKS / 64 / PT_NW) * PT_NW + wave) * 16 + (lane >> 2);
-                const int k = ik + (((lane & 3) ^ ((row >> 2) & 3)) << 2);
-                src = (k < r && row_wg + row < out) ? (const void*)(B + (size_t)(row_wg + row) * r + k) : (const void*)g_patch_zeros;
+        for (int j = 0; j < PT_A_LOADS; ++j) {       // one rank's 256 columns
+            const int k = ik + j * PT_NW + wave, c = col_wg + lane * 4;
+            patch_dma16(k < r && c < in ? (const void*)(A + (size_t)k * in + c) : (const void*)g_patch_zeros, dst + j * (PT_NW * 1024));
+        }
+        const uint32_t bdst = dst + PT_A_LOADS * (PT_NW * 1024);
+        if ((r & 3) == 0) {                          // this wavefront's 16 rows of B, 4 ranks per lane
+            const int row = wave * 16 + (lane >> 2), k = ik + (((lane & 3) ^ ((row >> 2) & 3)) << 2);
+            patch_dma16(k < r && row_wg + row < out ? (const void*)(B + (size_t)(row_wg + row) * r + k) : (const void*)g_patch_zeros, bdst);
+        } else {                                     // ... one rank per lane, in the same places
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int row = wave * 16 + j * 4 + (lane >> 4), k = ik + ((((lane >> 2) & 3) ^ ((row >> 2) & 3)) << 2) + (lane & 3);
+                patch_dma4(k < r && row_wg + row < out ? (const void*)(B + (size_t)(row_wg + row) * r + k) : (const void*)g_patch_zeros, bdst + j * 256);
             }
-            patch_dma16(src, dst + j * (PT_NW * 1024));
         }
         ik += PT_RC;
-        if (ik >= r) { ik = 0; ++ia; }
+        if (ik >= r && ++ia < ad.n) {
+            ik = 0;
+            r = ad.r[ia];
+            A = ad.A[ia];
+            B = ad.B[ia];
+        }
     };
     int total = 0;                 // chunks in all
     for (int a = 0; a < ad.n; ++a) total += (ad.r[a] + PT_RC - 1) / PT_RC;
@@ -173,9 +187,13 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
         if (s < total) issue(s);
 
     // ---- W, undo and serving addresses: the row of register v lies 8 * (v / 4) + v % 4 rows below
-    // the lane's first, a wave-uniform distance; one 32-bit byte offset per lane serves all arrays
-    // (the caller checked that the matrix has fewer than 2^30 elements)
-    const uint32_t woff = (uint32_t)(((size_t)(r0 + 4 * hi) * in + col) * 4);
+    // the lane's first, a wave-uniform distance; one 32-bit byte offset per lane, from the wavefront's
+    // first element, serves all arrays (the caller checked that in < 2^27)
+    const size_t first = (size_t)r0 * in + c0;
+    W += first;
+    Und += first;
+    if (S) S += first;
+    const uint32_t woff = ((uint32_t)(4 * hi) * (uint32_t)in + 4 * l32) * 4;
     auto row_of = [&](int v) { return 8 * (v >> 2) + (v & 3); };
     auto row_bytes = [&](int v) -> size_t { return (size_t)row_of(v) * in * 4; };
     const bool full = r0 + 32 <= out && c0 + 128 <= in;     // uniform: no lane of this wavefront is outside
@@ -207,11 +225,13 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
     int ma = 0, mk = 0, slot = 0;  // adapter and first rank of the chunk being multiplied, its ring slot
+    int mr = ad.r[0];
+    float scale = ad.scale[0];
     const int brow = (wave / PT_WC) * 32 + l32;
 #pragma unroll 1
     for (int c = 0; c < total; ++c) {
         static_assert(PT_STAGES == 2 || PT_STAGES == 3, "at most one chunk is in flight behind the one waited for");
-        if (c >= PT_STAGES - 1) {
+        if (c >= PT_STAGES - 1) {  // (a chunk behind it with more loads than PT_LOADS: some of those are waited for too)
             if (PT_STAGES == 3 && c + 1 < total) patch_wait_vmcnt<(PT_STAGES - 2) * PT_LOADS>();
             else patch_wait_vmcnt<0>();
         }
@@ -237,8 +257,7 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
         }
         slot = slot + 1 == PT_STAGES ? 0 : slot + 1;
         mk += PT_RC;
-        if (mk >= ad.r[ma]) {      // the adapter's last chunk
-            const float scale = ad.scale[ma];
+        if (mk >= mr) {            // the adapter's last chunk
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 w[v].x = __fadd_rn(w[v].x, __fmul_rn(scale, acc[0][v]));
@@ -251,16 +270,20 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[j][v] = 0.f;
             mk = 0;
-            ++ma;
+            if (++ma < ad.n) {
+                mr = ad.r[ma];
+                scale = ad.scale[ma];
+            }
         }
     }
-    // (the offset is laundered so that the row addresses are formed again here instead of being
-    // carried, or spilled, through the adapters' products)
+    // (the offset and the lane's row are laundered so that row addresses and bounds are formed again here
+    // instead of being carried, or spilled, through the adapters' products)
     uint32_t woff2 = woff;
-    asm volatile("" : "+v"(woff2));
+    int row2 = r0 + 4 * hi;
+    asm volatile("" : "+v"(woff2), "+v"(row2));
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        if (full || (col_in && r0 + 4 * hi + row_of(v) < out)) {
+        if (full || (col_in && row2 + row_of(v) < out)) {
             NT_STORE4(reinterpret_cast<float*>(reinterpret_cast<char*>(W) + row_bytes(v) + woff2), w[v]);
             if (S) {
                 bf16x4 o = {(__bf16)w[v].x, (__bf16)w[v].y, (__bf16)w[v].z, (__bf16)w[v].w};
@@ -270,24 +293,29 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
     }
 }
 
-// The same for any in and rank (and matrices of 2^30 elements or more): every access guarded, one
-// element at a time.
+// The same for rows that are not 16-byte aligned (in no multiple of 4): every access guarded, one
+// element at a time.  Lane l holds columns l % 32 of the four 32-column blocks, so that a half-wavefront
+// still touches 128 contiguous bytes, all loads ahead of all stores (20 matrices of 1000 x 1278 under ranks
+// 8 and 16: 119 us, 170 with four columns side by side in a lane and each element's store behind its load).
 __device__ __forceinline__ void patch_tile_any(float* __restrict__ W, float* __restrict__ Und, uint16_t* __restrict__ S, int out, int in,
                                                const PatchAdapters& ad, int tr, int tc) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, hi = lane >> 5;
     const int r0 = tr * PT_ROWS + (wave / PT_WC) * 32;
-    const int col = tc * PT_COLS + (wave % PT_WC) * 128 + 4 * l32;
+    const int col = tc * PT_COLS + (wave % PT_WC) * 128 + l32;
     float w[16][4];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int row = min(r0 + 8 * (v >> 2) + 4 * hi + (v & 3), out - 1);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) w[v][j] = W[(size_t)row * in + min(col + 32 * j, in - 1)];   // (outside: an element that is inside, not stored)
+    }
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const bool ok = row < out && col + j < in;
-            w[v][j] = ok ? W[(size_t)row * in + col + j] : 0.f;
-            if (ok) Und[(size_t)row * in + col + j] = w[v][j];
-        }
+        for (int j = 0; j < 4; ++j)
+            if (row < out && col + 32 * j < in) Und[(size_t)row * in + col + 32 * j] = w[v][j];
     }
     const int brow = r0 + l32;
 #pragma unroll 1
@@ -307,7 +335,7 @@ __device__ __forceinline__ void patch_tile_any(float* __restrict__ W, float* __r
             const float bv = (kv && brow < out) ? B[(size_t)brow * r + kk] : 0.f;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float av = (kv && col + j < in) ? A[(size_t)kk * in + col + j] : 0.f;
+                const float av = (kv && col + 32 * j < in) ? A[(size_t)kk * in + col + 32 * j] : 0.f;
                 acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(bv, av, acc[j], 0, 0, 0);
             }
         }
@@ -317,13 +345,15 @@ __device__ __forceinline__ void patch_tile_any(float* __restrict__ W, float* __r
 #pragma unroll
             for (int j = 0; j < 4; ++j) w[v][j] = __fadd_rn(w[v][j], __fmul_rn(scale, acc[j][v]));
     }
+    int row2 = r0 + 4 * hi, col2 = col;     // laundered, as above
+    asm volatile("" : "+v"(row2), "+v"(col2));
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        const int row = r0 + 8 * (v >> 2) + 4 * hi + (v & 3);
+        const int row = row2 + 8 * (v >> 2) + (v & 3);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            if (row >= out || col + j >= in) continue;
-            const size_t idx = (size_t)row * in + col + j;
+            if (row >= out || col2 + 32 * j >= in) continue;
+            const size_t idx = (size_t)row * in + col2 + 32 * j;
             W[idx] = w[v][j];
             if (S) S[idx] = __builtin_bit_cast(uint16_t, (__bf16)w[v][j]);
         }
@@ -333,8 +363,7 @@ __device__ __forceinline__ void patch_tile_any(float* __restrict__ W, float* __r
 template <int PT_STAGES>
 __device__ __forceinline__ void patch_matrix_tile(float* W, float* Und, uint16_t* S, int out, int in, const PatchAdapters& ad, int local, int tiles_c,
                                                   u32x4* const lds) {
-    bool quads = (in & 3) == 0 && (int64_t)out * in < (int64_t(1) << 30);
-    for (int a = 0; a < ad.n; ++a) quads = quads && (ad.r[a] & 3) == 0;
+    const bool quads = (in & 3) == 0 && in < (1 << 27);
     // pairs of the plan's tiles, then, under an odd number of tile rows, the last row two side by side
     const int tile_rows = (out + PLAN_ROWS - 1) / PLAN_ROWS, pairs = tiles_c * (tile_rows >> 1);
     int tr = local / tiles_c, tc = local % tiles_c, end = tc + 1;
@@ -343,7 +372,9 @@ __device__ __forceinline__ void patch_matrix_tile(float* W, float* Und, uint16_t
         tc = 2 * (local - pairs);
         end = min(tc + 2, tiles_c);
     }
+#pragma unroll 1
     for (; tc < end; ++tc) {
+        asm volatile("" : "+s"(tr), "+s"(out), "+s"(in));     // (nothing of a tile is carried, or spilled, around the loop)
         if (quads) patch_tile<PT_STAGES>(W, Und, S, out, in, ad, tr, tc, lds);
         else patch_tile_any(W, Und, S, out, in, ad, tr, tc);
         if (tc + 1 < end) __syncthreads();      // the next tile's loads reuse the ring

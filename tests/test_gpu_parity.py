@@ -645,6 +645,60 @@ def test_patch_rank_chunks(B, out, in_, ranks):
     assert Wm.cpu().numpy().tobytes() == W.tobytes()
 
 
+def patch_pair(B, W, ads, serving=True):
+    """The adapters in one multi pass and one after the other in single passes: (multi, single, undo, serving, plan)."""
+    import torch
+    d = [(torch.from_numpy(A).cuda(), torch.from_numpy(Bm).cuda(), sc) for A, Bm, sc in ads]
+    Wm, Ws = torch.from_numpy(W).cuda(), torch.from_numpy(W).cuda()
+    undo, S = torch.empty_like(Wm), torch.empty(Wm.shape, dtype=torch.bfloat16, device="cuda")
+    plan = B.PatchMultiPlan([(Wm, undo, S, d)])
+    B.lora_patch_multi(plan)
+    for A, Bm, sc in d:
+        B.lora_patch(B.PatchPlan([(Ws, A, Bm, torch.empty_like(Ws), sc)]))
+    return Wm, Ws, undo, S, plan
+
+
+# ranks that are no multiple of 4 (B rows at any 4-byte address), next to ones that are; rows of W that are 16-byte aligned and
+# rows that are not; tiles inside the matrix, ragged ones, an odd number of 32-row tiles
+@pytest.mark.parametrize("out,in_", [(64, 256), (96, 516), (65, 254), (33, 1027), (130, 1278)])
+@pytest.mark.parametrize("ranks", [(1,), (6,), (33,), (7, 30), (64, 3), (5, 16, 2, 17)])
+def test_patch_any_rank_any_row_length(B, out, in_, ranks):
+    import torch
+    r = rng(out * in_ + sum(ranks))
+    W = (0.02 * r.standard_normal((out, in_))).astype(np.float32)
+    ads = [((0.02 * r.standard_normal((rk, in_))).astype(np.float32), (0.02 * r.standard_normal((out, rk))).astype(np.float32), sc)
+           for rk, sc in zip(ranks, (1.0, 0.5, -2.0, 3.0))]
+    ref = O.lora_patch_multi(W, ads)[0]
+    Wm, Ws, undo, S, plan = patch_pair(B, W, ads)
+    assert rel_err(Wm.cpu().numpy(), ref) <= PATCH_TOL
+    assert rel_err(W, ref) > 10 * PATCH_TOL
+    assert torch.equal(Wm, Ws) and torch.equal(S, Wm.to(torch.bfloat16)) and undo.cpu().numpy().tobytes() == W.tobytes()
+    B.lora_unpatch_multi(plan)
+    assert Wm.cpu().numpy().tobytes() == W.tobytes()
+
+
+def test_patch_matrix_of_more_than_2_to_the_30_elements(B):
+    """Byte offsets past 2^32: the first, middle and last rows against float64 sums."""
+    import torch
+    out, in_, r = 8200, 131076, 6
+    assert out * in_ > 2 ** 30
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    normal = lambda *shape: torch.empty(shape, device="cuda").normal_(0.0, 0.02, generator=g)
+    W, A, Bm = normal(out, in_), normal(r, in_), normal(out, r)
+    undo = torch.empty_like(W)
+    rows = torch.tensor([0, 1, 31, 32, 63, 64, 4095, 4096, 8160, 8191, 8192, 8199], device="cuda")
+    before, first_sum = W[rows].clone(), W.double().sum()
+    plan = B.PatchPlan([(W, A, Bm, undo, 0.5)])
+    B.lora_patch(plan)
+    ref = before.double() + 0.5 * (Bm[rows].double() @ A.double())
+    assert float((W[rows].double() - ref).abs().max() / ref.abs().max()) <= PATCH_TOL
+    assert float((before.double() - ref).abs().max() / ref.abs().max()) > 10 * PATCH_TOL
+    assert torch.equal(undo[rows], before) and bool(undo.double().sum() == first_sum)
+    B.lora_unpatch(plan)
+    assert torch.equal(W, undo)
+
+
 def test_patch_exact_integers(B):
     r = rng(9)
     W = r.integers(-8, 9, (256, 384)).astype(np.float32)
