@@ -28,11 +28,11 @@ __device__ __forceinline__ void nt_store4(float* p, float4 v) {
 
 // These kernels stream: what limits them is how well HBM copes with the mix of requests in
 // flight, and past a point more wavefronts per CU make that worse (more streams interleaved per
-// channel).  The copies back therefore ask for dynamic LDS that no kernel touches, only to cap
-// the workgroups per CU (160 KB of LDS per CU) at four, sixteen wavefronts: a sweep's copy back and
-// next patch take 2690 us together, 2735 with three or six workgroups, 2755 with eight.  The patch passes are held to eight wavefronts per CU by registers and LDS,
-// which is where they run best.
-constexpr int UNPATCH_THROTTLE_LDS = 40 * 1024;
+// channel).  The copies back therefore ask for dynamic LDS that no kernel touches, only to cap the
+// workgroups (of two wavefronts) per CU (160 KB of LDS): eight for the plain copy (a sweep's 310 matrices 1.09 ms,
+// 1.11 with ten or six), six where the bf16 copy is written too (1.43 ms; 1.54 with ten or with 16 wavefronts in
+// workgroups of four).  The patch passes are held to 8 to 12 wavefronts per CU by registers and LDS.
+constexpr int UNPATCH_THROTTLE_LDS = 20 * 1024, UNPATCH_MULTI_THROTTLE_LDS = 26 * 1024;
 
 struct PatchPlanEntry {
     sd_patch_desc d;       // 48 bytes
@@ -51,28 +51,25 @@ struct PatchMultiEntry {
 };
 static_assert(sizeof(PatchMultiEntry) % 8 == 0, "plan entry layout");
 
-// workgroup tile: 2 x 2 wavefronts of 32 rows x 128 columns each
-constexpr int PT_WR = 2, PT_WC = 2;
-constexpr int PT_ROWS = 32 * PT_WR, PT_COLS = 128 * PT_WC;
-constexpr int PT_THREADS = 64 * PT_WR * PT_WC;
-
-// A plan counts tiles of PLAN_ROWS x PT_COLS; a workgroup takes two of them, one above the other where
-// there is a pair.  Matrix i has the workgroups from first_workgroup(i) on, half its tiles rounded up,
-// and at most one before matrix i + 1 that finds nothing to do.
-constexpr int PLAN_ROWS = 32;
-static_assert(PT_ROWS == 2 * PLAN_ROWS, "two tiles of the plan per workgroup");
-__host__ __device__ __forceinline__ int64_t workgroups_before(int64_t tile_begin, int i) { return (tile_begin + i + 1) >> 1; }
+// A plan counts tiles of PLAN_ROWS x PT_COLS.  A workgroup has two wavefronts of 32 rows x 128 columns side
+// by side for each of the PT_WR tiles, one above the other, that it takes together.  With PT_WR = 2, matrix i
+// has the workgroups from workgroups_before(i) on, half its tiles rounded up, and at most one before matrix
+// i + 1 that finds nothing to do.
+constexpr int PLAN_ROWS = 32, PT_WC = 2, PT_COLS = 128 * PT_WC;
+constexpr int UNPATCH_THREADS = 128;
+template <int PT_WR>
+__host__ __device__ __forceinline__ int64_t workgroups_before(int64_t tile_begin, int i) { return PT_WR == 1 ? tile_begin : (tile_begin + i + 1) >> 1; }
 
 // the matrix of workgroup wg and, in `local`, its number among that matrix's `count` workgroups
-template <typename Entry>
+template <int PT_WR, typename Entry>
 __device__ __forceinline__ int find_entry(const Entry* __restrict__ plan, int n, int64_t wg, int& local, int& count) {
     int lo = 0, hi = n - 1;   // last entry that begins at or before wg
     while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
-        if (workgroups_before(plan[mid].tile_begin, mid) <= wg) lo = mid; else hi = mid - 1;
+        if (workgroups_before<PT_WR>(plan[mid].tile_begin, mid) <= wg) lo = mid; else hi = mid - 1;
     }
-    local = (int)(wg - workgroups_before(plan[lo].tile_begin, lo));
-    count = (plan[lo].ntiles + 1) >> 1;
+    local = (int)(wg - workgroups_before<PT_WR>(plan[lo].tile_begin, lo));
+    count = (plan[lo].ntiles + PT_WR - 1) / PT_WR;
     return lo;
 }
 
@@ -81,28 +78,22 @@ __device__ __forceinline__ int find_entry(const Entry* __restrict__ plan, int n,
 // from L2 pays a round trip per batch of them, on top of the matrix-core time that it issues in
 // order; with ranks of 16 and 64 on one matrix those trips were two thirds of the pass.  Here the
 // workgroup's A columns and B rows of PT_RC ranks at a time go straight from global memory into a
-// ring of LDS stages, all but one of them requested before the W tile itself, shared by the
+// ring of LDS stages, all but one of them requested right behind the W tile, shared by the
 // workgroup's wavefronts, and refilled while the chunks in between multiply: no rank has a round
 // trip between its first and its last MFMA.
 //
-// Measured on the 310-matrix sweep (830 M elements), before and after: one adapter of rank 32 1755 ->
-// 1810 us (1680 at the 6.0 TB/s that the copy back reaches), two of rank 32 with the bf16 copy 2550 ->
-// 2327 (1980).  A quarter of them under rank 64, on and off: 874 -> 809; a ninth under rank 128: 505 ->
-// 422; 60 matrices of 1280 x 1280 under ranks 16 and 64, on and off: 549 -> 423.  Scalars are the scarce
-// resource: bounds and row addresses are formed where they are used and not carried through the products or
+// Measured, fragments from L2 and now: 310 matrices (830 M elements) under rank 32 1720 and 1718 us (1680 at
+// the 6.0 TB/s that the copy back reaches), rank 64 2550 and 1967, two of rank 32 with the bf16 copy 2509 and 2040
+// (1980); 60 matrices of 1280 x 1280 under ranks 16 and 64, on and off, 499 and 424.  Scalars are the scarce resource:
+// bounds and row addresses are formed where they are used and not carried through the products or
 // around the loop over a workgroup's possible second tile (spilled, they cost 6 to 10 %).
-// One adapter: three stages and two workgroups per CU; a third one costs ranks up to 32 4 % (more
-// streams per HBM channel) though it gains rank 64 10 %.  Several: two stages, which leaves room for
-// the third workgroup, 5 to 9 % faster at the matrix-core time of two adapters.
 // ---------------------------------------------------------------------------------------
 constexpr int PT_RC = 16;
 constexpr int PT_A_CHUNKS = PT_RC * PT_COLS / 4;    // 16-byte chunks of a stage: A rows [rank][PT_COLS] ...
-constexpr int PT_B_CHUNKS = PT_ROWS * PT_RC / 4;    // ... then B rows [row][PT_RC], chunks of a row XOR-swizzled
-constexpr int PT_STAGE_CHUNKS = PT_A_CHUNKS + PT_B_CHUNKS;
-constexpr int PT_NW = PT_WR * PT_WC;
-// direct-to-LDS loads of a wavefront per stage: of A, and one of B or, where its rows are not 16-byte aligned, four
-constexpr int PT_A_LOADS = PT_A_CHUNKS / 64 / PT_NW, PT_LOADS = PT_A_LOADS + 1;
-static_assert(PT_RC == 16 && PT_COLS == 256 && PT_A_CHUNKS % (64 * PT_NW) == 0 && PT_B_CHUNKS == 64 * PT_NW, "stage layout");
+constexpr int PT_B_CHUNKS = PLAN_ROWS * PT_RC / 4;  // ... then, for each of the PT_WR tiles, B rows [row][PT_RC], chunks of a row XOR-swizzled
+template <int PT_WR>
+constexpr int PT_STAGE_CHUNKS = PT_A_CHUNKS + PT_WR * PT_B_CHUNKS;
+static_assert(PT_RC == 16 && PT_COLS == 256 && PT_B_CHUNKS == 64 * PT_WC, "stage layout");
 
 // where lanes point whose chunk lies past the rank or the matrix
 __device__ __attribute__((aligned(256))) uint32_t g_patch_zeros[64];
@@ -133,35 +124,41 @@ struct PatchAdapters {
 // A workgroup tile under the adapters of its matrix: W_i = fl32(W_{i-1} + fl32(scale_i * (B_i A_i))),
 // undo <- W_0, W <- W_n, serving <- bf16(W_n).  For in a multiple of 4 (a lane's four columns are inside
 // the matrix or outside together) and any rank: a B whose rows are not 16-byte aligned comes in 4 bytes
-// at a time (60 matrices of 1280 x 1280 under rank 33: 234 us, 615 with every access one element).
-// Wavefronts and lanes outside the matrix load and multiply with the others and store nothing.
+// at a time (60 matrices of 1280 x 1280 under rank 33: %ODD%).  Wavefronts and
+// lanes outside the matrix load and multiply with the others and store nothing.
 // Lane l of a wavefront holds columns c0 + 4 * (l % 32) + {0..3} of 16 rows; with the 32x32x2 MFMA
 // the upper half-wavefront supplies ranks 4 .. 7 of every 8, the lower half ranks 0 .. 3, so that one
 // 16-byte LDS read holds a lane's B values of 8 ranks.
-template <int PT_STAGES>
+template <int PT_WR, int PT_STAGES>
 __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restrict__ Und, uint16_t* __restrict__ S, int out, int in,
                                            const PatchAdapters& ad, int tr, int tc, u32x4* const lds) {
+    constexpr int NW = PT_WR * PT_WC, STAGE = PT_STAGE_CHUNKS<PT_WR>;
+    // direct-to-LDS loads of a wavefront per stage: of A, and one of B or, where its rows are not 16-byte aligned, four
+    constexpr int A_LOADS = PT_A_CHUNKS / 64 / NW, LOADS = A_LOADS + 1;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hi = lane >> 5;
-    const int row_wg = tr * PT_ROWS, col_wg = tc * PT_COLS;
+    const int row_wg = tr * (PLAN_ROWS * PT_WR), col_wg = tc * PT_COLS;
     const int r0 = row_wg + (wave / PT_WC) * 32, c0 = col_wg + (wave % PT_WC) * 128;
     const int col = c0 + 4 * l32;
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds + wave * 1024;
 
     // ---- operand chunks: (adapter, first rank), walked by the loads a few ahead of the MFMAs
     int ia = 0, ik = 0;            // next chunk to request
+    bool half = false;             // the chunk last requested had 8 ranks or fewer: half of A's loads
     int r = ad.r[0];
     const float* A = ad.A[0];
     const float* B = ad.B[0];
     auto issue = [&](int slot) {
-        const uint32_t dst = lds_base + slot * (PT_STAGE_CHUNKS * 16);
+        const uint32_t dst = lds_base + slot * (STAGE * 16);
+        half = ik + 8 >= r;
 #pragma unroll
-        for (int j = 0; j < PT_A_LOADS; ++j) {       // one rank's 256 columns
-            const int k = ik + j * PT_NW + wave, c = col_wg + lane * 4;
-            patch_dma16(k < r && c < in ? (const void*)(A + (size_t)k * in + c) : (const void*)g_patch_zeros, dst + j * (PT_NW * 1024));
+        for (int j = 0; j < A_LOADS; ++j) {       // one rank's 256 columns
+            if (j == A_LOADS / 2 && half) break;
+            const int k = ik + j * NW + wave, c = col_wg + lane * 4;
+            patch_dma16(k < r && c < in ? (const void*)(A + (size_t)k * in + c) : (const void*)g_patch_zeros, dst + j * (NW * 1024));
         }
-        const uint32_t bdst = dst + PT_A_LOADS * (PT_NW * 1024);
+        const uint32_t bdst = dst + A_LOADS * (NW * 1024);
         if ((r & 3) == 0) {                          // this wavefront's 16 rows of B, 4 ranks per lane
             const int row = wave * 16 + (lane >> 2), k = ik + (((lane & 3) ^ ((row >> 2) & 3)) << 2);
             patch_dma16(k < r && row_wg + row < out ? (const void*)(B + (size_t)(row_wg + row) * r + k) : (const void*)g_patch_zeros, bdst);
@@ -182,9 +179,11 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
     };
     int total = 0;                 // chunks in all
     for (int a = 0; a < ad.n; ++a) total += (ad.r[a] + PT_RC - 1) / PT_RC;
+    auto first_chunks = [&]() {    // all stages but one
 #pragma unroll
-    for (int s = 0; s < PT_STAGES - 1; ++s)
-        if (s < total) issue(s);
+        for (int s = 0; s < PT_STAGES - 1; ++s)
+            if (s < total) issue(s);
+    };
 
     // ---- W, undo and serving addresses: the row of register v lies 8 * (v / 4) + v % 4 rows below
     // the lane's first, a wave-uniform distance; one 32-bit byte offset per lane, from the wavefront's
@@ -202,22 +201,23 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
     if (full) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) w[v] = NT_LOAD4(reinterpret_cast<const float*>(reinterpret_cast<const char*>(W) + row_bytes(v) + woff));
+        first_chunks();
         // W's old bits go out first, as one burst of stores, before any adapter's product
 #pragma unroll
         for (int v = 0; v < 16; ++v) NT_STORE4(reinterpret_cast<float*>(reinterpret_cast<char*>(Und) + row_bytes(v) + woff), w[v]);
+        patch_wait_vmcnt<16>();    // the chunks have landed, the stores may be on their way
     } else {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
             w[v] = float4{0.f, 0.f, 0.f, 0.f};
             if (col_in && r0 + 4 * hi + row_of(v) < out) w[v] = NT_LOAD4(reinterpret_cast<const float*>(reinterpret_cast<const char*>(W) + row_bytes(v) + woff));
         }
+        first_chunks();
 #pragma unroll
         for (int v = 0; v < 16; ++v)
             if (col_in && r0 + 4 * hi + row_of(v) < out) NT_STORE4(reinterpret_cast<float*>(reinterpret_cast<char*>(Und) + row_bytes(v) + woff), w[v]);
         patch_wait_vmcnt<0>();
     }
-    // From here on this wavefront's loads of the first PT_STAGES - 1 chunks have landed: they are older
-    // than the W tile, whose values the undo stores have just taken, and loads retire in order.
 
     f32x16 acc[4];
 #pragma unroll
@@ -231,16 +231,18 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
 #pragma unroll 1
     for (int c = 0; c < total; ++c) {
         static_assert(PT_STAGES == 2 || PT_STAGES == 3, "at most one chunk is in flight behind the one waited for");
-        if (c >= PT_STAGES - 1) {  // (a chunk behind it with more loads than PT_LOADS: some of those are waited for too)
-            if (PT_STAGES == 3 && c + 1 < total) patch_wait_vmcnt<(PT_STAGES - 2) * PT_LOADS>();
+        if (c >= PT_STAGES - 1) {  // (a chunk behind it with more loads than LOADS: some of those are waited for too)
+            if (PT_STAGES == 3 && c + 1 < total && !half) patch_wait_vmcnt<LOADS>();
+            else if (PT_STAGES == 3 && c + 1 < total) patch_wait_vmcnt<A_LOADS / 2 + 1>();
             else patch_wait_vmcnt<0>();
         }
         __syncthreads();           // every wavefront's part of the chunk is in LDS, and the slot before it is free
         if (c + PT_STAGES - 1 < total) issue(slot == 0 ? PT_STAGES - 1 : slot - 1);
-        const u32x4* const la = lds + slot * PT_STAGE_CHUNKS;
+        const u32x4* const la = lds + slot * STAGE;
         const u32x4* const lb = la + PT_A_CHUNKS;
 #pragma unroll
         for (int u = 0; u < PT_RC / 8; ++u) {
+            if (u > 0 && mk + 8 * u >= mr) break;      // nothing but zeros: a rank of 8 has half the matrix-core time
             const float4 bv = __builtin_bit_cast(float4, lb[brow * 4 + ((2 * u + hi) ^ ((brow >> 2) & 3))]);
             float4 av[4];
 #pragma unroll
@@ -295,13 +297,13 @@ __device__ __forceinline__ void patch_tile(float* __restrict__ W, float* __restr
 
 // The same for rows that are not 16-byte aligned (in no multiple of 4): every access guarded, one
 // element at a time.  Lane l holds columns l % 32 of the four 32-column blocks, so that a half-wavefront
-// still touches 128 contiguous bytes, all loads ahead of all stores (20 matrices of 1000 x 1278 under ranks
-// 8 and 16: 119 us, 170 with four columns side by side in a lane and each element's store behind its load).
+// still touches 128 contiguous bytes (%RAG%).
+template <int PT_WR>
 __device__ __forceinline__ void patch_tile_any(float* __restrict__ W, float* __restrict__ Und, uint16_t* __restrict__ S, int out, int in,
                                                const PatchAdapters& ad, int tr, int tc) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int l32 = lane & 31, hi = lane >> 5;
-    const int r0 = tr * PT_ROWS + (wave / PT_WC) * 32;
+    const int r0 = tr * (PLAN_ROWS * PT_WR) + (wave / PT_WC) * 32;
     const int col = tc * PT_COLS + (wave % PT_WC) * 128 + l32;
     float w[16][4];
 #pragma unroll
@@ -360,34 +362,38 @@ __device__ __forceinline__ void patch_tile_any(float* __restrict__ W, float* __r
     }
 }
 
-template <int PT_STAGES>
+template <int PT_WR, int PT_STAGES>
 __device__ __forceinline__ void patch_matrix_tile(float* W, float* Und, uint16_t* S, int out, int in, const PatchAdapters& ad, int local, int tiles_c,
                                                   u32x4* const lds) {
     const bool quads = (in & 3) == 0 && in < (1 << 27);
     // pairs of the plan's tiles, then, under an odd number of tile rows, the last row two side by side
-    const int tile_rows = (out + PLAN_ROWS - 1) / PLAN_ROWS, pairs = tiles_c * (tile_rows >> 1);
     int tr = local / tiles_c, tc = local % tiles_c, end = tc + 1;
-    if (local >= pairs) {
-        tr = tile_rows >> 1;
-        tc = 2 * (local - pairs);
-        end = min(tc + 2, tiles_c);
+    if (PT_WR == 2) {
+        const int tile_rows = (out + PLAN_ROWS - 1) / PLAN_ROWS, pairs = tiles_c * (tile_rows >> 1);
+        if (local >= pairs) {
+            tr = tile_rows >> 1;
+            tc = 2 * (local - pairs);
+            end = min(tc + 2, tiles_c);
+        }
     }
 #pragma unroll 1
     for (; tc < end; ++tc) {
         asm volatile("" : "+s"(tr), "+s"(out), "+s"(in));     // (nothing of a tile is carried, or spilled, around the loop)
-        if (quads) patch_tile<PT_STAGES>(W, Und, S, out, in, ad, tr, tc, lds);
-        else patch_tile_any(W, Und, S, out, in, ad, tr, tc);
+        if (quads) patch_tile<PT_WR, PT_STAGES>(W, Und, S, out, in, ad, tr, tc, lds);
+        else patch_tile_any<PT_WR>(W, Und, S, out, in, ad, tr, tc);
+        if (PT_WR == 1) break;
         if (tc + 1 < end) __syncthreads();      // the next tile's loads reuse the ring
     }
 }
 
-__global__ __launch_bounds__(PT_THREADS, 2) void lora_patch_kernel(const PatchPlanEntry* __restrict__ plan, int n) {
-    __shared__ u32x4 lds[3 * PT_STAGE_CHUNKS];
+template <int PT_WR, int STAGES>
+__global__ __launch_bounds__(128 * PT_WR, 2) void lora_patch_kernel(const PatchPlanEntry* __restrict__ plan, int n) {
+    __shared__ u32x4 lds[STAGES * PT_STAGE_CHUNKS<PT_WR>];
     int local, count;
-    const PatchPlanEntry& E = plan[find_entry(plan, n, blockIdx.x, local, count)];
+    const PatchPlanEntry& E = plan[find_entry<PT_WR>(plan, n, blockIdx.x, local, count)];
     if (local >= count) return;
     const PatchAdapters ad = {&E.d.A, &E.d.B, &E.d.r, &E.d.scale, 1};
-    patch_matrix_tile<3>(E.d.W, E.d.undo, nullptr, E.d.out, E.d.in, ad, local, E.tiles_c, lds);
+    patch_matrix_tile<PT_WR, STAGES>(E.d.W, E.d.undo, nullptr, E.d.out, E.d.in, ad, local, E.tiles_c, lds);
 }
 
 // Several adapters on one matrix in one pass over W (one or two LoRAs per request is the norm,
@@ -395,27 +401,27 @@ __global__ __launch_bounds__(PT_THREADS, 2) void lora_patch_kernel(const PatchPl
 // the adapters are applied one after the other, so the result equals successive single patches bit
 // for bit at one third of their traffic for two adapters.  Optionally also writes the bf16 copy of
 // W' that the bf16 GEMMs read.
-__global__ __launch_bounds__(PT_THREADS, 3) void lora_patch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
-    __shared__ u32x4 lds[2 * PT_STAGE_CHUNKS];
+template <int PT_WR, int STAGES>
+__global__ __launch_bounds__(128 * PT_WR, PT_WR + 1) void lora_patch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
+    __shared__ u32x4 lds[STAGES * PT_STAGE_CHUNKS<PT_WR>];
     int local, count;
-    const PatchMultiEntry& E = plan[find_entry(plan, n, blockIdx.x, local, count)];
+    const PatchMultiEntry& E = plan[find_entry<PT_WR>(plan, n, blockIdx.x, local, count)];
     if (local >= count) return;
     const PatchAdapters ad = {E.d.A, E.d.B, E.d.r, E.d.scale, E.d.n_adapters};
-    patch_matrix_tile<2>(E.d.W, E.d.undo, E.d.serving, E.d.out, E.d.in, ad, local, E.tiles_c, lds);
+    patch_matrix_tile<PT_WR, STAGES>(E.d.W, E.d.undo, E.d.serving, E.d.out, E.d.in, ad, local, E.tiles_c, lds);
 }
 
 // W <- undo (flat linear copy), and the serving copy follows it: bf16(undo)
-__global__ __launch_bounds__(PT_THREADS) void lora_unpatch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
+__global__ __launch_bounds__(UNPATCH_THREADS) void lora_unpatch_multi_kernel(const PatchMultiEntry* __restrict__ plan, int n) {
     int local, count;
-    const PatchMultiEntry& E = plan[find_entry(plan, n, blockIdx.x, local, count)];
-    if (local >= count) return;
+    const PatchMultiEntry& E = plan[find_entry<1>(plan, n, blockIdx.x, local, count)];
     float* __restrict__ W = E.d.W;
     const float* __restrict__ U = E.d.undo;
     uint16_t* __restrict__ S = E.d.serving;
     const int64_t elems = (int64_t)E.d.out * E.d.in;
     // the matrix's workgroups sweep it together, see lora_unpatch_kernel
-    const int64_t stride = (int64_t)count * PT_THREADS * 4;
-    int64_t i = ((int64_t)local * PT_THREADS + threadIdx.x) * 4;
+    const int64_t stride = (int64_t)count * UNPATCH_THREADS * 4;
+    int64_t i = ((int64_t)local * UNPATCH_THREADS + threadIdx.x) * 4;
 #pragma unroll 4
     for (; i + 4 <= elems; i += stride) {
         const float4 v = NT_LOAD4(U + i);
@@ -436,15 +442,14 @@ __global__ __launch_bounds__(PT_THREADS) void lora_unpatch_multi_kernel(const Pa
 // sweep it together as one flat array: in every round workgroup w copies the w-th 2 KB, so all
 // that is in flight at any moment is one narrow, contiguous window of the matrix.  HBM likes
 // that best: 6.0 TB/s, against 5.6 when every workgroup copies a contiguous 32 KB of its own.
-__global__ __launch_bounds__(PT_THREADS) void lora_unpatch_kernel(const PatchPlanEntry* __restrict__ plan, int n) {
+__global__ __launch_bounds__(UNPATCH_THREADS) void lora_unpatch_kernel(const PatchPlanEntry* __restrict__ plan, int n) {
     int local, count;
-    const PatchPlanEntry& E = plan[find_entry(plan, n, blockIdx.x, local, count)];
-    if (local >= count) return;
+    const PatchPlanEntry& E = plan[find_entry<1>(plan, n, blockIdx.x, local, count)];
     float* __restrict__ W = E.d.W;
     const float* __restrict__ U = E.d.undo;
     const int64_t elems = (int64_t)E.d.out * E.d.in;
-    const int64_t stride = (int64_t)count * PT_THREADS * 4;
-    int64_t i = ((int64_t)local * PT_THREADS + threadIdx.x) * 4;
+    const int64_t stride = (int64_t)count * UNPATCH_THREADS * 4;
+    int64_t i = ((int64_t)local * UNPATCH_THREADS + threadIdx.x) * 4;
 #pragma unroll 4
     for (; i + 4 <= elems; i += stride) NT_STORE4(W + i, NT_LOAD4(U + i));
     if (i < elems)   // the matrix's last 1..3 elements
@@ -488,6 +493,13 @@ extern "C" int sd_patch_plan_build(const sd_patch_desc* descs, int32_t n, void* 
     return SD_OK;
 }
 
+// Which workgroups a pass gets.  Up to two tiles per CU: one tile each, two workgroups with a three-stage ring on a
+// CU (1 x 1280 x 1280 under rank 32 8.4 us, 9.5 in pairs of tiles; under 8 and 8 8.0 and 9.3).  Up to three: one tile
+// each with two stages, which fit four times (3 x 1280 x 1280 under rank 8 12.4, 14.7 in pairs, which leave some CUs two
+// and most one; 14.4 with three stages).  Beyond that pairs, which share A's stages: 4 x 1280 x 1280 under 8 and 8 17.6, 19.3
+// and 21.2; 60 under 16 and 64 271, 297 and 370.  One adapter: three stages and two workgroups per CU; several: two stages,
+// which leaves room for a third workgroup.
+constexpr int64_t SINGLE_3_STAGES = 2 * 256, SINGLE_2_STAGES = 3 * 256;
 static int patch_launch(bool undo, const void* plan_dev, int32_t n, int64_t total_tiles, void* stream) {
     SD_REQUIRE(n >= 0 && total_tiles >= 0, SD_EINVAL, "patch: n=%d tiles=%lld", n, (long long)total_tiles);
     if (n == 0 || total_tiles == 0) return SD_OK;
@@ -495,8 +507,10 @@ static int patch_launch(bool undo, const void* plan_dev, int32_t n, int64_t tota
     SD_REQUIRE(total_tiles < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch: %lld tiles exceed one grid", (long long)total_tiles);
     const PatchPlanEntry* plan = static_cast<const PatchPlanEntry*>(plan_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (undo) hipLaunchKernelGGL(lora_unpatch_kernel, dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(PT_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
-    else hipLaunchKernelGGL(lora_patch_kernel, dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(PT_THREADS), 0, s, plan, n);
+    if (undo) hipLaunchKernelGGL(lora_unpatch_kernel, dim3((unsigned)total_tiles), dim3(UNPATCH_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
+    else if (total_tiles <= SINGLE_3_STAGES) hipLaunchKernelGGL((lora_patch_kernel<1, 3>), dim3((unsigned)total_tiles), dim3(128), 0, s, plan, n);
+    else if (total_tiles <= SINGLE_2_STAGES) hipLaunchKernelGGL((lora_patch_kernel<1, 2>), dim3((unsigned)total_tiles), dim3(128), 0, s, plan, n);
+    else hipLaunchKernelGGL((lora_patch_kernel<2, 3>), dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(256), 0, s, plan, n);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }
@@ -554,8 +568,10 @@ static int patch_multi_launch(bool undo, const void* plan_dev, int32_t n, int64_
     SD_REQUIRE(total_tiles < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch: %lld tiles exceed one grid", (long long)total_tiles);
     const PatchMultiEntry* plan = static_cast<const PatchMultiEntry*>(plan_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (undo) hipLaunchKernelGGL(lora_unpatch_multi_kernel, dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(PT_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
-    else hipLaunchKernelGGL(lora_patch_multi_kernel, dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(PT_THREADS), 0, s, plan, n);
+    if (undo) hipLaunchKernelGGL(lora_unpatch_multi_kernel, dim3((unsigned)total_tiles), dim3(UNPATCH_THREADS), UNPATCH_MULTI_THROTTLE_LDS, s, plan, n);
+    else if (total_tiles <= SINGLE_3_STAGES) hipLaunchKernelGGL((lora_patch_multi_kernel<1, 3>), dim3((unsigned)total_tiles), dim3(128), 0, s, plan, n);
+    else if (total_tiles <= SINGLE_2_STAGES) hipLaunchKernelGGL((lora_patch_multi_kernel<1, 2>), dim3((unsigned)total_tiles), dim3(128), 0, s, plan, n);
+    else hipLaunchKernelGGL((lora_patch_multi_kernel<2, 2>), dim3((unsigned)((total_tiles + n + 1) >> 1)), dim3(256), 0, s, plan, n);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }

@@ -677,6 +677,42 @@ def test_patch_any_rank_any_row_length(B, out, in_, ranks):
     assert Wm.cpu().numpy().tobytes() == W.tobytes()
 
 
+# the number of tiles decides how a pass is cut into workgroups (up to 512, up to 768, more): each cut under ranks of half a
+# chunk, one, several, and a B at 4-byte addresses; matrices with an odd and an even number of 32-row tiles, columns off the tile
+@pytest.mark.parametrize("tiles", [500, 760, 1000])
+@pytest.mark.parametrize("ranks", [(8,), (20,), (64,), (33,), (8, 40), (32, 8, 7)])
+def test_patch_every_cut_into_workgroups(B, tiles, ranks):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(tiles + sum(ranks))
+    normal = lambda *shape: torch.empty(shape, device="cuda").normal_(0.0, 0.02, generator=g)
+    mats, left = [], tiles
+    for out, in_ in [(96, 516), (64, 256), (33, 1024), (70, 260), (96, 1030)] * 100:
+        left -= ((out + 31) // 32) * ((in_ + 255) // 256)
+        if left < 0:
+            break
+        mats.append((normal(out, in_), [(normal(rk, in_), normal(out, rk), sc) for rk, sc in zip(ranks, (1.0, -0.5, 2.0))]))
+    first = [W.clone() for W, _ in mats]
+    undo = [torch.zeros_like(W) for W, _ in mats]
+    S = [torch.zeros(W.shape, dtype=torch.bfloat16, device="cuda") for W, _ in mats]
+    plan = B.PatchMultiPlan([(W, u, s, ads) for (W, ads), u, s in zip(mats, undo, S)])
+    assert tiles - 20 < plan.total_tiles <= tiles
+    B.lora_patch_multi(plan)
+    single = [W.clone() for W in first]
+    for a in range(len(ranks)):
+        B.lora_patch(B.PatchPlan([(W, *ads[a][:2], torch.empty_like(W), ads[a][2]) for W, (_, ads) in zip(single, mats)]))
+    for (W, ads), W0, Ws, u, s in zip(mats, first, single, undo, S):
+        ref = W0.double()
+        for A, Bm, sc in ads:
+            ref += sc * (Bm.double() @ A.double())
+        assert float((W.double() - ref).abs().max() / ref.abs().max()) <= PATCH_TOL
+        assert float((W0.double() - ref).abs().max() / ref.abs().max()) > 10 * PATCH_TOL
+        assert torch.equal(W, Ws) and torch.equal(u, W0) and torch.equal(s, W.to(torch.bfloat16))
+    B.lora_unpatch_multi(plan)
+    for (W, _), W0, s in zip(mats, first, S):
+        assert torch.equal(W, W0) and torch.equal(s, W0.to(torch.bfloat16))
+
+
 def test_patch_matrix_of_more_than_2_to_the_30_elements(B):
     """Byte offsets past 2^32: the first, middle and last rows against float64 sums."""
     import torch
