@@ -114,6 +114,9 @@ int32_t sd_version(void);
  *   the data of that call and of everything computed from it; the forward call itself has long
  *   returned SD_OK by then (calls only enqueue).  *count receives how many tiles, since the library
  *   was loaded, ran out of spins: 0 unless the protocol is broken.
+ *   A captured call some of whose tiles ran out of spins may go on answering its replays with NaN,
+ * and counting them, until its workspace is cleared or the call captured anew: what its producers
+ * wrote late must not be taken for the next replay's.
  *   count: host.  This call synchronises the device: a serving loop polls it once per request,
  *   after the request's last step, not per step. */
 int sd_gemm_dep_timeouts(int64_t* count);

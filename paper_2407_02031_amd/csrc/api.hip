@@ -182,7 +182,9 @@ static int layernorm(const void* x, int x_f32, const uint16_t* g, const uint16_t
 
 // A number that a dependency record holds only if a producer of this launch wrote it there: what is in
 // the memory before is anyone's, but equal to it with a chance of 2^-64; and no two launches of a process
-// have the same.  A replayed launch keeps its number, and every launch leaves its records without it.
+// have the same.  A replayed launch keeps its number; every launch leaves its records without it, or, where a
+// tile gave up waiting, marked (dep_record.hpp).  The sequence is SplitMix64 (Steele, Lea, Flood: Fast
+// splittable pseudorandom number generators), from a start that differs from process to process.
 static uint64_t next_nonce() {
     static std::atomic<uint64_t> count{[] {
         uint64_t s = (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count();

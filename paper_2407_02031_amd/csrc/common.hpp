@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "../../include/swiftdiff.h"
+#include "dep_record.hpp"
 
 namespace sd {
 
@@ -137,14 +138,10 @@ struct GemmProblem {
     // t = t_scale * x A^T by itself.
     float t_scale;
     int32_t readers;                           // filled by the launcher: tiles that wait for one row block
-    // nonce != 0: signal and wait are records of DEP_RECORD bytes per row-tile index that need not be
-    // zero when the launch starts (a random number says that a producer of this launch wrote them) and
-    // hold no such number any more when it ends; at most two column tiles of producers, wait_cols 0.
+    // nonce != 0: signal and wait are dependency records (dep_record.hpp), one per row-tile index, that need
+    // not be zero when the launch starts; at most DEP_PRODUCERS column tiles of producers, wait_cols 0.
     uint64_t nonce;
 };
-// one record: a 64-bit word for each of the producer's column tiles, then the 32-bit count of tiles that
-// have seen them all
-constexpr int DEP_RECORD = 32;
 
 constexpr int GEMM_MAX_PROBLEMS = 16;
 struct GemmGroup {

@@ -32,6 +32,12 @@ constexpr int EPI_STRIDE = 72;   // floats per staged row: 4 rows apart differ b
 // broken): the wait is bounded so that every wavefront exits whatever happens.
 __device__ unsigned long long g_gemm_dep_timeouts = 0;
 constexpr int DEP_SPIN_LIMIT = 1 << 19;
+struct DeviceMem {
+    __device__ __forceinline__ static uint64_t load64(const uint64_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ static void store64(uint64_t* p, uint64_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ static void store32(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+    __device__ __forceinline__ static int32_t add32(int32_t* p, int32_t v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+};
 // Tiles of signalling problems (down-projections, N = rank) run a body of their own inside the
 // same kernel: BN = 64 instead of the launch's BN, which frees LDS for a deeper ring.  Other
 // tiles of the launch wait for these, and what a down-projection tile spends is latency per
@@ -98,11 +104,12 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
     // have run on another XCD.
     const int32_t* const wflag = K1 ? P.wait : nullptr;
     const int32_t* fptr = nullptr;
-    // with a nonce: the record of this row block, lane l looks at the word of column tile l
-    const uint64_t* const rec = wflag && P.nonce ? reinterpret_cast<const uint64_t*>(wflag) + tm * (DEP_RECORD / 8) : nullptr;
+    // with a nonce: the record of this row block, and the word of it that this lane looks at
+    uint64_t* const rec = wflag && P.nonce ? reinterpret_cast<uint64_t*>(const_cast<int32_t*>(wflag)) + tm * (DEP_RECORD / 8) : nullptr;
+    const uint64_t* const rword = rec + dep_record_word(lane, P.wait_need);
     bool f_early = true;
     if (rec) {
-        f_early = __hip_atomic_load(rec + min(lane, P.wait_need - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == P.nonce;
+        f_early = dep_record_ready(lane, P.wait_need, DeviceMem::load64(rword), P.nonce);
     } else if (wflag) {
         const int lo = P.wait_cols ? n0 : m0;
         const int hi = P.wait_cols ? min(n0 + BN_OUT, N) : min(m0 + BM, Mp);
@@ -179,11 +186,18 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
             // the producer's tiles were dispatched before this one and wait for nothing, so
             // this ends; the bound is there so that it ends even if that reasoning is wrong
             for (int spins = 0;; ++spins) {
-                const bool seen = rec ? __hip_atomic_load(rec + min(lane, P.wait_need - 1), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == P.nonce
-                                      : __hip_atomic_load(fptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= P.wait_need;
+                bool seen, given_up = false;
+                if (rec) {
+                    const uint64_t v = DeviceMem::load64(rword);
+                    seen = dep_record_ready(lane, P.wait_need, v, P.nonce);
+                    given_up = dep_record_given_up(lane, P.wait_need, v, P.nonce);
+                } else {
+                    seen = __hip_atomic_load(fptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= P.wait_need;
+                }
                 if (__all(seen)) break;
-                if (spins >= DEP_SPIN_LIMIT) {
+                if (spins >= DEP_SPIN_LIMIT || __any(given_up)) {
                     if (tid == 0) atomicAdd(&g_gemm_dep_timeouts, 1ull);
+                    if (rec && lane == 0) DepRecord<DeviceMem>::give_up(rec, P.nonce);
                     timed_out = true;
                     break;
                 }
@@ -374,11 +388,10 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
     }
     multiply(1, no_load, 0, 0);
     __syncthreads();   // ring reads done before the epilogue reuses LDS
-    // a record's last reader takes the nonce out again: a replay of this launch finds none.  (Every wavefront
-    // of the tile has seen the words by now; the count was zeroed before the first of them was written.)
-    int32_t* const seen_by = rec ? reinterpret_cast<int32_t*>(const_cast<uint64_t*>(rec) + 2) : nullptr;
+    // a record's last reader takes the nonce out again.  (Every wavefront of the tile has seen the words by
+    // now, or has given up; the count was zeroed before the first of them was written.)
     int readers_before = -1;
-    if (rec && tid == 0) readers_before = __hip_atomic_fetch_add(seen_by, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (rec && tid == 0) readers_before = DepRecord<DeviceMem>::leave(rec);
 
     // ---- epilogue
     float* stage = reinterpret_cast<float*>(lds) + wave * 32 * EPI_STRIDE;
@@ -545,19 +558,16 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
             __builtin_amdgcn_wave_barrier();
         }
     }
-    if (rec && tid == 0 && readers_before == P.readers - 1) {
-        __hip_atomic_store(const_cast<uint64_t*>(rec), (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(const_cast<uint64_t*>(rec) + 1, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (rec && tid == 0 && readers_before == P.readers - 1) DepRecord<DeviceMem>::clear(rec);
     // ---- tell the tiles that wait for this one: every wave's stores have completed at device
     // scope (vmcnt counts a device-scope store until it is visible there), then one flag add, or
-    // the nonce in this column tile's word (the first one's writer zeroes the readers' count before)
+    // the nonce in this column tile's word
     if (sig && P.nonce) {
         uint64_t* const w = reinterpret_cast<uint64_t*>(sig) + tm * (DEP_RECORD / 8);
-        if (tid == 0 && tn == 0) __hip_atomic_store(reinterpret_cast<int32_t*>(w + 2), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) DepRecord<DeviceMem>::open(w, tn);
         wait_vmcnt<0>();
         __syncthreads();
-        if (tid == 0) __hip_atomic_store(w + tn, P.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) DepRecord<DeviceMem>::publish(w, tn, P.nonce);
     } else if (sig) {
         wait_vmcnt<0>();
         __syncthreads();
@@ -642,7 +652,7 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
             SD_REQUIRE(!P.y_f32 && !P.res && !P.wait && P.N % 4 == 0 && P.ldy % 4 == 0 && P.geglu_F == 0, SD_EINVAL,
                        "gemm problem %d: a signalling problem stores plain bf16 rows", i);
         }
-        SD_REQUIRE(!P.nonce || (P.signal ? P.N <= 2 * DOWN_BN : (P.wait && !P.wait_cols && P.K1 <= 2 * DOWN_BN)), SD_EINVAL,
+        SD_REQUIRE(!P.nonce || (P.signal ? P.N <= DEP_PRODUCERS * DOWN_BN : (P.wait && !P.wait_cols && P.K1 <= DEP_PRODUCERS * DOWN_BN)), SD_EINVAL,
                    "gemm problem %d: what a dependency record does not hold", i);
         SD_REQUIRE(!P.wait || (P.K1 > 0 && g.p[0].signal), SD_EINVAL, "gemm problem %d waits but the group has no producer", i);
         if (P.Mp == 0 || P.N == 0) continue;
