@@ -127,6 +127,13 @@ int sd_gemm_dep_timeouts(int64_t* count);
  * previous setting.  Process-wide, not thread-safe against concurrent forward calls. */
 int32_t sd_set_projection_fusion(int32_t on);
 
+/* Which kernels would run?  Between sd_dry_run(1) and sd_dry_run(0) the forward calls of this thread (projections,
+ * attention, sub-layers, GroupNorm, the stack, patches) check their arguments and choose their kernels as ever, but launch nothing:
+ * they write the names of what they would launch to sd_dry_run_text, in order, and need no device.  For tests that
+ * are meant for one kernel, and for reading a dispatch rule at a size.  Returns the previous setting. */
+int32_t sd_dry_run(int32_t on);
+const char* sd_dry_run_text(void);
+
 /* ---- instrumentation (off by default) --------------------------------------------------
  * Measurement support for the roofline figures: when enabled, the sub-layer and stack calls
  * record a HIP event on their stream immediately before and after the launch of the kernels

@@ -8,6 +8,7 @@ import fails: there is no fallback path.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes as C
 import os
 from typing import List, Optional, Sequence
@@ -76,6 +77,8 @@ def _load() -> C.CDLL:
     sig = {
         "sd_last_error": (C.c_char_p, []),
         "sd_version": (i32, []),
+        "sd_dry_run": (i32, [i32]),
+        "sd_dry_run_text": (C.c_char_p, []),
         "sd_gemm_dep_timeouts": (C.c_int, [P(i64)]),
         "sd_set_projection_fusion": (i32, [i32]),
         "sd_timing_enable": (C.c_int, [i32]),
@@ -129,7 +132,7 @@ def _load() -> C.CDLL:
 
 
 _lib = _load()
-EXPORTS = ["sd_last_error", "sd_version", "sd_gemm_dep_timeouts", "sd_set_projection_fusion", "sd_timing_enable", "sd_timing_collect", "sd_timing_disable", "sd_ceiling_mfma_bf16", "sd_ceiling_copy_f32", "sd_ceiling_copy_1r2w_f32", "sd_ceiling_valu",
+EXPORTS = ["sd_last_error", "sd_version", "sd_dry_run", "sd_dry_run_text", "sd_gemm_dep_timeouts", "sd_set_projection_fusion", "sd_timing_enable", "sd_timing_collect", "sd_timing_disable", "sd_ceiling_mfma_bf16", "sd_ceiling_copy_f32", "sd_ceiling_copy_1r2w_f32", "sd_ceiling_valu",
            "sd_lora_linear_workspace_bytes", "sd_lora_linear_fwd", "sd_lora_linear_fwd_static",
            "sd_attn_block_workspace_bytes", "sd_attn_block_fwd", "sd_attention_workspace_bytes", "sd_attention_fwd", "sd_ff_block_workspace_bytes",
            "sd_ff_block_fwd", "sd_groupnorm_workspace_bytes", "sd_groupnorm_fwd", "sd_groupnorm_silu_fwd",
@@ -146,6 +149,18 @@ def lib() -> C.CDLL:
 
 def set_projection_fusion(on: bool) -> bool:
     return bool(_lib.sd_set_projection_fusion(1 if on else 0))
+
+
+@contextlib.contextmanager
+def dry_run():
+    """Forward calls inside launch nothing; the list that this yields holds the kernels they would launch afterwards."""
+    names: list = []
+    _lib.sd_dry_run(1)
+    try:
+        yield names
+    finally:
+        _lib.sd_dry_run(0)
+        names.extend(n.strip() for n in _lib.sd_dry_run_text().decode().split(";") if n.strip())
 
 
 def gemm_dep_timeouts() -> int:

@@ -25,6 +25,17 @@ int hip_fail(hipError_t e, const char* what) {
     return SD_EHIP;
 }
 
+thread_local bool g_dry_run = false;
+static thread_local char g_dry_text[4096] = "";
+bool dry_note(const char* fmt, ...) {
+    const size_t n = strlen(g_dry_text);
+    va_list ap;
+    va_start(ap, fmt);
+    vsnprintf(g_dry_text + n, sizeof(g_dry_text) - n, fmt, ap);
+    va_end(ap);
+    return true;
+}
+
 // ---------------------------------------------------------------------------------------
 // optional instrumentation: HIP events around selected kernel launches (off by default)
 // ---------------------------------------------------------------------------------------
@@ -461,6 +472,13 @@ extern "C" int32_t sd_set_projection_fusion(int32_t on) {
     g_fuse_attention_merge = on != 0;
     return was;
 }
+extern "C" int32_t sd_dry_run(int32_t on) {
+    const int32_t was = g_dry_run ? 1 : 0;
+    if (on) g_dry_text[0] = 0;
+    g_dry_run = on != 0;
+    return was;
+}
+extern "C" const char* sd_dry_run_text(void) { return g_dry_text; }
 extern "C" int sd_gemm_dep_timeouts(int64_t* count) {
     SD_REQUIRE(count, SD_EINVAL, "gemm_dep_timeouts: null count");
     long long v = 0;

@@ -641,6 +641,8 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     // ahead at 77 too (a 32 x 32 stack 2690 for 2760); plain keys 355 for 372 at 8 x 3929 x 10 heads, 116 for 123 at
     // 8 x 1434 x 20, 22.7 for 22.9 at 2 x 1330 x 10, but 59.7 for 57.6 at 8 x 988 x 20.
     const int nt = (Tk + 63) / 64;
+    *cut_tiles = arrived ? 0 : nsplit;
+    if (SD_DRY_RUN("attention%s%s%s; ", k_prescaled ? " prescaled" : "", k_prescaled || nt >= 20 ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "")) return SD_OK;
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(nfull + 2 * nsplit)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
                            qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived);
@@ -649,13 +651,12 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     else if (nt >= 20) go(attention_kernel<false, true>);
     else go(attention_kernel<false, false>);
     SD_HIP_CHECK(hipGetLastError());
-    *cut_tiles = arrived ? 0 : nsplit;
     return SD_OK;
 }
 
 int launch_attention_merge(const void* scratch, uint16_t* out, int64_t ldo, int Bn, int Tq, int heads, bool k_prescaled, int cut_tiles,
                            hipStream_t stream) {
-    if (cut_tiles <= 0) return SD_OK;
+    if (cut_tiles <= 0 || SD_DRY_RUN("merge; ")) return SD_OK;
     // the halves' maxima are in score units, or already in exponent units when the keys were prescaled
     const float c = k_prescaled ? 1.0f : 0.125f * 1.44269504088896340736f;
     const int qtiles = (Tq + 127) / 128;

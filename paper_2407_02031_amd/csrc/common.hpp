@@ -80,6 +80,12 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
 void set_error(const char* fmt, ...);
 int hip_fail(hipError_t e, const char* what);
 
+// Dry runs (sd_dry_run): the launch sites of the forward calls ask first, and on a dry run write down what they
+// would launch instead of launching it.
+extern thread_local bool g_dry_run;
+bool dry_note(const char* fmt, ...);   // true
+#define SD_DRY_RUN(...) (__builtin_expect(::sd::g_dry_run, 0) && ::sd::dry_note(__VA_ARGS__))
+
 #define SD_HIP_CHECK(expr)                                         \
     do {                                                           \
         hipError_t _e = (expr);                                    \

@@ -613,6 +613,9 @@ static int launch_cfg(GemmGroup& g, bool guard, hipStream_t stream) {
     }
     g.total_tiles = total;
     if (total == 0) return SD_OK;
+    if (SD_DRY_RUN("gemm %dx%d/%d waves/%d stages%s%s%s%s; ", BM, BN, WGM * WGN, STAGES, GEGLU ? " geglu" : "", RES32 ? " res32" : "", guard ? " guard" : "",
+                   !g.p[0].signal ? "" : g.p[0].nonce ? " records" : " flags"))
+        return SD_OK;
     if (guard)
         hipLaunchKernelGGL((gemm_kernel<BM, BN, BK, WGM, WGN, STAGES, GEGLU, true, RES32>), dim3(g.n_lead + ((total - g.n_lead + 7) & ~7)), dim3(64 * WGM * WGN), 0, stream, g);
     else
@@ -726,7 +729,7 @@ __global__ void clear_flags_kernel(int32_t* p, int n) {
     if (i < n) p[i] = 0;
 }
 int launch_clear_flags(int32_t* p, int n, hipStream_t stream) {
-    if (n <= 0) return SD_OK;
+    if (n <= 0 || SD_DRY_RUN("clear; ")) return SD_OK;
     hipLaunchKernelGGL(clear_flags_kernel, dim3((n + 255) / 256), dim3(256), 0, stream, p, n);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;

@@ -387,7 +387,7 @@ static int launch16(GemmGroup& g, hipStream_t stream) {
         total += P.tiles_m * P.tiles_n;
     }
     g.total_tiles = total;
-    if (total == 0) return SD_OK;
+    if (total == 0 || SD_DRY_RUN("gemm16 %dx%d/%d; ", BM, BN, NRB)) return SD_OK;
     hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB>), dim3((total + 7) & ~7), dim3(64 * WGM * WGN * WGK), 0, stream, g);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;

@@ -264,6 +264,7 @@ __global__ __launch_bounds__(512, 2) void down_kernel(const uint16_t* __restrict
     }
 }
 int launch_down(const uint16_t* x, int64_t ldx, const uint16_t* A, float scale, uint16_t* t, int M, int K, int r, hipStream_t stream) {
+    if (SD_DRY_RUN("down; ")) return SD_OK;
     hipLaunchKernelGGL(down_kernel, dim3((M + DN_BM - 1) / DN_BM, (r + DN_BN - 1) / DN_BN), dim3(512), 0, stream, x, ldx, A, scale, t, M, K, r);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
@@ -277,6 +278,7 @@ static int launch_geglu_mi(GemmGroup& g, hipStream_t stream) {
     P.tile_begin = g.first_tile[0] = 0;
     g.n_lead = 0;
     g.total_tiles = P.tiles_m * P.tiles_n;
+    if (SD_DRY_RUN("geglu %dx160; ", MI * 128)) return SD_OK;
     hipLaunchKernelGGL((gemm_geglu_kernel<MI>), dim3((g.total_tiles + 7) & ~7), dim3(512), 0, stream, g);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;

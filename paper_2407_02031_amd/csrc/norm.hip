@@ -111,6 +111,7 @@ int launch_layernorm(const void* x, int x_f32, const uint16_t* gamma, const uint
     SD_REQUIRE(C % 4 == 0 && C > 0 && C <= 64 * 4 * LN_MAXJ, SD_EUNSUPPORTED, "layernorm: C=%d (need C %% 4 == 0, C <= %d)", C,
                64 * 4 * LN_MAXJ);
     if (M <= 0) return zero_n > 0 ? launch_clear_flags(zero_ptr, zero_n, stream) : SD_OK;
+    if (SD_DRY_RUN("layernorm%s; ", zero_n > 0 ? " clear" : "")) return SD_OK;
     if (C <= 768) {          // SDXL's 320 and 640 channels: three chunks per lane
         if (x_f32) launch_ln<true, 3, LN_ROWS>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream);
         else launch_ln<false, 3, LN_ROWS>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream);
@@ -151,13 +152,13 @@ __global__ __launch_bounds__(256) void cvt_f32_bf16_kernel(const float* __restri
     }
 }
 int launch_cvt_bf16_to_f32(const uint16_t* x, float* y, size_t n, hipStream_t stream) {
-    if (!n) return SD_OK;
+    if (!n || SD_DRY_RUN("convert; ")) return SD_OK;
     hipLaunchKernelGGL(cvt_bf16_f32_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, x, y, n);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }
 int launch_cvt_f32_to_bf16(const float* x, uint16_t* y, size_t n, hipStream_t stream) {
-    if (!n) return SD_OK;
+    if (!n || SD_DRY_RUN("convert; ")) return SD_OK;
     hipLaunchKernelGGL(cvt_f32_bf16_kernel, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, stream, x, y, n);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
@@ -393,7 +394,7 @@ int launch_groupnorm(const uint16_t* x, uint16_t* y, const uint16_t* gamma, cons
     SD_REQUIRE(groups > 0 && C % groups == 0 && (C / groups) % 2 == 0, SD_EUNSUPPORTED,
                "groupnorm: C=%d groups=%d (need an even number of channels per group)", C, groups);
     SD_REQUIRE(C <= 2048, SD_EUNSUPPORTED, "groupnorm: C=%d > 2048", C);
-    if (Bn <= 0 || T <= 0) return SD_OK;
+    if (Bn <= 0 || T <= 0 || SD_DRY_RUN("groupnorm; ")) return SD_OK;
     return C % 8 == 0 ? launch_gn<8>(x, y, gamma, beta, Bn, T, C, groups, eps, partials, stream, silu)
                       : launch_gn<2>(x, y, gamma, beta, Bn, T, C, groups, eps, partials, stream, silu);
 }

@@ -507,6 +507,8 @@ static int patch_launch(bool undo, const void* plan_dev, int32_t n, int64_t tota
     SD_REQUIRE(total_tiles < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch: %lld tiles exceed one grid", (long long)total_tiles);
     const PatchPlanEntry* plan = static_cast<const PatchPlanEntry*>(plan_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (SD_DRY_RUN(undo ? "unpatch; " : total_tiles <= SINGLE_3_STAGES ? "patch 1 tile/3 stages; " : total_tiles <= SINGLE_2_STAGES ? "patch 1 tile/2 stages; " : "patch 2 tiles/3 stages; "))
+        return SD_OK;
     if (undo) hipLaunchKernelGGL(lora_unpatch_kernel, dim3((unsigned)total_tiles), dim3(UNPATCH_THREADS), UNPATCH_THROTTLE_LDS, s, plan, n);
     else if (total_tiles <= SINGLE_3_STAGES) hipLaunchKernelGGL((lora_patch_kernel<1, 3>), dim3((unsigned)total_tiles), dim3(128), 0, s, plan, n);
     else if (total_tiles <= SINGLE_2_STAGES) hipLaunchKernelGGL((lora_patch_kernel<1, 2>), dim3((unsigned)total_tiles), dim3(128), 0, s, plan, n);
@@ -568,6 +570,8 @@ static int patch_multi_launch(bool undo, const void* plan_dev, int32_t n, int64_
     SD_REQUIRE(total_tiles < (int64_t)0x7fffffff, SD_EUNSUPPORTED, "patch: %lld tiles exceed one grid", (long long)total_tiles);
     const PatchMultiEntry* plan = static_cast<const PatchMultiEntry*>(plan_dev);
     hipStream_t s = static_cast<hipStream_t>(stream);
+    if (SD_DRY_RUN(undo ? "unpatch multi; " : total_tiles <= SINGLE_3_STAGES ? "patch multi 1 tile/3 stages; " : total_tiles <= SINGLE_2_STAGES ? "patch multi 1 tile/2 stages; " : "patch multi 2 tiles/2 stages; "))
+        return SD_OK;
     if (undo) hipLaunchKernelGGL(lora_unpatch_multi_kernel, dim3((unsigned)total_tiles), dim3(UNPATCH_THREADS), UNPATCH_MULTI_THROTTLE_LDS, s, plan, n);
     else if (total_tiles <= SINGLE_3_STAGES) hipLaunchKernelGGL((lora_patch_multi_kernel<1, 3>), dim3((unsigned)total_tiles), dim3(128), 0, s, plan, n);
     else if (total_tiles <= SINGLE_2_STAGES) hipLaunchKernelGGL((lora_patch_multi_kernel<1, 2>), dim3((unsigned)total_tiles), dim3(128), 0, s, plan, n);

@@ -1,0 +1,64 @@
+"""Which kernels the forward calls choose, read off without a GPU: on a dry run a call checks its arguments, takes its
+decisions and launches nothing.  The pointers are made up and never followed."""
+import ctypes as C
+import os
+import threading
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_2407_02031_amd", "libswiftdiff.so")
+BF16, F32 = 0, 1
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not os.path.exists(LIB):
+        from paper_2407_02031_amd import build
+        build.build(verbose=False)
+    from paper_2407_02031_amd import binding
+    return binding
+
+
+def linear(B, M, K, N, r=0, ln=False, geglu=False, res=False, f32=False):
+    """The kernels of one projection."""
+    L = B.lib()
+    p = B.sd_proj(0x10000, 0x20000, 0x30000 if r else None, 0x40000 if r else None, r, 1.0)
+    need = L.sd_lora_linear_workspace_bytes(M, N, K, r, int(ln))
+    g = 0x50000 if ln else None
+    with B.dry_run() as names:
+        rc = L.sd_lora_linear_fwd(0x60000, BF16, C.byref(p), g, g, 1e-5, 0x70000 if res else None, 0x80000, F32 if f32 else BF16, int(geglu), M, N, K, 0x100000, need, None)
+    assert rc == 0, L.sd_last_error()
+    return names
+
+
+def test_dry_run_launches_nothing_and_belongs_to_its_thread(B):
+    L = B.lib()
+    assert linear(B, 300, 328, 200) == ["gemm 64x128/4 waves/3 stages guard"]
+    assert linear(B, 300, 328, 200, r=200) == ["clear", "gemm 64x128/4 waves/3 stages guard flags"]
+    assert linear(B, 300, 328, 200, r=128) == ["gemm 64x128/4 waves/3 stages guard records"]
+    assert linear(B, 300, 328, 200, r=8, ln=True)[0] == "layernorm clear"
+    assert linear(B, 0, 328, 200) == []
+    seen = []
+    with B.dry_run() as mine:
+        t = threading.Thread(target=lambda: seen.append((L.sd_dry_run(0), L.sd_dry_run_text())))
+        t.start()
+        t.join()
+        assert L.sd_lora_patch(0x1000, 1, 10, None) == 0
+    assert seen == [(0, b"")] and mine == ["patch 1 tile/3 stages"]
+    with B.dry_run() as names:
+        assert L.sd_attention_fwd(0x1000, 0x2000, 0x3000, 0x4000, 2, 64, 1300, 128, 2, None, 0, None) == 0
+        assert L.sd_attention_fwd(0x1000, 0x2000, 0x3000, 0x4000, 2, 64, 1216, 128, 2, None, 0, None) == 0
+        assert L.sd_attention_fwd(0x1000, 0x2000, 0x3000, 0x4008, 2, 64, 1216, 128, 2, None, 0, None) == -1
+    assert names == ["attention try", "attention"]
+
+
+@pytest.mark.parametrize("tiles,single,multi", [(1, "1 tile/3 stages", "1 tile/3 stages"), (512, "1 tile/3 stages", "1 tile/3 stages"), (513, "1 tile/2 stages", "1 tile/2 stages"),
+                                                (768, "1 tile/2 stages", "1 tile/2 stages"), (769, "2 tiles/3 stages", "2 tiles/2 stages"), (100000, "2 tiles/3 stages", "2 tiles/2 stages")])
+def test_patch_cuts(B, tiles, single, multi):
+    L = B.lib()
+    with B.dry_run() as names:
+        L.sd_lora_patch(0x1000, 1, tiles, None)
+        L.sd_lora_patch_multi(0x1000, 1, tiles, None)
+        L.sd_lora_unpatch(0x1000, 1, tiles, None)
+    assert names == ["patch " + single, "patch multi " + multi, "unpatch"]
