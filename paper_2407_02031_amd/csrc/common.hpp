@@ -169,6 +169,10 @@ bool gemm16_takes(const GemmGroup& g, bool flags_clean);
 int launch_gemm16(GemmGroup& g, bool flags_clean, hipStream_t stream);
 // t = scale * x A^T (x [M, K], A [r, K], t bf16 [M, r]) by itself, in the time of a short launch; K % 64 == 0
 int launch_down(const uint16_t* x, int64_t ldx, const uint16_t* A, float scale, uint16_t* t, int M, int K, int r, hipStream_t stream);
+// Tiles of a feed-forward in-projection [M, K] -> [M, F] with an adapter of rank r (0: none): rows x output columns.
+// The WIDE ones are gemm_geglu's, the others the general kernel's.
+enum GegluTiles { GEGLU_64x64_3STAGES, GEGLU_64x64, GEGLU_128x64, GEGLU_256x128, GEGLU_WIDE_256x160, GEGLU_WIDE_128x160 };
+GegluTiles geglu_tiles(int M, int F, int K, int r, bool wide_ok);
 // One GEGLU projection that gemm_geglu_takes; its down-projection, if any, has been computed.
 bool gemm_geglu_takes(const GemmProblem& P);
 int launch_gemm_geglu(GemmGroup& g, hipStream_t stream);

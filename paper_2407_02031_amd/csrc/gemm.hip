@@ -633,6 +633,7 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     double lead = 0;      // down-projection tiles of 128 rows: workgroups too, ahead of the others
     double depth = 0;     // K, summed over those tiles
     long t128 = 0, t256 = 0;   // workgroup tiles of 128 and 256 rows x 128 output columns, down-projections aside
+    int gM = 0, gF = 0, gK = 0, gr = 0;   // the GEGLU problems: rows in all, largest F, K and rank
     bool res32 = false;   // some problem adds an fp32 residual: take the kernel that prefetches it
     int n_main = 0;       // problems that are not down-projections
     for (int i = 0; i < g.n; ++i) {
@@ -661,6 +662,12 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
         if (P.Mp == 0 || P.N == 0) continue;
         if ((P.K0 & 63) || (P.K1 & 63)) guard = true;
         if (P.N > maxN) maxN = P.N;
+        if (P.geglu_F > 0) {
+            gM += P.Mp;
+            gF = P.N > gF ? P.N : gF;
+            gK = P.K0 > gK ? P.K0 : gK;
+            gr = P.K1 > gr ? P.K1 : gr;
+        }
         if (!P.signal) t128 += (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
         if (!P.signal) t256 += (long)((P.Mp + 255) / 256) * ((P.N + 127) / 128);
         if (P.signal) lead += (double)((P.Mp + 127) / 128) * ((P.N + DOWN_BN - 1) / DOWN_BN);
@@ -677,49 +684,46 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     // as its most loaded CU; so: the largest tiles that still give every CU the same number of them.
     // Times below are single projections of rank 64, us, measured on one machine.
     const double meanK = t128 ? depth / t128 : 0;
-    // Down-projections (N = rank <= 64) alone: 64x64 tiles, 5-stage ring.  (A GEGLU group never takes
-    // this one: its tiles need the value / gate pairing, which the bodies below provide for any F.)
-    if (maxN <= 64 && !geglu) return launch_cfg<64, 64, 64, 2, 2, 5, false, false>(g, guard, stream);
+    // GEGLU: geglu_tiles (128 columns of W are 64 of the output)
+    if (geglu) switch (geglu_tiles(gM, gF, gK, gr, false)) {
+        case GEGLU_64x64_3STAGES: return launch_cfg<64, 128, 64, 2, 2, 3, true, false>(g, guard, stream);
+        case GEGLU_64x64: return launch_cfg<64, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
+        case GEGLU_256x128: return launch_cfg<256, 256, 64, 4, 2, 2, true, false>(g, guard, stream);
+        default: return launch_cfg<128, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
+        }
+    // Down-projections (N = rank <= 64) alone: 64x64 tiles, 5-stage ring.
+    if (maxN <= 64) return launch_cfg<64, 64, 64, 2, 2, 5, false, false>(g, guard, stream);
     if (t128 < 512) {
         // at most one 128x128 tile per CU, and most CUs have one: that tile with a deep ring, one
         // workgroup per CU (2048x1280x5120: 42.0, 53.7 with 64x128 tiles, of which 64 CUs get two)
         if (t128 > 128 && t128 + lead <= 256) {
-            if (geglu) return launch_cfg<128, 128, 64, 4, 2, 4, true, false>(g, guard, stream);
             if (res32) return launch_cfg<128, 128, 64, 4, 2, 4, false, true>(g, guard, stream);
             return launch_cfg<128, 128, 64, 4, 2, 4, false, false>(g, guard, stream);
         }
         // more than that, but at most one of 256x128 per CU, and no short K loop: those
         // (8192x640x2560: 41.1, 48.2 with 128x128 tiles; 4757x1280x1280: 26.4, 33.1 with 64x128;
         // at K = 640 the ramps of the larger tile lose: 24.1 against 21.0)
-        if (!geglu && t128 > 256 && t256 + lead / 2 <= 256 && meanK >= 1024) {
+        if (t128 > 256 && t256 + lead / 2 <= 256 && meanK >= 1024) {
             if (res32) return launch_cfg<256, 128, 64, 4, 2, 3, false, true>(g, guard, stream);
             return launch_cfg<256, 128, 64, 4, 2, 3, false, false>(g, guard, stream);
         }
         // few tiles: 64x128 spreads them over more CUs, two workgroups on a CU at most: three ring stages
         if (t128 <= 128) {
-            if (geglu) return launch_cfg<64, 128, 64, 2, 2, 3, true, false>(g, guard, stream);
             if (res32) return launch_cfg<64, 128, 64, 2, 2, 3, false, true>(g, guard, stream);
             return launch_cfg<64, 128, 64, 2, 2, 3, false, false>(g, guard, stream);
         }
-        // up to three on a CU where the K loop is short, or GEGLU's epilogue long and 128x128 tiles would leave
-        // most CUs with one and some with two (8192x640x640: 17.3, 18.3 with 128x128; 988x10240x1280 GEGLU: 35.7, 39.2)
-        if (t128 > 256 && (meanK < 1024 || (geglu && t128 <= 384))) {
-            if (geglu) return launch_cfg<64, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
+        // up to three on a CU where the K loop is short (8192x640x640: 17.3, 18.3 with 128x128)
+        if (t128 > 256 && meanK < 1024) {
             if (res32) return launch_cfg<64, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
             return launch_cfg<64, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
         }
     }
-    // The feed-forward in-projection at 8192 tokens: 256x256 tiles (128 output columns after GEGLU)
-    // of eight 64x128 wavefronts, one workgroup per CU, when that still gives every CU two rounds
-    // or more.  Half the operand bytes per FLOP from L2 and from LDS.
-    if (geglu && t256 >= 512) return launch_cfg<256, 256, 64, 4, 2, 2, true, false>(g, guard, stream);
     // One large plain projection with a long K loop (no launch of the transformer block: the
     // 8192 x 4096 x 4096 yardstick takes 224, 248 at 128x128).  Not for grouped
     // launches: the q/k/v group with its short text-context problems loses a third.
-    if (!geglu && !res32 && n_main == 1 && t256 >= 512 && meanK >= 2048) return launch_cfg<256, 256, 64, 4, 2, 2, false, false>(g, guard, stream);
-    // 128x128 tiles of four 64x64 wavefronts, two workgroups per CU (2048x10240x1280 GEGLU: 66.9, 75.3
-    // with 64x128, 68.3 with eight 32x64 wavefronts; 4757x1280x1280: 25.9, 33.1, 26.9)
-    if (geglu) return launch_cfg<128, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
+    if (!res32 && n_main == 1 && t256 >= 512 && meanK >= 2048) return launch_cfg<256, 256, 64, 4, 2, 2, false, false>(g, guard, stream);
+    // 128x128 tiles of four 64x64 wavefronts, two workgroups per CU (4757x1280x1280: 25.9, 33.1 with 64x128,
+    // 26.9 with eight 32x64 wavefronts)
     if (res32) return launch_cfg<128, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
     return launch_cfg<128, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
 }

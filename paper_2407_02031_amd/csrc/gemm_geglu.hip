@@ -283,28 +283,43 @@ static int launch_geglu_mi(GemmGroup& g, hipStream_t stream) {
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }
-// Rows per tile, or 0: the smaller tiles of the general kernel.  Estimates in us, fitted to launches of 4
-// to 21 steps on one machine: a round of 256 tiles takes 6 + 2.1 per step with 256 rows and 5.6 + 1.12
-// with 128; the general kernel's 64x128 tiles (64 output columns), or the larger ones that it
-// prefers, 6 + 0.30 per step and 64x128 tile on the most loaded CU.  (7904x5120x640: 72 general, 59.7 with 256 rows, 71.7 with 128; 988x10240x1280: 37.1,
-// 41.6, 30.6; 512x2560x320 + 8: 11.1, 25.7, 19.2.)
-static int geglu_rows(const GemmProblem& P) {
-    const double steps = P.K0 / 64 + (P.K1 + 63) / 64;
-    auto tiles = [&](int rows, int cols) { return (double)((P.Mp + rows - 1) / rows) * ((P.N + cols - 1) / cols); };
-    auto rounds = [&](double n) { return (double)(long)((n + 255) / 256); };
-    const double by256 = rounds(tiles(256, GG_OUT)) * (6.0 + 2.1 * steps);
-    const double by128 = rounds(tiles(128, GG_OUT)) * (5.6 + 1.12 * steps);
-    const double down = P.K1 ? 5.0 : 0.0;   // a launch of its own, where the general kernel hides it
-    const double general = 6.0 + 0.30 * steps * rounds(tiles(64, 64));
-    if (general <= by256 + down && general <= by128 + down) return 0;
-    return by256 < by128 ? 256 : 128;
+// Which tiles.  Up to four 64x64 tiles per CU, that many workgroups of the general kernel in one round: 64x64 (three
+// ring stages while there are at most two per CU and the K loop is not short), 128x64 from three on.  Beyond that the
+// estimate, us, that fits 600 launches of 154 to 16384 rows and C = 320 to 2048: rounds of workgroups over 256 CUs (128x64:
+// over two per CU), each with a fixed part and one per 64 deep step; the wide tiles' down-projection is a launch of its own
+// where the general kernel hides it.  Measured over those launches: 0.8 % slower than the best of the six in the mean, one in ten by
+// more than 3 %, none by more than 14.  (us with the LayerNorm in front, 64x64 with three stages / 64x64 / 128x64 / 256x128 / wide 256 /
+// wide 128: 2048x1280x320 15.1 13.2 14.3 19.8 21.9 16.1; 988x5120x1280 44.3 45.2 47.5 47.8 46.8 36.6; 7904x2560x640 88.3 85.7 76.4 85.4
+// 69.0 79.4; 7904x4096x2048 327 331 283 257 272 286.)
+GegluTiles geglu_tiles(int M, int F, int K, int r, bool wide_ok) {
+    const int k_steps = K / 64, steps = k_steps + (r + 63) / 64;
+    auto tiles = [&](int rows, int cols) { return (long)((M + rows - 1) / rows) * ((F + cols - 1) / cols); };
+    const long t64 = tiles(64, 64);
+    if (t64 <= 256) return k_steps <= 5 && r > 0 ? GEGLU_64x64 : GEGLU_64x64_3STAGES;
+    if (t64 <= 2 * 256) return k_steps <= 10 ? GEGLU_64x64 : GEGLU_64x64_3STAGES;
+    if (t64 <= 3 * 256) return GEGLU_64x64;
+    if (t64 <= 4 * 256) return GEGLU_128x64;
+    auto us = [&](long n, int slots, double fixed, double per_step) { return (double)((n + slots - 1) / slots) * (fixed + per_step * steps); };
+    const double down = r > 0 ? 3.5 + 1.7 * (double)((M + 31) / 32) * ((r + 63) / 64) / 256 : 0.0;
+    GegluTiles best = GEGLU_128x64;
+    double least = us(tiles(128, 64), 512, 3.8, 0.90);
+    auto consider = [&](GegluTiles t, double v) {
+        if (v < least) { least = v; best = t; }
+    };
+    consider(GEGLU_256x128, us(tiles(256, 128), 256, 7.3, 1.73));
+    if (wide_ok) {
+        consider(GEGLU_WIDE_256x160, us(tiles(256, GG_OUT), 256, 10.4, 1.75) + down);
+        consider(GEGLU_WIDE_128x160, us(tiles(128, GG_OUT), 256, 6.0, 1.08) + down);
+    }
+    return best;
 }
 bool gemm_geglu_takes(const GemmProblem& P) {
     return P.geglu_F == P.N && P.N > 0 && P.Mp > 0 && P.K0 % 64 == 0 && P.N % 8 == 0 && P.ldy % 8 == 0 && !P.y_f32 && !P.res && !P.bias_on_rows && aligned16(P.bias) && aligned16(P.y) &&
-           P.ldp0 * 512 < (1ll << 31) && P.ldq0 * 4 * P.N < (1ll << 32) && geglu_rows(P) > 0;
+           P.ldp0 * 512 < (1ll << 31) && P.ldq0 * 4 * P.N < (1ll << 32) && geglu_tiles(P.Mp, P.N, P.K0, P.K1, true) >= GEGLU_WIDE_256x160;
 }
 int launch_gemm_geglu(GemmGroup& g, hipStream_t stream) {
-    return geglu_rows(g.p[0]) == 256 ? launch_geglu_mi<2>(g, stream) : launch_geglu_mi<1>(g, stream);
+    const GemmProblem& P = g.p[0];
+    return geglu_tiles(P.Mp, P.N, P.K0, P.K1, true) == GEGLU_WIDE_256x160 ? launch_geglu_mi<2>(g, stream) : launch_geglu_mi<1>(g, stream);
 }
 
 }  // namespace sd

@@ -219,6 +219,39 @@ def test_lora_linear_geglu_wide_tiles(B, M, C, F, rank):
     assert rel_err(host(y)[rows], ref) <= BF16_TOL
 
 
+# each body of the in-projection, asserted to be the one that runs: the general kernel's four, with and without an adapter and
+# K or rank off 64, and the wide tiles of 256 and 128 rows with ragged rows and columns, one, two and more steps, an adapter
+# segment of less than 64 columns, of exactly 64 and of more, its down-projection with one and two column tiles and a last stage of
+# 320 that is full, partly filled and the only one
+@pytest.mark.parametrize("M,C,F,rank,kernel", [
+    (250, 1280, 2560, 24, "gemm 64x128/4 waves/3 stages geglu guard flags"), (130, 640, 1284, 0, "gemm 64x128/4 waves/3 stages geglu"),
+    (2000, 320, 1284, 64, "gemm 64x128/4 waves/2 stages geglu flags"), (1001, 328, 2564, 8, "gemm 64x128/4 waves/2 stages geglu guard flags"),
+    (1500, 640, 2564, 72, "gemm 128x128/4 waves/2 stages geglu guard flags"), (1500, 640, 2564, 0, "gemm 128x128/4 waves/2 stages geglu"),
+    (1490, 1280, 5124, 128, "gemm 256x256/8 waves/2 stages geglu flags"), (1490, 1288, 5124, 16, "gemm 256x256/8 waves/2 stages geglu guard flags"),
+    (3900, 64, 2552, 0, "geglu 256x160"), (7900, 128, 1272, 0, "geglu 256x160"), (2047, 128, 5112, 72, "geglu 256x160"), (3900, 192, 2552, 8, "geglu 256x160"),
+    (3900, 384, 2560, 64, "geglu 256x160"), (2047, 1280, 5120, 128, "geglu 256x160"),
+    (3900, 64, 1272, 0, "geglu 128x160"), (988, 192, 5112, 24, "geglu 128x160"), (3900, 320, 1272, 72, "geglu 128x160"), (988, 1280, 5120, 16, "geglu 128x160"),
+    (1000, 640, 5120, 72, "geglu 128x160"), (988, 1344, 5112, 64, "geglu 128x160"), (1003, 960, 5112, 128, "geglu 128x160"),
+])
+def test_lora_linear_geglu_every_kernel(B, M, C, F, rank, kernel):
+    r = rng(M + C + F + rank)
+    p = mkproj(r, 2 * F, C, rank, bias=rank != 64, scale=0.6, w_std=0.05)
+    x = G.bf16_round(r.standard_normal((M, C)).astype(np.float32))
+    xd, pd, ones, zeros = dev(x, B), B.Proj.from_numpy(p), dev(np.ones(C, np.float32), B), dev(np.zeros(C, np.float32), B)
+    call = lambda: B.lora_linear_fwd(xd, pd, ln_gamma=ones, ln_beta=zeros, epilogue=B.SD_EPI_GEGLU)
+    with B.dry_run() as names:
+        call()
+    assert names[-1] == kernel
+    y = call()
+    rows = np.unique(np.concatenate([np.arange(0, M, 97), np.arange(max(0, M - 40), M), np.arange(96, min(160, M)), np.arange(min(250, M - 1), min(262, M))]))
+    n = O.layernorm(x[rows], np.ones(C, np.float32), np.zeros(C, np.float32))
+    ref = O.geglu(O.lora_linear(n, p["W"], p["b"], p["A"], p["B"], p["scale"]))
+    assert rel_err(host(y)[rows], ref) <= BF16_TOL
+    if rank:        # the adapter would be missed
+        assert rel_err(O.geglu(O.linear(n, p["W"], p["b"])), ref) > 3 * BF16_TOL
+    assert B.gemm_dep_timeouts() == 0
+
+
 # ---------------------------------------------------------------------- attention_fwd
 def vt_layout(v, B):
     """[Bn, Tk, C] -> the transposed, per-sample padded layout [C, Bn * Tkp]."""

@@ -62,3 +62,23 @@ def test_patch_cuts(B, tiles, single, multi):
         L.sd_lora_patch_multi(0x1000, 1, tiles, None)
         L.sd_lora_unpatch(0x1000, 1, tiles, None)
     assert names == ["patch " + single, "patch multi " + multi, "unpatch"]
+
+
+# one round of 64-row tiles (three ring stages, two), of 128-row tiles; beyond that by estimate, against what was measured:
+# the general kernel's 256x128 ahead of the wide tiles where the K loop is long and the rounds come out even for it, the wide
+# ones at the feed-forward widths of 640 and 1280 channels
+@pytest.mark.parametrize("M,K,F,r,kernel", [
+    (256, 1280, 2560, 16, "gemm 64x128/4 waves/3 stages geglu"), (2048, 320, 1280, 0, "gemm 64x128/4 waves/2 stages geglu"),
+    (3952, 320, 640, 64, "gemm 64x128/4 waves/2 stages geglu"), (988, 640, 2560, 8, "gemm 64x128/4 waves/2 stages geglu"),
+    (1500, 640, 2560, 8, "gemm 128x128/4 waves/2 stages geglu"), (512, 2048, 8192, 8, "gemm 128x128/4 waves/2 stages geglu"),
+    (1500, 1280, 5120, 128, "gemm 256x256/8 waves/2 stages geglu"), (7904, 2048, 4096, 64, "gemm 256x256/8 waves/2 stages geglu"),
+    (8192, 2048, 4096, 0, "gemm 256x256/8 waves/2 stages geglu"), (988, 1280, 5120, 16, "geglu 128x160"),
+    (2048, 1280, 5120, 64, "geglu 256x160"), (8192, 640, 2560, 64, "geglu 256x160"), (7904, 640, 2560, 0, "geglu 256x160"),
+    (1000, 640, 5120, 72, "geglu 128x160"), (8192, 640, 2564, 0, "gemm 256x256/8 waves/2 stages geglu"), (8192, 648, 2560, 0, "gemm 128x128/4 waves/2 stages geglu"),
+])
+def test_feed_forward_in_projection(B, M, K, F, r, kernel):
+    names = linear(B, M, K, F, r, ln=True, geglu=True)
+    assert names[0].startswith("layernorm")
+    if kernel.startswith("gemm"):
+        kernel += (" guard" if K % 64 or r % 64 else "") + (" flags" if r else "")
+    assert names[1:] == (["down"] if r and kernel.startswith("geglu") else []) + [kernel]
