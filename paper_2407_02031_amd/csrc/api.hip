@@ -248,10 +248,9 @@ static int run_projections(const ProjCall* calls, int n, hipStream_t stream, int
                 P.ldp1 = calls[i].K;
                 P.t_scale = calls[i].p->scale;
             }
-        const bool flags_clean = dep && dep->f[0] && !dep->pending;
-        if (gemm16_takes(g, flags_clean)) {
+        if (gemm16_takes(g)) {
             timing_mark(tag, 0, stream);
-            rc = launch_gemm16(g, flags_clean, stream);
+            rc = launch_gemm16(g, stream);
             timing_mark(tag, 1, stream);
             return rc;
         }

@@ -164,9 +164,8 @@ struct GemmGroup {
 // problems come first and every problem that waits on one is in the same group.
 int launch_gemm_group(GemmGroup& g, hipStream_t stream);
 // The same for groups that gemm16_takes: plain projections with the adapter in the tile.
-// flags_clean: cleared dependency flags are at hand for the general kernel.
-bool gemm16_takes(const GemmGroup& g, bool flags_clean);
-int launch_gemm16(GemmGroup& g, bool flags_clean, hipStream_t stream);
+bool gemm16_takes(const GemmGroup& g);
+int launch_gemm16(GemmGroup& g, hipStream_t stream);
 // t = scale * x A^T (x [M, K], A [r, K], t bf16 [M, r]) by itself, in the time of a short launch; K % 64 == 0
 int launch_down(const uint16_t* x, int64_t ldx, const uint16_t* A, float scale, uint16_t* t, int M, int K, int r, hipStream_t stream);
 // Tiles of a feed-forward in-projection [M, K] -> [M, F] with an adapter of rank r (0: none): rows x output columns.

@@ -33,7 +33,7 @@ struct Tile16 {
     static constexpr int STAGE_CH = ROWS * 8;                      // 16-byte chunks of a stage
     // as many stages as 160 KB hold, five at most; two workgroups per CU if three stages leave room for that
     static constexpr int FIT = 160 * 1024 / (ROWS * 128);
-    static constexpr int STAGES = FIT >= 6 ? 3 : (FIT > 5 ? 5 : FIT);
+    static constexpr int STAGES = FIT >= 6 ? 3 : FIT;
     static constexpr int EXCH = WGK > 1 ? NW * (MI / 2) * NI * 64 : 0;   // chunks of the exchange of the groups' sums
     static constexpr int LDS_CH = STAGES * STAGE_CH > EXCH ? STAGES * STAGE_CH : EXCH;
     static_assert(WGK == 1 || WGK == 2, "a stage has two 32 deep k-steps");
@@ -400,16 +400,21 @@ static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
     return launch16<BM, BN, WGM, WGN, WGK, 64 / 16 / WGN>(g, stream);
 }
 
-// Which tile, or 0 for the general kernel (any K, rank, layout and alignment; four columns are one access here): the largest of the three with which the group is one round that
-// uses more than half the CUs (64x80: any number, two workgroups fit a CU).  An adapter costs the tile its
-// A rows in every step: cheaper than a producer tile only while those are few, or while the flags that a
-// producer needs would have to be cleared by a launch of their own (flags_clean false: +3.5 us).  us, general
-// kernel with clean flags / here: 8192x640x640 14.0 / 13.0, + 64: 17.9 / 19.8; 7904x640x2560 35.8 / 31.9;
-// 2048x1280x1280 13.0 / 11.9, + 64: 16.7 / 18.0; 988x1280x1280 + 16: 12.2 / 10.6; 988x1280x5120 28.8 / 26.9;
-// 1000x640x640 + 32: 9.4 / 8.4; 512x320x320 + 8: 8.2 / 7.7; 154x1280x2048 + 64: 10.2 / 14.7;
-// the q, k, v and text key / value group of 988 tokens of 1280 channels + 16
-// 37.6 / 27.6, of 2 x 256 of 320 + 8 20.4 / 13.9 (values stored transposed).
-static int tile16(const GemmGroup& g, bool flags_clean) {
+// Which tile, or 0 for the general kernel (any K, rank, layout and alignment; four columns are one access here): the
+// largest of the three with which the group is one round of at most one workgroup per CU, and, for the larger two, more
+// than half the CUs have one.
+//   An adapter costs the tile its A rows in every step (up to rank 32 16 or 32 of them, above 64), the general kernel a
+// producer tile, its stores and the wait for them: up to rank 32 the former is cheaper at any K (0.96 to 1.7 times
+// as fast over 400 projections of 64 to 16384 rows), of rank 64 while K is short.
+//   A lone projection that leaves many CUs without a tile is better off in the general kernel's smaller ones: without an
+// adapter below 201 tiles (170 at K = 320); with one below 192, never at K = 320, nor at 640 with tiles of 64 rows.  The q, k, v
+// groups always gain: their alternative is three rounds of uneven tiles.
+// us, general kernel / here: 512x320x320 + 8 10.4 / 6.1, + 64 9.1 / 7.3; 1000x1280x1280 + 16 13.4 / 9.6, + 64 12.3 / 12.4;
+// 3952x640x640 + 16 13.4 / 10.6, + 64 12.7 / 11.3; 8192x640x640 + 64 17.7 / 15.8; 2048x1280x1280 + 64 16.1 / 15.6; 154x1280x2048 + 8
+// 14.7 / 11.2, + 64 13.8 / 14.8; 2048x1280x5120 + 32 38.0 / 38.5, + 64 38.8 / 43.8; 4100x640x640 (132 tiles) 11.5 / 14.6, + 16 15.1 / 16.9;
+// 6100x640x640 (192) 13.5 / 15.8, + 16 18.4 / 17.7; 8100x640x2560 (256) 36.4 / 32.5, + 16 39.8 / 36.5; the q, k, v and text key / value
+// group of 988 tokens of 1280 channels + 16 37.6 / 27.6, of 2 x 256 of 320 + 8 20.4 / 13.9 (values stored transposed).
+static int tile16(const GemmGroup& g) {
     long big = 0, mid = 0, small = 0;
     int rmax = 0, kmax = 0;
     for (int i = 0; i < g.n; ++i) {
@@ -424,16 +429,17 @@ static int tile16(const GemmGroup& g, bool flags_clean) {
         rmax = P.K1 > rmax ? P.K1 : rmax;
         kmax = P.K0 > kmax ? P.K0 : kmax;
     }
-    if (rmax > 0 && kmax >= 2048 && g.n == 1) return 0;
+    if (rmax > 32 && kmax > 640) return 0;
     const int tile = big <= 256 && big > 128 ? 3 : mid <= 256 && mid > 128 ? 2 : small <= 256 ? 1 : 0;
-    if (rmax > 0 && flags_clean && (rmax > 32 || !(tile == 1 || (tile == 3 && g.n > 1)))) return 0;
+    const int least = rmax == 0 ? (kmax <= 320 ? 170 : 201) : kmax <= 320 || (kmax <= 640 && tile == 2) ? 0 : 192;
+    if (g.n == 1 && tile > 1 && (tile == 3 ? big : mid) < least) return 0;
     return tile;
 }
-bool gemm16_takes(const GemmGroup& g, bool flags_clean) { return tile16(g, flags_clean) > 0; }
-int launch_gemm16(GemmGroup& g, bool flags_clean, hipStream_t stream) {
+bool gemm16_takes(const GemmGroup& g) { return tile16(g) > 0; }
+int launch_gemm16(GemmGroup& g, hipStream_t stream) {
     int rmax = 0;
     for (int i = 0; i < g.n; ++i) rmax = g.p[i].K1 > rmax ? g.p[i].K1 : rmax;
-    switch (tile16(g, flags_clean)) {
+    switch (tile16(g)) {
     case 3: return launch16r<128, 160, 4, 2, 1>(g, rmax, stream);
     case 2: return launch16r<64, 160, 2, 2, 2>(g, rmax, stream);
     default: return launch16r<64, 80, 2, 1, 2>(g, rmax, stream);

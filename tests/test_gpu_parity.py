@@ -219,6 +219,56 @@ def test_lora_linear_geglu_wide_tiles(B, M, C, F, rank):
     assert rel_err(host(y)[rows], ref) <= BF16_TOL
 
 
+# each body of the plain projection, asserted to be the one that runs: in-tile adapters with every number of A columns, the
+# general kernel's tiles with dependency flags (a LayerNorm in front has cleared them), with records, and without an adapter, with an
+# fp32 residual, with K or the rank off 64, two column tiles of producers, ragged rows and columns.  mode: plain, res (fp32 residual), ln
+@pytest.mark.parametrize("M,K,N,rank,mode,kernel", [
+    (16380, 64, 320, 0, "res", "gemm16 128x160/0"), (3900, 64, 644, 8, "plain", "gemm16 128x160/1"), (5000, 640, 644, 40, "res", "gemm16 128x160/2"), (8190, 640, 640, 64, "ln", "gemm16 128x160/2"),
+    (16380, 64, 40, 0, "plain", "gemm16 64x160/0"), (4757, 1280, 324, 24, "ln", "gemm16 64x160/1"), (8190, 320, 320, 40, "res", "gemm16 64x160/2"),
+    (2500, 2048, 324, 0, "res", "gemm16 64x80/0"), (63, 5120, 84, 16, "res", "gemm16 64x80/1"), (1000, 2048, 644, 32, "ln", "gemm16 64x80/2"), (777, 192, 1284, 64, "plain", "gemm16 64x80/4"),
+    (4100, 640, 640, 16, "plain", "gemm 128x128/8 waves/4 stages guard records"), (2100, 1280, 1284, 0, "res", "gemm 128x128/8 waves/4 stages res32"),
+    (1990, 64, 1284, 128, "ln", "gemm 128x128/8 waves/4 stages flags"), (3900, 72, 644, 0, "plain", "gemm 128x128/8 waves/4 stages guard"),
+    (1990, 128, 1284, 200, "res", "gemm 128x128/8 waves/4 stages res32 guard flags"), (2500, 1280, 1284, 64, "res", "gemm 128x128/8 waves/4 stages res32 records"),
+    (12000, 1280, 324, 0, "plain", "gemm 256x128/8 waves/3 stages"), (4757, 1280, 1284, 64, "plain", "gemm 256x128/8 waves/3 stages records"), (4700, 1280, 1284, 128, "ln", "gemm 256x128/8 waves/3 stages flags"),
+    (4757, 1288, 1284, 24, "plain", "gemm 256x128/8 waves/3 stages guard records"), (3900, 1288, 1284, 200, "res", "gemm 256x128/8 waves/3 stages res32 guard flags"), (12000, 1280, 320, 16, "res", "gemm 256x128/8 waves/3 stages res32 guard records"),
+    (12000, 128, 1284, 0, "plain", "gemm 128x128/4 waves/2 stages"), (12000, 64, 644, 0, "res", "gemm 128x128/4 waves/2 stages res32"), (8190, 64, 324, 128, "ln", "gemm 128x128/4 waves/2 stages flags"),
+    (8190, 64, 324, 72, "plain", "gemm 128x128/4 waves/2 stages guard records"), (12000, 128, 1284, 128, "res", "gemm 128x128/4 waves/2 stages res32 records"), (4757, 648, 644, 200, "res", "gemm 128x128/4 waves/2 stages res32 guard flags"),
+    (4757, 320, 1284, 64, "ln", "gemm 64x128/4 waves/2 stages flags"), (12000, 64, 324, 8, "plain", "gemm 64x128/4 waves/2 stages guard records"), (12000, 72, 324, 0, "res", "gemm 64x128/4 waves/2 stages res32 guard"),
+    (5000, 320, 1284, 200, "res", "gemm 64x128/4 waves/2 stages res32 guard flags"),
+    (4757, 1280, 324, 128, "ln", "gemm 64x128/4 waves/3 stages flags"), (1, 64, 40, 128, "plain", "gemm 64x128/4 waves/3 stages records"), (1000, 1288, 324, 24, "res", "gemm 64x128/4 waves/3 stages res32 guard records"),
+    (5000, 2048, 64, 64, "ln", "gemm 64x64/4 waves/5 stages flags"), (333, 1288, 40, 24, "plain", "gemm 64x64/4 waves/5 stages guard records"), (12000, 72, 64, 0, "plain", "gemm 64x64/4 waves/5 stages guard"),
+    (12000, 2048, 1284, 64, "plain", "gemm 256x256/8 waves/2 stages records"),
+])
+def test_lora_linear_every_kernel(B, M, K, N, rank, mode, kernel):
+    import torch
+    r = rng(M + K + N + rank)
+    p = mkproj(r, N, K, rank, bias=M % 2 == 0, scale=0.7)
+    x = G.bf16_round(r.standard_normal((M, K)).astype(np.float32))
+    ones, zeros = np.ones(K, np.float32), np.zeros(K, np.float32)
+    kw = {}
+    if mode == "ln":
+        kw = dict(ln_gamma=dev(ones, B), ln_beta=dev(zeros, B))
+    if mode == "res":
+        res = r.standard_normal((M, N)).astype(np.float32)
+        kw = dict(residual=torch.from_numpy(res).cuda(), out_dtype=torch.float32)
+    xd, pd = dev(x, B), B.Proj.from_numpy(p)
+    call = lambda: B.lora_linear_fwd(xd, pd, **kw)
+    with B.dry_run() as names:
+        call()
+    assert names[-1] == kernel
+    got = host(call())
+    rows = np.unique(np.concatenate([np.arange(0, M, 61), np.arange(max(0, M - 140), M), np.arange(min(M, 300))]))
+    xr = O.layernorm(x[rows], ones, zeros) if mode == "ln" else x[rows]
+    ref = O.lora_linear(xr, p["W"], p["b"], p["A"], p["B"], p["scale"])
+    upd = got[rows] - (res[rows] if mode == "res" else 0)
+    assert rel_err(upd, ref) <= BF16_TOL
+    # every tile by itself: a wrong one must not hide behind the largest value of the whole
+    assert np.isfinite(got).all() and np.abs(got - (res if mode == "res" else 0)).max() <= 2 * np.abs(ref).max()
+    if rank:
+        assert rel_err(O.linear(xr, p["W"], p["b"]), ref) > 3 * BF16_TOL
+    assert B.gemm_dep_timeouts() == 0
+
+
 # each body of the in-projection, asserted to be the one that runs: the general kernel's four, with and without an adapter and
 # K or rank off 64, and the wide tiles of 256 and 128 rows with ragged rows and columns, one, two and more steps, an adapter
 # segment of less than 64 columns, of exactly 64 and of more, its down-projection with one and two column tiles and a last stage of

@@ -82,3 +82,16 @@ def test_feed_forward_in_projection(B, M, K, F, r, kernel):
     if kernel.startswith("gemm"):
         kernel += (" guard" if K % 64 or r % 64 else "") + (" flags" if r else "")
     assert names[1:] == (["down"] if r and kernel.startswith("geglu") else []) + [kernel]
+
+
+# an adapter in the tile up to rank 32, to rank 64 while K is short; a lone projection only if enough CUs get a tile
+@pytest.mark.parametrize("M,K,N,r,kernel", [
+    (512, 320, 320, 8, "gemm16 64x80/1"), (512, 320, 320, 64, "gemm16 64x80/4"), (154, 2048, 1280, 16, "gemm16 64x80/1"), (154, 2048, 1280, 64, "gemm 64x128/4 waves/3 stages records"),
+    (8192, 640, 640, 64, "gemm16 128x160/2"), (8192, 640, 640, 72, "gemm 64x128/4 waves/2 stages guard records"), (2048, 1280, 1280, 32, "gemm16 64x160/1"), (2048, 1280, 1280, 40, "gemm 128x128/8 waves/4 stages guard records"),
+    (4100, 640, 640, 0, "gemm 128x128/8 waves/4 stages"), (6400, 640, 640, 0, "gemm 128x128/8 waves/4 stages"), (6500, 640, 640, 0, "gemm16 128x160/0"), (5900, 640, 640, 16, "gemm 128x128/4 waves/2 stages guard records"),
+    (6144, 640, 640, 16, "gemm16 128x160/1"), (4100, 320, 320, 32, "gemm16 64x160/1"), (4100, 320, 320, 0, "gemm 64x128/4 waves/3 stages"), (6000, 320, 320, 0, "gemm16 64x160/0"), (2300, 640, 640, 16, "gemm16 64x160/1"), (2300, 1280, 640, 16, "gemm 64x128/4 waves/3 stages guard records"), (8192, 320, 320, 64, "gemm16 64x160/2"),
+])
+@pytest.mark.parametrize("ln", [False, True])
+def test_projection_in_tile_or_not(B, M, K, N, r, kernel, ln):
+    names = linear(B, M, K, N, r, ln=ln)
+    assert names[-1] == (kernel.replace("records", "flags") if ln else kernel)
