@@ -174,16 +174,21 @@ int launch_cvt_f32_to_bf16(const float* x, uint16_t* y, size_t n, hipStream_t st
 // HBM-bound: x is read twice (the second time mostly out of the last-level cache) and y written
 // once.  Both passes are streams, so a thread moves 16 bytes (VEC = 8 channels) per access and has
 // all of its accesses in flight at once: a workgroup is `rows` tokens x C / VEC threads wide and
-// takes GN_ITERS of such slabs.  Combining the partials is the other cost: nchunks * groups pairs
-// per workgroup.  It is kept small against the slab by few, large workgroups in both passes (at
-// most 128 chunks a sample, up to 1024 threads each).  2 x 16384 x 320 with SiLU: 42.4 us with
-// 4-byte accesses and 8-token workgroups, 17.5 us this way.
+// takes up to GN_ITERS of such slabs.  Combining the partials is the other cost, nchunks * groups pairs
+// per workgroup, and for short samples the chain of it is the pass: so a partial workgroup takes
+// GN_PSLABS slabs at least, a thread fetches GN_RUN partials at once, and the sums in LDS are unrolled.
+// us with SiLU, 4-byte accesses and 8-token workgroups / one slab per partial workgroup of 1024 threads
+// and partials fetched one after the other / this way: 2 x 16384 x 320 42.7 17.8 17.7; 2 x 4096 x 640 14.6 13.1
+// 11.9; 4 x 1140 x 960 11.5 12.9 11.2; 2 x 1024 x 1280 9.6 10.7 10.1; 2 x 411 x 1280 8.7 10.4 8.9; 1 x 337 x 320 7.5 8.2 7.6.
 // Channels whose count is not a multiple of 8 take VEC = 2 (groups hold an even number of channels).
 // ---------------------------------------------------------------------------------------
 constexpr int GN_ITERS = 6;          // slabs of a workgroup that are in flight together
-constexpr int GN_PARTIAL_THREADS = 1024, GN_APPLY_THREADS = 512;
-constexpr int GN_MAX_PCHUNKS = 128;  // partial-sum workgroups of a sample, at most
-constexpr int GN_TARGET_WGS = 256;   // ... and in all: one per CU
+constexpr int GN_THREADS = 512, GN_MAX_THREADS = 1024;   // of a workgroup in both passes; the larger where one row needs it
+constexpr int GN_TARGET_WGS = 256;   // partial-sum workgroups of a launch, one per CU, ...
+constexpr int GN_MAX_PCHUNKS = 128;  // ... of a sample at most this many, ...
+constexpr int GN_PSLABS = 4;         // ... and fewer rather than with fewer slabs
+constexpr int GN_APPLY_WGS = 170;    // apply workgroups take more than one slab while this many are left (256: up to 8 % slower at 1 to 6 M elements)
+constexpr int GN_RUN = 8;            // partials that a thread fetches together
 
 template <int VEC>
 struct GnVec;
@@ -198,7 +203,7 @@ __device__ __forceinline__ uint32_t gn_word(const typename GnVec<VEC>::type& v, 
 }
 
 template <int VEC>
-__global__ __launch_bounds__(GN_PARTIAL_THREADS) void groupnorm_partial_kernel(const uint16_t* __restrict__ x, float* __restrict__ partials,
+__global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_partial_kernel(const uint16_t* __restrict__ x, float* __restrict__ partials,
                                                                                int T, int C, int groups, int nchunks, int pchunk, int rows) {
     typedef typename GnVec<VEC>::type vec;
     constexpr int NP = VEC / 2;     // channel pairs of a thread
@@ -210,10 +215,12 @@ __global__ __launch_bounds__(GN_PARTIAL_THREADS) void groupnorm_partial_kernel(c
     const int t1 = min(T, (chunk + 1) * pchunk);
     if (row < rows) {
         float s1[NP], s2[NP], shift[NP];
+        int g0 = cv * VEC / cpg * cpg;       // first channel of the pair's group
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             s1[i] = s2[i] = 0.f;
-            shift[i] = bf16_to_f32(xb[(cv * VEC + 2 * i) / cpg * cpg]);
+            while (cv * VEC + 2 * i >= g0 + cpg) g0 += cpg;
+            shift[i] = bf16_to_f32(xb[g0]);
         }
         for (int t = chunk * pchunk + row; t < t1; t += rows * GN_ITERS) {
             vec v[GN_ITERS];
@@ -238,6 +245,7 @@ __global__ __launch_bounds__(GN_PARTIAL_THREADS) void groupnorm_partial_kernel(c
     __syncthreads();
     for (int p = tid; p < npairs; p += blockDim.x) {   // tokens of a pair, in row order, into row 0
         float a1 = 0.f, a2 = 0.f;
+#pragma unroll 4
         for (int r = 0; r < rows; ++r) {
             const float2 q = *reinterpret_cast<const float2*>(sh + 2 * ((size_t)r * npairs + p));
             a1 += q.x;
@@ -249,6 +257,7 @@ __global__ __launch_bounds__(GN_PARTIAL_THREADS) void groupnorm_partial_kernel(c
     const int ppg = cpg >> 1;
     for (int g = tid; g < groups; g += blockDim.x) {
         float a1 = 0.f, a2 = 0.f;
+#pragma unroll 4
         for (int i = 0; i < ppg; ++i) {
             const float2 q = *reinterpret_cast<const float2*>(sh + 2 * (g * ppg + i));
             a1 += q.x;
@@ -261,7 +270,7 @@ __global__ __launch_bounds__(GN_PARTIAL_THREADS) void groupnorm_partial_kernel(c
 // SILU: y = n * sigmoid(n) on the normalised value, the GroupNorm + SiLU pair of the base model's
 // ResNet blocks as one operator (Section 4.3, "Kernel-level optimizations")
 template <int VEC, bool SILU>
-__global__ __launch_bounds__(1024) void groupnorm_apply_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ y,
+__global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_apply_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ y,
                                                                            const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
                                                                            const float* __restrict__ partials, int T, int C, int groups, int nchunks,
                                                                            int parts, int rows, int iters, float eps) {
@@ -290,11 +299,13 @@ __global__ __launch_bounds__(1024) void groupnorm_apply_kernel(const uint16_t* _
         const int g = i % groups, part = i / groups;
         float a1 = 0.f, a2 = 0.f;
         const int c1 = min(nchunks, (part + 1) * run);
-#pragma unroll 8
-        for (int c = part * run; c < c1; ++c) {
-            const float2 q = src[(size_t)c * groups + g];
-            a1 += q.x;
-            a2 += q.y;
+        for (int c = part * run; c < c1; c += GN_RUN) {
+            float2 q[GN_RUN];
+#pragma unroll
+            for (int k = 0; k < GN_RUN; ++k) q[k] = src[(size_t)min(c + k, c1 - 1) * groups + g];    // all in flight together
+#pragma unroll
+            for (int k = 0; k < GN_RUN; ++k)
+                if (c + k < c1) { a1 += q[k].x; a2 += q[k].y; }
         }
         sub[i] = make_float2(a1, a2);
     }
@@ -302,6 +313,7 @@ __global__ __launch_bounds__(1024) void groupnorm_apply_kernel(const uint16_t* _
     float2* stat = sub + parts * groups;
     for (int g = tid; g < groups; g += blockDim.x) {
         float a1 = 0.f, a2 = 0.f;
+#pragma unroll 4
         for (int p = 0; p < parts; ++p) {
             a1 += sub[p * groups + g].x;
             a2 += sub[p * groups + g].y;
@@ -315,9 +327,11 @@ __global__ __launch_bounds__(1024) void groupnorm_apply_kernel(const uint16_t* _
     if (!mine) return;
     float mean[NP], g0[NP], g1[NP], b0[NP], b1[NP];
     const vec gv = reinterpret_cast<const vec*>(gamma)[cv], bv = reinterpret_cast<const vec*>(beta)[cv];
+    int g = cv * VEC / cpg;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-        const float2 q = stat[(cv * VEC + 2 * i) / cpg];
+        while (cv * VEC + 2 * i >= (g + 1) * cpg) ++g;
+        const float2 q = stat[g];
         const uint32_t gw = gn_word<VEC>(gv, i), bw = gn_word<VEC>(bv, i);
         mean[i] = q.x;
         g0[i] = bf16lo_to_f32(gw) * q.y;
@@ -361,25 +375,26 @@ static int launch_gn(const uint16_t* x, uint16_t* y, const uint16_t* gamma, cons
         if (*rows < 1) *rows = 1;
         return (nv * *rows + 63) / 64 * 64;
     };
-    // partial sums: one workgroup per CU over the batch
+    // partial sums
     int want = (GN_TARGET_WGS + Bn - 1) / Bn;
     if (want > GN_MAX_PCHUNKS) want = GN_MAX_PCHUNKS;
     int rows;
-    int pchunk = std::max((T + want - 1) / want, GN_PARTIAL_THREADS / nv);   // short samples: a workgroup's one slab rather than more partials
-    const int pthreads = shape(GN_PARTIAL_THREADS, pchunk, &rows);
+    const int most = nv > GN_THREADS ? GN_MAX_THREADS : GN_THREADS;
+    const int pchunk = std::max((T + want - 1) / want, GN_PSLABS * (most / nv));   // short samples: a few slabs rather than more partials
+    const int pthreads = shape(most, pchunk, &rows);
     const int nchunks = (T + pchunk - 1) / pchunk;
-    SD_REQUIRE(pthreads <= GN_PARTIAL_THREADS, SD_EUNSUPPORTED, "groupnorm: C=%d", C);
+    SD_REQUIRE(pthreads <= GN_MAX_THREADS, SD_EUNSUPPORTED, "groupnorm: C=%d", C);
     hipLaunchKernelGGL((groupnorm_partial_kernel<VEC>), dim3(nchunks, Bn), dim3(pthreads), (size_t)rows * C * sizeof(float), stream, x, partials, T, C,
                        groups, nchunks, pchunk, rows);
     SD_HIP_CHECK(hipGetLastError());
-    const int athreads = shape(nv > GN_APPLY_THREADS ? GN_PARTIAL_THREADS : GN_APPLY_THREADS, T, &rows);
+    const int athreads = shape(most, T, &rows);
     int parts = athreads / groups;
-    if (parts > nchunks) parts = nchunks;
+    if (parts > (nchunks + GN_RUN - 1) / GN_RUN) parts = (nchunks + GN_RUN - 1) / GN_RUN;
     if (parts < 1) parts = 1;
     const size_t lds = (size_t)(parts + 1) * groups * 2 * sizeof(float);
     // slabs per workgroup: all of them in flight for large inputs, fewer where that would leave CUs without a workgroup
     const int64_t slabs = (int64_t)Bn * ((T + rows - 1) / rows);
-    const int iters = (int)std::min<int64_t>(GN_ITERS, std::max<int64_t>(1, slabs / GN_TARGET_WGS));
+    const int iters = (int)std::min<int64_t>(GN_ITERS, std::max<int64_t>(1, slabs / GN_APPLY_WGS));
     const dim3 grid((T + rows * iters - 1) / (rows * iters), Bn);
     if (silu)
         hipLaunchKernelGGL((groupnorm_apply_kernel<VEC, true>), grid, dim3(athreads), lds, stream, x, y, gamma, beta, partials, T, C, groups, nchunks, parts, rows, iters, eps);

@@ -552,6 +552,20 @@ def test_groupnorm_slabs_match_oracle(B, Bn, T, C, groups):
     assert rel_err(host(y), O.groupnorm(x, g, b, groups=groups)) <= BF16_TOL
 
 
+# partials per thread in one batch, in several and in a last one that is partly empty; chunks whose last slab is; three and more
+# partial workgroups whose count is not a multiple of anything
+@pytest.mark.parametrize("Bn,T,C,groups", [(1, 400, 2048, 1024), (2, 700, 1000, 250), (1, 1023, 1280, 32), (3, 49, 320, 32), (2, 8191, 640, 16), (70, 33, 64, 2)])
+def test_groupnorm_partial_batches_match_oracle(B, Bn, T, C, groups):
+    r = rng(T + C + groups)
+    x = G.bf16_round((r.standard_normal((Bn, T, C)) * 1.5 + r.standard_normal((Bn, 1, C)) * 2).astype(np.float32))
+    g = G.bf16_round((1 + 0.1 * r.standard_normal(C)).astype(np.float32))
+    b = G.bf16_round((0.1 * r.standard_normal(C)).astype(np.float32))
+    ref = O.groupnorm(x, g, b, groups=groups)
+    got = host(B.groupnorm_fwd(dev(x, B), dev(g, B), dev(b, B), groups=groups))
+    assert rel_err(got, ref) <= BF16_TOL
+    assert np.abs(got - ref).mean() <= 2e-3 * np.abs(ref).mean() * 2       # bf16 rounds by 2^-9 at most, a wrong statistic moves everything
+
+
 # ------------------------------------------------------------ spatial_transformer_fwd
 def run_stack(B, cfg, seed=0):
     p = G.make_stack_inputs(cfg, seed)
