@@ -163,6 +163,9 @@ struct GemmGroup {
 // Launch every problem of `g` in one grid.  Problems must all be GEGLU or all plain; signalling
 // problems come first and every problem that waits on one is in the same group.
 int launch_gemm_group(GemmGroup& g, hipStream_t stream);
+// Do so many tiles, and the producers' tiles ahead of them, run one to a CU?  Both are dealt over 8 XCDs of 32 CUs.
+// (42 producers and 210 tiles do not: 5350x640x1280 + 16 26.0 us with 128x128 tiles one per CU, 23.7 with other tiles)
+inline bool gemm_one_round(long tiles, long producers) { return (tiles + 7) / 8 + (producers + 7) / 8 <= 32; }
 // The same for groups that gemm16_takes: plain projections with the adapter in the tile.
 bool gemm16_takes(const GemmGroup& g);
 int launch_gemm16(GemmGroup& g, hipStream_t stream);

@@ -696,14 +696,14 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     if (t128 < 512) {
         // at most one 128x128 tile per CU, and most CUs have one: that tile with a deep ring, one
         // workgroup per CU (2048x1280x5120: 42.0, 53.7 with 64x128 tiles, of which 64 CUs get two)
-        if (t128 > 128 && t128 + lead <= 256) {
+        if (t128 > 128 && gemm_one_round(t128, (long)lead)) {
             if (res32) return launch_cfg<128, 128, 64, 4, 2, 4, false, true>(g, guard, stream);
             return launch_cfg<128, 128, 64, 4, 2, 4, false, false>(g, guard, stream);
         }
-        // more than that, but at most one of 256x128 per CU, and no short K loop: those
+        // more than that (the down-projection's tiles count), but at most one of 256x128 per CU, and no short K loop: those
         // (8192x640x2560: 41.1, 48.2 with 128x128 tiles; 4757x1280x1280: 26.4, 33.1 with 64x128;
-        // at K = 640 the ramps of the larger tile lose: 24.1 against 21.0)
-        if (t128 > 256 && t256 + lead / 2 <= 256 && meanK >= 1024) {
+        // 6000x640x2560 34.5, 44.5 with 128x128 tiles; at K = 640 the ramps of the larger tile lose: 24.1 against 21.0)
+        if (t128 > 128 && t256 + lead / 2 <= 256 && meanK >= 1024) {
             if (res32) return launch_cfg<256, 128, 64, 4, 2, 3, false, true>(g, guard, stream);
             return launch_cfg<256, 128, 64, 4, 2, 3, false, false>(g, guard, stream);
         }

@@ -405,9 +405,10 @@ static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
 // than half the CUs have one.
 //   An adapter costs the tile its A rows in every step (up to rank 32 16 or 32 of them, above 64), the general kernel a
 // producer tile, its stores and the wait for them: up to rank 32 the former is cheaper at any K (0.96 to 1.7 times
-// as fast over 400 projections of 64 to 16384 rows), of rank 64 while K is short.
-//   A lone projection that leaves many CUs without a tile is better off in the general kernel's smaller ones: without an
-// adapter below 201 tiles (170 at K = 320); with one below 192, never at K = 320, nor at 640 with tiles of 64 rows.  The q, k, v
+// as fast over 400 projections of 64 to 16384 rows), of rank 64 while K is short, or where two column tiles are all that repeat it
+// (8200x320x1280 + 64 24.3 / 21.1).
+//   A lone projection that the general kernel fits into one round (128x128 tiles with a deep ring, its producers among them; in
+// place of the 64-row tiles its own) is better off there; with an adapter of rank 32 and a short K the 64-row tiles stay ahead.  The q, k, v
 // groups always gain: their alternative is three rounds of uneven tiles.
 // us, general kernel / here: 512x320x320 + 8 10.4 / 6.1, + 64 9.1 / 7.3; 1000x1280x1280 + 16 13.4 / 9.6, + 64 12.3 / 12.4;
 // 3952x640x640 + 16 13.4 / 10.6, + 64 12.7 / 11.3; 8192x640x640 + 64 17.7 / 15.8; 2048x1280x1280 + 64 16.1 / 15.6; 154x1280x2048 + 8
@@ -415,8 +416,8 @@ static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
 // 6100x640x640 (192) 13.5 / 15.8, + 16 18.4 / 17.7; 8100x640x2560 (256) 36.4 / 32.5, + 16 39.8 / 36.5; the q, k, v and text key / value
 // group of 988 tokens of 1280 channels + 16 37.6 / 27.6, of 2 x 256 of 320 + 8 20.4 / 13.9 (values stored transposed).
 static int tile16(const GemmGroup& g) {
-    long big = 0, mid = 0, small = 0;
-    int rmax = 0, kmax = 0;
+    long big = 0, mid = 0, small = 0, general = 0, lead = 0;   // tiles; of the general kernel: 128x128, and its producers'
+    int rmax = 0, kmax = 0, nmax = 0;
     for (int i = 0; i < g.n; ++i) {
         const GemmProblem& P = g.p[i];
         if (P.geglu_F > 0 || P.bias_on_rows == 1 || P.K0 % 64 || P.K1 > 64 || P.N % 4 || (P.bias_on_rows == 2 ? P.y_f32 || P.res : P.ldy % 4) || (P.res && P.ldr % 4) || P.Mp <= 0 || P.N <= 0 ||
@@ -426,13 +427,16 @@ static int tile16(const GemmGroup& g) {
         big += (long)((P.Mp + 127) / 128) * ((P.N + 159) / 160);
         mid += (long)((P.Mp + 63) / 64) * ((P.N + 159) / 160);
         small += (long)((P.Mp + 63) / 64) * ((P.N + 79) / 80);
+        general += (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
+        lead += (long)((P.Mp + 127) / 128) * ((P.K1 + 63) / 64);
         rmax = P.K1 > rmax ? P.K1 : rmax;
         kmax = P.K0 > kmax ? P.K0 : kmax;
+        nmax = P.N > nmax ? P.N : nmax;
     }
-    if (rmax > 32 && kmax > 640) return 0;
     const int tile = big <= 256 && big > 128 ? 3 : mid <= 256 && mid > 128 ? 2 : small <= 256 ? 1 : 0;
-    const int least = rmax == 0 ? (kmax <= 320 ? 170 : 201) : kmax <= 320 || (kmax <= 640 && tile == 2) ? 0 : 192;
-    if (g.n == 1 && tile > 1 && (tile == 3 ? big : mid) < least) return 0;
+    if (rmax > 32 && kmax > 640 && !(nmax <= 320 && tile > 1)) return 0;
+    if (g.n == 1 && tile == 3 && gemm_one_round(general, lead)) return 0;
+    if (g.n == 1 && tile == 2 && general <= 128 && general + lead <= 140 && !(rmax > 0 && rmax <= 32 && kmax <= 640)) return 0;
     return tile;
 }
 bool gemm16_takes(const GemmGroup& g) { return tile16(g) > 0; }
