@@ -96,6 +96,65 @@ def test_lora_linear_same_workspace_new_inputs(B):
     assert B.gemm_dep_timeouts() == 0
 
 
+# base tiles that read what other tiles of the same launch wrote, announced by flags and by records: one workspace, changing inputs and
+# adapters, large enough that every XCD runs tiles of both kinds; and the same bits as with the two GEMMs as two launches
+@pytest.mark.parametrize("M,K,N,rank,ln,kernel", [(4133, 640, 640, 72, True, "flags"), (4133, 640, 640, 72, False, "records"), (8192, 1280, 1280, 64, True, "flags"), (8192, 640, 1280, 128, False, "records"),
+                                                  (4133, 640, 640, 136, False, "flags")])
+def test_lora_linear_waits_inside_the_launch(B, M, K, N, rank, ln, kernel):
+    import torch
+    r = rng(M + K + N + rank)
+    ws = torch.zeros(B.lib().sd_lora_linear_workspace_bytes(M, N, K, rank, int(ln)), dtype=torch.uint8, device="cuda")
+    ones, zeros = dev(np.ones(K, np.float32), B), dev(np.zeros(K, np.float32), B)
+    kw = dict(ln_gamma=ones, ln_beta=zeros) if ln else {}
+    for trial in range(3):
+        p = mkproj(r, N, K, rank, bias=True, scale=1.0 + trial)
+        x = G.bf16_round(r.standard_normal((M, K)).astype(np.float32))
+        rows = np.arange(trial, M, 7)
+        xr = O.layernorm(x[rows], np.ones(K, np.float32), np.zeros(K, np.float32)) if ln else x[rows]
+        ref = O.lora_linear(xr, p["W"], p["b"], p["A"], p["B"], p["scale"])
+        assert rel_err(O.linear(xr, p["W"], p["b"]), ref) > 10 * BF16_TOL       # the adapter term carries most of the output
+        xd, pd = dev(x, B), B.Proj.from_numpy(p)
+        with B.dry_run() as names:
+            B.lora_linear_fwd(xd, pd, ws=ws, **kw)
+        assert names[-1].startswith("gemm ") and names[-1].endswith(kernel)
+        ys = [B.lora_linear_fwd(xd, pd, ws=ws, **kw) for _ in range(3)]
+        assert rel_err(host(ys[0])[rows], ref) <= BF16_TOL, trial
+        try:
+            B.set_projection_fusion(False)
+            with B.dry_run() as names:
+                B.lora_linear_fwd(xd, pd, ws=ws, **kw)
+            assert sum(n.startswith("gemm ") for n in names) == 2 and not names[-1].endswith(kernel)
+            ys.append(B.lora_linear_fwd(xd, pd, ws=ws, **kw))
+        finally:
+            B.set_projection_fusion(True)
+        assert all(torch.equal(ys[0], y) for y in ys[1:]), trial
+    assert B.gemm_dep_timeouts() == 0
+
+
+def test_stack_as_one_launch_or_two_gives_the_same_bits_where_tiles_wait(B):
+    """A stack whose projections wait inside their launches (rank 72: no tile forms t by itself; the in-projection's tiles are the
+    general kernel's), its cut attention merged inside the launch and by a kernel of its own."""
+    import torch
+    cfg = small_cfg(Bn=2, T=2560, C=1024, heads=16, depth=1, r=72, alpha=8.0)
+    p = G.make_stack_inputs(cfg, seed=9)
+    sp = B.StackParams(p)
+    x, ctx = dev(p["x"], B), dev(p["ctx"], B)
+    outs, names = {}, {}
+    try:
+        for on in (True, False):
+            B.set_projection_fusion(on)
+            with B.dry_run() as names[on]:
+                B.spatial_transformer_fwd(x, ctx, sp, cfg.heads)
+            outs[on] = B.spatial_transformer_fwd(x, ctx, sp, cfg.heads).clone()
+    finally:
+        B.set_projection_fusion(True)
+    waits = lambda ns: sum(n.endswith(("flags", "records")) for n in ns)
+    assert waits(names[True]) >= 4 and waits(names[False]) == 0
+    assert "attention prescaled try cut" in names[True] and "attention prescaled try cut merge" in names[False]
+    assert torch.equal(outs[True], outs[False])
+    assert B.gemm_dep_timeouts() == 0
+
+
 def test_lora_linear_random_shapes(B):
     """Seeded sweep over ragged shapes and ranks (rank > 64: two column tiles of down-projection
     per row block, so a base tile waits for a count of 2; rank not a multiple of 64; one-row and
@@ -205,8 +264,8 @@ def test_lora_linear_one_round_of_tiles(B, M, K, N, rank, f32):
         assert rel_err(host(y) - res, upd) <= BF16_TOL
 
 
-# tiles of 256 and 128 rows x 160 output columns: ragged rows and columns, one, two, three and more steps, the adapter's segment of less
-# and more than 64 columns, its down-projection with one and two column tiles and one to four stages of 320
+# feed-forward in-projections about the sizes where the wide tiles begin and end to pay: K loops of one, two, three and more steps, ranks of
+# less and more than 64 (which kernel each of them takes: test_lora_linear_geglu_every_kernel)
 @pytest.mark.parametrize("M,C,F,rank", [(6300, 64, 1288, 0), (8192, 128, 2560, 8), (4000, 192, 2568, 0), (1000, 640, 5120, 72), (988, 1280, 5120, 0), (2047, 1280, 5120, 64)])
 def test_lora_linear_geglu_wide_tiles(B, M, C, F, rank):
     r = rng(M + F + rank)
@@ -382,6 +441,63 @@ def test_attention_large_scores_in_alternate_key_octets(B):
     assert rel_err(got2, ref2) <= BF16_TOL
 
 
+# Plain keys of 1217 and more try without measuring the key tiles between the first and the last: ordinary scores, ragged and whole
+# last tiles, key ranges cut in half; shorter ones measure every tile
+@pytest.mark.parametrize("Bn,Tq,Tk,heads,qscale,kernel", [(2, 150, 1217, 2, 1.0, "attention try"), (1, 300, 1344, 1, 3.0, "attention try"), (1, 77, 1999, 3, 6.0, "attention try"),
+                                                          (1, 4096, 1285, 20, 1.0, "attention try cut merge"), (2, 150, 1216, 2, 1.0, "attention")])
+def test_attention_long_plain_keys(B, Bn, Tq, Tk, heads, qscale, kernel):
+    r = rng(Tq + Tk)
+    C = heads * 64
+    q = G.bf16_round((qscale * r.standard_normal((Bn, Tq, C))).astype(np.float32))
+    k = G.bf16_round(r.standard_normal((Bn, Tk, C)).astype(np.float32))
+    v = G.bf16_round(r.standard_normal((Bn, Tk, C)).astype(np.float32))
+    args = (dev(q, B), dev(k, B), vt_layout(v, B), heads)
+    with B.dry_run() as names:
+        B.attention_fwd(*args)
+    assert names[0] == kernel
+    got = host(B.attention_fwd(*args))
+    h = np.arange(heads) if Tq * Tk < 10 ** 6 else np.array([0, 7, heads - 1])       # (of many heads, three: the last query tiles are the cut ones)
+    cols = (h[:, None] * 64 + np.arange(64)).ravel()
+    ref = O.attention(q[..., cols], k[..., cols], v[..., cols], len(h), dtype=np.float32 if Tq > 1000 else np.float64)
+    assert np.isfinite(got).all()
+    per_tile = [rel_err(got[:, i:i + 128][..., cols], ref[:, i:i + 128]) for i in range(0, Tq, 128)]
+    assert max(per_tile) <= BF16_TOL
+    assert rel_err(O.attention(q[:, :8][..., cols], k[..., cols], np.roll(v[..., cols], 1, axis=1), len(h)), ref[:, :8]) > 10 * BF16_TOL
+
+
+# ... scores that climb from key tile to key tile, by less than 2^100 (the attempt stands) and by more than 2^128 in a middle tile
+# and in the last (it overflows, and the measured form takes over), falling for half of the queries; whole and cut key ranges
+@pytest.mark.parametrize("boost", [1.0, 3.2])
+@pytest.mark.parametrize("Tq,Tk,heads", [(200, 64 * 20 + 23, 2), (4096, 64 * 21, 20)])
+def test_attention_plain_scores_that_climb(B, boost, Tq, Tk, heads):
+    r = rng(Tq + Tk)
+    C = heads * 64
+    nt = (Tk + 63) // 64
+    level = np.zeros(nt, np.float32)                     # natural-log score of a key tile for the climbing queries
+    level[3], level[nt // 2:], level[nt // 2 + 1], level[nt - 1] = 14.0, 30.0, 47.0, 40.0
+    n0 = r.choice([-1.0, 1.0], 64).astype(np.float32)
+    sign = np.where(r.random((1, Tq, heads, 1)) < 0.5, 1.0, -1.0)
+    q = G.bf16_round((sign * n0 + 0.1 * r.standard_normal((1, Tq, heads, 64))).astype(np.float32))
+    k = G.bf16_round((boost * level[np.arange(Tk) // 64][None, :, None, None] * n0 / 8.0 + 0.3 * r.standard_normal((1, Tk, heads, 64))).astype(np.float32))
+    v = G.bf16_round(r.standard_normal((1, Tk, C)).astype(np.float32))
+    q, k = q.reshape(1, Tq, C), k.reshape(1, Tk, C)
+    up = int(np.argmax(sign[0, :, 0, 0] > 0))
+    s = (q[0, up, :64].astype(np.float64) @ k[0, :, :64].T.astype(np.float64)) / 8.0 * 1.4426950408889634
+    climb = max(s[64 * (nt // 2 + 1):64 * (nt // 2 + 2)].max(), 0) - s[:64].max()
+    assert (40 < climb < 95) if boost == 1.0 else climb > 140
+    args = (dev(q, B), dev(k, B), vt_layout(v, B), heads)
+    with B.dry_run() as names:
+        B.attention_fwd(*args)
+    assert names[0] == ("attention try cut merge" if Tq == 4096 else "attention try")
+    got = host(B.attention_fwd(*args))
+    assert np.isfinite(got).all()
+    h = np.array([0, 1]) if heads == 2 else np.array([0, 11, 19])
+    cols = (h[:, None] * 64 + np.arange(64)).ravel()
+    ref = O.attention(q[..., cols], k[..., cols], v[..., cols], len(h), dtype=np.float32 if Tq > 1000 else np.float64)
+    per_tile = [rel_err(got[:, i:i + 128][..., cols], ref[:, i:i + 128]) for i in range(0, Tq, 128)]
+    assert max(per_tile) <= BF16_TOL
+
+
 # Row sums just under the top of the fp32 range: one key of each half-wavefront's octets scores 2^127.3 above the first key
 # tile, so either half's sum is finite and their sum is not.  (1217 keys and more take the attempt without maxima; the values
 # are small, so that the accumulators stay in range.)  Whole tiles, and tiles whose halves are merged.
@@ -508,6 +624,23 @@ def test_attn_block_with_biased_q_k_v(B, T, Tc):
             qs[drop] = dict(qs[drop], b=None)
             e = rel_err(O.attn_sublayer(h, ctx, g, b, *qs, po, cfg.heads) - h, ref - h)
             assert (e < 1e-9) if drop == 1 else (e > 3 * BF16_TOL), (cross, drop, e)
+
+
+def test_attn_block_long_keys_with_a_k_bias(B):
+    """A k bias keeps the keys from being prescaled: in a self-attention of 1300 tokens the attention kernel tries on plain keys."""
+    import torch
+    T, C = 1300, 128
+    r = rng(T)
+    ps = [mkproj(r, C, C, 16, bias=True, scale=0.5) for _ in range(4)]
+    g, b = np.ones(C, np.float32), np.zeros(C, np.float32)
+    x = r.standard_normal((1, T, C)).astype(np.float32)
+    args = (torch.from_numpy(x).cuda(), None, dev(g, B), dev(b, B), *[B.Proj.from_numpy(p) for p in ps], 2)
+    with B.dry_run() as names:
+        B.attn_block_fwd(*args)
+    assert "attention try" in names
+    y = B.attn_block_fwd(*args)
+    ref = O.attn_sublayer(x, None, g, b, *ps, 2)
+    assert rel_err(host(y) - x, ref - x) <= BF16_TOL
 
 
 def test_ff_block_matches_oracle(B):
