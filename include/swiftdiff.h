@@ -120,9 +120,11 @@ int32_t sd_version(void);
  *   count: host.  This call synchronises the device: a serving loop polls it once per request,
  *   after the request's last step, not per step. */
 int sd_gemm_dep_timeouts(int64_t* count);
-/* Diagnostic switch for the same: on = 0 makes every later call run a projection as two
- * launches (all down-projections, then all base GEMMs) instead of one, and merge the halves
- * of cut attention tiles in a kernel of their own instead of inside the attention launch;
+/* Diagnostic switch for the same: on = 0 takes every wait and every meeting of workgroups out of
+ * the launches of later calls.  A projection whose tiles would wait runs as two launches (all
+ * down-projections, then all base GEMMs), and the halves of cut attention tiles are merged by a
+ * kernel of their own; projections whose tiles form t by themselves (one launch) or have it formed
+ * by a launch in front (wide GEGLU tiles) wait for nothing and run the same with either setting.
  * on = 1 (the default) restores the single launches.  Both give the same bits.  Returns the
  * previous setting.  Process-wide, not thread-safe against concurrent forward calls. */
 int32_t sd_set_projection_fusion(int32_t on);
