@@ -636,9 +636,14 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     int gM = 0, gF = 0, gK = 0, gr = 0;   // the GEGLU problems: rows in all, largest F, K and rank
     bool res32 = false;   // some problem adds an fp32 residual: take the kernel that prefetches it
     int n_main = 0;       // problems that are not down-projections
+    bool mixed = false;   // ... of different widths or depths
+    int N0 = 0, K0 = 0;
     for (int i = 0; i < g.n; ++i) {
         const GemmProblem& P = g.p[i];
-        if (!P.signal && P.Mp > 0 && P.N > 0) ++n_main;
+        if (!P.signal && P.Mp > 0 && P.N > 0) {
+            mixed = mixed || (n_main++ && (P.N != N0 || P.K0 != K0));
+            N0 = P.N, K0 = P.K0;
+        }
         if (P.res && P.res_f32 && P.Mp > 0 && P.N > 0) res32 = true;
         SD_REQUIRE((P.geglu_F > 0) == geglu || P.signal, SD_EINVAL, "gemm group mixes GEGLU and plain problems");
         SD_REQUIRE(P.Mp >= 0 && P.N >= 0 && P.K0 > 0 && P.K0 % 8 == 0 && P.K1 >= 0 && P.K1 % 8 == 0, SD_EINVAL,
@@ -722,8 +727,13 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     // 8192 x 4096 x 4096 yardstick takes 224, 248 at 128x128).  Not for grouped
     // launches: the q/k/v group with its short text-context problems loses a third.
     if (!res32 && n_main == 1 && t256 >= 512 && meanK >= 2048) return launch_cfg<256, 256, 64, 4, 2, 2, false, false>(g, guard, stream);
-    // 128x128 tiles of four 64x64 wavefronts, two workgroups per CU (4757x1280x1280: 25.9, 33.1 with 64x128,
-    // 26.9 with eight 32x64 wavefronts)
+    // 128x128 tiles, two workgroups per CU.  Of eight 32x64 wavefronts where problems of different sizes share the launch (q, k,
+    // v transposed, text keys): their tiles load the CUs unevenly, and one that has a CU to itself is faster with more
+    // wavefronts (attention blocks, us, four / eight: 4 x 3952 tokens of 640 channels with text keys + 64 106.7 / 100.4, 2 x 988 of
+    // 1280 + 16 85.6 / 79.8, 2 x 4096 of 320 + 8 109.8 / 100.5, 4 x 3952 of 640 + 32 275.4 / 279.2; 80 of them 0.91 to 1.014)
+    if (mixed && !res32) return launch_cfg<128, 128, 64, 4, 2, 2, false, false>(g, guard, stream);
+    // ... of four 64x64 otherwise (4757x1280x1280: 25.9, 33.1 with 64x128, 26.9 with eight wavefronts; the segments of a multi-adapter
+    // call: 8 x 4096 of 640 channels 45.0 / 45.6, 2999,2221,1552,1847,895 of 1280 48.6 / 50.7, of 320 up to 12 % the other way)
     if (res32) return launch_cfg<128, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
     return launch_cfg<128, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
 }

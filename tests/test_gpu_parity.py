@@ -583,6 +583,35 @@ def test_attn_block_ragged_sizes(B, Bn, T, Tc, C, heads, rank):
     assert B.gemm_dep_timeouts() == 0
 
 
+# q, k and v transposed sharing a launch of more than one round (eight wavefronts): adapters of whole and partial k-steps, none,
+# and two column tiles of them; row, column and token remainders
+@pytest.mark.parametrize("rank,flags", [(64, " flags"), (8, " guard flags"), (0, ""), (72, " guard flags")])
+def test_attn_block_projections_in_several_rounds(B, rank, flags):
+    import torch
+    # Weights that hold the scores near 1.  q and k are each rounded to bf16, so a score of size s is off by up to s 2^-8 and its
+    # probability by that fraction; with small_cfg's own the scores of 320 channels and rank 8 reach 17 (17 2^-8 = 0.066 of a
+    # probability that may be most of its row), here 6, of which the row's mean over 3101 keys leaves a tenth.
+    cfg = small_cfg(Bn=3, T=3101, Tc=5, C=320, heads=5, r=max(rank, 8), alpha=8.0, Dc=72, w_std=0.05, a_std=0.15)
+    p = G.make_stack_inputs(cfg, seed=rank)
+    blk = p["blocks"][0]
+    h = rng(rank).standard_normal(p["x"].shape).astype(np.float32)
+    projs = [dict(blk[n], A=None, B=None) if rank == 0 else blk[n] for n in ("q1", "k1", "v1", "o1")]
+    ref = O.attn_sublayer(h, None, blk["ln1_g"], blk["ln1_b"], *projs, cfg.heads)
+    args = (torch.from_numpy(h).cuda(), None, dev(blk["ln1_g"], B), dev(blk["ln1_b"], B), *[B.Proj.from_numpy(q) for q in projs], cfg.heads)
+    with B.dry_run() as names:
+        B.attn_block_fwd(*args)
+    assert "gemm 128x128/8 waves/2 stages" + flags in names
+    y = B.attn_block_fwd(*args)
+    assert rel_err(host(y) - h, ref - h) <= BF16_TOL
+    try:        # the same call as two launches per projection: same bits
+        B.set_projection_fusion(False)
+        y2 = B.attn_block_fwd(*args)
+    finally:
+        B.set_projection_fusion(True)
+    assert torch.equal(y, y2)
+    assert B.gemm_dep_timeouts() == 0
+
+
 # self-attention whose q, k and transposed v are one round of 128x160 tiles (token counts off every tile, adapters or none) or of 64x80
 @pytest.mark.parametrize("Bn,T,C,rank", [(2, 700, 640, 16), (1, 1003, 640, 0), (2, 261, 320, 24)])
 def test_attn_block_projections_in_one_round(B, Bn, T, C, rank):
@@ -765,6 +794,29 @@ def test_multi_lora_small(B):
     assert rel_err(host(y), ref) <= BF16_TOL
     wrong = O.multi_lora_linear(p["x"], pr["W"], pr["b"], pr["A"], pr["B"], [0.5, 1.0, 2.0], offs, [0, 1, 0, -1, 1, 2])
     assert rel_err(wrong, ref) > 3 * BF16_TOL
+
+
+# several problems of one launch on more than one round of 128x128 tiles: whole and partial k-steps of
+# the adapters, segments without one, column and row remainders, flags of several column tiles of producers
+@pytest.mark.parametrize("lengths,ranks,kernel", [([3001, 900, 2690], [64, 128, 64], "records"), ([2999, 129, 3500], [8, 72, 0], "guard records"),
+                                                  ([130, 6400, 60], [200, 64, 16], "guard flags"), ([3300, 3300], [0, 0], "")])
+def test_multi_lora_many_tiles(B, lengths, ranks, kernel):
+    r = rng(sum(lengths))
+    K, N, M = 64, 1284, sum(lengths)
+    draw = lambda *shape, s: G.bf16_round((s * r.standard_normal(shape)).astype(np.float32))
+    x, W, bias = draw(M, K, s=1.0), draw(N, K, s=0.1), draw(N, s=0.5)
+    A, Bm = [draw(k, K, s=0.3) for k in ranks if k], [draw(N, k, s=0.1) for k in ranks if k]
+    offsets = [sum(lengths[:i]) for i in range(len(lengths) + 1)]
+    have = [k > 0 for k in ranks]
+    adapters = [sum(have[:i]) if h else -1 for i, h in enumerate(have)]
+    args = (dev(x, B), dev(W, B), dev(bias, B), [dev(a, B) for a in A], [dev(b, B) for b in Bm], [0.5] * len(A), offsets, adapters)
+    with B.dry_run() as names:
+        B.multi_lora_linear_fwd(*args)
+    assert names[-1] == ("gemm 128x128/4 waves/2 stages " + kernel).strip()
+    ref = O.multi_lora_linear(x, W, bias, A, Bm, [0.5] * len(A), offsets, adapters)
+    assert rel_err(host(B.multi_lora_linear_fwd(*args)), ref) <= BF16_TOL
+    if A:
+        assert rel_err(O.linear(x, W, bias), ref) > 3 * BF16_TOL
 
 
 # ------------------------------------------------------------- lora_patch / lora_unpatch
