@@ -29,7 +29,7 @@ PEAK_HBM_GBS = 8000.0        # MI355X HBM3E
 # known size (lora_unpatch): see profiles/lora_patch_hbm_traffic.txt
 PATCH_TRAFFIC_BYTES = 10.64e9   # FETCH_SIZE + WRITE_SIZE per patch launch, scaled (profiles/lora_patch_hbm_traffic.txt)
 # the same two counters for the kernels that can be the stack's dominant one (same file), bytes per launch
-STACK_TRAFFIC_BYTES = {"self_attention": 59.8e6, "ff1": 142.9e6}
+STACK_TRAFFIC_BYTES = {"self_attention": 59.8e6, "ff1": 149.3e6}
 
 
 def stack_flops(cfg) -> float:
@@ -72,11 +72,11 @@ KERNEL_NAMES = {
     "self_attention": "attention_kernel, latent self-attention",
     "cross_attention": "attention_kernel, cross-attention to the text tokens",
     "qkv": "gemm_kernel, grouped q/k/v^T projections (+ the next cross-attention's text k/v)",
-    "attn_out": "gemm_kernel, attention output projection + residual",
-    "cross_q": "gemm_kernel, cross-attention query projection",
-    "ff1": "gemm_kernel, feed-forward in-projection with GEGLU epilogue",
+    "attn_out": "gemm16_kernel or gemm_kernel, attention output projection + residual",
+    "cross_q": "gemm16_kernel or gemm_kernel, cross-attention query projection",
+    "ff1": "gemm_geglu_kernel with down_kernel, or gemm_kernel: feed-forward in-projection with GEGLU epilogue",
     "ff2": "gemm_kernel, feed-forward out-projection + residual",
-    "proj_io": "gemm_kernel, proj_in / proj_out",
+    "proj_io": "gemm16_kernel or gemm_kernel, proj_in / proj_out",
     "layernorm": "layernorm_kernel",
     "groupnorm": "groupnorm_partial_kernel + groupnorm_apply_kernel",
 }
