@@ -43,8 +43,9 @@ struct Tile16 {
 };
 
 template <int V> struct IntC { static constexpr int v = V; };
+constexpr int RES_NONE = 0, RES_BF16 = 1, RES_F32 = 2;
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NRB>
+template <int BM, int BN, int WGM, int WGN, int WGK, int NRB, int RES>
 __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const GemmGroup g) {
     using T = Tile16<BM, BN, WGM, WGN, WGK, NRB>;
     constexpr int NW = T::NW, MI = T::MI, NI = T::NI, RN = T::RN, LPT = T::LPT, STAGES = T::STAGES, STAGE = T::STAGE_CH, NBLK = T::NBLK;
@@ -72,33 +73,30 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
 
     // ---- loader.  Load j of wavefront w fills 1 KB block j * NW + w of a stage (x rows, W rows, A rows);
     // where NW does not divide the blocks, the last wavefronts load the last block once more.
+    // (every wavefront-uniform choice is a select of scalars: as branches they cost more than the first loads' latency)
     uint32_t off[LPT];            // byte offset of this lane's chunk from its operand's first row
     uint32_t offb[LPT];           // ... in the tile of B (P.q1), or past what it holds: NONE
     const char* base[LPT];
     int dst[LPT];
     constexpr uint32_t NONE = 0xffffffffu;
+    const char* const xbase = reinterpret_cast<const char*>(P.p0 + (int64_t)m0 * P.ldp0);
+    const char* const wbase = reinterpret_cast<const char*>(P.q0 + (int64_t)n0 * P.ldq0);
+    const char* const abase = reinterpret_cast<const char*>(r ? P.p1 : P.q0);   // (a projection without adapter in a launch that has some: rows of W, and nothing done with the product)
+    const int xld = (int)P.ldp0 * 2, wld = (int)P.ldq0 * 2, ald = r ? (int)P.ldp1 * 2 : 0, bld = (int)P.ldq1 * 2;
 #pragma unroll
     for (int j = 0; j < LPT; ++j) {
         const int blk = min(j * NW + wave, NBLK - 1);
         dst[j] = blk * 1024;
         const int row = blk * 8 + (lane >> 3);
-        const int c = swz<8>(row, lane & 7);
-        offb[j] = NONE;
-        if (blk < BM / 8) {
-            const int m = min(m0 + row, Mp - 1) - m0;
-            off[j] = (uint32_t)((m * P.ldp0 + c * 8) * 2);
-            base[j] = reinterpret_cast<const char*>(P.p0 + (int64_t)m0 * P.ldp0);
-        } else if (NRB == 0 || blk < (BM + BN) / 8) {
-            const int n = min(n0 + row - BM, N - 1) - n0;
-            off[j] = (uint32_t)((n * P.ldq0 + c * 8) * 2);
-            base[j] = reinterpret_cast<const char*>(P.q0 + (int64_t)n0 * P.ldq0);
-            if (NRB && c * 8 < r) offb[j] = (uint32_t)((n * P.ldq1 + c * 8) * 2);
-        } else {
-            // (a projection without adapter in a launch that has some: rows of W, and nothing done with the product)
-            const int a = r ? min(row - BM - BN, r - 1) : 0;
-            off[j] = (uint32_t)((a * (r ? P.ldp1 : 0) + c * 8) * 2);
-            base[j] = reinterpret_cast<const char*>(r ? P.p1 : P.q0);
-        }
+        const int c16 = swz<8>(row, lane & 7) * 16;
+        const bool isx = blk < BM / 8, isa = NRB && blk >= (BM + BN) / 8;
+        const int first = isx ? 0 : isa ? BM + BN : BM;
+        const int last = isx ? Mp - 1 - m0 : isa ? (r ? r - 1 : 0) : N - 1 - n0;
+        const int ld = isx ? xld : isa ? ald : wld;
+        base[j] = isx ? xbase : isa ? abase : wbase;
+        const int k = min(row - first, last);
+        off[j] = (uint32_t)(k * ld + c16);
+        offb[j] = NRB && !isx && !isa && c16 < 2 * r ? (uint32_t)(k * bld + c16) : NONE;
     }
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
     auto load = [&](int t, int stg, int j) {
@@ -132,18 +130,23 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
     bf16x8 xf[2][MI], wf[2][NI], rf[2][NRB ? NRB : 1];
     // rows that are 16 apart share the swizzle: one LDS address per k-step, the rest are offsets
     const int lrow = l16 * 8, lsw = (l16 >> 1) & 7;
-    auto fetch = [&](int st, int kk, int fs, bool down) {
-        const u32x4* const s = lds + (st * STAGE + lrow + ((kk * 4 + quad) ^ lsw));
-        const u32x4* const sx = s + wm * 8;
-        const u32x4* const sw = s + (BM + wn) * 8;
-        const u32x4* const sr = s + (BM + BN + wr) * 8;
+    auto frag = [&](int st, int kk) { return lds + (st * STAGE + lrow + ((kk * 4 + quad) ^ lsw)); };
+    auto fetch_x = [&](int st, int kk, int fs) {
+        const u32x4* const sx = frag(st, kk) + wm * 8;
 #pragma unroll
         for (int mi = 0; mi < MI; ++mi) xf[fs][mi] = __builtin_bit_cast(bf16x8, sx[mi * 128]);
+    };
+    auto fetch_w = [&](int st, int kk, int fs) {
+        const u32x4* const sw = frag(st, kk) + (BM + wn) * 8;
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) wf[fs][ni] = __builtin_bit_cast(bf16x8, sw[ni * 128]);
-        if (down)
+    };
+    auto fetch = [&](int st, int kk, int fs) {
+        const u32x4* const sr = frag(st, kk) + (BM + BN + wr) * 8;
+        fetch_x(st, kk, fs);
+        fetch_w(st, kk, fs);
 #pragma unroll
-            for (int ri = 0; ri < NRB; ++ri) rf[fs][ri] = __builtin_bit_cast(bf16x8, sr[ri * 128]);
+        for (int ri = 0; ri < NRB; ++ri) rf[fs][ri] = __builtin_bit_cast(bf16x8, sr[ri * 128]);
     };
     // one k-step, loads [j0, j1) dealt between its MFMAs
     auto multiply = [&](int fs, bool down, auto ld, int j0, int j1) {
@@ -167,23 +170,56 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
         __builtin_amdgcn_sched_barrier(0);
     };
     auto no_load = [](int) {};
-    auto wait_tiles = [&](int newer) {
-        if (STAGES >= 5 && newer >= 4) wait_vmcnt<4 * LPT>();
-        else if (STAGES >= 4 && newer >= 3) wait_vmcnt<3 * LPT>();
-        else if (newer >= 2) wait_vmcnt<2 * LPT>();
-        else if (newer >= 1) wait_vmcnt<LPT>();
-        else wait_vmcnt<0>();
+    // ---- what the epilogue adds, requested when the first stage has landed: as long as one of the first STAGES is waited
+    // for, these NEXTRA loads may stay in flight too (loads retire in order).  Every lane loads, rows and columns past the end their
+    // last ones, so that the number is what it says.  (Requested at the last MFMAs, as before, a launch that is one round of
+    // tiles has nothing to hide them behind.  With the branch-free prologue and the straight-line epilogue below, operands from
+    // HBM: 8192x640x640 + 64 with an fp32 residual 24.2 -> 23.4 us, 1000x640x640 + 32 9.2 -> 8.2, 512x320x320 + 8 6.6 -> 6.0.)
+    constexpr int ME = WGK == 2 ? MI / 2 : MI;   // row blocks this wavefront finishes
+    const int mfirst = WGK == 2 ? wk * ME : 0;
+    const int mrow = m0 + wm + mfirst * 16 + l16, ncol = n0 + wn + quad * 4;
+    constexpr int NEXTRA = NI + (RES ? ME * NI : 0);
+    f32x4 resf[RES == RES_F32 ? ME : 1][NI];
+    u32x2 resb[RES == RES_BF16 ? ME : 1][NI], bias[NI];
+    auto load_extra = [&]() {
+        const uint16_t* const bp = P.bias ? P.bias : reinterpret_cast<const uint16_t*>(g_gemm_zeros);
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni) bias[ni] = *as_global(reinterpret_cast<const u32x2*>(bp + (P.bias ? min(ncol + ni * 16, N - 4) : 0)));
+#pragma unroll
+        for (int mi = 0; mi < (RES ? ME : 0); ++mi) {
+            const int64_t row = (int64_t)min(mrow + mi * 16, Mp - 1) * P.ldr;
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                const int64_t at = row + min(ncol + ni * 16, N - 4);
+                if (RES == RES_F32) resf[mi][ni] = *as_global(reinterpret_cast<const f32x4*>(static_cast<const float*>(P.res) + at));
+                else resb[mi][ni] = *as_global(reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(P.res) + at));
+            }
+        }
+    };
+    // tiles newer than the one waited for, which may stay in flight, and the loads above with them
+    auto wait_more = [&](int newer, auto extra) {
+        constexpr int E = decltype(extra)::v;
+        if (STAGES >= 5 && newer >= 4) wait_vmcnt<4 * LPT + E>();
+        else if (STAGES >= 4 && newer >= 3) wait_vmcnt<3 * LPT + E>();
+        else if (newer >= 2) wait_vmcnt<2 * LPT + E>();
+        else if (newer >= 1) wait_vmcnt<LPT + E>();
+        else wait_vmcnt<E>();
+    };
+    auto wait_tiles = [&](int newer, bool first) {      // first: the tile is one of the first STAGES
+        if (first) wait_more(newer, IntC<NEXTRA>());
+        else wait_more(newer, IntC<0>());
     };
 
     // ---- prologue
 #pragma unroll
     for (int d = 0; d < STAGES; ++d)
         if (d < nkt) issue(d, d);
-    wait_tiles(min(nkt - 1, STAGES - 1));
+    wait_tiles(min(nkt - 1, STAGES - 1), false);
     __syncthreads();
-    fetch(0, wk, 0, true);
+    fetch(0, wk, 0);
+    load_extra();
     if (PH == 2) {
-        fetch(0, 1, 1, true);
+        fetch(0, 1, 1);
         multiply(0, true, no_load, 0, 0);
     }
 
@@ -195,23 +231,23 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
     int st = 0, t = 0;
     auto step = [&](auto par, auto full) {
         constexpr int FS = PH == 2 ? 1 : decltype(par)::v;
-        if (decltype(full)::v) wait_vmcnt<(STAGES - 2) * LPT>();
-        else wait_tiles(min(nkt - 2 - t, STAGES - 2));
+        if (decltype(full)::v) wait_tiles(STAGES - 2, t + 1 < STAGES);
+        else wait_tiles(min(nkt - 2 - t, STAGES - 2), t + 1 < STAGES);
         __syncthreads();
         const int sn = st + 1 == STAGES ? 0 : st + 1;
-        fetch(sn, wk, FS ^ 1, true);
+        fetch(sn, wk, FS ^ 1);
         if (decltype(full)::v) {
             auto ld = [&](int j) { load(t + STAGES, st, j); };
             multiply(FS, true, ld, 0, LPT / PH);
             if (PH == 2) {
-                fetch(sn, 1, 1, true);
+                fetch(sn, 1, 1);
                 multiply(0, true, ld, LPT / PH, LPT);
             }
         } else {
             if (t + STAGES < nkt) issue(t + STAGES, st);
             multiply(FS, true, no_load, 0, 0);
             if (PH == 2) {
-                fetch(sn, 1, 1, true);
+                fetch(sn, 1, 1);
                 multiply(0, true, no_load, 0, 0);
             }
         }
@@ -241,32 +277,6 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
         step(IntC<1>(), IntC<0>());
     }
 
-    // residual rows of the blocks this wavefront will store, requested before the last MFMAs
-    constexpr int ME = WGK == 2 ? MI / 2 : MI;   // row blocks this wavefront finishes
-    const int mfirst = WGK == 2 ? wk * ME : 0;
-    f32x4 res[ME][NI];
-    const int mrow = m0 + wm + mfirst * 16 + l16, ncol = n0 + wn + quad * 4;
-#pragma unroll
-    for (int mi = 0; mi < ME; ++mi)
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-            res[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
-            const int m = mrow + mi * 16, n = ncol + ni * 16;
-            if (P.res && m < Mp && n < N) {
-                if (P.res_f32) {
-                    res[mi][ni] = *reinterpret_cast<const f32x4*>(static_cast<const float*>(P.res) + (int64_t)m * P.ldr + n);
-                } else {
-                    const u32x2 v = *reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(P.res) + (int64_t)m * P.ldr + n);
-                    res[mi][ni] = __builtin_bit_cast(f32x4, u32x4{v[0], v[1], 0u, 0u});   // raw: widened where it is used
-                }
-            }
-        }
-    u32x2 bias[NI];
-#pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-        bias[ni] = u32x2{0u, 0u};
-        if (P.bias && ncol + ni * 16 < N) bias[ni] = *reinterpret_cast<const u32x2*>(P.bias + ncol + ni * 16);
-    }
     multiply(PH == 2 ? 1 : 0, true, no_load, 0, 0);
 
     // ---- adapter: t = x A^T is whole (over the K groups) after this, rounded to bf16, and becomes the
@@ -275,6 +285,9 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
         wait_vmcnt<0>();
         __syncthreads();                    // the tile of B has landed; every fragment of the last tile is in registers
         const int sb = st + 1 == STAGES ? 0 : st + 1;
+        const bool both = PH == 2 && r > 32;                                 // its second k-step holds columns of the adapter too
+        fetch_w(sb, wk, 0);
+        if (both) fetch_w(sb, 1, 1);
         f32x4* const xch = reinterpret_cast<f32x4*>(lds + st * STAGE) + wmn * (MI * NRB * 64) + lane;
         if (WGK == 2) {
             if (wk == 1)
@@ -301,12 +314,10 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
         }
         // (a rank of at most RN: what lies between its columns and the 64 of the stage was loaded as zeros)
         __syncthreads();
-        fetch(sb, wk, 0, false);
+        fetch_x(sb, wk, 0);
+        if (both) fetch_x(sb, 1, 1);
         multiply(0, false, no_load, 0, 0);
-        if (PH == 2) {
-            fetch(sb, 1, 0, false);
-            multiply(0, false, no_load, 0, 0);
-        }
+        if (both) multiply(1, false, no_load, 0, 0);
     }
 
     // ---- sums of the K groups: each gives the other the half of the row blocks it does not finish
@@ -335,42 +346,61 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
             for (int ni = 0; ni < NI; ++ni) fin[mi][ni] = acc[mi][ni];
     }
 
-    // ---- bias, residual, store
+    // ---- bias, residual, store: what the problem asks for is decided once, and each choice is straight-line code.  (Two
+    // wavefronts on a SIMD issue an instruction every eight clocks or so: with the choices made per block the
+    // ten blocks of a 128x160 tile took 1.6 us.)
     const float alpha = P.alpha;
+    const int64_t ldy = P.ldy;
+    // (landed long ago; said here once, or the compiler waits piece by piece, for the stores ahead of a piece too)
 #pragma unroll
-    for (int mi = 0; mi < ME; ++mi)
+    for (int ni = 0; ni < NI; ++ni) {
+        asm volatile("" : "+v"(bias[ni]));
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-            const int m = mrow + mi * 16, n = ncol + ni * 16;
-            f32x4 v = fin[mi][ni];
-            v[0] = alpha * v[0] + bf16lo_to_f32(bias[ni][0]);
-            v[1] = alpha * v[1] + bf16hi_to_f32(bias[ni][0]);
-            v[2] = alpha * v[2] + bf16lo_to_f32(bias[ni][1]);
-            v[3] = alpha * v[3] + bf16hi_to_f32(bias[ni][1]);
-            if (P.res) {
-                if (P.res_f32) {
-                    v += res[mi][ni];
-                } else {
-                    const u32x4 w = __builtin_bit_cast(u32x4, res[mi][ni]);
+        for (int mi = 0; mi < (RES ? ME : 0); ++mi) {
+            if (RES == RES_F32) asm volatile("" : "+v"(resf[mi][ni]));
+            else asm volatile("" : "+v"(resb[mi][ni]));
+        }
+    }
+    constexpr int OUT_BF16 = 0, OUT_F32 = 1, OUT_TRANSPOSED = 2;   // transposed: 16 rows of x are 32 contiguous bytes
+    auto store = [&](auto out_kind, auto bounds) {
+        constexpr int OK = decltype(out_kind)::v;
+        char* const y = static_cast<char*>(P.y) + (OK == OUT_TRANSPOSED ? ((int64_t)ncol * ldy + mrow) * 2 : ((int64_t)mrow * ldy + ncol) * (OK == OUT_F32 ? 4 : 2));
+#pragma unroll
+        for (int mi = 0; mi < ME; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) {
+                f32x4 v = fin[mi][ni];
+                v[0] = alpha * v[0] + bf16lo_to_f32(bias[ni][0]);
+                v[1] = alpha * v[1] + bf16hi_to_f32(bias[ni][0]);
+                v[2] = alpha * v[2] + bf16lo_to_f32(bias[ni][1]);
+                v[3] = alpha * v[3] + bf16hi_to_f32(bias[ni][1]);
+                if (RES == RES_F32) v += resf[mi][ni];
+                if (RES == RES_BF16) {
+                    const u32x2 w = resb[mi][ni];
                     v[0] += bf16lo_to_f32(w[0]); v[1] += bf16hi_to_f32(w[0]);
                     v[2] += bf16lo_to_f32(w[1]); v[3] += bf16hi_to_f32(w[1]);
                 }
-            }
-            if (m < Mp && n < N) {
-                if (P.bias_on_rows == 2) {      // transposed: 16 rows of x are 32 contiguous bytes
-                    uint16_t* const yt = static_cast<uint16_t*>(P.y) + (int64_t)n * P.ldy + m;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) yt[e * P.ldy] = __builtin_bit_cast(uint16_t, (__bf16)v[e]);
-                } else if (P.y_f32) {
-                    *reinterpret_cast<f32x4*>(static_cast<float*>(P.y) + (int64_t)m * P.ldy + n) = v;
-                } else {
-                    bf16x4 o;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
-                    *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(P.y) + (int64_t)m * P.ldy + n) = o;
+                if (decltype(bounds)::v && !(mrow + mi * 16 < Mp && ncol + ni * 16 < N)) continue;
+                if (OK == OUT_F32) {
+                    *as_global(reinterpret_cast<f32x4*>(y + mi * ldy * 64 + ni * 64)) = v;
+                    continue;
                 }
+                bf16x4 o;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) o[e] = (__bf16)v[e];
+                if (OK == OUT_BF16) *as_global(reinterpret_cast<bf16x4*>(y + mi * ldy * 32 + ni * 32)) = o;
+                else
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) *as_global(reinterpret_cast<__bf16*>(y + (ni * 16 + e) * ldy * 2 + mi * 32)) = o[e];
             }
-        }
+    };
+    auto by_bounds = [&](auto out_kind) {
+        if (m0 + BM <= Mp && n0 + BN <= N) store(out_kind, IntC<0>());
+        else store(out_kind, IntC<1>());
+    };
+    if (RES == RES_NONE && P.bias_on_rows == 2) by_bounds(IntC<OUT_TRANSPOSED>());
+    else if (RES != RES_BF16 && P.y_f32) by_bounds(IntC<OUT_F32>());
+    else by_bounds(IntC<OUT_BF16>());
 }
 
 template <int BM, int BN, int WGM, int WGN, int WGK, int NRB>
@@ -388,7 +418,10 @@ static int launch16(GemmGroup& g, hipStream_t stream) {
     }
     g.total_tiles = total;
     if (total == 0 || SD_DRY_RUN("gemm16 %dx%d/%d; ", BM, BN, NRB)) return SD_OK;
-    hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB>), dim3((total + 7) & ~7), dim3(64 * WGM * WGN * WGK), 0, stream, g);
+    const dim3 grid((total + 7) & ~7), block(64 * WGM * WGN * WGK);
+    if (!g.p[0].res) hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_NONE>), grid, block, 0, stream, g);
+    else if (g.p[0].res_f32) hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_F32>), grid, block, 0, stream, g);
+    else hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_BF16>), grid, block, 0, stream, g);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }
@@ -422,7 +455,7 @@ static int tile16(const GemmGroup& g) {
         const GemmProblem& P = g.p[i];
         if (P.geglu_F > 0 || P.bias_on_rows == 1 || P.K0 % 64 || P.K1 > 64 || P.N % 4 || (P.bias_on_rows == 2 ? P.y_f32 || P.res : P.ldy % 4) || (P.res && P.ldr % 4) || P.Mp <= 0 || P.N <= 0 ||
             (uintptr_t)P.bias % 8 || (uintptr_t)P.y % (P.bias_on_rows == 2 ? 2 : P.y_f32 ? 16 : 8) || (uintptr_t)P.res % (P.res_f32 ? 16 : 8) ||
-            P.ldp0 * 512 >= (1ll << 31) || P.ldq0 * 512 >= (1ll << 31))
+            P.ldp0 * 512 >= (1ll << 31) || P.ldq0 * 512 >= (1ll << 31) || (P.res && (g.n > 1 || (P.y_f32 && !P.res_f32))))
             return 0;
         big += (long)((P.Mp + 127) / 128) * ((P.N + 159) / 160);
         mid += (long)((P.Mp + 63) / 64) * ((P.N + 159) / 160);

@@ -58,6 +58,12 @@ __device__ __forceinline__ void dma16_so(const void* sbase, uint32_t voff, uint3
     else
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(__builtin_amdgcn_readfirstlane(lds_base)), "v"(voff), "s"(uniform_ptr(sbase)) : "memory", "m0");
 }
+// A pointer to device memory that came out of the kernel's argument words, as one the compiler knows to be
+// global: it emits flat accesses otherwise, which hold up every wait for an LDS read too
+template <class T>
+__device__ __forceinline__ __attribute__((address_space(1))) T* as_global(T* p) {
+    return (__attribute__((address_space(1))) T*)p;
+}
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
@@ -81,47 +87,56 @@ static_assert(sizeof(GemmProblem) == sizeof(ProblemWords), "problem record size"
 // The tiles of signalling problems (down-projections that tiles of this same launch wait
 // for) come first and are dealt round-robin: they are the first workgroups dispatched on
 // every XCD, so all of them are running, or done, before any tile can wait for them.
-// Kernel arguments arrive through scalar loads of ~0.25 us each, and the compiler issues a
-// load next to its first use: left alone, a workgroup pays six or seven such rounds one after
-// the other before its first operand load.  Two rounds are forced instead: the header in one
-// batch (made opaque right away, so no load can sink below), then the whole problem record.
+// Kernel arguments arrive through scalar loads, and the compiler issues a load next to its first
+// use: left alone, a workgroup pays six or seven such rounds one after the other before its
+// first operand load.  One round is forced instead, 0.4 us: the header and the first problem's record
+// (made opaque right away, so no load can sink below); a tile of a later problem takes a second.
 // False: a workgroup beyond the last tile.
+struct ProblemRegs { u32x16u a, b; u32x8u c; u32x4u d, e; };
+__device__ __forceinline__ void load_problem(const GemmProblem& p, ProblemRegs& r) {
+    const uint32_t* const pw = reinterpret_cast<const uint32_t*>(&p);
+    r.a = *reinterpret_cast<const u32x16u*>(pw);
+    r.b = *reinterpret_cast<const u32x16u*>(pw + 16);
+    r.c = *reinterpret_cast<const u32x8u*>(pw + 32);
+    r.d = *reinterpret_cast<const u32x4u*>(pw + 40);
+    r.e = *reinterpret_cast<const u32x4u*>(pw + 44);
+}
 __device__ __forceinline__ bool gemm_pick_tile(const GemmGroup& g, int& tile, GemmProblem& P, int& zero_n, int32_t*& zero_ptr) {
     const uint32_t* const hw = reinterpret_cast<const uint32_t*>(&g);
     u32x16u ha = *reinterpret_cast<const u32x16u*>(hw);
     u32x4u hb = *reinterpret_cast<const u32x4u*>(hw + 16);
     u32x2u hc = *reinterpret_cast<const u32x2u*>(hw + 20);
-    uint32_t grid = gridDim.x;     // one more kernel argument (the launch geometry): same batch
-    asm volatile("" : "+s"(ha), "+s"(hb), "+s"(hc), "+s"(grid));
+    ProblemRegs r;
+    load_problem(g.p[0], r);
+    asm volatile("" : "+s"(ha), "+s"(hb), "+s"(hc), "+s"(r.a), "+s"(r.b), "+s"(r.c), "+s"(r.d), "+s"(r.e));
     const int total = (int)ha[1], lead = (int)ha[2], np = (int)ha[0];
     zero_n = (int)ha[3];
     zero_ptr = reinterpret_cast<int32_t*>(((uint64_t)ha[5] << 32) | ha[4]);
     tile = blockIdx.x;
     if (tile >= lead) {
-        const int per = ((int)grid - lead) >> 3, i = tile - lead;   // the grid holds a multiple of 8 beyond the leading tiles
+        const int per = (total - lead + 7) >> 3, i = tile - lead;   // the grid holds a multiple of 8 beyond the leading tiles
         tile = lead + (i & 7) * per + (i >> 3);
         if (tile >= total) return false;
     }
-    int pi = 0;
+    if (np > 1) {
+        int pi = 0;
 #pragma unroll
-    for (int i = 1; i < GEMM_MAX_PROBLEMS; ++i) {
-        const int ft = (int)(i < 10 ? ha[6 + i] : i < 14 ? hb[i - 10] : hc[i - 14]);
-        if (i < np && tile >= ft) pi = i;
+        for (int i = 1; i < GEMM_MAX_PROBLEMS; ++i) {
+            const int ft = (int)(i < 10 ? ha[6 + i] : i < 14 ? hb[i - 10] : hc[i - 14]);
+            if (i < np && tile >= ft) pi = i;
+        }
+        if (pi) {
+            load_problem(g.p[pi], r);
+            asm volatile("" : "+s"(r.a), "+s"(r.b), "+s"(r.c), "+s"(r.d), "+s"(r.e));
+        }
     }
-    const uint32_t* const pw = reinterpret_cast<const uint32_t*>(&g.p[pi]);
-    u32x16u ra = *reinterpret_cast<const u32x16u*>(pw);
-    u32x16u rb = *reinterpret_cast<const u32x16u*>(pw + 16);
-    u32x8u rc = *reinterpret_cast<const u32x8u*>(pw + 32);
-    u32x4u rd = *reinterpret_cast<const u32x4u*>(pw + 40);
-    u32x4u re = *reinterpret_cast<const u32x4u*>(pw + 44);
-    asm volatile("" : "+s"(ra), "+s"(rb), "+s"(rc), "+s"(rd), "+s"(re));
     ProblemWords words;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { words.w[i] = ra[i]; words.w[16 + i] = rb[i]; }
+    for (int i = 0; i < 16; ++i) { words.w[i] = r.a[i]; words.w[16 + i] = r.b[i]; }
 #pragma unroll
-    for (int i = 0; i < 8; ++i) words.w[32 + i] = rc[i];
+    for (int i = 0; i < 8; ++i) words.w[32 + i] = r.c[i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) { words.w[40 + i] = rd[i]; words.w[44 + i] = re[i]; }
+    for (int i = 0; i < 4; ++i) { words.w[40 + i] = r.d[i]; words.w[44 + i] = r.e[i]; }
     P = __builtin_bit_cast(GemmProblem, words);
     return true;
 }

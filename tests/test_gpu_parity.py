@@ -264,6 +264,30 @@ def test_lora_linear_one_round_of_tiles(B, M, K, N, rank, f32):
         assert rel_err(host(y) - res, upd) <= BF16_TOL
 
 
+# one round of in-tile tiles (128x160, 64x160, 64x80) with a residual in the output's type, which is requested while the first
+# stages are in flight: fewer steps than stages, as many, one more, many; ragged rows and columns, no rows of a second block
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("M,K,N,rank", [(16380, 64, 320, 0), (5000, 192, 644, 40), (8192, 256, 640, 64), (8190, 320, 636, 0), (4757, 128, 324, 24), (5900, 384, 320, 0),
+                                        (1, 64, 4, 8), (65, 128, 84, 0), (777, 192, 1284, 64), (130, 256, 76, 16), (63, 1280, 164, 32)])
+def test_lora_linear_one_round_of_tiles_residual(B, M, K, N, rank, f32):
+    import torch
+    r = rng(M + K + N + rank)
+    p = mkproj(r, N, K, rank, bias=M % 2 == 0, scale=0.7)
+    x = G.bf16_round(r.standard_normal((M, K)).astype(np.float32))
+    res = G.bf16_round(r.standard_normal((M, N)).astype(np.float32))
+    rd = torch.from_numpy(res).cuda()
+    call = lambda: B.lora_linear_fwd(dev(x, B), B.Proj.from_numpy(p), residual=rd if f32 else rd.bfloat16(), out_dtype=torch.float32 if f32 else torch.bfloat16)
+    with B.dry_run() as names:
+        call()
+    assert names[-1].startswith("gemm16 ")
+    got = host(call())
+    ref = O.lora_linear(x, p["W"], p["b"], p["A"], p["B"], p["scale"])
+    # a bf16 sum of up to |update| + |residual| is rounded once more: half a unit in the last of 8 bits of it
+    allow = 0 if f32 else 2.0 ** -9 * (np.abs(ref).max() + np.abs(res).max())
+    assert np.abs(got - res - ref).max() <= BF16_TOL * np.abs(ref).max() + allow
+    assert np.abs(got - ref).max() > 0.3 * np.abs(res).max()         # negative control: the residual is seen
+
+
 # feed-forward in-projections about the sizes where the wide tiles begin and end to pay: K loops of one, two, three and more steps, ranks of
 # less and more than 64 (which kernel each of them takes: test_lora_linear_geglu_every_kernel)
 @pytest.mark.parametrize("M,C,F,rank", [(6300, 64, 1288, 0), (8192, 128, 2560, 8), (4000, 192, 2568, 0), (1000, 640, 5120, 72), (988, 1280, 5120, 0), (2047, 1280, 5120, 64)])
