@@ -178,14 +178,14 @@ struct DepFlags {
 
 // LayerNorm that also clears the first flag array of the call if that is still due
 static int layernorm(const void* x, int x_f32, const uint16_t* g, const uint16_t* b, float eps, uint16_t* y, int M, int C,
-                     hipStream_t stream, DepFlags* dep) {
+                     hipStream_t stream, DepFlags* dep, ReadAhead* ahead = nullptr) {
     timing_mark(SD_TIMING_LAYERNORM, 0, stream);
     int rc;
     if (dep && dep->pending && M > 0) {
         dep->pending = false;
-        rc = launch_layernorm(x, x_f32, g, b, eps, y, M, C, stream, dep->f[0], dep->clear_words());
+        rc = launch_layernorm(x, x_f32, g, b, eps, y, M, C, stream, dep->f[0], dep->clear_words(), ahead);
     } else {
-        rc = launch_layernorm(x, x_f32, g, b, eps, y, M, C, stream);
+        rc = launch_layernorm(x, x_f32, g, b, eps, y, M, C, stream, nullptr, 0, ahead);
     }
     timing_mark(SD_TIMING_LAYERNORM, 1, stream);
     return rc;
@@ -383,6 +383,20 @@ static bool push_kv_calls(std::vector<ProjCall>& calls, const uint16_t* src, int
     return k_prescaled;
 }
 
+// Stacks whose weights and workspace take so many bytes have their weights read ahead: a little less than the last-level cache
+// holds.  What fits it stays there from call to call, and reading it again only costs (us without / with; MB of weights and workspace:
+// 2 x 1024 tokens of 1280 channels, 2 blocks + 64 524 / 537, 220; 3 blocks 800 / 749, 280; 4 blocks 1067 / 989;
+// 2 x 1000 of 640, 10 blocks + 16 1241 / 1250, 240; 2 x 4096 of 640, 10 blocks + 64 3492 / 3432, 370).
+constexpr uint64_t READ_AHEAD_FROM = 244ull << 20;
+// the weights of a projection [K] -> [N], for a launch ahead of it to read
+static void will_read(ReadAhead& ra, const sd_proj& p, int K, int N) {
+    ra.add(p.W, (size_t)N * K * 2);
+    if (p.r > 0) {
+        ra.add(p.A, (size_t)p.r * K * 2);
+        ra.add(p.B, (size_t)N * p.r * 2);
+    }
+}
+
 // ahead:    projections that do not depend on x, launched in this sub-layer's grouped GEMMs (the
 //           stack driver puts the next cross-attention's text keys / values here: on their own
 //           their long K loops set the duration of a launch, inside the much larger self-attention
@@ -391,12 +405,13 @@ static bool push_kv_calls(std::vector<ProjCall>& calls, const uint16_t* src, int
 static int attn_sublayer(const void* x, void* y, int io_f32, const uint16_t* ctx, int Tc, int Dc,
                          const uint16_t* g, const uint16_t* b, float eps, const sd_proj& pq, const sd_proj& pk,
                          const sd_proj& pv, const sd_proj& po, int Bn, int T, int C, int heads, const AttnWs& w,
-                         hipStream_t stream, const std::vector<ProjCall>* ahead = nullptr, bool kv_ready = false, DepFlags* dep = nullptr) {
+                         hipStream_t stream, const std::vector<ProjCall>* ahead = nullptr, bool kv_ready = false, DepFlags* dep = nullptr,
+                         ReadAhead* read_ahead = nullptr) {
     const int M = Bn * T;
     const int Tk = ctx ? Tc : T;
     const int Kkv = ctx ? Dc : C;
     const int Tkp = pad8(Tk);
-    int rc = layernorm(x, io_f32, g, b, eps, w.n, M, C, stream, dep);
+    int rc = layernorm(x, io_f32, g, b, eps, w.n, M, C, stream, dep, read_ahead);
     if (rc) return rc;
     const uint16_t* src = ctx ? ctx : w.n;
     std::vector<ProjCall> calls;
@@ -413,17 +428,19 @@ static int attn_sublayer(const void* x, void* y, int io_f32, const uint16_t* ctx
         k_prescaled = push_kv_calls(calls, src, Kkv, Tk, pk, pv, w.k, w.vt, w.tk, w.tv, Bn, C);
     }
     if ((rc = run_projections(calls.data(), (int)calls.size(), stream, ctx ? SD_TIMING_CROSS_Q : SD_TIMING_QKV, dep))) return rc;
+    if (read_ahead) read_ahead->launched();
     const int atag = ctx ? SD_TIMING_CROSS_ATTENTION : SD_TIMING_SELF_ATTENTION;
     timing_mark(atag, 0, stream);
     int cut = 0;
     // the counters were cleared by this call's first LayerNorm launch, at the latest by the one above
     int32_t* const arrived = (dep && dep->arrived && !dep->pending && g_fuse_attention_merge) ? dep->arrived : nullptr;
     rc = launch_attention(w.q, C, kbuf, C, vtbuf, (int64_t)Bn * Tkp, w.a, C, Bn, T, Tk, Tkp, heads, k_prescaled, w.scratch, w.scratch_bytes, &cut, stream,
-                          arrived, DepFlags::ARRIVED);
+                          arrived, DepFlags::ARRIVED, read_ahead);
     timing_mark(atag, 1, stream);
     if (rc) return rc;
     if ((rc = launch_attention_merge(w.scratch, w.a, C, Bn, T, heads, k_prescaled, cut, stream))) return rc;
     ProjCall oc = {w.a, C, M, C, C, &po, w.to, {y, C, io_f32, x, C, false, 0}};
+    if (read_ahead) read_ahead->launched();
     return run_projections(&oc, 1, stream, SD_TIMING_ATTN_OUT, dep);
 }
 
@@ -440,9 +457,10 @@ static bool carve_ff(Workspace& ws, FfWs& w, int M, int C, int F, int rmax) {
 
 static int ff_sublayer(const void* x, void* y, int io_f32, const uint16_t* g, const uint16_t* b, float eps,
                        const sd_proj& p1, const sd_proj& p2, int M, int C, int F, const FfWs& w, hipStream_t stream, DepFlags* dep = nullptr,
-                       uint16_t* y_bf16 = nullptr) {
-    int rc = layernorm(x, io_f32, g, b, eps, w.n, M, C, stream, dep);
+                       uint16_t* y_bf16 = nullptr, ReadAhead* read_ahead = nullptr) {
+    int rc = layernorm(x, io_f32, g, b, eps, w.n, M, C, stream, dep, read_ahead);
     if (rc) return rc;
+    if (read_ahead) read_ahead->launched(), read_ahead->launched();
     ProjCall c1 = {w.n, C, M, C, F, &p1, w.t1, {w.g, F, 0, nullptr, 0, false, F}};
     if ((rc = run_projections(&c1, 1, stream, SD_TIMING_FF1, dep))) return rc;
     // y_bf16: the sub-layer's output goes there, rounded once from the fp32 sum, instead of to y
@@ -834,18 +852,36 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
     ProjCall cin = {sw.g, C, M, C, C, &p->proj_in, sw.f.t1, {sw.h, C, 1, nullptr, 0, false, 0}};
     sw.dep.reset();
     if ((rc = run_projections(&cin, 1, s, SD_TIMING_PROJ_IO, &sw.dep))) return rc;
+    // what the launches read, launch by launch
+    ReadAhead weights;
+    for (int i = 0; i < p->depth; ++i) {
+        const sd_block_params& b = p->blocks[i];
+        for (const sd_proj* q : {&b.k2, &b.v2}) will_read(weights, *q, Dc, C);
+        for (const sd_proj* q : {&b.q1, &b.k1, &b.v1}) will_read(weights, *q, C, C);
+        weights.mark();
+        for (const sd_proj* q : {&b.o1, &b.q2, &b.o2}) {
+            will_read(weights, *q, C, C);
+            weights.mark();
+        }
+        will_read(weights, b.ff1, C, 8 * C);
+        weights.mark();
+        will_read(weights, b.ff2, 4 * C, C);
+        weights.mark();
+    }
+    will_read(weights, p->proj_out, C, C);
+    ReadAhead* const read_ahead = weights.total + w.used >= READ_AHEAD_FROM ? &weights : nullptr;
     for (int i = 0; i < p->depth; ++i) {
         const sd_block_params& b = p->blocks[i];
         // the text keys / values of this block's cross-attention ride in the self-attention launches
         std::vector<ProjCall> ahead;
         push_kv_calls(ahead, ctx, Dc, Tc, b.k2, b.v2, sw.a.k2, sw.a.vt2, sw.a.tk2, sw.a.tv2, Bn, C);
-        if ((rc = attn_sublayer(sw.h, sw.h, 1, nullptr, 0, 0, b.ln1_g, b.ln1_b, 1e-5f, b.q1, b.k1, b.v1, b.o1, Bn, T, C, heads, sw.a, s, &ahead, false, &sw.dep)))
+        if ((rc = attn_sublayer(sw.h, sw.h, 1, nullptr, 0, 0, b.ln1_g, b.ln1_b, 1e-5f, b.q1, b.k1, b.v1, b.o1, Bn, T, C, heads, sw.a, s, &ahead, false, &sw.dep, read_ahead)))
             return rc;
-        if ((rc = attn_sublayer(sw.h, sw.h, 1, ctx, Tc, Dc, b.ln2_g, b.ln2_b, 1e-5f, b.q2, b.k2, b.v2, b.o2, Bn, T, C, heads, sw.a, s, nullptr, true, &sw.dep)))
+        if ((rc = attn_sublayer(sw.h, sw.h, 1, ctx, Tc, Dc, b.ln2_g, b.ln2_b, 1e-5f, b.q2, b.k2, b.v2, b.o2, Bn, T, C, heads, sw.a, s, nullptr, true, &sw.dep, read_ahead)))
             return rc;
         // the last block hands its output to proj_out as bf16 directly
         if ((rc = ff_sublayer(sw.h, sw.h, 1, b.ln3_g, b.ln3_b, 1e-5f, b.ff1, b.ff2, M, C, 4 * C, sw.f, s, &sw.dep,
-                              i == p->depth - 1 ? sw.g : nullptr)))
+                              i == p->depth - 1 ? sw.g : nullptr, read_ahead)))
             return rc;
     }
     // proj_out + input residual, bf16 out

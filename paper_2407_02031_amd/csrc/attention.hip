@@ -26,6 +26,7 @@
 // per-tile counter; the half that arrives second merges the two inside the launch (without
 // counters, a second, small kernel merges them).
 #include "common.hpp"
+#include "read_ahead.hpp"
 
 namespace sd {
 
@@ -105,7 +106,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
                                                const uint16_t* __restrict__ vt, int64_t ldvt,
                                                uint16_t* __restrict__ out, int64_t ldo,
                                                int Tq, int Tk, int Tkp, int heads, int qtiles, float c,
-                                               int nfull, int nsplit, float* __restrict__ parts, int32_t* __restrict__ arrived,
+                                               int nfull, int nsplit, int total, float* __restrict__ parts, int32_t* __restrict__ arrived,
                                                lds_u32x4* const ldsK, lds_u32x4* const ldsV, lds_i32* const wg_redo, const int tid, const int bid) {
     constexpr int QB = 1;             // 32-query blocks per wavefront
     constexpr int BQ = 4 * 32 * QB;
@@ -115,7 +116,6 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     const int nt = (Tk + 63) >> 6;
     int tile, s0 = 0, s1 = nt, part = -1;   // steps [s0, s1) of the tile; part >= 0: a half tile
     if (nsplit == 0) {
-        const int total = gridDim.x;
         tile = bid;
         if ((total & 7) == 0) tile = (tile & 7) * (total >> 3) + (tile >> 3);
     } else {
@@ -533,13 +533,23 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     return false;
 }
 
-template <bool PRE, bool TRY>
+template <bool PRE, bool TRY, bool AHEAD>
 __global__ __launch_bounds__(256, 3) void attention_kernel(const uint16_t* __restrict__ q, int64_t ldq,
                                                         const uint16_t* __restrict__ k, int64_t ldk,
                                                         const uint16_t* __restrict__ vt, int64_t ldvt,
                                                         uint16_t* __restrict__ out, int64_t ldo,
                                                         int Tq, int Tk, int Tkp, int heads, int qtiles, float c,
-                                                        int nfull, int nsplit, float* __restrict__ parts, int32_t* __restrict__ arrived) {
+                                                        int nfull, int nsplit, float* __restrict__ parts, int32_t* __restrict__ arrived,
+                                                        const std::conditional_t<AHEAD, ReadRanges, NoRanges> ra) {
+    const int total = AHEAD ? nfull + 2 * nsplit : (int)gridDim.x;
+    if constexpr (AHEAD) {
+        // (the arguments in one batch, not a second one behind the branch)
+        asm volatile("" ::"s"(q), "s"(ldq), "s"(k), "s"(ldk), "s"(vt), "s"(ldvt), "s"(Tq), "s"(Tk), "s"(Tkp), "s"(heads), "s"(qtiles));
+        if ((int)blockIdx.x >= total) {
+            read_ahead<16>(ra, (int)blockIdx.x - total, (int)threadIdx.x);
+            return;
+        }
+    }
     __shared__ u32x4 ldsK[2 * 64 * 8];
     __shared__ u32x4 ldsV[3 * 64 * 8];
     __shared__ int32_t wg_redo;         // some wavefront's unmeasured attempt overflowed
@@ -548,9 +558,9 @@ __global__ __launch_bounds__(256, 3) void attention_kernel(const uint16_t* __res
     lds_i32* const redo = (lds_i32*)&wg_redo;
     if (TRY && threadIdx.x == 0) *redo = 0;    // (ordered before its first use by the key loop's barriers)
     if (!TRY) {
-        (void)attention_body<PRE, true>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk, lv, redo,
+        (void)attention_body<PRE, true>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, total, parts, arrived, lk, lv, redo,
                                         (int)threadIdx.x, (int)blockIdx.x);
-    } else if (attention_body<PRE, false>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk, lv, redo,
+    } else if (attention_body<PRE, false>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, total, parts, arrived, lk, lv, redo,
                                    (int)threadIdx.x, (int)blockIdx.x)) {
         // Second attempt, in the measured form, for inputs whose scores climb by more than 2^100
         // over a key range.  Its inputs pass through empty assembly statements so that it shares
@@ -561,7 +571,7 @@ __global__ __launch_bounds__(256, 3) void attention_kernel(const uint16_t* __res
         uint16_t* out2 = out;
         lds_u32x4 *lk2 = lk, *lv2 = lv;
         asm volatile("" : "+v"(tid2), "+s"(bid2), "+s"(q2), "+s"(k2), "+s"(vt2), "+s"(out2), "+s"(lk2), "+s"(lv2));
-        (void)attention_body<PRE, true>(q2, ldq, k2, ldk, vt2, ldvt, out2, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, parts, arrived, lk2, lv2,
+        (void)attention_body<PRE, true>(q2, ldq, k2, ldk, vt2, ldvt, out2, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, total, parts, arrived, lk2, lv2,
                                         redo, tid2, bid2);
     }
 }
@@ -620,7 +630,7 @@ size_t attention_scratch_bytes(int Bn, int Tq, int Tk, int heads) {
 int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t ldk,
                      const uint16_t* vt, int64_t ldvt, uint16_t* out, int64_t ldo,
                      int Bn, int Tq, int Tk, int Tkp, int heads, bool k_prescaled, void* scratch, size_t scratch_bytes, int* cut_tiles,
-                     hipStream_t stream, int32_t* arrived, int arrived_n) {
+                     hipStream_t stream, int32_t* arrived, int arrived_n, ReadAhead* ahead) {
     SD_REQUIRE(q && k && vt && out, SD_EINVAL, "attention: null pointer");
     SD_REQUIRE(Tk >= 1 && Tkp >= Tk && Tkp % 8 == 0, SD_EINVAL, "attention: Tk=%d Tkp=%d", Tk, Tkp);
     SD_REQUIRE(ldq % 8 == 0 && ldk % 8 == 0 && ldvt % 8 == 0 && ldo % 4 == 0, SD_EINVAL, "attention: leading dimensions");
@@ -643,13 +653,17 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     const int nt = (Tk + 63) / 64;
     *cut_tiles = arrived ? 0 : nsplit;
     if (SD_DRY_RUN("attention%s%s%s; ", k_prescaled ? " prescaled" : "", k_prescaled || nt >= 20 ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "")) return SD_OK;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(nfull + 2 * nsplit)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
-                           qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived);
+    // Read-ahead in the room that three workgroups to a CU leave: 8 MB and 2 MB per key tile, which the launch is long
+    // enough for.  (With 1 MB per key tile the queue falls behind at 32 x 32 tokens: 2540 us per stack for 2500, 2658 without any.)
+    const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, 3l * device_cus() - (nfull + 2l * nsplit), 16) : ReadRanges{};
+    auto go = [&](auto kernel, const auto& ranges) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(nfull + 2 * nsplit + ra.wgs)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
+                           qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived, ranges);
     };
-    if (k_prescaled) go(attention_kernel<true, true>);
-    else if (nt >= 20) go(attention_kernel<false, true>);
-    else go(attention_kernel<false, false>);
+    if (k_prescaled && ra.wgs) go(attention_kernel<true, true, true>, ra);
+    else if (k_prescaled) go(attention_kernel<true, true, false>, NoRanges{});
+    else if (nt >= 20) go(attention_kernel<false, true, false>, NoRanges{});
+    else go(attention_kernel<false, false, false>, NoRanges{});
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }

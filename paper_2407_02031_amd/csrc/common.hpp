@@ -10,6 +10,7 @@
 
 #include "../../include/swiftdiff.h"
 #include "dep_record.hpp"
+#include "read_queue.hpp"
 
 namespace sd {
 
@@ -187,7 +188,7 @@ int gemm_dep_timeouts(long long* count);
 // LayerNorm rows of x [M, C] (fp32 or bf16) -> bf16.
 // zero_ptr[0 .. zero_n) is cleared by the same launch (dependency flags of a later launch)
 int launch_layernorm(const void* x, int x_f32, const uint16_t* gamma, const uint16_t* beta, float eps,
-                     uint16_t* y, int M, int C, hipStream_t stream, int32_t* zero_ptr = nullptr, int zero_n = 0);
+                     uint16_t* y, int M, int C, hipStream_t stream, int32_t* zero_ptr = nullptr, int zero_n = 0, ReadAhead* ahead = nullptr);
 // fp32 [n] -> bf16, bf16 -> fp32 converters for the stack boundary
 int launch_cvt_bf16_to_f32(const uint16_t* x, float* y, size_t n, hipStream_t stream);
 int launch_cvt_f32_to_bf16(const float* x, uint16_t* y, size_t n, hipStream_t stream);
@@ -203,7 +204,7 @@ size_t groupnorm_partials_bytes(int Bn, int T, int groups);
 int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t ldk,
                      const uint16_t* vt, int64_t ldvt, uint16_t* out, int64_t ldo,
                      int Bn, int Tq, int Tk, int Tkp, int heads, bool k_prescaled, void* scratch, size_t scratch_bytes, int* cut_tiles,
-                     hipStream_t stream, int32_t* arrived = nullptr, int arrived_n = 0);
+                     hipStream_t stream, int32_t* arrived = nullptr, int arrived_n = 0, ReadAhead* ahead = nullptr);
 // second kernel of a launch that cut tiles (*cut_tiles > 0 above): merges the halves into `out`
 int launch_attention_merge(const void* scratch, uint16_t* out, int64_t ldo, int Bn, int Tq, int heads, bool k_prescaled, int cut_tiles,
                            hipStream_t stream);

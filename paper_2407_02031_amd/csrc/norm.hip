@@ -2,6 +2,7 @@
 // converters at the stack boundary.  All statistics in fp32, biased variance, two passes
 // over register-resident (LayerNorm) or shift-centred (GroupNorm) data.  HBM-bound.
 #include "common.hpp"
+#include "read_ahead.hpp"
 
 #include <algorithm>
 
@@ -15,10 +16,17 @@ constexpr int LN_MAXJ = 8;   // float4 chunks per lane: 64 lanes * 4 * 8 = 2048 
 // JN: chunks per lane the row needs (C <= 256 * JN); R: rows per wavefront, all of whose loads
 // are issued before the first is used (the kernel is a stream: bytes in flight are what counts).
 // zero_ptr/zero_n: flags that a later launch of the same call expects to find cleared.
-template <bool XF32, int JN, int R>
+template <bool XF32, int JN, int R, bool AHEAD>
 __global__ __launch_bounds__(256) void layernorm_kernel(const void* __restrict__ xv, const uint16_t* __restrict__ gamma,
                                                         const uint16_t* __restrict__ beta, float eps,
-                                                        uint16_t* __restrict__ y, int M, int C, int32_t* zero_ptr, int zero_n) {
+                                                        uint16_t* __restrict__ y, int M, int C, int32_t* zero_ptr, int zero_n, const std::conditional_t<AHEAD, ReadRanges, NoRanges> ra) {
+    if constexpr (AHEAD) {
+        const int wgs = (M + 4 * R - 1) / (4 * R);
+        if ((int)blockIdx.x >= wgs) {
+            read_ahead<8>(ra, (int)blockIdx.x - wgs, (int)threadIdx.x);
+            return;
+        }
+    }
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < zero_n; i += 256) zero_ptr[i] = 0;
     const int lane = threadIdx.x & 63;
@@ -101,26 +109,29 @@ __global__ __launch_bounds__(256) void layernorm_kernel(const void* __restrict__
 constexpr int LN_ROWS = 1;
 template <bool XF32, int JN, int R>
 static void launch_ln(const void* x, const uint16_t* gamma, const uint16_t* beta, float eps, uint16_t* y, int M, int C,
-                      int32_t* zero_ptr, int zero_n, hipStream_t stream) {
-    hipLaunchKernelGGL((layernorm_kernel<XF32, JN, R>), dim3((M + 4 * R - 1) / (4 * R)), dim3(256), 0, stream, x, gamma, beta, eps, y, M, C,
-                       zero_ptr, zero_n);
+                      int32_t* zero_ptr, int zero_n, hipStream_t stream, const ReadRanges& ra) {
+    const dim3 grid((M + 4 * R - 1) / (4 * R) + ra.wgs);
+    if (ra.wgs) hipLaunchKernelGGL((layernorm_kernel<XF32, JN, R, true>), grid, dim3(256), 0, stream, x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, ra);
+    else hipLaunchKernelGGL((layernorm_kernel<XF32, JN, R, false>), grid, dim3(256), 0, stream, x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, NoRanges{});
 }
 
 int launch_layernorm(const void* x, int x_f32, const uint16_t* gamma, const uint16_t* beta, float eps,
-                     uint16_t* y, int M, int C, hipStream_t stream, int32_t* zero_ptr, int zero_n) {
+                     uint16_t* y, int M, int C, hipStream_t stream, int32_t* zero_ptr, int zero_n, ReadAhead* ahead) {
     SD_REQUIRE(C % 4 == 0 && C > 0 && C <= 64 * 4 * LN_MAXJ, SD_EUNSUPPORTED, "layernorm: C=%d (need C %% 4 == 0, C <= %d)", C,
                64 * 4 * LN_MAXJ);
     if (M <= 0) return zero_n > 0 ? launch_clear_flags(zero_ptr, zero_n, stream) : SD_OK;
     if (SD_DRY_RUN("layernorm%s; ", zero_n > 0 ? " clear" : "")) return SD_OK;
+    // read-ahead: 8 MB, in workgroups small enough to leave eight on a CU (4 MB: the queue falls behind; 12: the launch takes longer than they save)
+    const ReadRanges ra = ahead ? ahead->take(8ull << 20, 512, 8) : ReadRanges{};
     if (C <= 768) {          // SDXL's 320 and 640 channels: three chunks per lane
-        if (x_f32) launch_ln<true, 3, LN_ROWS>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream);
-        else launch_ln<false, 3, LN_ROWS>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream);
+        if (x_f32) launch_ln<true, 3, LN_ROWS>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream, ra);
+        else launch_ln<false, 3, LN_ROWS>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream, ra);
     } else if (C <= 1280) {
-        if (x_f32) launch_ln<true, 5, 1>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream);
-        else launch_ln<false, 5, 1>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream);
+        if (x_f32) launch_ln<true, 5, 1>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream, ra);
+        else launch_ln<false, 5, 1>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream, ra);
     } else {
-        if (x_f32) launch_ln<true, LN_MAXJ, 1>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream);
-        else launch_ln<false, LN_MAXJ, 1>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream);
+        if (x_f32) launch_ln<true, LN_MAXJ, 1>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream, ra);
+        else launch_ln<false, LN_MAXJ, 1>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream, ra);
     }
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
