@@ -457,7 +457,7 @@ static bool carve_ff(Workspace& ws, FfWs& w, int M, int C, int F, int rmax) {
 
 static int ff_sublayer(const void* x, void* y, int io_f32, const uint16_t* g, const uint16_t* b, float eps,
                        const sd_proj& p1, const sd_proj& p2, int M, int C, int F, const FfWs& w, hipStream_t stream, DepFlags* dep = nullptr,
-                       uint16_t* y_bf16 = nullptr, ReadAhead* read_ahead = nullptr) {
+                       uint16_t* y_bf16 = nullptr, ReadAhead* read_ahead = nullptr, const std::vector<ProjCall>* riders = nullptr) {
     int rc = layernorm(x, io_f32, g, b, eps, w.n, M, C, stream, dep, read_ahead);
     if (rc) return rc;
     if (read_ahead) read_ahead->launched(), read_ahead->launched();
@@ -467,7 +467,36 @@ static int ff_sublayer(const void* x, void* y, int io_f32, const uint16_t* g, co
     // (the stack's last block: what follows reads bf16, and the fp32 stream is not needed again)
     ProjCall c2 = {w.g, F, M, F, C, &p2, w.t2, {y, C, io_f32, x, C, false, 0}};
     if (y_bf16) c2.o = {y_bf16, C, 0, x, C, false, 0, 0.f, io_f32};
-    return run_projections(&c2, 1, stream, SD_TIMING_FF2, dep);
+    if (!riders) return run_projections(&c2, 1, stream, SD_TIMING_FF2, dep);
+    std::vector<ProjCall> calls{c2};
+    calls.insert(calls.end(), riders->begin(), riders->end());
+    return run_projections(calls.data(), (int)calls.size(), stream, SD_TIMING_FF2, dep);
+}
+
+// Whether the text keys / values of the next block (`riders`) go into this block's ff2 launch instead of into the next q, k, v
+// launch: where ff2 takes the general kernel and leaves CUs idle that hold all of their tiles, and its K loop is the longer one.
+static bool ff2_takes_riders(const sd_proj& p2, int M, int C, int F, const std::vector<ProjCall>& riders, bool fused) {
+    long general = 0, tall = 0, lead = 0;
+    int problems = 0;
+    auto count = [&](int m, int n, int r, bool transposed) {
+        const int rows = transposed ? n : m, cols = transposed ? m : n;
+        general += (long)((rows + 127) / 128) * ((cols + 127) / 128);
+        tall += (long)((rows + 255) / 256) * ((cols + 127) / 128);
+        lead += (long)((m + 127) / 128) * ((r + 63) / 64);
+        problems += r > 0 ? 2 : 1;
+    };
+    count(M, C, p2.r, false);
+    if (general <= 128 || !fused) return false;
+    for (const ProjCall& c : riders) {
+        if (c.K > F) return false;
+        count(c.M, c.N, c.p->r, c.o.transposed);
+    }
+    if (problems > GEMM_MAX_PROBLEMS) return false;
+    GemmGroup g;
+    memset(&g, 0, sizeof(g));
+    ProjCall c2 = {reinterpret_cast<const uint16_t*>(256), F, M, F, C, &p2, reinterpret_cast<uint16_t*>(256), {reinterpret_cast<void*>(256), C, 1, reinterpret_cast<const void*>(256), C, false, 0}};
+    if (push_main(g, nullptr, c2) || gemm16_takes(g)) return false;
+    return gemm_one_round(general, lead) || tall + lead / 2 <= 256;
 }
 
 static int rmax_of(const sd_proj* const* ps, int n) {
@@ -854,9 +883,18 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
     if ((rc = run_projections(&cin, 1, s, SD_TIMING_PROJ_IO, &sw.dep))) return rc;
     // what the launches read, launch by launch
     ReadAhead weights;
+    auto text_calls = [&](const sd_block_params& b) {
+        std::vector<ProjCall> calls;
+        push_kv_calls(calls, ctx, Dc, Tc, b.k2, b.v2, sw.a.k2, sw.a.vt2, sw.a.tk2, sw.a.tv2, Bn, C);
+        return calls;
+    };
+    // the text keys / values of a block's cross-attention ride in a launch before it
+    std::vector<char> early(p->depth + 1, 0);     // ... in the ff2 launch of the block before, not in the block's q, k, v launch
+    for (int i = 1; i < p->depth; ++i) early[i] = ff2_takes_riders(p->blocks[i - 1].ff2, M, C, 4 * C, text_calls(p->blocks[i]), g_fuse_projections);
     for (int i = 0; i < p->depth; ++i) {
         const sd_block_params& b = p->blocks[i];
-        for (const sd_proj* q : {&b.k2, &b.v2}) will_read(weights, *q, Dc, C);
+        if (!early[i])
+            for (const sd_proj* q : {&b.k2, &b.v2}) will_read(weights, *q, Dc, C);
         for (const sd_proj* q : {&b.q1, &b.k1, &b.v1}) will_read(weights, *q, C, C);
         weights.mark();
         for (const sd_proj* q : {&b.o1, &b.q2, &b.o2}) {
@@ -866,22 +904,24 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
         will_read(weights, b.ff1, C, 8 * C);
         weights.mark();
         will_read(weights, b.ff2, 4 * C, C);
+        if (early[i + 1])
+            for (const sd_proj* q : {&p->blocks[i + 1].k2, &p->blocks[i + 1].v2}) will_read(weights, *q, Dc, C);
         weights.mark();
     }
     will_read(weights, p->proj_out, C, C);
     ReadAhead* const read_ahead = weights.total + w.used >= READ_AHEAD_FROM ? &weights : nullptr;
     for (int i = 0; i < p->depth; ++i) {
         const sd_block_params& b = p->blocks[i];
-        // the text keys / values of this block's cross-attention ride in the self-attention launches
-        std::vector<ProjCall> ahead;
-        push_kv_calls(ahead, ctx, Dc, Tc, b.k2, b.v2, sw.a.k2, sw.a.vt2, sw.a.tk2, sw.a.tv2, Bn, C);
+        std::vector<ProjCall> ahead, riders;
+        if (!early[i]) ahead = text_calls(b);
+        if (early[i + 1]) riders = text_calls(p->blocks[i + 1]);
         if ((rc = attn_sublayer(sw.h, sw.h, 1, nullptr, 0, 0, b.ln1_g, b.ln1_b, 1e-5f, b.q1, b.k1, b.v1, b.o1, Bn, T, C, heads, sw.a, s, &ahead, false, &sw.dep, read_ahead)))
             return rc;
         if ((rc = attn_sublayer(sw.h, sw.h, 1, ctx, Tc, Dc, b.ln2_g, b.ln2_b, 1e-5f, b.q2, b.k2, b.v2, b.o2, Bn, T, C, heads, sw.a, s, nullptr, true, &sw.dep, read_ahead)))
             return rc;
         // the last block hands its output to proj_out as bf16 directly
         if ((rc = ff_sublayer(sw.h, sw.h, 1, b.ln3_g, b.ln3_b, 1e-5f, b.ff1, b.ff2, M, C, 4 * C, sw.f, s, &sw.dep,
-                              i == p->depth - 1 ? sw.g : nullptr, read_ahead)))
+                              i == p->depth - 1 ? sw.g : nullptr, read_ahead, early[i + 1] ? &riders : nullptr)))
             return rc;
     }
     // proj_out + input residual, bf16 out
