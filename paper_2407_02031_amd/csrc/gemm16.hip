@@ -22,7 +22,8 @@
 
 namespace sd {
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NRB>
+// DEPTH: ring stages of a tile of which 160 KB hold six or more
+template <int BM, int BN, int WGM, int WGN, int WGK, int NRB, int DEPTH>
 struct Tile16 {
     static constexpr int NW = WGM * WGN * WGK;
     static constexpr int MI = BM / WGM / 16, NI = BN / WGN / 16;   // 16x16 blocks of a wavefront
@@ -31,13 +32,12 @@ struct Tile16 {
     static constexpr int NBLK = ROWS / 8;                          // 1 KB blocks (8 rows of 128 bytes) of a stage
     static constexpr int LPT = (NBLK + NW - 1) / NW;               // loads per wavefront and stage
     static constexpr int STAGE_CH = ROWS * 8;                      // 16-byte chunks of a stage
-    // as many stages as 160 KB hold, five at most; two workgroups per CU if three stages leave room for that
     static constexpr int FIT = 160 * 1024 / (ROWS * 128);
-    static constexpr int STAGES = FIT >= 6 ? 3 : FIT;
+    static constexpr int STAGES = FIT >= 6 ? DEPTH : FIT;
     static constexpr int EXCH = WGK > 1 ? NW * (MI / 2) * NI * 64 : 0;   // chunks of the exchange of the groups' sums
     static constexpr int LDS_CH = STAGES * STAGE_CH > EXCH ? STAGES * STAGE_CH : EXCH;
     static_assert(WGK == 1 || WGK == 2, "a stage has two 32 deep k-steps");
-    static_assert(STAGES >= 3, "ring");
+    static_assert(STAGES >= 3 && STAGES <= 5, "ring");
     static_assert(WGK == 1 || MI % 2 == 0, "the groups share the epilogue by row blocks");
     static_assert(BM * RN * 4 <= STAGE_CH * 16, "the exchange of t fits a stage");
 };
@@ -45,9 +45,9 @@ struct Tile16 {
 template <int V> struct IntC { static constexpr int v = V; };
 constexpr int RES_NONE = 0, RES_BF16 = 1, RES_F32 = 2;
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NRB, int RES>
+template <int BM, int BN, int WGM, int WGN, int WGK, int NRB, int RES, int DEPTH>
 __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const GemmGroup g) {
-    using T = Tile16<BM, BN, WGM, WGN, WGK, NRB>;
+    using T = Tile16<BM, BN, WGM, WGN, WGK, NRB, DEPTH>;
     constexpr int NW = T::NW, MI = T::MI, NI = T::NI, RN = T::RN, LPT = T::LPT, STAGES = T::STAGES, STAGE = T::STAGE_CH, NBLK = T::NBLK;
     constexpr int PH = 2 / WGK;             // k-steps of a stage that this wavefront multiplies
     __shared__ u32x4 lds[T::LDS_CH];
@@ -403,7 +403,7 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
     else by_bounds(IntC<OUT_BF16>());
 }
 
-template <int BM, int BN, int WGM, int WGN, int WGK, int NRB>
+template <int BM, int BN, int WGM, int WGN, int WGK, int NRB, int DEPTH>
 static int launch16(GemmGroup& g, hipStream_t stream) {
     int total = 0;
     g.n_lead = 0;
@@ -419,18 +419,18 @@ static int launch16(GemmGroup& g, hipStream_t stream) {
     g.total_tiles = total;
     if (total == 0 || SD_DRY_RUN("gemm16 %dx%d/%d; ", BM, BN, NRB)) return SD_OK;
     const dim3 grid((total + 7) & ~7), block(64 * WGM * WGN * WGK);
-    if (!g.p[0].res) hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_NONE>), grid, block, 0, stream, g);
-    else if (g.p[0].res_f32) hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_F32>), grid, block, 0, stream, g);
-    else hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_BF16>), grid, block, 0, stream, g);
+    if (!g.p[0].res) hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_NONE, DEPTH>), grid, block, 0, stream, g);
+    else if (g.p[0].res_f32) hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_F32, DEPTH>), grid, block, 0, stream, g);
+    else hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_BF16, DEPTH>), grid, block, 0, stream, g);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }
-template <int BM, int BN, int WGM, int WGN, int WGK>
+template <int BM, int BN, int WGM, int WGN, int WGK, int DEPTH = 5>
 static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
-    if (rmax == 0) return launch16<BM, BN, WGM, WGN, WGK, 0>(g, stream);
-    if (rmax <= 16 * WGN) return launch16<BM, BN, WGM, WGN, WGK, 1>(g, stream);
-    if (rmax <= 32 * WGN) return launch16<BM, BN, WGM, WGN, WGK, 2>(g, stream);
-    return launch16<BM, BN, WGM, WGN, WGK, 64 / 16 / WGN>(g, stream);
+    if (rmax == 0) return launch16<BM, BN, WGM, WGN, WGK, 0, DEPTH>(g, stream);
+    if (rmax <= 16 * WGN) return launch16<BM, BN, WGM, WGN, WGK, 1, DEPTH>(g, stream);
+    if (rmax <= 32 * WGN) return launch16<BM, BN, WGM, WGN, WGK, 2, DEPTH>(g, stream);
+    return launch16<BM, BN, WGM, WGN, WGK, 64 / 16 / WGN, DEPTH>(g, stream);
 }
 
 // Which tile, or 0 for the general kernel (any K, rank, layout and alignment; four columns are one access here): the
@@ -474,12 +474,20 @@ static int tile16(const GemmGroup& g) {
 }
 bool gemm16_takes(const GemmGroup& g) { return tile16(g) > 0; }
 int launch_gemm16(GemmGroup& g, hipStream_t stream) {
-    int rmax = 0;
-    for (int i = 0; i < g.n; ++i) rmax = g.p[i].K1 > rmax ? g.p[i].K1 : rmax;
+    int rmax = 0, kmax = 0;
+    for (int i = 0; i < g.n; ++i) {
+        rmax = g.p[i].K1 > rmax ? g.p[i].K1 : rmax;
+        kmax = g.p[i].K0 > kmax ? g.p[i].K0 : kmax;
+    }
     switch (tile16(g)) {
     case 3: return launch16r<128, 160, 4, 2, 1>(g, rmax, stream);
     case 2: return launch16r<64, 160, 2, 2, 2>(g, rmax, stream);
-    default: return launch16r<64, 80, 2, 1, 2>(g, rmax, stream);
+    // One workgroup of four wavefronts per CU: the two stages that three leave in flight (37 KB) come in at 54 GB/s, the latency of
+    // the last-level cache.  Four take 15 % off a long K loop and more first loads in front of a short one (988 rows, us, three /
+    // four / five stages; four wavefronts more that split K in four took as much off and cost 1 us in front):
+    // 5120x1280 + 16 28.9 / 25.0 / 25.2, 2048x1280 13.5 / 13.0 / 13.2, 1280x1280 + 16 11.0 / 10.8 / 11.1, 640x1280 7.2 / 7.3 / 7.6,
+    // 512 rows of 320x320 + 8 5.5 / 5.7 / 6.0, 1000 of 640x640 + 64 8.6 / 9.2 / 9.5.
+    default: return kmax > 640 ? launch16r<64, 80, 2, 1, 2, 4>(g, rmax, stream) : launch16r<64, 80, 2, 1, 2, 3>(g, rmax, stream);
     }
 }
 
