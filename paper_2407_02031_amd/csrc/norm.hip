@@ -371,6 +371,146 @@ __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_apply_kernel(const u
     }
 }
 
+// ---- one launch for samples that fit: a workgroup holds all tokens of a few groups (as many as fill whole 16-byte pieces of a
+// row) in registers, so nothing has to be waited for across workgroups and x is read once.
+//
+// What bounds it: latency (launch, one round of loads, three barriers of the reduction) for short samples, and what one CU takes
+// in and gives out for long ones, because there are only groups / unit workgroups to a sample and their pieces of a row are short.
+// us with SiLU, two launches / this, by the rows that a thread holds: two 2 x 256 x 320 6.9 / 5.2, 1 x 337 x 320 6.9 / 5.3, one
+// 2 x 64 x 1280 7.3 / 4.8, three 2 x 411 x 1280 9.1 / 7.1, five 4 x 300 x 960 8.9 / 8.5; six 2 x 1024 x 640 8.7 / 10.4,
+// 2 x 1024 x 1280 10.4 / 10.7; eleven 2 x 2048 x 320 8.7 / 16.2.
+constexpr int GN1_THREADS = 1024;
+constexpr int GN1_MAX_ITERS = 4;
+template <int ITERS, bool SILU>
+__global__ __launch_bounds__(GN1_THREADS) void groupnorm_unit_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ y,
+                                                                     const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
+                                                                     int T, int C, int cpg, int unit_groups, int units, float eps) {
+    __shared__ float2 sh[GN1_THREADS * 4];      // [rows][pairs] sums of a thread's channel pairs
+    __shared__ float2 part[GN1_THREADS];        // [pairs][parts] runs of rows
+    __shared__ float2 stat[4];                  // (mean, rstd) of the unit's groups
+    const int total = (int)gridDim.x;
+    int wg = blockIdx.x;
+    if ((total & 7) == 0) wg = (wg & 7) * (total >> 3) + (wg >> 3);     // neighbouring pieces of a row on one XCD
+    const int b = wg / units, unit = wg - b * units, tid = threadIdx.x;
+    const int nv = cpg * unit_groups >> 3, npairs = nv * 4, rows = GN1_THREADS / nv;
+    const int row = tid / nv, cv = tid - row * nv;
+    const bool mine = row < rows;
+    const size_t at = (size_t)b * T * C + (size_t)unit * unit_groups * cpg;
+    const uint16_t* const xb = x + at;
+    u32x4 v[ITERS];
+#pragma unroll
+    for (int k = 0; k < ITERS; ++k) {
+        v[k] = u32x4{0u, 0u, 0u, 0u};
+        if (mine && row + k * rows < T) v[k] = reinterpret_cast<const u32x4*>(xb + (size_t)(row + k * rows) * C)[cv];
+    }
+    const int cg = unit * unit_groups * cpg / 8 + (mine ? cv : 0);
+    const u32x4 gv = reinterpret_cast<const u32x4*>(gamma)[cg], bv = reinterpret_cast<const u32x4*>(beta)[cg];
+    int grp[4];
+    float shift[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        grp[i] = (cv * 8 + 2 * i) / cpg;
+        shift[i] = bf16_to_f32(xb[grp[i] * cpg]);
+    }
+    if (mine) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+            for (int k = 0; k < ITERS; ++k)
+                if (row + k * rows < T) {
+                    const float a = bf16lo_to_f32(v[k][i]) - shift[i], c = bf16hi_to_f32(v[k][i]) - shift[i];
+                    s1 += a + c;
+                    s2 += a * a + c * c;
+                }
+            sh[row * npairs + cv * 4 + i] = make_float2(s1, s2);
+        }
+    }
+    __syncthreads();
+    const int used = min(rows, T), parts = GN1_THREADS / npairs;
+    {
+        const int p = tid % npairs, j = tid / npairs;
+        if (j < parts) {
+            float2 a = make_float2(0.f, 0.f);
+            for (int r = j; r < used; r += parts) {
+                const float2 q = sh[r * npairs + p];
+                a.x += q.x;
+                a.y += q.y;
+            }
+            part[p * parts + j] = a;
+        }
+    }
+    __syncthreads();
+    const int wave = tid >> 6, lane = tid & 63;
+    if (wave < unit_groups) {
+        const int ppg = cpg >> 1, n = ppg * parts;
+        float2 a = make_float2(0.f, 0.f);
+        for (int i = lane; i < n; i += 64) {
+            const float2 q = part[wave * n + i];
+            a.x += q.x;
+            a.y += q.y;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            a.x += __shfl_xor(a.x, o);
+            a.y += __shfl_xor(a.y, o);
+        }
+        if (lane == 0) {
+            const float m = (float)T * (float)cpg;
+            const float m1 = a.x / m;
+            stat[wave] = make_float2(bf16_to_f32(xb[wave * cpg]) + m1, rsqrtf(fmaxf(a.y / m - m1 * m1, 0.f) + eps));
+        }
+    }
+    __syncthreads();
+    if (!mine) return;
+    uint16_t* const yb = y + at;
+    float mean[4], g0[4], g1[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float2 q = stat[grp[i]];
+        mean[i] = q.x;
+        g0[i] = bf16lo_to_f32(gv[i]) * q.y;
+        g1[i] = bf16hi_to_f32(gv[i]) * q.y;
+    }
+#pragma unroll
+    for (int k = 0; k < ITERS; ++k) {
+        if (row + k * rows >= T) break;
+        u32x4 o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float o0 = (bf16lo_to_f32(v[k][i]) - mean[i]) * g0[i] + bf16lo_to_f32(bv[i]);
+            float o1 = (bf16hi_to_f32(v[k][i]) - mean[i]) * g1[i] + bf16hi_to_f32(bv[i]);
+            if (SILU) {
+                o0 = o0 * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * o0));
+                o1 = o1 * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.44269504088896340736f * o1));
+            }
+            const bf16x2 pk = {(__bf16)o0, (__bf16)o1};
+            o[i] = __builtin_bit_cast(uint32_t, pk);
+        }
+        reinterpret_cast<u32x4*>(yb + (size_t)(row + k * rows) * C)[cv] = o;
+    }
+}
+
+// groups of a unit (0: two launches instead) and the rows that a thread of it holds.  Not where a unit's piece of a row is much
+// less than a cache line, which every unit would fetch again, nor for batches that no longer fit the caches of the CUs at work.
+static int gn_unit(int Bn, int T, int C, int groups, int* iters) {
+    const int cpg = C / groups, unit = cpg % 8 == 0 ? 1 : cpg % 4 == 0 ? 2 : 4;
+    const int nv = cpg * unit / 8;
+    if (C % 8 || groups % unit || nv < 4 || nv * 4 > GN1_THREADS || (int64_t)Bn * T * C > (1 << 22)) return 0;
+    const int rows = GN1_THREADS / nv;
+    *iters = (T + rows - 1) / rows;
+    return *iters <= GN1_MAX_ITERS ? unit : 0;
+}
+template <int ITERS>
+static int launch_gn_unit(const uint16_t* x, uint16_t* y, const uint16_t* gamma, const uint16_t* beta, int Bn, int T, int C, int groups, int unit,
+                          float eps, hipStream_t stream, bool silu) {
+    const int units = groups / unit;
+    if (silu) hipLaunchKernelGGL((groupnorm_unit_kernel<ITERS, true>), dim3(Bn * units), dim3(GN1_THREADS), 0, stream, x, y, gamma, beta, T, C, C / groups, unit, units, eps);
+    else hipLaunchKernelGGL((groupnorm_unit_kernel<ITERS, false>), dim3(Bn * units), dim3(GN1_THREADS), 0, stream, x, y, gamma, beta, T, C, C / groups, unit, units, eps);
+    SD_HIP_CHECK(hipGetLastError());
+    return SD_OK;
+}
+
 size_t groupnorm_partials_bytes(int Bn, int T, int groups) {
     (void)T;
     return round_up((size_t)Bn * GN_MAX_PCHUNKS * groups * 2 * sizeof(float), 256);
@@ -420,7 +560,12 @@ int launch_groupnorm(const uint16_t* x, uint16_t* y, const uint16_t* gamma, cons
     SD_REQUIRE(groups > 0 && C % groups == 0 && (C / groups) % 2 == 0, SD_EUNSUPPORTED,
                "groupnorm: C=%d groups=%d (need an even number of channels per group)", C, groups);
     SD_REQUIRE(C <= 2048, SD_EUNSUPPORTED, "groupnorm: C=%d > 2048", C);
-    if (Bn <= 0 || T <= 0 || SD_DRY_RUN("groupnorm; ")) return SD_OK;
+    if (Bn <= 0 || T <= 0) return SD_OK;
+    int iters = 0;
+    const int unit = gn_unit(Bn, T, C, groups, &iters);
+    if (SD_DRY_RUN(unit ? "groupnorm unit; " : "groupnorm; ")) return SD_OK;
+    if (unit && iters <= 2) return launch_gn_unit<2>(x, y, gamma, beta, Bn, T, C, groups, unit, eps, stream, silu);
+    if (unit) return launch_gn_unit<GN1_MAX_ITERS>(x, y, gamma, beta, Bn, T, C, groups, unit, eps, stream, silu);
     return C % 8 == 0 ? launch_gn<8>(x, y, gamma, beta, Bn, T, C, groups, eps, partials, stream, silu)
                       : launch_gn<2>(x, y, gamma, beta, Bn, T, C, groups, eps, partials, stream, silu);
 }

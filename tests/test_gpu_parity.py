@@ -752,6 +752,27 @@ def test_groupnorm_partial_batches_match_oracle(B, Bn, T, C, groups):
     assert np.abs(got - ref).mean() <= 2e-3 * np.abs(ref).mean() * 2       # bf16 rounds by 2^-9 at most, a wrong statistic moves everything
 
 
+# samples of one launch: a thread holds one row, two, three, four and, one token later, two launches; units of one group, two and
+# four; pieces of a row of 64 bytes and of a whole row; a batch just too large
+@pytest.mark.parametrize("Bn,T,C,groups,unit", [(1, 1, 320, 32, 1), (2, 204, 320, 32, 1), (2, 205, 640, 32, 1), (1, 408, 1280, 32, 1), (3, 409, 320, 32, 1), (1, 816, 640, 32, 1),
+                                                (1, 817, 640, 32, 0), (2, 100, 960, 32, 1), (1, 4, 2048, 1, 1), (1, 5, 2048, 1, 1), (2, 17, 2048, 1, 0), (2, 300, 64, 2, 1),
+                                                (2, 300, 96, 4, 0), (1, 777, 48, 2, 0), (8, 409, 1280, 32, 1), (8, 410, 1280, 32, 0)])
+def test_groupnorm_one_launch_matches_oracle(B, Bn, T, C, groups, unit):
+    r = rng(T + C + groups)
+    x = G.bf16_round((r.standard_normal((Bn, T, C)) * 1.5 + r.standard_normal((Bn, 1, C)) * 2).astype(np.float32))
+    g = G.bf16_round((1 + 0.1 * r.standard_normal(C)).astype(np.float32))
+    b = G.bf16_round((0.1 * r.standard_normal(C)).astype(np.float32))
+    xd, gd, bd = dev(x, B), dev(g, B), dev(b, B)
+    with B.dry_run() as names:
+        B.groupnorm_fwd(xd, gd, bd, groups=groups)
+    assert names == ["groupnorm unit" if unit else "groupnorm"]
+    for call, ref in ((B.groupnorm_fwd, O.groupnorm), (B.groupnorm_silu_fwd, O.groupnorm_silu)):
+        want = ref(x, g, b, groups=groups)
+        got = host(call(xd, gd, bd, groups=groups))
+        assert rel_err(got, want) <= BF16_TOL
+        assert np.abs(got - want).mean() <= 2e-3 * np.abs(want).mean() * 2     # bf16 rounds by 2^-9 at most
+
+
 # ------------------------------------------------------------ spatial_transformer_fwd
 def run_stack(B, cfg, seed=0):
     p = G.make_stack_inputs(cfg, seed)
