@@ -344,7 +344,9 @@ struct AttnWs {
     void* scratch; size_t scratch_bytes;
 };
 
-static bool carve_attn(Workspace& ws, AttnWs& w, int Bn, int T, int C, int Tk, int rmax, int heads, int Tc_ahead = 0) {
+// small: without the room that cutting the tiles of a short attention launch takes (it is done without where the caller's
+// workspace lacks that room alone)
+static bool carve_attn(Workspace& ws, AttnWs& w, int Bn, int T, int C, int Tk, int rmax, int heads, int Tc_ahead = 0, bool small = false) {
     const size_t M = (size_t)Bn * T, Mk = (size_t)Bn * Tk;
     const size_t r = rmax > 0 ? rmax : 8;
     w.n = (uint16_t*)ws.take(M * C * 2);
@@ -362,7 +364,9 @@ static bool carve_attn(Workspace& ws, AttnWs& w, int Bn, int T, int C, int Tk, i
     w.tk2 = (uint16_t*)ws.take(Mc * r * 2);
     w.tv2 = (uint16_t*)ws.take(Mc * r * 2);
     // sized for the larger of the two key counts the sub-layer is used with (Tk here, T for self-attention)
-    w.scratch_bytes = std::max(attention_scratch_bytes(Bn, T, Tk, heads), attention_scratch_bytes(Bn, T, T, heads));
+    w.scratch_bytes = 0;
+    for (int keys : {Tk, T})
+        for (bool block : {false, !small}) w.scratch_bytes = std::max(w.scratch_bytes, attention_scratch_bytes(Bn, T, keys, heads, block));
     w.scratch = ws.take(w.scratch_bytes);
     return ws.ok();
 }
@@ -694,7 +698,7 @@ extern "C" int sd_lora_linear_fwd_static(const void* x, int32_t x_dtype, const s
 // attention_fwd / attn_block_fwd
 // ---------------------------------------------------------------------------------------
 extern "C" size_t sd_attention_workspace_bytes(int32_t Bn, int32_t Tq, int32_t Tk, int32_t heads) {
-    return attention_scratch_bytes(Bn, Tq, Tk, heads) + 256;
+    return attention_scratch_bytes(Bn, Tq, Tk, heads, false) + 256;
 }
 
 extern "C" int sd_attention_fwd(const uint16_t* q, const uint16_t* k, const uint16_t* vt, uint16_t* out, int32_t Bn,
@@ -705,7 +709,7 @@ extern "C" int sd_attention_fwd(const uint16_t* q, const uint16_t* k, const uint
     SD_REQUIRE(Tk >= 1, SD_EINVAL, "attention: no keys");
     SD_REQUIRE(aligned16(q) && aligned16(k) && aligned16(vt) && aligned16(out), SD_EINVAL, "attention: pointers must be 16-byte aligned");
     const int Tkp = pad8(Tk);
-    const size_t need = attention_scratch_bytes(Bn, Tq, Tk, heads);
+    const size_t need = attention_scratch_bytes(Bn, Tq, Tk, heads, false);
     Workspace w(ws, ws_bytes);
     void* scratch = need ? w.take(need) : nullptr;
     SD_REQUIRE(need == 0 || (ws && w.ok()), SD_EWORKSPACE, "attention: workspace of %zu bytes, need %zu", ws_bytes,
@@ -748,7 +752,11 @@ extern "C" int sd_attn_block_fwd(const void* x, void* y, int32_t io_dtype, const
     Workspace w(ws, ws_bytes);
     AttnWs aw;
     DepFlags dep;
-    SD_REQUIRE(ws && carve_attn(w, aw, Bn, T, C, Tk, rmax, heads) && dep.carve(w, (size_t)Bn * (Tk > T ? Tk : T)), SD_EWORKSPACE,
+    auto carve = [&](bool small) {
+        w = Workspace(ws, ws_bytes);
+        return carve_attn(w, aw, Bn, T, C, Tk, rmax, heads, 0, small) && dep.carve(w, (size_t)Bn * (Tk > T ? Tk : T));
+    };
+    SD_REQUIRE(ws && (carve(false) || carve(true)), SD_EWORKSPACE,
                "attn_block: workspace of %zu bytes is too small", ws_bytes);
     dep.reset();
     return attn_sublayer(x, y, io_dtype == SD_F32, ctx, Tc, Dc, ln_gamma, ln_beta, ln_eps, *q, *k, *v, *o, Bn, T, C, heads, aw,
@@ -820,12 +828,12 @@ extern "C" int sd_groupnorm_silu_fwd(const uint16_t* x, uint16_t* y, const uint1
 // ---------------------------------------------------------------------------------------
 namespace sd {
 struct StackWs { float* h; uint16_t* g; float* gn; AttnWs a; FfWs f; DepFlags dep; };
-static bool carve_stack(Workspace& ws, StackWs& w, int Bn, int T, int C, int Tc, int rmax) {
+static bool carve_stack(Workspace& ws, StackWs& w, int Bn, int T, int C, int Tc, int rmax, bool small = false) {
     const size_t M = (size_t)Bn * T;
     w.h = (float*)ws.take(M * C * 4);
     w.g = (uint16_t*)ws.take(M * C * 2);
     w.gn = (float*)ws.take(groupnorm_partials_bytes(Bn, T, 32));
-    carve_attn(ws, w.a, Bn, T, C, Tc > T ? Tc : T, rmax, C / 64, Tc);
+    carve_attn(ws, w.a, Bn, T, C, Tc > T ? Tc : T, rmax, C / 64, Tc, small);
     carve_ff(ws, w.f, (int)M, C, 4 * C, rmax);
     w.dep.carve(ws, std::max(M, (size_t)Bn * Tc));
     return ws.ok();
@@ -869,7 +877,12 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
     SD_REQUIRE(x && y && ctx && aligned16(x) && aligned16(y) && aligned16(ctx), SD_EINVAL, "spatial_transformer: x/y/ctx null or misaligned");
     Workspace w(ws, ws_bytes);
     StackWs sw;
-    SD_REQUIRE(ws && carve_stack(w, sw, Bn, T, C, Tc, rmax), SD_EWORKSPACE, "spatial_transformer: workspace of %zu bytes, need %zu", ws_bytes,
+    auto carve = [&](bool small) {
+        w = Workspace(ws, ws_bytes);
+        sw = StackWs();
+        return carve_stack(w, sw, Bn, T, C, Tc, rmax, small);
+    };
+    SD_REQUIRE(ws && (carve(false) || carve(true)), SD_EWORKSPACE, "spatial_transformer: workspace of %zu bytes, need %zu", ws_bytes,
                sd_spatial_transformer_workspace_bytes(Bn, T, C, Tc, Dc, rmax));
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int M = Bn * T;

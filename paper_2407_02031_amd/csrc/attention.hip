@@ -21,7 +21,8 @@
 // When the tile count lies between two and three per CU (640 tiles on 256 CUs leaves half
 // the CUs with three tiles and half with two), the launch is padded to exactly three
 // workgroups per CU by cutting the key range of the surplus tiles in half: every CU then
-// holds two whole tiles and one half.  The two halves of a cut tile leave their unnormalised
+// holds two whole tiles and one half.  Where there are at most two tiles per CU and many keys,
+// all tiles are cut (attention_nsplit).  The two halves of a cut tile leave their unnormalised
 // accumulator, reference maximum and row sum in a scratch buffer and count themselves in on a
 // per-tile counter; the half that arrives second merges the two inside the launch (without
 // counters, a second, small kernel merges them).
@@ -92,9 +93,10 @@ __device__ __forceinline__ void store_queries(const f32x16 (&o)[2], float l, uin
 // its row sum and accumulator: if anything is not finite or close to it, some score lay 2^100 or more
 // above the first tile's; a workgroup in which any wavefront saw that returns true without storing
 // anything, and its caller runs the segment again in the measured form.
-// nsplit == 0: workgroup i takes tile i.  Otherwise the grid holds nfull whole tiles and
-// 2 * nsplit half tiles (both multiples of 8), dealt so that each XCD, and in dispatch order
+// nsplit == 0: workgroup i takes tile i.  Otherwise the grid holds nfull whole tiles (a multiple of 8) and
+// 2 * nsplit half tiles, rounded up to a multiple of 8, dealt so that each XCD, and in dispatch order
 // each CU, first receives its share of whole tiles and then its share of halves.
+__host__ __device__ __forceinline__ int attention_grid(int nfull, int nsplit) { return nsplit ? nfull + (nsplit + 3) / 4 * 8 : nfull; }
 typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) int32_t lds_i32;
 typedef __attribute__((address_space(3))) uint16_t lds_u16;
@@ -120,11 +122,12 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         if ((total & 7) == 0) tile = (tile & 7) * (total >> 3) + (tile >> 3);
     } else {
         const int xcd = bid & 7, j = bid >> 3;
-        const int fpx = nfull >> 3, hpx = nsplit >> 2;   // whole tiles / halves per XCD
+        const int fpx = nfull >> 3, hpx = (nsplit + 3) >> 2;   // whole tiles / halves per XCD
         if (j < fpx) {
             tile = xcd * fpx + j;
         } else {
             const int h = xcd * hpx + (j - fpx);
+            if (h >= 2 * nsplit) return false;
             tile = nfull + (h >> 1);
             part = h & 1;
             const int mid = (nt + 1) >> 1;
@@ -541,7 +544,7 @@ __global__ __launch_bounds__(256, 3) void attention_kernel(const uint16_t* __res
                                                         int Tq, int Tk, int Tkp, int heads, int qtiles, float c,
                                                         int nfull, int nsplit, float* __restrict__ parts, int32_t* __restrict__ arrived,
                                                         const std::conditional_t<AHEAD, ReadRanges, NoRanges> ra) {
-    const int total = AHEAD ? nfull + 2 * nsplit : (int)gridDim.x;
+    const int total = AHEAD ? attention_grid(nfull, nsplit) : (int)gridDim.x;
     if constexpr (AHEAD) {
         // (the arguments in one batch, not a second one behind the branch)
         asm volatile("" ::"s"(q), "s"(ldq), "s"(k), "s"(ldk), "s"(vt), "s"(ldvt), "s"(Tq), "s"(Tk), "s"(Tkp), "s"(heads), "s"(qtiles));
@@ -612,19 +615,26 @@ static int device_cus() {
 }
 
 // number of tiles to cut in half (0: one workgroup per tile)
-static int attention_nsplit(int Bn, int Tq, int Tk, int heads) {
+// block: inside an attention block, where the halves are merged in the launch.  Up to two tiles per CU and from 24 key tiles on, all
+// are cut there if the most loaded CU then has less to do, and from 48 on also one per CU: more wavefronts cover latencies better.  (us, a
+// whole self-attention block, whole / cut: 1 x 1500 x 640 channels 43.6 / 39.6, 1 x 2048 x 1280 84.5 / 82.3, 1 x 3952 x 320 60.9 / 58.6,
+// 1 x 4096 x 320 63.3 / 57.3, 1 x 3952 x 640 103.4 / 97.2, 2 x 4096 x 320 103.6 / 92.0; with as much on a CU as before 1 x 1500 x 1280
+// 62.4 / 64.2, 1 x 2048 x 640 47.6 / 47.6, 1 x 3840 x 512 68.5 / 65.0, 1 x 4096 x 960 129.1 / 132.5; at 16 key tiles the merge costs what that gives or more: 2 x 988 x 640 38.8 / 39.1,
+// 1 x 1024 x 1280 44.0 / 45.6.)
+static int attention_nsplit(int Bn, int Tq, int Tk, int heads, bool block) {
     const long tiles = (long)((Tq + 127) / 128) * heads * Bn;
     const int nt = (Tk + 63) / 64;
     const long cus = device_cus();
+    if (block && nt >= 24 && tiles <= 2 * cus && ((nt >= 48 && tiles <= cus) || (2 * tiles + cus - 1) / cus < 2 * ((tiles + cus - 1) / cus))) return (int)tiles;
     if (nt < 8 || tiles <= 2 * cus || tiles >= 3 * cus) return 0;
     const long nsplit = 3 * cus - tiles, nfull = tiles - nsplit;
     if (nfull <= 0 || (nfull & 7) || (nsplit & 3)) return 0;
     return (int)nsplit;
 }
 
-size_t attention_scratch_bytes(int Bn, int Tq, int Tk, int heads) {
+size_t attention_scratch_bytes(int Bn, int Tq, int Tk, int heads, bool block) {
     if (Bn <= 0 || Tq <= 0 || Tk <= 0 || heads <= 0) return 0;
-    return (size_t)attention_nsplit(Bn, Tq, Tk, heads) * 2 * PART_FLOATS * sizeof(float);
+    return (size_t)attention_nsplit(Bn, Tq, Tk, heads, block) * 2 * PART_FLOATS * sizeof(float);
 }
 
 int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t ldk,
@@ -641,7 +651,7 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     const int qtiles = (Tq + 127) / 128;
     const long tiles = (long)qtiles * heads * Bn;
     SD_REQUIRE(tiles < (1l << 30), SD_EINVAL, "attention: problem too large");
-    int nsplit = attention_nsplit(Bn, Tq, Tk, heads);
+    int nsplit = attention_nsplit(Bn, Tq, Tk, heads, k_prescaled);
     const size_t need = (size_t)nsplit * 2 * PART_FLOATS * sizeof(float);
     if (nsplit > 0 && !(scratch && scratch_bytes >= need && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0)) nsplit = 0;
     const int nfull = (int)tiles - nsplit;
@@ -655,9 +665,9 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     if (SD_DRY_RUN("attention%s%s%s; ", k_prescaled ? " prescaled" : "", k_prescaled || nt >= 20 ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "")) return SD_OK;
     // Read-ahead in the room that three workgroups to a CU leave: 8 MB and 2 MB per key tile, which the launch is long
     // enough for.  (With 1 MB per key tile the queue falls behind at 32 x 32 tokens: 2540 us per stack for 2500, 2658 without any.)
-    const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, 3l * device_cus() - (nfull + 2l * nsplit), 16) : ReadRanges{};
+    const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, 3l * device_cus() - attention_grid(nfull, nsplit), 16) : ReadRanges{};
     auto go = [&](auto kernel, const auto& ranges) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(nfull + 2 * nsplit + ra.wgs)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(attention_grid(nfull, nsplit) + ra.wgs)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
                            qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived, ranges);
     };
     if (k_prescaled && ra.wgs) go(attention_kernel<true, true, true>, ra);

@@ -210,6 +210,6 @@ int launch_attention_merge(const void* scratch, uint16_t* out, int64_t ldo, int 
                            hipStream_t stream);
 // softmax scale in exponent-of-2 units: k_prescaled means the keys were multiplied by this
 constexpr float ATTN_KSCALE = 0.125f * 1.44269504088896340736f;
-size_t attention_scratch_bytes(int Bn, int Tq, int Tk, int heads);
+size_t attention_scratch_bytes(int Bn, int Tq, int Tk, int heads, bool block);
 
 }  // namespace sd

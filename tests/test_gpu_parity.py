@@ -636,6 +636,46 @@ def test_attn_block_projections_in_several_rounds(B, rank, flags):
     assert B.gemm_dep_timeouts() == 0
 
 
+# every tile cut in half along the keys: from 24 key tiles and up to two tiles per CU, where that takes work off the most loaded CU, from
+# 48 also at one tile per CU; tile counts that are a multiple of 4 and not,
+# odd and ragged key tiles.  Bits do not depend on which half arrives last nor on where the halves are merged; a workspace without
+# room for them still does.
+@pytest.mark.parametrize("Bn,T,heads,cut", [(1, 1472, 2, ""), (1, 1473, 2, " cut"), (3, 1601, 1, " cut"), (1, 2050, 5, " cut"), (2, 1536, 13, " cut"), (2, 1536, 20, ""), (8, 1473, 8, ""), (1, 4096, 5, " cut")])
+def test_attn_block_every_tile_cut(B, Bn, T, heads, cut):
+    import torch
+    C = 64 * heads
+    cfg = small_cfg(Bn=Bn, T=T, Tc=5, C=C, heads=heads, r=8, alpha=8.0, Dc=72, w_std=0.05 * (320 / C) ** 0.5, a_std=0.15)
+    p = G.make_stack_inputs(cfg, seed=T)
+    blk = p["blocks"][0]
+    h = rng(T).standard_normal(p["x"].shape).astype(np.float32)
+    projs = [dict(blk[n], A=None, B=None) for n in ("q1", "k1", "v1", "o1")]
+    args = (torch.from_numpy(h).cuda(), None, dev(blk["ln1_g"], B), dev(blk["ln1_b"], B), *[B.Proj.from_numpy(q) for q in projs], heads)
+    need = B.lib().sd_attn_block_workspace_bytes(Bn, T, C, 0, 0, 0)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    with B.dry_run() as names:
+        B.attn_block_fwd(*args, ws=ws)
+    assert "attention prescaled try" + cut in names
+    y = B.attn_block_fwd(*args, ws=ws)
+    ref = O.attn_sublayer(h, None, blk["ln1_g"], blk["ln1_b"], *projs, heads)
+    assert rel_err(host(y) - h, ref - h) <= BF16_TOL
+    for _ in range(3):
+        assert torch.equal(B.attn_block_fwd(*args, ws=ws), y)
+    try:
+        B.set_projection_fusion(False)
+        assert torch.equal(B.attn_block_fwd(*args, ws=ws), y)
+    finally:
+        B.set_projection_fusion(True)
+    if cut:
+        tiles = (T + 127) // 128 * heads * Bn
+        little = ws[:need - tiles * 2 * 34 * 256 * 4]
+        with B.dry_run() as names:
+            B.attn_block_fwd(*args, ws=little)
+        assert "attention prescaled try" in names
+        assert rel_err(host(B.attn_block_fwd(*args, ws=little)) - h, ref - h) <= BF16_TOL
+        with pytest.raises(Exception):
+            B.attn_block_fwd(*args, ws=little[:-256])
+
+
 # self-attention whose q, k and transposed v are one round of 128x160 tiles (token counts off every tile, adapters or none) or of 64x80
 @pytest.mark.parametrize("Bn,T,C,rank", [(2, 700, 640, 16), (1, 1003, 640, 0), (2, 261, 320, 24)])
 def test_attn_block_projections_in_one_round(B, Bn, T, C, rank):
