@@ -829,6 +829,32 @@ def test_stack_small_ragged(B):
     assert rel_err(got - p["x"], ref - p["x"]) <= 2 * BF16_TOL     # what the stack adds, bf16 output rounding included
 
 
+# text keys / values of the second block in the first one's ff2 launch (128x128 tiles in one round, 256x128 tiles) or, where ff2 takes its
+# adapter into the tile, in the block's own q, k, v launch; as two launches per projection they are in the latter: same bits
+@pytest.mark.parametrize("Bn,T,Tc,rank,ff2", [(1, 3300, 77, 64, "gemm 128x128/8 waves/4 stages res32 flags"), (3, 1800, 131, 64, "gemm 256x128/8 waves/3 stages res32 flags"),
+                                              (1, 3300, 77, 16, "gemm16 64x160/1")])
+def test_stack_text_keys_in_the_ff2_launch(B, Bn, T, Tc, rank, ff2):
+    import torch
+    # adapter scale 1/8 at either rank.  (At 1/2, rank 16, q and k have a deviation of 1.4 and scores reach 10: rounded to bf16, q and k
+    # put such a score off by 10 2^-8 = 0.04, and with it a probability that is most of its row.)
+    cfg = small_cfg(Bn=Bn, T=T, Tc=Tc, C=640, heads=10, r=rank, alpha=rank / 8, depth=2, w_std=0.03)
+    p = G.make_stack_inputs(cfg, seed=T)
+    sp = B.StackParams(p)
+    x, ctx = dev(p["x"], B), dev(p["ctx"], B)
+    with B.dry_run() as names:
+        B.spatial_transformer_fwd(x, ctx, sp, cfg.heads)
+    assert ff2 in names
+    y = B.spatial_transformer_fwd(x, ctx, sp, cfg.heads).clone()
+    ref = O.spatial_transformer(p["x"], p["ctx"], p, cfg.heads)
+    assert rel_err(host(y), ref) <= BF16_TOL
+    try:
+        B.set_projection_fusion(False)
+        assert torch.equal(B.spatial_transformer_fwd(x, ctx, sp, cfg.heads), y)
+    finally:
+        B.set_projection_fusion(True)
+    assert B.gemm_dep_timeouts() == 0
+
+
 def test_stack_with_biased_q_k_v(B):
     """SDXL's q, k, v carry no bias, but a projection record may: the stack takes them too (the
     text keys / values projected ahead inside the self-attention launches included)."""
