@@ -132,7 +132,9 @@ int32_t sd_set_projection_fusion(int32_t on);
 /* Which kernels would run?  Between sd_dry_run(1) and sd_dry_run(0) the forward calls of this thread (projections,
  * attention, sub-layers, GroupNorm, the stack, patches) check their arguments and choose their kernels as ever, but launch nothing:
  * they write the names of what they would launch to sd_dry_run_text, in order, and need no device.  For tests that
- * are meant for one kernel, and for reading a dispatch rule at a size.  Returns the previous setting. */
+ * are meant for one kernel, and for reading a dispatch rule at a size.  sd_dry_run(2) also writes, behind a comma, how many
+ * problems a projection launch holds, the in-tile kernel's ring stages and residual, and the ranges of weights that an
+ * attention or LayerNorm launch reads ahead (address+bytes, in hex and decimal).  Returns the previous setting. */
 int32_t sd_dry_run(int32_t on);
 const char* sd_dry_run_text(void);
 

@@ -26,7 +26,8 @@ int hip_fail(hipError_t e, const char* what) {
 }
 
 thread_local bool g_dry_run = false;
-static thread_local char g_dry_text[4096] = "";
+static thread_local bool g_dry_detail = false;
+static thread_local char g_dry_text[32768] = "";   // (twenty blocks and more, ten with the details)
 bool dry_note(const char* fmt, ...) {
     const size_t n = strlen(g_dry_text);
     va_list ap;
@@ -34,6 +35,25 @@ bool dry_note(const char* fmt, ...) {
     vsnprintf(g_dry_text + n, sizeof(g_dry_text) - n, fmt, ap);
     va_end(ap);
     return true;
+}
+const char* dry_detail(const char* fmt, ...) {
+    static thread_local char text[256];
+    text[0] = 0;
+    if (!g_dry_detail) return text;
+    va_list ap;
+    va_start(ap, fmt);
+    vsnprintf(text, sizeof(text), fmt, ap);
+    va_end(ap);
+    return text;
+}
+const char* dry_ranges(const ReadRanges& ra) {
+    static thread_local char text[40 * ReadRanges::MAX + 8];
+    text[0] = 0;
+    if (!g_dry_detail || ra.n == 0) return text;
+    size_t n = (size_t)snprintf(text, sizeof(text), ", ahead");
+    for (int i = 0; i < ra.n; ++i)
+        n += (size_t)snprintf(text + n, sizeof(text) - n, " %llx+%u", (unsigned long long)reinterpret_cast<uintptr_t>(ra.p[i]), ra.bytes[i]);
+    return text;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -523,9 +543,10 @@ extern "C" int32_t sd_set_projection_fusion(int32_t on) {
     return was;
 }
 extern "C" int32_t sd_dry_run(int32_t on) {
-    const int32_t was = g_dry_run ? 1 : 0;
+    const int32_t was = g_dry_run ? (g_dry_detail ? 2 : 1) : 0;
     if (on) g_dry_text[0] = 0;
     g_dry_run = on != 0;
+    g_dry_detail = on == 2;
     return was;
 }
 extern "C" const char* sd_dry_run_text(void) { return g_dry_text; }

@@ -662,10 +662,10 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     // 8 x 1434 x 20, 22.7 for 22.9 at 2 x 1330 x 10, but 59.7 for 57.6 at 8 x 988 x 20.
     const int nt = (Tk + 63) / 64;
     *cut_tiles = arrived ? 0 : nsplit;
-    if (SD_DRY_RUN("attention%s%s%s; ", k_prescaled ? " prescaled" : "", k_prescaled || nt >= 20 ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "")) return SD_OK;
     // Read-ahead in the room that three workgroups to a CU leave: 8 MB and 2 MB per key tile, which the launch is long
     // enough for.  (With 1 MB per key tile the queue falls behind at 32 x 32 tokens: 2540 us per stack for 2500, 2658 without any.)
     const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, 3l * device_cus() - attention_grid(nfull, nsplit), 16) : ReadRanges{};
+    if (SD_DRY_RUN("attention%s%s%s%s; ", k_prescaled ? " prescaled" : "", k_prescaled || nt >= 20 ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "", dry_ranges(ra))) return SD_OK;
     auto go = [&](auto kernel, const auto& ranges) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(attention_grid(nfull, nsplit) + ra.wgs)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
                            qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived, ranges);

@@ -85,6 +85,9 @@ int hip_fail(hipError_t e, const char* what);
 // would launch instead of launching it.
 extern thread_local bool g_dry_run;
 bool dry_note(const char* fmt, ...);   // true
+// what a note adds where details are asked for (sd_dry_run(2)), empty elsewhere
+const char* dry_detail(const char* fmt, ...);
+const char* dry_ranges(const ReadRanges& ra);
 #define SD_DRY_RUN(...) (__builtin_expect(::sd::g_dry_run, 0) && ::sd::dry_note(__VA_ARGS__))
 
 #define SD_HIP_CHECK(expr)                                         \

@@ -613,8 +613,8 @@ static int launch_cfg(GemmGroup& g, bool guard, hipStream_t stream) {
     }
     g.total_tiles = total;
     if (total == 0) return SD_OK;
-    if (SD_DRY_RUN("gemm %dx%d/%d waves/%d stages%s%s%s%s; ", BM, BN, WGM * WGN, STAGES, GEGLU ? " geglu" : "", RES32 ? " res32" : "", guard ? " guard" : "",
-                   !g.p[0].signal ? "" : g.p[0].nonce ? " records" : " flags"))
+    if (SD_DRY_RUN("gemm %dx%d/%d waves/%d stages%s%s%s%s%s; ", BM, BN, WGM * WGN, STAGES, GEGLU ? " geglu" : "", RES32 ? " res32" : "", guard ? " guard" : "",
+                   !g.p[0].signal ? "" : g.p[0].nonce ? " records" : " flags", dry_detail(", %d problems", g.n)))
         return SD_OK;
     if (guard)
         hipLaunchKernelGGL((gemm_kernel<BM, BN, BK, WGM, WGN, STAGES, GEGLU, true, RES32>), dim3(g.n_lead + ((total - g.n_lead + 7) & ~7)), dim3(64 * WGM * WGN), 0, stream, g);

@@ -417,7 +417,9 @@ static int launch16(GemmGroup& g, hipStream_t stream) {
         total += P.tiles_m * P.tiles_n;
     }
     g.total_tiles = total;
-    if (total == 0 || SD_DRY_RUN("gemm16 %dx%d/%d; ", BM, BN, NRB)) return SD_OK;
+    if (total == 0 || SD_DRY_RUN("gemm16 %dx%d/%d%s; ", BM, BN, NRB,
+                                 dry_detail(", %d problems, %d stages%s", g.n, Tile16<BM, BN, WGM, WGN, WGK, NRB, DEPTH>::STAGES, !g.p[0].res ? "" : g.p[0].res_f32 ? ", fp32 residual" : ", bf16 residual")))
+        return SD_OK;
     const dim3 grid((total + 7) & ~7), block(64 * WGM * WGN * WGK);
     if (!g.p[0].res) hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_NONE, DEPTH>), grid, block, 0, stream, g);
     else if (g.p[0].res_f32) hipLaunchKernelGGL((gemm16_kernel<BM, BN, WGM, WGN, WGK, NRB, RES_F32, DEPTH>), grid, block, 0, stream, g);

@@ -120,9 +120,9 @@ int launch_layernorm(const void* x, int x_f32, const uint16_t* gamma, const uint
     SD_REQUIRE(C % 4 == 0 && C > 0 && C <= 64 * 4 * LN_MAXJ, SD_EUNSUPPORTED, "layernorm: C=%d (need C %% 4 == 0, C <= %d)", C,
                64 * 4 * LN_MAXJ);
     if (M <= 0) return zero_n > 0 ? launch_clear_flags(zero_ptr, zero_n, stream) : SD_OK;
-    if (SD_DRY_RUN("layernorm%s; ", zero_n > 0 ? " clear" : "")) return SD_OK;
     // read-ahead: 8 MB, in workgroups small enough to leave eight on a CU (4 MB: the queue falls behind; 12: the launch takes longer than they save)
     const ReadRanges ra = ahead ? ahead->take(8ull << 20, 512, 8) : ReadRanges{};
+    if (SD_DRY_RUN("layernorm%s%s; ", zero_n > 0 ? " clear" : "", dry_ranges(ra))) return SD_OK;
     if (C <= 768) {          // SDXL's 320 and 640 channels: three chunks per lane
         if (x_f32) launch_ln<true, 3, LN_ROWS>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream, ra);
         else launch_ln<false, 3, LN_ROWS>(x, gamma, beta, eps, y, M, C, zero_ptr, zero_n, stream, ra);
