@@ -116,6 +116,7 @@ struct ProjCall {
     const sd_proj* p; uint16_t* tbuf; ProjOut o;
 };
 
+static int problems_of(const ProjCall& c) { return c.M <= 0 ? 0 : (c.p->r > 0 ? 2 : 1); }
 static int push_down(GemmGroup& g, hipStream_t stream, const ProjCall& c, int32_t* signal = nullptr, uint64_t nonce = 0) {
     const sd_proj& p = *c.p;
     if (p.r <= 0) return SD_OK;
@@ -246,7 +247,6 @@ static int run_projections(const ProjCall* calls, int n, hipStream_t stream, int
     GemmGroup g;
     memset(&g, 0, sizeof(g));
     int rc;
-    auto problems_of = [](const ProjCall& c) { return c.M <= 0 ? 0 : (c.p->r > 0 ? 2 : 1); };
     auto flags_of = [](const ProjCall& c) { return (c.M > 0 && c.p->r > 0) ? ((size_t)c.M + 63) / 64 : (size_t)0; };
     // adapters inside the tiles, where that kernel takes the whole group
     int live = 0;
@@ -498,29 +498,33 @@ static int ff_sublayer(const void* x, void* y, int io_f32, const uint16_t* g, co
 }
 
 // Whether the text keys / values of the next block (`riders`) go into this block's ff2 launch instead of into the next q, k, v
-// launch: where ff2 takes the general kernel and leaves CUs idle that hold all of their tiles, and its K loop is the longer one.
-static bool ff2_takes_riders(const sd_proj& p2, int M, int C, int F, const std::vector<ProjCall>& riders, bool fused) {
-    long general = 0, tall = 0, lead = 0;
+// launch: where ff2 takes the general kernel in one round, whose idle CUs hold them (their K loops are no longer than ff2's), and
+// keeps its tiles.  Pushed out of a round of 128x128 tiles into 256x128 ones on half the CUs it loses more than q, k, v gains (stacks of two
+// blocks + 64, us: text keys with q, k, v / in such an ff2: 2 x 1230 tokens of 1280 channels 625 / 642, 2 x 1360 664 / 677, 1 x 2700
+// 701 / 719, 2 x 2500 of 640 507 / 514); adapters of a rank off 64 that make the loads of an ff2 without adapter guarded cost nothing (+ 16
+// on attention alone: 2 x 1100 of 1280 572 / 571, 2 x 2500 of 640 498 / 495, 1 x 4150 of 640 496 / 490).
+//   qkv: the problems of that q, k, v launch.  If it has no place for them they are a launch of their own there, and any one round of ff2
+// holds them better (4 x 576 of 1280 616 / 610, 4 x 1200 of 640 496 / 485, 3 x 1600 of 640 497 / 490).
+static bool ff2_takes_riders(const sd_proj& p2, int M, int C, int F, const std::vector<ProjCall>& riders, int qkv, bool fused) {
+    if (!fused) return false;
+    // (made-up operands: no choice looks at more than sizes and alignments)
+    ProjCall c2 = {reinterpret_cast<const uint16_t*>(256), F, M, F, C, &p2, reinterpret_cast<uint16_t*>(256), {reinterpret_cast<void*>(256), C, 1, reinterpret_cast<const void*>(256), C, false, 0}};
+    int32_t* const flags = reinterpret_cast<int32_t*>(256);
     int problems = 0;
-    auto count = [&](int m, int n, int r, bool transposed) {
-        const int rows = transposed ? n : m, cols = transposed ? m : n;
-        general += (long)((rows + 127) / 128) * ((cols + 127) / 128);
-        tall += (long)((rows + 255) / 256) * ((cols + 127) / 128);
-        lead += (long)((m + 127) / 128) * ((r + 63) / 64);
-        problems += r > 0 ? 2 : 1;
-    };
-    count(M, C, p2.r, false);
-    if (general <= 128 || !fused) return false;
     for (const ProjCall& c : riders) {
         if (c.K > F) return false;
-        count(c.M, c.N, c.p->r, c.o.transposed);
+        problems += problems_of(c);
     }
-    if (problems > GEMM_MAX_PROBLEMS) return false;
+    if (problems + problems_of(c2) > GEMM_MAX_PROBLEMS) return false;
     GemmGroup g;
     memset(&g, 0, sizeof(g));
-    ProjCall c2 = {reinterpret_cast<const uint16_t*>(256), F, M, F, C, &p2, reinterpret_cast<uint16_t*>(256), {reinterpret_cast<void*>(256), C, 1, reinterpret_cast<const void*>(256), C, false, 0}};
-    if (push_main(g, nullptr, c2) || gemm16_takes(g)) return false;
-    return gemm_one_round(general, lead) || tall + lead / 2 <= 256;
+    if (push_main(g, nullptr, c2) || gemm16_takes(g) || push_down(g, nullptr, c2, flags)) return false;
+    const GemmChoice alone = gemm_choice(g);
+    if (!alone.one_round()) return false;
+    for (const ProjCall& c : riders)
+        if (push_main(g, nullptr, c) || push_down(g, nullptr, c, flags)) return false;
+    const GemmChoice with = gemm_choice(g);
+    return with.tiles == alone.tiles || (with.one_round() && qkv + problems > GEMM_MAX_PROBLEMS);
 }
 
 static int rmax_of(const sd_proj* const* ps, int n) {
@@ -924,7 +928,11 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
     };
     // the text keys / values of a block's cross-attention ride in a launch before it
     std::vector<char> early(p->depth + 1, 0);     // ... in the ff2 launch of the block before, not in the block's q, k, v launch
-    for (int i = 1; i < p->depth; ++i) early[i] = ff2_takes_riders(p->blocks[i - 1].ff2, M, C, 4 * C, text_calls(p->blocks[i]), g_fuse_projections);
+    for (int i = 1; i < p->depth; ++i) {
+        const sd_block_params& b = p->blocks[i];
+        const int qkv = (b.q1.r > 0 ? 2 : 1) + (b.k1.r > 0 ? 2 : 1) + Bn * (b.v1.r > 0 ? 2 : 1);
+        early[i] = ff2_takes_riders(p->blocks[i - 1].ff2, M, C, 4 * C, text_calls(b), qkv, g_fuse_projections);
+    }
     for (int i = 0; i < p->depth; ++i) {
         const sd_block_params& b = p->blocks[i];
         if (!early[i])

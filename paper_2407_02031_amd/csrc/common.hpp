@@ -167,6 +167,16 @@ struct GemmGroup {
 // Launch every problem of `g` in one grid.  Problems must all be GEGLU or all plain; signalling
 // problems come first and every problem that waits on one is in the same group.
 int launch_gemm_group(GemmGroup& g, hipStream_t stream);
+// The kernel that launch_gemm_group takes for a group (rows x columns of W; GEGLU, then plain), and two of its switches: guarded
+// loads (a depth or rank off a multiple of 64), an fp32 residual fetched early.
+enum GemmTiles { GEMM_GEGLU_64x128_3STAGES, GEMM_GEGLU_64x128, GEMM_GEGLU_128x128, GEMM_GEGLU_256x256,
+                 GEMM_64x64, GEMM_64x128_3STAGES, GEMM_64x128, GEMM_128x128_ONE_ROUND, GEMM_128x128, GEMM_128x128_8WAVES, GEMM_256x128_ONE_ROUND, GEMM_256x256 };
+struct GemmChoice {
+    GemmTiles tiles;
+    bool guard, res32;
+    bool one_round() const { return tiles == GEMM_128x128_ONE_ROUND || tiles == GEMM_256x128_ONE_ROUND; }
+};
+GemmChoice gemm_choice(const GemmGroup& g);
 // Do so many tiles, and the producers' tiles ahead of them, run one to a CU?  Both are dealt over 8 XCDs of 32 CUs.
 // (42 producers and 210 tiles do not: 5350x640x1280 + 16 26.0 us with 128x128 tiles one per CU, 23.7 with other tiles)
 inline bool gemm_one_round(long tiles, long producers) { return (tiles + 7) / 8 + (producers + 7) / 8 <= 32; }

@@ -624,10 +624,15 @@ static int launch_cfg(GemmGroup& g, bool guard, hipStream_t stream) {
     return SD_OK;
 }
 
-int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
-    SD_REQUIRE(g.n >= 1 && g.n <= GEMM_MAX_PROBLEMS, SD_EINVAL, "gemm group: %d problems", g.n);
+template <int BM, int BN, int BK, int WGM, int WGN, int STAGES>
+static int launch_res(GemmGroup& g, const GemmChoice& c, hipStream_t stream) {
+    if (c.res32) return launch_cfg<BM, BN, BK, WGM, WGN, STAGES, false, true>(g, c.guard, stream);
+    return launch_cfg<BM, BN, BK, WGM, WGN, STAGES, false, false>(g, c.guard, stream);
+}
+
+// Which kernel, from the problems' sizes alone.
+GemmChoice gemm_choice(const GemmGroup& g) {
     bool geglu = false;   // a GEGLU group: GEGLU problems plus, possibly, the plain down-projections they wait for
-    for (int i = 0; i < g.n; ++i) geglu = geglu || g.p[i].geglu_F > 0;
     bool guard = false;
     int maxN = 0;
     double lead = 0;      // down-projection tiles of 128 rows: workgroups too, ahead of the others
@@ -640,11 +645,76 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
     int N0 = 0, K0 = 0;
     for (int i = 0; i < g.n; ++i) {
         const GemmProblem& P = g.p[i];
-        if (!P.signal && P.Mp > 0 && P.N > 0) {
-            mixed = mixed || (n_main++ && (P.N != N0 || P.K0 != K0));
-            N0 = P.N, K0 = P.K0;
+        if (P.geglu_F > 0) geglu = true;
+        if (P.Mp == 0 || P.N == 0) continue;
+        if ((P.K0 & 63) || (P.K1 & 63)) guard = true;
+        if (P.res && P.res_f32) res32 = true;
+        if (P.N > maxN) maxN = P.N;
+        if (P.signal) {
+            lead += (double)((P.Mp + 127) / 128) * ((P.N + DOWN_BN - 1) / DOWN_BN);
+            continue;
         }
-        if (P.res && P.res_f32 && P.Mp > 0 && P.N > 0) res32 = true;
+        mixed = mixed || (n_main++ && (P.N != N0 || P.K0 != K0));
+        N0 = P.N, K0 = P.K0;
+        if (P.geglu_F > 0) {
+            gM += P.Mp;
+            gF = P.N > gF ? P.N : gF;
+            gK = P.K0 > gK ? P.K0 : gK;
+            gr = P.K1 > gr ? P.K1 : gr;
+        }
+        const long tiles = (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
+        t128 += tiles;
+        t256 += (long)((P.Mp + 255) / 256) * ((P.N + 127) / 128);
+        depth += (double)tiles * P.K0;
+    }
+    auto take = [&](GemmTiles t) { return GemmChoice{t, guard, res32}; };
+    // Tile choice.  What a tile costs per 64 deep step is its operand bytes (a CU takes in 100-125 GB/s
+    // from L2 whatever the ring depth) or its MFMAs, whichever is longer, and the launch takes as long
+    // as its most loaded CU; so: the largest tiles that still give every CU the same number of them.
+    // Times below are single projections of rank 64, us, measured on one machine.
+    const double meanK = t128 ? depth / t128 : 0;
+    // GEGLU: geglu_tiles (128 columns of W are 64 of the output)
+    if (geglu) switch (geglu_tiles(gM, gF, gK, gr, false)) {
+        case GEGLU_64x64_3STAGES: return take(GEMM_GEGLU_64x128_3STAGES);
+        case GEGLU_64x64: return take(GEMM_GEGLU_64x128);
+        case GEGLU_256x128: return take(GEMM_GEGLU_256x256);
+        default: return take(GEMM_GEGLU_128x128);
+        }
+    // Down-projections (N = rank <= 64) alone: 64x64 tiles, 5-stage ring.
+    if (maxN <= 64) return take(GEMM_64x64);
+    if (t128 < 512) {
+        // at most one 128x128 tile per CU, and most CUs have one: that tile with a deep ring, one
+        // workgroup per CU (2048x1280x5120: 42.0, 53.7 with 64x128 tiles, of which 64 CUs get two)
+        if (t128 > 128 && gemm_one_round(t128, (long)lead)) return take(GEMM_128x128_ONE_ROUND);
+        // more than that (the down-projection's tiles count), but at most one of 256x128 per CU, and no short K loop: those
+        // (8192x640x2560: 41.1, 48.2 with 128x128 tiles; 4757x1280x1280: 26.4, 33.1 with 64x128;
+        // 6000x640x2560 34.5, 44.5 with 128x128 tiles; at K = 640 the ramps of the larger tile lose: 24.1 against 21.0)
+        if (t128 > 128 && t256 + lead / 2 <= 256 && meanK >= 1024) return take(GEMM_256x128_ONE_ROUND);
+        // few tiles: 64x128 spreads them over more CUs, two workgroups on a CU at most: three ring stages
+        if (t128 <= 128) return take(GEMM_64x128_3STAGES);
+        // up to three on a CU where the K loop is short (8192x640x640: 17.3, 18.3 with 128x128)
+        if (t128 > 256 && meanK < 1024) return take(GEMM_64x128);
+    }
+    // One large plain projection with a long K loop (no launch of the transformer block: the
+    // 8192 x 4096 x 4096 yardstick takes 224, 248 at 128x128).  Not for grouped
+    // launches: the q/k/v group with its short text-context problems loses a third.
+    if (!res32 && n_main == 1 && t256 >= 512 && meanK >= 2048) return take(GEMM_256x256);
+    // 128x128 tiles, two workgroups per CU.  Of eight 32x64 wavefronts where problems of different sizes share the launch (q, k,
+    // v transposed, text keys): their tiles load the CUs unevenly, and one that has a CU to itself is faster with more
+    // wavefronts (attention blocks, us, four / eight: 4 x 3952 tokens of 640 channels with text keys + 64 106.7 / 100.4, 2 x 988 of
+    // 1280 + 16 85.6 / 79.8, 2 x 4096 of 320 + 8 109.8 / 100.5, 4 x 3952 of 640 + 32 275.4 / 279.2; 80 of them 0.91 to 1.014)
+    if (mixed && !res32) return take(GEMM_128x128_8WAVES);
+    // ... of four 64x64 otherwise (4757x1280x1280: 25.9, 33.1 with 64x128, 26.9 with eight wavefronts; the segments of a multi-adapter
+    // call: 8 x 4096 of 640 channels 45.0 / 45.6, 2999,2221,1552,1847,895 of 1280 48.6 / 50.7, of 320 up to 12 % the other way)
+    return take(GEMM_128x128);
+}
+
+int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
+    SD_REQUIRE(g.n >= 1 && g.n <= GEMM_MAX_PROBLEMS, SD_EINVAL, "gemm group: %d problems", g.n);
+    bool geglu = false;
+    for (int i = 0; i < g.n; ++i) geglu = geglu || g.p[i].geglu_F > 0;
+    for (int i = 0; i < g.n; ++i) {
+        const GemmProblem& P = g.p[i];
         SD_REQUIRE((P.geglu_F > 0) == geglu || P.signal, SD_EINVAL, "gemm group mixes GEGLU and plain problems");
         SD_REQUIRE(P.Mp >= 0 && P.N >= 0 && P.K0 > 0 && P.K0 % 8 == 0 && P.K1 >= 0 && P.K1 % 8 == 0, SD_EINVAL,
                    "gemm problem %d: bad sizes M=%d N=%d K0=%d K1=%d", i, P.Mp, P.N, P.K0, P.K1);
@@ -664,19 +734,6 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
         SD_REQUIRE(!P.nonce || (P.signal ? P.N <= DEP_PRODUCERS * DOWN_BN : (P.wait && !P.wait_cols && P.K1 <= DEP_PRODUCERS * DOWN_BN)), SD_EINVAL,
                    "gemm problem %d: what a dependency record does not hold", i);
         SD_REQUIRE(!P.wait || (P.K1 > 0 && g.p[0].signal), SD_EINVAL, "gemm problem %d waits but the group has no producer", i);
-        if (P.Mp == 0 || P.N == 0) continue;
-        if ((P.K0 & 63) || (P.K1 & 63)) guard = true;
-        if (P.N > maxN) maxN = P.N;
-        if (P.geglu_F > 0) {
-            gM += P.Mp;
-            gF = P.N > gF ? P.N : gF;
-            gK = P.K0 > gK ? P.K0 : gK;
-            gr = P.K1 > gr ? P.K1 : gr;
-        }
-        if (!P.signal) t128 += (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
-        if (!P.signal) t256 += (long)((P.Mp + 255) / 256) * ((P.N + 127) / 128);
-        if (P.signal) lead += (double)((P.Mp + 127) / 128) * ((P.N + DOWN_BN - 1) / DOWN_BN);
-        if (!P.signal) depth += (double)((P.Mp + 127) / 128) * ((P.N + 127) / 128) * P.K0;
     }
     // drop empty problems
     int w = 0;
@@ -684,58 +741,21 @@ int launch_gemm_group(GemmGroup& g, hipStream_t stream) {
         if (g.p[i].Mp > 0 && g.p[i].N > 0) { if (w != i) g.p[w] = g.p[i]; ++w; }
     g.n = w;
     if (w == 0) return SD_OK;
-    // Tile choice.  What a tile costs per 64 deep step is its operand bytes (a CU takes in 100-125 GB/s
-    // from L2 whatever the ring depth) or its MFMAs, whichever is longer, and the launch takes as long
-    // as its most loaded CU; so: the largest tiles that still give every CU the same number of them.
-    // Times below are single projections of rank 64, us, measured on one machine.
-    const double meanK = t128 ? depth / t128 : 0;
-    // GEGLU: geglu_tiles (128 columns of W are 64 of the output)
-    if (geglu) switch (geglu_tiles(gM, gF, gK, gr, false)) {
-        case GEGLU_64x64_3STAGES: return launch_cfg<64, 128, 64, 2, 2, 3, true, false>(g, guard, stream);
-        case GEGLU_64x64: return launch_cfg<64, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
-        case GEGLU_256x128: return launch_cfg<256, 256, 64, 4, 2, 2, true, false>(g, guard, stream);
-        default: return launch_cfg<128, 128, 64, 2, 2, 2, true, false>(g, guard, stream);
-        }
-    // Down-projections (N = rank <= 64) alone: 64x64 tiles, 5-stage ring.
-    if (maxN <= 64) return launch_cfg<64, 64, 64, 2, 2, 5, false, false>(g, guard, stream);
-    if (t128 < 512) {
-        // at most one 128x128 tile per CU, and most CUs have one: that tile with a deep ring, one
-        // workgroup per CU (2048x1280x5120: 42.0, 53.7 with 64x128 tiles, of which 64 CUs get two)
-        if (t128 > 128 && gemm_one_round(t128, (long)lead)) {
-            if (res32) return launch_cfg<128, 128, 64, 4, 2, 4, false, true>(g, guard, stream);
-            return launch_cfg<128, 128, 64, 4, 2, 4, false, false>(g, guard, stream);
-        }
-        // more than that (the down-projection's tiles count), but at most one of 256x128 per CU, and no short K loop: those
-        // (8192x640x2560: 41.1, 48.2 with 128x128 tiles; 4757x1280x1280: 26.4, 33.1 with 64x128;
-        // 6000x640x2560 34.5, 44.5 with 128x128 tiles; at K = 640 the ramps of the larger tile lose: 24.1 against 21.0)
-        if (t128 > 128 && t256 + lead / 2 <= 256 && meanK >= 1024) {
-            if (res32) return launch_cfg<256, 128, 64, 4, 2, 3, false, true>(g, guard, stream);
-            return launch_cfg<256, 128, 64, 4, 2, 3, false, false>(g, guard, stream);
-        }
-        // few tiles: 64x128 spreads them over more CUs, two workgroups on a CU at most: three ring stages
-        if (t128 <= 128) {
-            if (res32) return launch_cfg<64, 128, 64, 2, 2, 3, false, true>(g, guard, stream);
-            return launch_cfg<64, 128, 64, 2, 2, 3, false, false>(g, guard, stream);
-        }
-        // up to three on a CU where the K loop is short (8192x640x640: 17.3, 18.3 with 128x128)
-        if (t128 > 256 && meanK < 1024) {
-            if (res32) return launch_cfg<64, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
-            return launch_cfg<64, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
-        }
+    const GemmChoice c = gemm_choice(g);
+    switch (c.tiles) {
+    case GEMM_GEGLU_64x128_3STAGES: return launch_cfg<64, 128, 64, 2, 2, 3, true, false>(g, c.guard, stream);
+    case GEMM_GEGLU_64x128: return launch_cfg<64, 128, 64, 2, 2, 2, true, false>(g, c.guard, stream);
+    case GEMM_GEGLU_256x256: return launch_cfg<256, 256, 64, 4, 2, 2, true, false>(g, c.guard, stream);
+    case GEMM_GEGLU_128x128: return launch_cfg<128, 128, 64, 2, 2, 2, true, false>(g, c.guard, stream);
+    case GEMM_64x64: return launch_cfg<64, 64, 64, 2, 2, 5, false, false>(g, c.guard, stream);
+    case GEMM_128x128_ONE_ROUND: return launch_res<128, 128, 64, 4, 2, 4>(g, c, stream);
+    case GEMM_256x128_ONE_ROUND: return launch_res<256, 128, 64, 4, 2, 3>(g, c, stream);
+    case GEMM_64x128_3STAGES: return launch_res<64, 128, 64, 2, 2, 3>(g, c, stream);
+    case GEMM_64x128: return launch_res<64, 128, 64, 2, 2, 2>(g, c, stream);
+    case GEMM_256x256: return launch_cfg<256, 256, 64, 4, 2, 2, false, false>(g, c.guard, stream);
+    case GEMM_128x128_8WAVES: return launch_cfg<128, 128, 64, 4, 2, 2, false, false>(g, c.guard, stream);
+    default: return launch_res<128, 128, 64, 2, 2, 2>(g, c, stream);
     }
-    // One large plain projection with a long K loop (no launch of the transformer block: the
-    // 8192 x 4096 x 4096 yardstick takes 224, 248 at 128x128).  Not for grouped
-    // launches: the q/k/v group with its short text-context problems loses a third.
-    if (!res32 && n_main == 1 && t256 >= 512 && meanK >= 2048) return launch_cfg<256, 256, 64, 4, 2, 2, false, false>(g, guard, stream);
-    // 128x128 tiles, two workgroups per CU.  Of eight 32x64 wavefronts where problems of different sizes share the launch (q, k,
-    // v transposed, text keys): their tiles load the CUs unevenly, and one that has a CU to itself is faster with more
-    // wavefronts (attention blocks, us, four / eight: 4 x 3952 tokens of 640 channels with text keys + 64 106.7 / 100.4, 2 x 988 of
-    // 1280 + 16 85.6 / 79.8, 2 x 4096 of 320 + 8 109.8 / 100.5, 4 x 3952 of 640 + 32 275.4 / 279.2; 80 of them 0.91 to 1.014)
-    if (mixed && !res32) return launch_cfg<128, 128, 64, 4, 2, 2, false, false>(g, guard, stream);
-    // ... of four 64x64 otherwise (4757x1280x1280: 25.9, 33.1 with 64x128, 26.9 with eight wavefronts; the segments of a multi-adapter
-    // call: 8 x 4096 of 640 channels 45.0 / 45.6, 2999,2221,1552,1847,895 of 1280 48.6 / 50.7, of 320 up to 12 % the other way)
-    if (res32) return launch_cfg<128, 128, 64, 2, 2, 2, false, true>(g, guard, stream);
-    return launch_cfg<128, 128, 64, 2, 2, 2, false, false>(g, guard, stream);
 }
 
 __global__ void clear_flags_kernel(int32_t* p, int n) {

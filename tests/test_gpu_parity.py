@@ -830,10 +830,11 @@ def test_stack_small_ragged(B):
 
 
 # text keys / values of the second block in the first one's ff2 launch (128x128 tiles in one round, 256x128 tiles) or, where ff2 takes its
-# adapter into the tile, in the block's own q, k, v launch; as two launches per projection they are in the latter: same bits
-@pytest.mark.parametrize("Bn,T,Tc,rank,ff2", [(1, 3300, 77, 64, "gemm 128x128/8 waves/4 stages res32 flags"), (3, 1800, 131, 64, "gemm 256x128/8 waves/3 stages res32 flags"),
-                                              (1, 3300, 77, 16, "gemm16 64x160/1")])
-def test_stack_text_keys_in_the_ff2_launch(B, Bn, T, Tc, rank, ff2):
+# adapter into the tile, in the block's own q, k, v launch; of three samples, where ff2 takes 256x128 tiles for them, too; as two launches per
+# projection they are in the latter: same bits
+@pytest.mark.parametrize("Bn,T,Tc,rank,ff2,alone", [(1, 3300, 77, 64, "gemm 128x128/8 waves/4 stages res32 flags", ""), (3, 1800, 131, 64, "gemm 256x128/8 waves/3 stages res32 flags", ""),
+                                                    (3, 1600, 131, 64, "gemm 256x128/8 waves/3 stages res32 flags", "gemm 128x128/8 waves/4 stages res32 flags"), (1, 3300, 77, 16, "gemm16 64x160/1", "")])
+def test_stack_text_keys_in_the_ff2_launch(B, Bn, T, Tc, rank, ff2, alone):
     import torch
     # adapter scale 1/8 at either rank.  (At 1/2, rank 16, q and k have a deviation of 1.4 and scores reach 10: rounded to bf16, q and k
     # put such a score off by 10 2^-8 = 0.04, and with it a probability that is most of its row.)
@@ -841,9 +842,13 @@ def test_stack_text_keys_in_the_ff2_launch(B, Bn, T, Tc, rank, ff2):
     p = G.make_stack_inputs(cfg, seed=T)
     sp = B.StackParams(p)
     x, ctx = dev(p["x"], B), dev(p["ctx"], B)
-    with B.dry_run() as names:
+    with B.dry_run(detail=True) as names:
         B.spatial_transformer_fwd(x, ctx, sp, cfg.heads)
-    assert ff2 in names
+    norms = [i for i, n in enumerate(names) if n.startswith("layernorm")]
+    kernel, problems = zip(*(n.split(", ")[:2] for n in (names[norms[3] - 1], names[-2])))       # ff2 of both blocks, the last launches of theirs
+    assert kernel == (ff2, alone or ff2)
+    text = 0 if ff2.startswith("gemm16") else 2 + 2 * Bn
+    assert [int(p.split()[0]) for p in problems] == [text + (1 if ff2.startswith("gemm16") else 2), 1 if ff2.startswith("gemm16") else 2]
     y = B.spatial_transformer_fwd(x, ctx, sp, cfg.heads).clone()
     ref = O.spatial_transformer(p["x"], p["ctx"], p, cfg.heads)
     assert rel_err(host(y), ref) <= BF16_TOL

@@ -62,9 +62,12 @@ class Stack:
             self.at[b, "text"] = self.at[b - 1, "ff2"] if b and self.rides(b) else self.at[b, "qkv"]
 
     def launch(self, block, which):
-        """(kernel, problems)"""
-        m = re.match(r"(.*?), (\d+) problems", self.names[self.at[block, which]])
-        return m.group(1), int(m.group(2))
+        """(kernel, problems); q, k, v of many samples are two launches, whose problems are added"""
+        at = end = self.at[block, which]
+        while which == "qkv" and not self.names[end + 1].startswith("attention"):
+            end += 1
+        got = [re.match(r"(.*?), (\d+) problems", n) for n in self.names[at:end + 1]]
+        return got[0].group(1), sum(int(m.group(2)) for m in got)
 
     def rides(self, b):
         """Whether block b's text keys / values are in the ff2 launch of the block before.  They are in one of the two."""
@@ -91,6 +94,32 @@ def test_text_keys_ride_in_the_ff2_launch(B, Bn, T, Cc, r, rf, ff2):  # noqa: F8
 @pytest.mark.parametrize("Bn,T,Cc,r,rf", [(1, 3300, 640, 16, 16), (2, 256, 320, 8, 0), (1, 988, 1280, 16, 0), (2, 4200, 1280, 64, 64)])
 def test_text_keys_stay_with_the_queries(B, Bn, T, Cc, r, rf):  # noqa: F811
     assert not Stack(B, Bn, T, Cc, 2, r, rf).rides(1)     # ff2 in its in-tile kernel, or in several rounds
+
+
+# One rule for ff2's tiles, with riders and without: ranges of token counts about the ends of a round of 128x128 tiles (where the text keys'
+# tiles would push ff2 out of it into 256x128 tiles on half the CUs) and of 256x128 tiles; adapters everywhere, on attention only, on nothing.
+# Where q, k, v with them would be two launches (more than 16 problems: three samples and more with adapters), any one round will do.
+@pytest.mark.parametrize("Bn,Cc,r,rf,lo,hi", [
+    (2, 1280, 64, 64, 1000, 1700), (2, 1280, 32, 32, 1000, 1700), (2, 1280, 16, 0, 1000, 1700), (2, 1280, 0, 0, 1000, 1700), (1, 1280, 64, 64, 2500, 3100), (4, 1280, 0, 0, 500, 800),
+    (2, 640, 64, 64, 2100, 4400), (2, 640, 16, 0, 2500, 4400), (4, 640, 0, 0, 1000, 1400), (1, 640, 8, 0, 3000, 4400), (2, 320, 64, 64, 3500, 4400),
+    (3, 1280, 64, 64, 600, 1100), (4, 1280, 64, 64, 450, 850), (4, 640, 64, 64, 1000, 1400), (3, 640, 32, 0, 1300, 1800),
+])
+def test_riders_leave_ff2_its_tiles(B, Bn, Cc, r, rf, lo, hi):  # noqa: F811
+    tiles = lambda name: re.match(r"(.*) stages", name).group(1) if name.startswith("gemm ") else name
+    one_round = ("gemm 128x128/8 waves/4", "gemm 256x128/8 waves/3")
+    two_launches = r > 0 and 4 + 2 * Bn + 2 + 2 * Bn > 16
+    for T in sorted({*range(lo, hi, 53), *(t for e in range(lo // 128, hi // 128) for t in (128 * e, 128 * e + 4))}):
+        s = Stack(B, Bn, T, Cc, 2, r, rf)
+        with_text, alone = tiles(s.launch(0, "ff2")[0]), tiles(s.launch(1, "ff2")[0])
+        if s.rides(1):
+            assert with_text in one_round and alone in one_round and (with_text == alone or two_launches), T
+        else:
+            assert with_text == alone and not (two_launches and alone == one_round[0]), T
+
+
+@pytest.mark.parametrize("Bn,T,Cc,r,rf", [(2, 1296, 1280, 64, 64), (2, 1440, 1280, 64, 64), (1, 2800, 1280, 64, 64), (4, 640, 1280, 0, 0), (2, 2500, 640, 64, 64), (2, 1400, 1280, 16, 0)])
+def test_text_keys_that_do_not_fit_stay_with_the_queries(B, Bn, T, Cc, r, rf):  # noqa: F811
+    assert not Stack(B, Bn, T, Cc, 2, r, rf).rides(1)
 
 
 # ---- weights read ahead
