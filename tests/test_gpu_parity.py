@@ -288,6 +288,26 @@ def test_lora_linear_one_round_of_tiles_residual(B, M, K, N, rank, f32):
     assert np.abs(got - ref).max() > 0.3 * np.abs(res).max()         # negative control: the residual is seen
 
 
+# every number of steps about the ring's depth (three and four stages of 64x80, five of 64x160, four of 128x160): loops of no step, one pair
+# and more for the steps that wait for the first stages, for those behind them and for the last ones, odd and even
+@pytest.mark.parametrize("M,N,rank,kernel", [(70, 84, 8, "gemm16 64x80/1"), (63, 76, 0, "gemm16 64x80/0"), (8250, 160, 8, "gemm16 64x160/1"), (16400, 160, 0, "gemm16 128x160/0")])
+def test_lora_linear_in_tile_every_number_of_steps(B, M, N, rank, kernel):
+    import torch
+    r = rng(M + N)
+    for steps in range(1, 15):
+        K = 64 * steps
+        p = mkproj(r, N, K, rank, bias=steps % 2 == 0, scale=0.7)
+        x = G.bf16_round(r.standard_normal((M, K)).astype(np.float32))
+        res = r.standard_normal((M, N)).astype(np.float32)
+        call = lambda: B.lora_linear_fwd(dev(x, B), B.Proj.from_numpy(p), residual=torch.from_numpy(res).cuda(), out_dtype=torch.float32)
+        with B.dry_run(detail=True) as names:
+            call()
+        stages = {"gemm16 64x80": 3 if K <= 640 else 4, "gemm16 64x160": 5, "gemm16 128x160": 4}[kernel.split("/")[0]]
+        assert names[-1] == "%s, 1 problems, %d stages, fp32 residual" % (kernel, stages), K
+        ref = O.lora_linear(x, p["W"], p["b"], p["A"], p["B"], p["scale"])
+        assert np.abs(host(call()) - res - ref).max() <= BF16_TOL * np.abs(ref).max(), K
+
+
 # feed-forward in-projections about the sizes where the wide tiles begin and end to pay: K loops of one, two, three and more steps, ranks of
 # less and more than 64 (which kernel each of them takes: test_lora_linear_geglu_every_kernel)
 @pytest.mark.parametrize("M,C,F,rank", [(6300, 64, 1288, 0), (8192, 128, 2560, 8), (4000, 192, 2568, 0), (1000, 640, 5120, 72), (988, 1280, 5120, 0), (2047, 1280, 5120, 64)])
