@@ -172,7 +172,8 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
     auto no_load = [](int) {};
     // ---- what the epilogue adds, requested when the first stage has landed: as long as one of the first STAGES is waited
     // for, these NEXTRA loads may stay in flight too (loads retire in order).  Every lane loads, rows and columns past the end their
-    // last ones, so that the number is what it says.  (Requested at the last MFMAs, as before, a launch that is one round of
+    // last ones, and the compiler does not see which columns those are: equal addresses (no bias) would be one load, and the waits, which
+    // count NEXTRA, would let a stage's own loads pass.  (Requested at the last MFMAs, as before, a launch that is one round of
     // tiles has nothing to hide them behind.  With the branch-free prologue and the straight-line epilogue below, operands from
     // HBM: 8192x640x640 + 64 with an fp32 residual 24.2 -> 23.4 us, 1000x640x640 + 32 9.2 -> 8.2, 512x320x320 + 8 6.6 -> 6.0.)
     constexpr int ME = WGK == 2 ? MI / 2 : MI;   // row blocks this wavefront finishes
@@ -183,14 +184,21 @@ __global__ __launch_bounds__(64 * WGM * WGN * WGK, 2) void gemm16_kernel(const G
     u32x2 resb[RES == RES_BF16 ? ME : 1][NI], bias[NI];
     auto load_extra = [&]() {
         const uint16_t* const bp = P.bias ? P.bias : reinterpret_cast<const uint16_t*>(g_gemm_zeros);
+        int col[NI];
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) bias[ni] = *as_global(reinterpret_cast<const u32x2*>(bp + (P.bias ? min(ncol + ni * 16, N - 4) : 0)));
+        for (int ni = 0; ni < NI; ++ni) {
+            col[ni] = min(ncol + ni * 16, N - 4);
+            uint32_t at = P.bias ? col[ni] : 0;
+            asm volatile("" : "+v"(at));
+            bias[ni] = *as_global(reinterpret_cast<const u32x2*>(bp + at));
+        }
 #pragma unroll
         for (int mi = 0; mi < (RES ? ME : 0); ++mi) {
-            const int64_t row = (int64_t)min(mrow + mi * 16, Mp - 1) * P.ldr;
+            int64_t row = (int64_t)min(mrow + mi * 16, Mp - 1) * P.ldr;
+            asm volatile("" : "+v"(row));
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
-                const int64_t at = row + min(ncol + ni * 16, N - 4);
+                const int64_t at = row + col[ni];
                 if (RES == RES_F32) resf[mi][ni] = *as_global(reinterpret_cast<const f32x4*>(static_cast<const float*>(P.res) + at));
                 else resb[mi][ni] = *as_global(reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(P.res) + at));
             }
