@@ -457,13 +457,14 @@ static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
 //   An adapter costs the tile its A rows in every step (up to rank 32 16 or 32 of them, above 64), the general kernel a
 // producer tile, its stores and the wait for them: up to rank 32 the former is cheaper at any K (0.96 to 1.7 times
 // as fast over 400 projections of 64 to 16384 rows), of rank 64 while K is short, or where two column tiles are all that repeat it
-// (8200x320x1280 + 64 24.3 / 21.1).
+// (8200x320x1280 + 64 24.3 / 21.1).  (64x80 tiles of rank 64, 77 to 988 rows, K = 1280 to 2560: 0.97 to 1.10 of the general kernel's time,
+// of rank 40 0.90 to 1.08, the longer the K loop the worse.)
 //   A lone projection that the general kernel fits into one round (128x128 tiles with a deep ring, its producers among them; in
 // place of the 64-row tiles its own) is better off there; with an adapter of rank 32 and a short K the 64-row tiles stay ahead.  The q, k, v
 // groups always gain: their alternative is three rounds of uneven tiles.
 // us, general kernel / here: 512x320x320 + 8 10.4 / 6.1, + 64 9.1 / 7.3; 1000x1280x1280 + 16 13.4 / 9.6, + 64 12.3 / 12.4;
 // 3952x640x640 + 16 13.4 / 10.6, + 64 12.7 / 11.3; 8192x640x640 + 64 17.7 / 15.8; 2048x1280x1280 + 64 16.1 / 15.6; 154x1280x2048 + 8
-// 14.7 / 11.2, + 64 13.8 / 14.8; 2048x1280x5120 + 32 38.0 / 38.5, + 64 38.8 / 43.8; 4100x640x640 (132 tiles) 11.5 / 14.6, + 16 15.1 / 16.9;
+// 14.7 / 10.9, + 64 14.0 / 14.8; 2048x1280x5120 + 32 38.0 / 38.5, + 64 38.8 / 43.8; 4100x640x640 (132 tiles) 11.5 / 14.6, + 16 15.1 / 16.9;
 // 6100x640x640 (192) 13.5 / 15.8, + 16 18.4 / 17.7; 8100x640x2560 (256) 36.4 / 32.5, + 16 39.8 / 36.5; the q, k, v and text key / value
 // group of 988 tokens of 1280 channels + 16 37.6 / 27.6, of 2 x 256 of 320 + 8 20.4 / 13.9 (values stored transposed).
 static int tile16(const GemmGroup& g) {
@@ -473,7 +474,7 @@ static int tile16(const GemmGroup& g) {
         const GemmProblem& P = g.p[i];
         if (P.geglu_F > 0 || P.bias_on_rows == 1 || P.K0 % 64 || P.K1 > 64 || P.N % 4 || (P.bias_on_rows == 2 ? P.y_f32 || P.res : P.ldy % 4) || (P.res && P.ldr % 4) || P.Mp <= 0 || P.N <= 0 ||
             (uintptr_t)P.bias % 8 || (uintptr_t)P.y % (P.bias_on_rows == 2 ? 2 : P.y_f32 ? 16 : 8) || (uintptr_t)P.res % (P.res_f32 ? 16 : 8) ||
-            P.ldp0 * 512 >= (1ll << 31) || P.ldq0 * 512 >= (1ll << 31) || (P.res && (g.n > 1 || (P.y_f32 && !P.res_f32))))
+            P.ldp0 * 512 >= (1ll << 31) || P.ldq0 * 512 >= (1ll << 31) || (P.res && g.n > 1))
             return 0;
         big += (long)((P.Mp + 127) / 128) * ((P.N + 159) / 160);
         mid += (long)((P.Mp + 63) / 64) * ((P.N + 159) / 160);
@@ -501,11 +502,15 @@ int launch_gemm16(GemmGroup& g, hipStream_t stream) {
     case 3: return launch16r<128, 160, 4, 2, 1>(g, rmax, stream);
     case 2: return launch16r<64, 160, 2, 2, 2>(g, rmax, stream);
     // One workgroup of four wavefronts per CU: the two stages that three leave in flight (37 KB) come in at 54 GB/s, the latency of
-    // the last-level cache.  Four take 15 % off a long K loop and more first loads in front of a short one (988 rows, us, three /
-    // four / five stages; four wavefronts more that split K in four took as much off and cost 1 us in front):
-    // 5120x1280 + 16 28.9 / 25.0 / 25.2, 2048x1280 13.5 / 13.0 / 13.2, 1280x1280 + 16 11.0 / 10.8 / 11.1, 640x1280 7.2 / 7.3 / 7.6,
-    // 512 rows of 320x320 + 8 5.5 / 5.7 / 6.0, 1000 of 640x640 + 64 8.6 / 9.2 / 9.5.
-    default: return kmax > 640 ? launch16r<64, 80, 2, 1, 2, 4>(g, rmax, stream) : launch16r<64, 80, 2, 1, 2, 3>(g, rmax, stream);
+    // the last-level cache.  Four take 15 % off a long K loop and more first loads in front of a short one.  988 rows of 1280 columns + 8, us,
+    // three / four stages, weights from the last-level cache: K = 5120 29.4 / 25.6, 2048 13.4 / 12.7, 1280 10.2 / 9.8; in L2 from a call
+    // before: 26.8 / 22.6, 11.1 / 11.4, 8.8 / 9.1; K = 640 without adapter 7.2 / 7.3.  (512 rows of 320x320 + 8 5.5 / 5.7, 1000 of 640x640 + 64 8.6 / 9.2; five
+    // stages 0.1 to 0.3 more than four.  Four wavefronts more that split K in four took as much off and cost 1 us in front.)
+    default:
+        if (kmax <= 640) return launch16r<64, 80, 2, 1, 2, 3>(g, rmax, stream);
+        if (rmax == 0) return launch16<64, 80, 2, 1, 2, 0, 4>(g, stream);
+        if (rmax <= 16) return launch16<64, 80, 2, 1, 2, 1, 4>(g, stream);
+        return launch16<64, 80, 2, 1, 2, 2, 4>(g, stream);     // (above rank 32 this tile is for K <= 640)
     }
 }
 
