@@ -408,7 +408,9 @@ static bool push_kv_calls(std::vector<ProjCall>& calls, const uint16_t* src, int
 }
 
 // Stacks whose weights and workspace take so many bytes have their weights read ahead: a little less than the last-level cache
-// holds.  What fits it stays there from call to call, and reading it again only costs (us without / with; MB of weights and workspace:
+// holds.  What fits it stays there from call to call of the same stack, and reading it again only costs.  (Where other stacks run in between,
+// as in a denoising step, smaller ones lose their weights too, and would gain: the line was drawn with one stack called again and
+// again.  us without / with; MB of weights and workspace:
 // 2 x 1024 tokens of 1280 channels, 2 blocks + 64 524 / 537, 220; 3 blocks 800 / 749, 280; 4 blocks 1067 / 989;
 // 2 x 1000 of 640, 10 blocks + 16 1241 / 1250, 240; 2 x 4096 of 640, 10 blocks + 64 3492 / 3432, 370).
 constexpr uint64_t READ_AHEAD_FROM = 244ull << 20;
@@ -863,15 +865,17 @@ static bool carve_stack(Workspace& ws, StackWs& w, int Bn, int T, int C, int Tc,
     w.dep.carve(ws, std::max(M, (size_t)Bn * Tc));
     return ws.ok();
 }
+static size_t stack_bytes(int Bn, int T, int C, int Tc, int rmax, bool small) {
+    Workspace ws((void*)256, (size_t)-1 / 2);
+    StackWs w;
+    carve_stack(ws, w, Bn, T, C, Tc, rmax, small);
+    return ws.used;
+}
 }  // namespace sd
 
 extern "C" size_t sd_spatial_transformer_workspace_bytes(int32_t Bn, int32_t T, int32_t C, int32_t Tc, int32_t Dc, int32_t r_max) {
     (void)Dc;
-    if (Bn <= 0 || T <= 0 || C <= 0) return 256;
-    Workspace ws((void*)256, (size_t)-1 / 2);
-    StackWs w;
-    carve_stack(ws, w, Bn, T, C, Tc, r_max);
-    return ws.used;
+    return Bn <= 0 || T <= 0 || C <= 0 ? 256 : stack_bytes(Bn, T, C, Tc, r_max, false);
 }
 
 extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx, const sd_stack_params* p, uint16_t* y,
@@ -907,8 +911,8 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
         sw = StackWs();
         return carve_stack(w, sw, Bn, T, C, Tc, rmax, small);
     };
-    SD_REQUIRE(ws && (carve(false) || carve(true)), SD_EWORKSPACE, "spatial_transformer: workspace of %zu bytes, need %zu", ws_bytes,
-               sd_spatial_transformer_workspace_bytes(Bn, T, C, Tc, Dc, rmax));
+    SD_REQUIRE(ws && (carve(false) || carve(true)), SD_EWORKSPACE, "spatial_transformer: workspace of %zu bytes, need %zu (%zu at the least, with attention tiles uncut)", ws_bytes,
+               stack_bytes(Bn, T, C, Tc, rmax, false), stack_bytes(Bn, T, C, Tc, rmax, true));
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int M = Bn * T;
     // GroupNorm -> proj_in -> fp32 residual stream h

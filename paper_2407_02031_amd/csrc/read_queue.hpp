@@ -21,10 +21,11 @@ struct NoRanges {};                    // the argument of kernels that read none
 
 // The queue the parts come from, in order of use.
 struct ReadAhead {
-    // No part begins or ends further ahead of the launches than this.  It has to reach across both feed-forward projections
-    // (39 MB at 1280 channels), because nothing reads between them; what lies beyond is driven out again before its turn.
-    // (26 x 38 tokens, one sample, ten blocks of 1280 channels, 62 MB a block; us per stack: without 1806, 32 MB 1662, 40 MB
-    // 1569, 44 MB 1627, 64 MB 1645, 96 MB 1672, no limit 1647.)
+    // No part begins or ends further ahead of the launches than this.  It has to reach across both feed-forward projections, because
+    // nothing reads between them: 39 MB at 1280 channels without adapters, 10 at 640; what lies beyond is driven out again before its
+    // turn.  One number for all: swept at 26 x 38 tokens, one sample, ten blocks of 1280 channels, 62 MB a block (us per stack: without 1806,
+    // 32 MB 1662, 40 MB 1569, 44 MB 1627, 64 MB 1645, 96 MB 1672, no limit 1647).  With adapters of rank 64 and the next block's text weights
+    // in ff2 (32 x 32 tokens) the two launches read 52 MB, of which the last 12 come from HBM.
     static constexpr uint64_t LEAD = 40ull << 20;
     struct Range { const char* p; uint64_t bytes; };
     std::vector<Range> ranges;

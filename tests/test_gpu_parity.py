@@ -880,6 +880,50 @@ def test_stack_text_keys_in_the_ff2_launch(B, Bn, T, Tc, rank, ff2, alone):
     assert B.gemm_dep_timeouts() == 0
 
 
+# a stack in a workspace that lacks the room for the halves of cut attention tiles, and what lies behind that room moves up
+@pytest.mark.parametrize("Bn,T,C", [(1, 4096, 320), (1, 1500, 640)])
+def test_stack_in_a_workspace_without_room_for_cut_tiles(B, Bn, T, C):
+    import torch
+    cfg = small_cfg(Bn=Bn, T=T, Tc=77, C=C, heads=C // 64, r=16, alpha=2.0, depth=1, w_std=0.03)
+    p = G.make_stack_inputs(cfg, seed=T)
+    sp = B.StackParams(p)
+    x, ctx = dev(p["x"], B), dev(p["ctx"], B)
+    need = B.spatial_transformer_workspace_bytes(Bn, T, C, 77, cfg.Dc, sp.r_max)
+    least = need - (T + 127) // 128 * cfg.heads * Bn * 2 * 34 * 256 * 4
+    ref = O.spatial_transformer(p["x"], p["ctx"], p, cfg.heads)
+    for size, cut in ((need, " cut"), (least, "")):
+        ws = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")       # and what lies behind it stays as it is
+        with B.dry_run() as names:
+            B.spatial_transformer_fwd(x, ctx, sp, cfg.heads, ws=ws[:size])
+        assert "attention prescaled try" + cut in names
+        y = B.spatial_transformer_fwd(x, ctx, sp, cfg.heads, ws=ws[:size])
+        assert rel_err(host(y), ref) <= BF16_TOL
+        assert bool((ws[size:] == 0x5A).all())
+    with pytest.raises(B.SwiftDiffError) as e:
+        B.spatial_transformer_fwd(x, ctx, sp, cfg.heads, ws=ws[:least - 256])
+    assert e.value.code == -3
+
+
+# deep stacks, whose attention (tiles cut in half; whole ones to the text) and LayerNorm launches (rows of 640 and of 1280 channels) read
+# weights ahead
+@pytest.mark.parametrize("Bn,T,C,depth", [(1, 1500, 640, 11), (1, 2100, 1280, 3)])
+def test_deep_stack_reads_weights_ahead(B, Bn, T, C, depth):
+    import torch
+    cfg = small_cfg(Bn=Bn, T=T, Tc=77, C=C, heads=C // 64, Dc=2048, r=16, alpha=2.0, depth=depth, w_std=0.02)
+    p = G.make_stack_inputs(cfg, seed=T)
+    sp = B.StackParams(p)
+    x, ctx = dev(p["x"], B), dev(p["ctx"], B)
+    with B.dry_run(detail=True) as names:
+        B.spatial_transformer_fwd(x, ctx, sp, cfg.heads)
+    for what in ("attention prescaled try cut, ahead", "attention prescaled try, ahead", "layernorm, ahead"):
+        assert any(n.startswith(what) for n in names), what
+    y = B.spatial_transformer_fwd(x, ctx, sp, cfg.heads).clone()
+    ref = O.spatial_transformer(p["x"], p["ctx"], p, cfg.heads)
+    assert rel_err(host(y), ref) <= BF16_TOL
+    for _ in range(3):
+        assert torch.equal(B.spatial_transformer_fwd(x, ctx, sp, cfg.heads), y)
+
+
 def test_stack_with_biased_q_k_v(B):
     """SDXL's q, k, v carry no bias, but a projection record may: the stack takes them too (the
     text keys / values projected ahead inside the self-attention launches included)."""

@@ -122,6 +122,20 @@ def test_text_keys_that_do_not_fit_stay_with_the_queries(B, Bn, T, Cc, r, rf):  
     assert not Stack(B, Bn, T, Cc, 2, r, rf).rides(1)
 
 
+# ---- workspaces without room for the halves of cut attention tiles
+@pytest.mark.parametrize("Bn,T,Cc", [(1, 4096, 320), (2, 3100, 320), (1, 1500, 640)])
+def test_workspace_without_room_for_cut_tiles(B, Bn, T, Cc):  # noqa: F811
+    L = B.lib()
+    need = L.sd_spatial_transformer_workspace_bytes(Bn, T, Cc, Tc, Dc, 8)
+    least = need - (T + 127) // 128 * (Cc // 64) * Bn * 2 * 34 * 256 * 4
+    assert "attention prescaled try cut" in Stack(B, Bn, T, Cc, 2, 8).names
+    for ws in (need - 256, least):
+        names = Stack(B, Bn, T, Cc, 2, 8, ws=ws).names
+        assert "attention prescaled try cut" not in names and names.count("attention prescaled try") == 4
+    Stack(B, Bn, T, Cc, 2, 8, ws=least - 256, expect=-3)
+    assert ("need %d (%d at the least" % (need, least)) in L.sd_last_error().decode()
+
+
 # ---- weights read ahead
 def ranges(name):
     return [(int(p, 16), int(n)) for p, n in re.findall(r" ([0-9a-f]+)\+(\d+)", name.split("ahead", 1)[1])] if ", ahead" in name else []
