@@ -16,6 +16,7 @@ from __future__ import annotations
 import argparse
 import json
 import os
+import re
 import sys
 import time
 
@@ -71,11 +72,11 @@ GROUPS = 5     # timed groups of K steps each; the median group is the figure re
 KERNEL_NAMES = {
     "self_attention": "attention_kernel, latent self-attention",
     "cross_attention": "attention_kernel, cross-attention to the text tokens",
-    "qkv": "gemm_kernel, grouped q/k/v^T projections (+ the next cross-attention's text k/v)",
+    "qkv": "gemm_kernel, grouped q/k/v^T projections (+ the next cross-attention's text k/v, unless an ff2 launch has them)",
     "attn_out": "gemm16_kernel or gemm_kernel, attention output projection + residual",
     "cross_q": "gemm16_kernel or gemm_kernel, cross-attention query projection",
     "ff1": "gemm_geglu_kernel with down_kernel, or gemm_kernel: feed-forward in-projection with GEGLU epilogue",
-    "ff2": "gemm_kernel, feed-forward out-projection + residual",
+    "ff2": "gemm_kernel, feed-forward out-projection + residual (+ the next block's text k/v, where they fit)",
     "proj_io": "gemm16_kernel or gemm_kernel, proj_in / proj_out",
     "layernorm": "layernorm_kernel",
     "groupnorm": "groupnorm_partial_kernel + groupnorm_apply_kernel",
@@ -162,24 +163,31 @@ def kernel_table(B, leg, K, ms_per_step):
     M, C, T, Bn, F, r = cfg.M, cfg.C, cfg.T, cfg.Bn, cfg.F, cfg.r
     rl = r if cfg.lora_ff else 0
 
-    # every projection launch holds its down-projection tiles (x A^T), its base GEMM with the
-    # K segment extended by r, and nothing else; the q/k/v launch also holds the next
-    # cross-attention's text keys / values
     def proj(m, k, n, rr):
         return 2.0 * m * k * n + (2.0 * m * k * rr + 2.0 * m * rr * n if rr else 0.0)
+
+    # every projection launch holds its down-projection tiles (x A^T), its base GEMM with the
+    # K segment extended by r, and nothing else; a block's text keys / values are in its q/k/v
+    # launch or, counted as problems there, in the ff2 launch of the block before
+    with B.dry_run(detail=True) as names:
+        leg.step()
+    problems = [int(m.group(1)) if (m := re.search(r", (\d+) problems", n)) else 0 for n in names]
+    block_starts = [i for i, n in enumerate(names) if n.startswith("layernorm")][::3]
+    in_ff2 = sum(problems[i - 1] > problems[-2] for i in block_starts[1:]) / d     # share of the blocks
+    text = 2 * proj(Bn * cfg.Tc, cfg.Dc, C, r)
     flop_per_launch = {
         "self_attention": 4.0 * Bn * T * T * C,
         "cross_attention": 4.0 * Bn * T * cfg.Tc * C,
-        "qkv": 3 * proj(M, C, C, r) + 2 * proj(Bn * cfg.Tc, cfg.Dc, C, r),
+        "qkv": 3 * proj(M, C, C, r) + (1 - in_ff2) * text,
         "attn_out": proj(M, C, C, r),
         "cross_q": proj(M, C, C, r),
         "ff1": proj(M, C, 2 * F, rl),
-        "ff2": proj(M, F, C, rl),
+        "ff2": proj(M, F, C, rl) + in_ff2 * text,
         "proj_io": proj(M, C, C, 0),
     }
     # HBM-bound kernels: algorithmic bytes per launch (LayerNorm: fp32 stream in, bf16 out;
-    # GroupNorm: bf16 in twice (statistics, apply), bf16 out)
-    bytes_per_launch = {"layernorm": 6.0 * M * C, "groupnorm": 6.0 * M * C}
+    # GroupNorm: bf16 in twice (statistics, apply; once where it is one launch), bf16 out)
+    bytes_per_launch = {"layernorm": 6.0 * M * C, "groupnorm": (4.0 if names[0] == "groupnorm unit" else 6.0) * M * C}
     B.timing_enable(K * max(per_step.values()) + 8)
     for _ in range(K):
         leg.step()

@@ -147,10 +147,12 @@ const char* sd_dry_run_text(void);
  * the host array, disable() destroys them.  One process-wide instance, not thread-safe. */
 #define SD_TIMING_SELF_ATTENTION 0   /* flash attention over the latent tokens            */
 #define SD_TIMING_CROSS_ATTENTION 1  /* flash attention to the text tokens                */
-#define SD_TIMING_QKV 2              /* grouped q, k, v^T base GEMMs of self-attention     */
+#define SD_TIMING_QKV 2              /* grouped q, k, v^T projections of self-attention; in the
+                                        stack also the text keys / values of its block, unless
+                                        the ff2 launch of the block before has them        */
 #define SD_TIMING_ATTN_OUT 3         /* attention output projection + residual            */
 #define SD_TIMING_FF1 4              /* feed-forward in-projection with GEGLU epilogue     */
-#define SD_TIMING_FF2 5              /* feed-forward out-projection + residual             */
+#define SD_TIMING_FF2 5              /* feed-forward out-projection + residual (see QKV)   */
 #define SD_TIMING_CROSS_Q 6          /* cross-attention query projection                   */
 #define SD_TIMING_PROJ_IO 7          /* the stack's proj_in and proj_out                   */
 #define SD_TIMING_LAYERNORM 8        /* every LayerNorm launch                             */
