@@ -78,6 +78,7 @@ KERNEL_NAMES = {
     "ff1": "gemm_geglu_kernel with down_kernel, or gemm_kernel: feed-forward in-projection with GEGLU epilogue",
     "ff2": "gemm_kernel, feed-forward out-projection + residual (+ the next block's text k/v, where they fit)",
     "proj_io": "gemm16_kernel or gemm_kernel, proj_in / proj_out",
+    "chain": "chain_kernel, attention output projection to feed-forward input: three projections, two LayerNorms, cross-attention",
     "layernorm": "layernorm_kernel",
     "groupnorm": "groupnorm_partial_kernel + groupnorm_apply_kernel",
 }
@@ -166,11 +167,15 @@ def kernel_table(B, leg, K, ms_per_step):
     def proj(m, k, n, rr):
         return 2.0 * m * k * n + (2.0 * m * k * rr + 2.0 * m * rr * n if rr else 0.0)
 
+    with B.dry_run(detail=True) as names:
+        leg.step()
+    if any(n.endswith("of the chain") for n in names):
+        per_step = {k: v for k, v in per_step.items() if k not in ("cross_attention", "attn_out", "cross_q")}
+        per_step.update(chain=d, layernorm=d)
+
     # every projection launch holds its down-projection tiles (x A^T), its base GEMM with the
     # K segment extended by r, and nothing else; a block's text keys / values are in its q/k/v
     # launch or, counted as problems there, in the ff2 launch of the block before
-    with B.dry_run(detail=True) as names:
-        leg.step()
     problems = [int(m.group(1)) if (m := re.search(r", (\d+) problems", n)) else 0 for n in names]
     block_starts = [i for i, n in enumerate(names) if n.startswith("layernorm")][::3]
     in_ff2 = sum(problems[i - 1] > problems[-2] for i in block_starts[1:]) / d     # share of the blocks
@@ -184,6 +189,7 @@ def kernel_table(B, leg, K, ms_per_step):
         "ff1": proj(M, C, 2 * F, rl),
         "ff2": proj(M, F, C, rl) + in_ff2 * text,
         "proj_io": proj(M, C, C, 0),
+        "chain": 3 * proj(M, C, C, r) + 4.0 * Bn * T * cfg.Tc * C,
     }
     # HBM-bound kernels: algorithmic bytes per launch (LayerNorm: fp32 stream in, bf16 out;
     # GroupNorm: bf16 in twice (statistics, apply; once where it is one launch), bf16 out)

@@ -132,7 +132,7 @@ int32_t sd_set_projection_fusion(int32_t on);
 /* Which kernels would run?  Between sd_dry_run(1) and sd_dry_run(0) the forward calls of this thread (projections,
  * attention, sub-layers, GroupNorm, the stack, patches) check their arguments and choose their kernels as ever, but launch nothing:
  * they write the names of what they would launch to sd_dry_run_text, in order, and need no device.  For tests that
- * are meant for one kernel, and for reading a dispatch rule at a size.  sd_dry_run(2) also writes, behind a comma, how many
+ * are meant for one kernel, and for reading a dispatch rule at a size.  A launch that runs several steps names them one by one, "of the chain" behind each.  sd_dry_run(2) also writes, behind a comma, how many
  * problems a projection launch holds, the in-tile kernel's ring stages and residual, and the ranges of weights that an
  * attention or LayerNorm launch reads ahead (address+bytes, in hex and decimal).  Returns the previous setting. */
 int32_t sd_dry_run(int32_t on);
@@ -157,7 +157,10 @@ const char* sd_dry_run_text(void);
 #define SD_TIMING_PROJ_IO 7          /* the stack's proj_in and proj_out                   */
 #define SD_TIMING_LAYERNORM 8        /* every LayerNorm launch                             */
 #define SD_TIMING_GROUPNORM 9        /* the stack's GroupNorm (partial sums + apply)       */
-#define SD_TIMING_TAGS 10
+#define SD_TIMING_CHAIN 10           /* attention output projection to feed-forward input in one
+                                        launch (blocks of 320 and 640 channels): no launches of
+                                        tags 1, 3 and 6 then, and one LayerNorm of three         */
+#define SD_TIMING_TAGS 11
 int sd_timing_enable(int32_t records_per_tag);
 int sd_timing_collect(int32_t tag, float* ms_host, int32_t capacity, int32_t* count);
 int sd_timing_disable(void);

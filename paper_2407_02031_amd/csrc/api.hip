@@ -432,7 +432,7 @@ static int attn_sublayer(const void* x, void* y, int io_f32, const uint16_t* ctx
                          const uint16_t* g, const uint16_t* b, float eps, const sd_proj& pq, const sd_proj& pk,
                          const sd_proj& pv, const sd_proj& po, int Bn, int T, int C, int heads, const AttnWs& w,
                          hipStream_t stream, const std::vector<ProjCall>* ahead = nullptr, bool kv_ready = false, DepFlags* dep = nullptr,
-                         ReadAhead* read_ahead = nullptr) {
+                         ReadAhead* read_ahead = nullptr, bool project_out = true) {
     const int M = Bn * T;
     const int Tk = ctx ? Tc : T;
     const int Kkv = ctx ? Dc : C;
@@ -464,7 +464,7 @@ static int attn_sublayer(const void* x, void* y, int io_f32, const uint16_t* ctx
                           arrived, DepFlags::ARRIVED, read_ahead);
     timing_mark(atag, 1, stream);
     if (rc) return rc;
-    if ((rc = launch_attention_merge(w.scratch, w.a, C, Bn, T, heads, k_prescaled, cut, stream))) return rc;
+    if ((rc = launch_attention_merge(w.scratch, w.a, C, Bn, T, heads, k_prescaled, cut, stream)) || !project_out) return rc;
     ProjCall oc = {w.a, C, M, C, C, &po, w.to, {y, C, io_f32, x, C, false, 0}};
     if (read_ahead) read_ahead->launched();
     return run_projections(&oc, 1, stream, SD_TIMING_ATTN_OUT, dep);
@@ -483,8 +483,8 @@ static bool carve_ff(Workspace& ws, FfWs& w, int M, int C, int F, int rmax) {
 
 static int ff_sublayer(const void* x, void* y, int io_f32, const uint16_t* g, const uint16_t* b, float eps,
                        const sd_proj& p1, const sd_proj& p2, int M, int C, int F, const FfWs& w, hipStream_t stream, DepFlags* dep = nullptr,
-                       uint16_t* y_bf16 = nullptr, ReadAhead* read_ahead = nullptr, const std::vector<ProjCall>* riders = nullptr) {
-    int rc = layernorm(x, io_f32, g, b, eps, w.n, M, C, stream, dep, read_ahead);
+                       uint16_t* y_bf16 = nullptr, ReadAhead* read_ahead = nullptr, const std::vector<ProjCall>* riders = nullptr, bool normed = false) {
+    int rc = normed ? SD_OK : layernorm(x, io_f32, g, b, eps, w.n, M, C, stream, dep, read_ahead);
     if (rc) return rc;
     if (read_ahead) read_ahead->launched(), read_ahead->launched();
     ProjCall c1 = {w.n, C, M, C, F, &p1, w.t1, {w.g, F, 0, nullptr, 0, false, F}};
@@ -911,7 +911,8 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
         sw = StackWs();
         return carve_stack(w, sw, Bn, T, C, Tc, rmax, small);
     };
-    SD_REQUIRE(ws && (carve(false) || carve(true)), SD_EWORKSPACE, "spatial_transformer: workspace of %zu bytes, need %zu (%zu at the least, with attention tiles uncut)", ws_bytes,
+    const bool room = ws && carve(false);     // (a smaller workspace keeps the launches it was sized for)
+    SD_REQUIRE(room || (ws && carve(true)), SD_EWORKSPACE, "spatial_transformer: workspace of %zu bytes, need %zu (%zu at the least, with attention tiles uncut)", ws_bytes,
                stack_bytes(Bn, T, C, Tc, rmax, false), stack_bytes(Bn, T, C, Tc, rmax, true));
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int M = Bn * T;
@@ -961,13 +962,22 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
         std::vector<ProjCall> ahead, riders;
         if (!early[i]) ahead = text_calls(b);
         if (early[i + 1]) riders = text_calls(p->blocks[i + 1]);
-        if ((rc = attn_sublayer(sw.h, sw.h, 1, nullptr, 0, 0, b.ln1_g, b.ln1_b, 1e-5f, b.q1, b.k1, b.v1, b.o1, Bn, T, C, heads, sw.a, s, &ahead, false, &sw.dep, read_ahead)))
+        const bool chain = room && chain_takes(Bn, T, C, Tc, b.o1, b.q2, b.o2);
+        if ((rc = attn_sublayer(sw.h, sw.h, 1, nullptr, 0, 0, b.ln1_g, b.ln1_b, 1e-5f, b.q1, b.k1, b.v1, b.o1, Bn, T, C, heads, sw.a, s, &ahead, false, &sw.dep, read_ahead, !chain)))
             return rc;
-        if ((rc = attn_sublayer(sw.h, sw.h, 1, ctx, Tc, Dc, b.ln2_g, b.ln2_b, 1e-5f, b.q2, b.k2, b.v2, b.o2, Bn, T, C, heads, sw.a, s, nullptr, true, &sw.dep, read_ahead)))
+        if (chain) {
+            if (read_ahead)
+                for (int l = 0; l < 3; ++l) read_ahead->launched();
+            const ChainCall c = {sw.a.a, sw.h, sw.f.n, sw.a.k2, sw.a.vt2, &b.o1, &b.q2, &b.o2, b.ln2_g, b.ln2_b, b.ln3_g, b.ln3_b, 1e-5f, Bn, T, C, Tc, b.k2.bias == nullptr};
+            timing_mark(SD_TIMING_CHAIN, 0, s);
+            rc = launch_chain(c, s, read_ahead);
+            timing_mark(SD_TIMING_CHAIN, 1, s);
+            if (rc) return rc;
+        } else if ((rc = attn_sublayer(sw.h, sw.h, 1, ctx, Tc, Dc, b.ln2_g, b.ln2_b, 1e-5f, b.q2, b.k2, b.v2, b.o2, Bn, T, C, heads, sw.a, s, nullptr, true, &sw.dep, read_ahead)))
             return rc;
         // the last block hands its output to proj_out as bf16 directly
         if ((rc = ff_sublayer(sw.h, sw.h, 1, b.ln3_g, b.ln3_b, 1e-5f, b.ff1, b.ff2, M, C, 4 * C, sw.f, s, &sw.dep,
-                              i == p->depth - 1 ? sw.g : nullptr, read_ahead, early[i + 1] ? &riders : nullptr)))
+                              i == p->depth - 1 ? sw.g : nullptr, read_ahead, early[i + 1] ? &riders : nullptr, chain)))
             return rc;
     }
     // proj_out + input residual, bf16 out

@@ -225,4 +225,18 @@ int launch_attention_merge(const void* scratch, uint16_t* out, int64_t ldo, int 
 constexpr float ATTN_KSCALE = 0.125f * 1.44269504088896340736f;
 size_t attention_scratch_bytes(int Bn, int Tq, int Tk, int heads, bool block);
 
+// From self-attention's output to the feed-forward's input: output projection + residual, LayerNorm, cross-attention over text keys
+// that have been computed, its output projection + residual, LayerNorm (chain.hip).  h is the fp32 stream, before and after.
+struct ChainCall {
+    const uint16_t* a; float* h; uint16_t* n;
+    const uint16_t *k, *vt;
+    const sd_proj *o1, *q2, *o2;
+    const uint16_t *g2, *b2, *g3, *b3;
+    float eps;
+    int Bn, T, C, Tc;
+    bool k_prescaled;
+};
+bool chain_takes(int Bn, int T, int C, int Tc, const sd_proj& o1, const sd_proj& q2, const sd_proj& o2);
+int launch_chain(const ChainCall& c, hipStream_t stream, ReadAhead* ahead = nullptr);
+
 }  // namespace sd
