@@ -12,7 +12,7 @@
 //
 // Wavefront w owns columns 64 w .. 64 w + 63 of every product, which are also attention head w: the query it computes is the one
 // it needs, and the output it computes is its part of the next operand.  What it needs of the weights nobody else does, so
-// each wavefront has a ring of its own in LDS, fed in order of use without barriers and over the products' edges.  Barriers
+// each wavefront has a slot of its own in LDS, fed in order of use without barriers and over the products' edges.  Barriers
 // remain where rows change hands: one to see t = x A^T, one before and one after the operand tile is rewritten, one per LayerNorm.
 #include "gemm_dma.hpp"
 #include "read_ahead.hpp"

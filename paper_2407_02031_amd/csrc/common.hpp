@@ -183,6 +183,8 @@ inline bool gemm_one_round(long tiles, long producers) { return (tiles + 7) / 8 
 // The same for groups that gemm16_takes: plain projections with the adapter in the tile.
 bool gemm16_takes(const GemmGroup& g);
 int launch_gemm16(GemmGroup& g, hipStream_t stream);
+// ... of few rows (gemm_thin.hip; which of its tiles: launch_gemm16's rule)
+int launch_gemm_thin(GemmGroup& g, int size, hipStream_t stream);
 // t = scale * x A^T (x [M, K], A [r, K], t bf16 [M, r]) by itself, in the time of a short launch; K % 64 == 0
 int launch_down(const uint16_t* x, int64_t ldx, const uint16_t* A, float scale, uint16_t* t, int M, int K, int r, hipStream_t stream);
 // Tiles of a feed-forward in-projection [M, K] -> [M, F] with an adapter of rank r (0: none): rows x output columns.

@@ -467,8 +467,15 @@ static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
 // 14.7 / 10.9, + 64 14.0 / 14.8; 2048x1280x5120 + 32 38.0 / 38.5, + 64 38.8 / 43.8; 4100x640x640 (132 tiles) 11.5 / 14.6, + 16 15.1 / 16.9;
 // 6100x640x640 (192) 13.5 / 15.8, + 16 18.4 / 17.7; 8100x640x2560 (256) 36.4 / 32.5, + 16 39.8 / 36.5; the q, k, v and text key / value
 // group of 988 tokens of 1280 channels + 16 37.6 / 27.6, of 2 x 256 of 320 + 8 20.4 / 13.9 (values stored transposed).
+//   Fewer rows than that: gemm_thin's tiles, the smallest that are one round.  us, here (or the general kernel) / there: 154x1280x2048 9.6 / 5.2, + 8 11.3 / 6.2,
+// + 64 14.2 / 8.9; 77x1280x1280 + 32 10.0 / 5.5; 512x320x320 + 8 5.6 / 4.1, x1280 7.5 / 4.4; 32x64: 308x1280x2048 9.8 / 6.9, 1000x320x320 + 8 5.7 / 4.6;
+// 64x64, where the K loop is long: 500x1280x5120 21.4 / 19.5, 1000x640x2560 + 16 13.7 / 13.1, 2000x320x1280 7.8 / 7.2 (1000x640x640 + 16 6.9 / 7.0).
+// They have whole tiles of columns only, and a bias only with a residual, as the layers of a stack do.
+constexpr int THIN_32x32 = 4, THIN_32x64 = 5, THIN_64x64 = 6;
 static int tile16(const GemmGroup& g) {
     long big = 0, mid = 0, small = 0, general = 0, lead = 0;   // tiles; of the general kernel: 128x128, and its producers'
+    long thin[3] = {0, 0, 0};                                  // gemm_thin's: 32x32, 32x64, 64x64 (64x32 above rank 32)
+    bool thin_ok = true;
     int rmax = 0, kmax = 0, nmax = 0;
     for (int i = 0; i < g.n; ++i) {
         const GemmProblem& P = g.p[i];
@@ -481,9 +488,18 @@ static int tile16(const GemmGroup& g) {
         small += (long)((P.Mp + 63) / 64) * ((P.N + 79) / 80);
         general += (long)((P.Mp + 127) / 128) * ((P.N + 127) / 128);
         lead += (long)((P.Mp + 127) / 128) * ((P.K1 + 63) / 64);
+        for (int i = 0; i < 2; ++i) thin[i] += (long)((P.Mp + 31) / 32) * (P.N / (32 << i));
+        thin[2] += (long)((P.Mp + 63) / 64) * P.N;             // (columns: how many a tile has is up to the largest rank)
+        thin_ok = thin_ok && P.N % 64 == 0 && (!P.bias || P.res);
         rmax = P.K1 > rmax ? P.K1 : rmax;
         kmax = P.K0 > kmax ? P.K0 : kmax;
         nmax = P.N > nmax ? P.N : nmax;
+    }
+    thin[2] /= rmax > 32 ? 32 : 64;
+    if (thin_ok && kmax >= 320) {
+        if (thin[0] <= 256) return THIN_32x32;
+        if (thin[1] <= 256 && rmax <= 32) return THIN_32x64;
+        if (thin[2] <= 256 && (rmax > 32 || kmax >= 1024)) return THIN_64x64;
     }
     const int tile = big <= 256 && big > 128 ? 3 : mid <= 256 && mid > 128 ? 2 : small <= 256 ? 1 : 0;
     if (rmax > 32 && kmax > 640 && !(nmax <= 320 && tile > 1)) return 0;
@@ -498,7 +514,11 @@ int launch_gemm16(GemmGroup& g, hipStream_t stream) {
         rmax = g.p[i].K1 > rmax ? g.p[i].K1 : rmax;
         kmax = g.p[i].K0 > kmax ? g.p[i].K0 : kmax;
     }
-    switch (tile16(g)) {
+    const int tile = tile16(g);
+    switch (tile) {
+    case THIN_32x32:
+    case THIN_32x64:
+    case THIN_64x64: return launch_gemm_thin(g, tile - THIN_32x32, stream);
     case 3: return launch16r<128, 160, 4, 2, 1>(g, rmax, stream);
     case 2: return launch16r<64, 160, 2, 2, 2>(g, rmax, stream);
     // One workgroup of four wavefronts per CU: the two stages that three leave in flight (37 KB) come in at 54 GB/s, the latency of

@@ -924,6 +924,48 @@ def test_deep_stack_reads_weights_ahead(B, Bn, T, C, depth):
         assert torch.equal(B.spatial_transformer_fwd(x, ctx, sp, cfg.heads), y)
 
 
+# few rows: K split over eight wavefronts (fewer slices than wavefronts, uneven shares, one and two stages in flight), tiles of 32x32, 32x64, 64x64
+# and 64x32, rows cut off, ranks that fill one block of A, two, four and none whole; no bias, or one with a residual
+@pytest.mark.parametrize("M,K,N,rank,res,kernel", [
+    (1, 320, 64, 8, "", "thin 32x32/1"), (33, 384, 320, 0, "f32", "thin 32x32/0"), (154, 2048, 1280, 64, "", "thin 32x32/4"), (250, 1088, 640, 40, "bf16", "thin 32x32/4"), (77, 576, 128, 32, "f32", "thin 32x32/2"),
+    (300, 1280, 1280, 16, "", "thin 32x64/1"), (1000, 320, 320, 24, "bf16", "thin 32x64/2"), (309, 1024, 1280, 0, "", "thin 32x64/0"),
+    (1000, 2560, 640, 16, "f32", "thin 64x64/1"), (499, 1280, 1280, 32, "", "thin 64x64/2"), (1990, 1088, 320, 0, "f32", "thin 64x64/0"), (305, 640, 1280, 64, "f32", "thin 64x32/4"),
+])
+def test_lora_linear_few_rows(B, M, K, N, rank, res, kernel):
+    import torch
+    r = rng(M + K + N + rank)
+    p = mkproj(r, N, K, rank, bias=bool(res), scale=0.7)
+    x = G.bf16_round(r.standard_normal((M, K)).astype(np.float32))
+    rs = G.bf16_round(r.standard_normal((M, N)).astype(np.float32))
+    rd = None if not res else torch.from_numpy(rs).cuda() if res == "f32" else torch.from_numpy(rs).cuda().bfloat16()
+    call = lambda: B.lora_linear_fwd(dev(x, B), B.Proj.from_numpy(p), residual=rd, out_dtype=torch.float32 if res == "f32" else torch.bfloat16)
+    with B.dry_run() as names:
+        call()
+    assert names[-1] == kernel
+    ref = O.lora_linear(x, p["W"], p["b"], p["A"], p["B"], p["scale"])
+    got = host(call()) - (rs if res else 0)
+    # (a bf16 sum is rounded once more: half a unit in the last of 8 bits of it)
+    allow = 2.0 ** -9 * (np.abs(ref).max() + np.abs(rs).max()) if res == "bf16" else 0
+    assert np.abs(got - ref).max() <= BF16_TOL * np.abs(ref).max() + allow
+
+
+def test_attn_block_few_rows(B):
+    """q, keys and values (stored transposed) of one group, cut-off rows, an adapter on the keys only."""
+    import torch
+    r = rng(77)
+    Bn, T, C, Tc, Dc = 2, 77, 128, 21, 320
+    h = r.standard_normal((Bn, T, C)).astype(np.float32)
+    ctx = G.bf16_round(r.standard_normal((Bn, Tc, Dc)).astype(np.float32))
+    g, b = np.ones(C, np.float32), np.zeros(C, np.float32)
+    projs = [mkproj(r, C, C, 0, bias=False), mkproj(r, C, Dc, 40, bias=False, scale=0.1), mkproj(r, C, Dc, 0, bias=False), mkproj(r, C, C, 8, scale=0.5)]
+    args = (torch.from_numpy(h).cuda(), dev(ctx, B), dev(g, B), dev(b, B), *[B.Proj.from_numpy(p) for p in projs], C // 64)
+    with B.dry_run() as names:
+        B.attn_block_fwd(*args)
+    assert "thin 32x32/4" in names
+    got = host(B.attn_block_fwd(*args))
+    assert rel_err(got - h, O.attn_sublayer(h, ctx, g, b, *projs, C // 64) - h) <= BF16_TOL
+
+
 # from self-attention's output to the feed-forward's input in one launch: blocks of 32 rows cut off at each row count, text keys about the ends
 # of the 64 and 16 that are fetched together and of groups of eight, ranks about those of the tiles of A and of the steps of B (none, less than a
 # tile, beside each other), biased projections (keys that are not scaled ahead).  640 channels take it from 90 blocks on, and in several rounds whose last is full.
