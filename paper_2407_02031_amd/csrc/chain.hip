@@ -571,11 +571,12 @@ __global__ __launch_bounds__(64 * HEADS, 3) void chain_kernel(const ChainArgs g,
 // their time by the row.  us of a one-block stack, launches / chain, by blocks of rows: 32 113 / 123, 63 141 / 147, 94 190 / 188 (+ 64 200 / 194),
 // 126 196 / 192 (208 / 198), 164 250 / 238, 208 293 / 277 (310 / 287), 256 333 / 315 (348 / 325); in a second round, 288 351 / 364 (379 / 387),
 // 512 653 / 646 (686 / 670).  So: one round that is a third full, or several whose last is nearly full.  Of 320 channels two workgroups
-// share a CU: 16 82.8 / 81.1, 126 + 64 143 / 131, 256 205 / 187, 376 263 / 257, 512 + 64 309 / 304.
+// share a CU; 16 + 8 69.0 / 71.0, 26 + 8 74.7 / 78.6, 38 + 8 88.1 / 88.9, + 64 96 / 92, 64 + 8 104 / 99, 126 + 8 134 / 125, 256 205 / 187, 376 263 / 257,
+// 512 + 64 309 / 304.
 bool chain_takes(int Bn, int T, int C, int Tc, const sd_proj& o1, const sd_proj& q2, const sd_proj& o2) {
     if (Tc > CHAIN_KEYS || o1.r > CHAIN_RANK || q2.r > CHAIN_RANK || o2.r > CHAIN_RANK || Bn > 65535) return false;
     const long blocks = (long)Bn * ((T + CHAIN_ROWS - 1) / CHAIN_ROWS), rounds = (blocks + 255) / 256;
-    if (C == 320) return true;
+    if (C == 320) return blocks >= 38;
     return C == 640 && (rounds == 1 ? blocks >= 90 : blocks >= 256 * rounds - 24);
 }
 

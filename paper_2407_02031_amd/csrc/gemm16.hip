@@ -470,7 +470,7 @@ static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
 //   Fewer rows than that: gemm_thin's tiles, the smallest that are one round.  us, here (or the general kernel) / there: 154x1280x2048 9.6 / 5.2, + 8 11.3 / 6.2,
 // + 64 14.2 / 8.9; 77x1280x1280 + 32 10.0 / 5.5; 512x320x320 + 8 5.6 / 4.1, x1280 7.5 / 4.4; 32x64: 308x1280x2048 9.8 / 6.9, 1000x320x320 + 8 5.7 / 4.6;
 // 64x64, where the K loop is long: 500x1280x5120 21.4 / 19.5, 1000x640x2560 + 16 13.7 / 13.1, 2000x320x1280 7.8 / 7.2 (1000x640x640 + 16 6.9 / 7.0).
-// They have whole tiles of columns only, and a bias only with a residual, as the layers of a stack do.
+// They have whole tiles of columns only, and a bias only with a residual or an fp32 result, as the layers of a stack do.
 constexpr int THIN_32x32 = 4, THIN_32x64 = 5, THIN_64x64 = 6;
 static int tile16(const GemmGroup& g) {
     long big = 0, mid = 0, small = 0, general = 0, lead = 0;   // tiles; of the general kernel: 128x128, and its producers'
@@ -490,7 +490,7 @@ static int tile16(const GemmGroup& g) {
         lead += (long)((P.Mp + 127) / 128) * ((P.K1 + 63) / 64);
         for (int i = 0; i < 2; ++i) thin[i] += (long)((P.Mp + 31) / 32) * (P.N / (32 << i));
         thin[2] += (long)((P.Mp + 63) / 64) * P.N;             // (columns: how many a tile has is up to the largest rank)
-        thin_ok = thin_ok && P.N % 64 == 0 && (!P.bias || P.res);
+        thin_ok = thin_ok && P.N % 64 == 0 && (!P.bias || P.res || P.y_f32);
         rmax = P.K1 > rmax ? P.K1 : rmax;
         kmax = P.K0 > kmax ? P.K0 : kmax;
         nmax = P.N > nmax ? P.N : nmax;
