@@ -1,5 +1,5 @@
 // What launches behind this one will read (their weights), brought into the last-level cache by workgroups of 256 threads behind
-// the launch's own: each reads LOADS * 4 KB of the ranges, taken as one string of bytes, all of it in flight at once,
+// the launch's own (in the chain by its own workgroups, when they are done): each reads LOADS * 4 KB of the ranges, taken as one string of bytes, all of it in flight at once,
 // and uses nothing.  (Loads with the non-temporal hint are not kept in that cache.)
 //
 // A deep stack's weights do not stay in the last-level cache from block to block, and a projection of one round of tiles has
