@@ -280,7 +280,10 @@ __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_partial_kernel(const
 
 // SILU: y = n * sigmoid(n) on the normalised value, the GroupNorm + SiLU pair of the base model's
 // ResNet blocks as one operator (Section 4.3, "Kernel-level optimizations")
-template <int VEC, bool SILU>
+// EARLY: what the statistics and the affine need is requested ahead of the rows.  Loads come back in the order they are issued in: behind the rows of
+// large inputs they take as long as those do (us with SiLU, inputs in turn from HBM, behind / ahead: 4 x 16384 x 320 30.9 / 28.7, 1 x 16384 x 1280 33.8 /
+// 31.9, 2 x 16384 x 320 19.3 / 18.8, 4 x 1200 x 960 12.2 / 11.9; where a workgroup has few slabs the rows want to be first: 2 x 4096 x 320 10.2 / 10.4).
+template <int VEC, bool SILU, bool EARLY>
 __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_apply_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ y,
                                                                            const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
                                                                            const float* __restrict__ partials, int T, int C, int groups, int nchunks,
@@ -293,35 +296,46 @@ __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_apply_kernel(const u
     const int row = tid / nv, cv = tid - row * nv;
     const uint16_t* xb = x + (size_t)b * T * C;
     uint16_t* yb = y + (size_t)b * T * C;
-    // this thread's inputs first: they are in flight while the statistics are put together
     const int t0 = blockIdx.x * rows * iters + row;
     const int t1 = min(T, (blockIdx.x + 1) * rows * iters);
     const bool mine = row < rows;
-    vec v[GN_ITERS];
-#pragma unroll
-    for (int k = 0; k < GN_ITERS; ++k)
-        if (mine && t0 + k * rows < t1) v[k] = reinterpret_cast<const vec*>(xb + (size_t)(t0 + k * rows) * C)[cv];
     // ---- statistics of the sample's groups.  A group's chunks are summed in `parts` contiguous runs
     // by as many threads, and the runs then in run order: a fixed order for a given shape
     const float2* src = reinterpret_cast<const float2*>(partials) + (size_t)b * nchunks * groups;
     float2* sub = reinterpret_cast<float2*>(sh);
-    const int run = (nchunks + parts - 1) / parts;
-    for (int i = tid; i < parts * groups; i += blockDim.x) {
-        const int g = i % groups, part = i / groups;
-        float a1 = 0.f, a2 = 0.f;
-        const int c1 = min(nchunks, (part + 1) * run);
-        for (int c = part * run; c < c1; c += GN_RUN) {
-            float2 q[GN_RUN];
+    const int run = (nchunks + parts - 1) / parts, sums = parts * groups;
+    float2 q[GN_RUN];
+    auto fetch = [&](int i, int c) {      // run i's partials from its c-th on, all in flight together
+        const int part = i / groups, last = min(nchunks, (part + 1) * run) - 1;
 #pragma unroll
-            for (int k = 0; k < GN_RUN; ++k) q[k] = src[(size_t)min(c + k, c1 - 1) * groups + g];    // all in flight together
+        for (int k = 0; k < GN_RUN; ++k) q[k] = src[(size_t)max(min(part * run + c + k, last), 0) * groups + (i - part * groups)];
+    };
+    float shift = 0.f;
+    vec gv, bv;
+    if (EARLY) {
+        fetch(min(tid, sums - 1), 0);
+        shift = bf16_to_f32(xb[min(tid, groups - 1) * cpg]);
+        gv = reinterpret_cast<const vec*>(gamma)[mine ? cv : 0];
+        bv = reinterpret_cast<const vec*>(beta)[mine ? cv : 0];
+    }
+    // this thread's inputs: they are in flight while the statistics are put together
+    vec v[GN_ITERS];
+#pragma unroll
+    for (int k = 0; k < GN_ITERS; ++k)
+        if (mine && t0 + k * rows < t1) v[k] = reinterpret_cast<const vec*>(xb + (size_t)(t0 + k * rows) * C)[cv];
+    for (int i = tid; i < sums; i += blockDim.x) {
+        float a1 = 0.f, a2 = 0.f;
+        const int n = min(nchunks, (i / groups + 1) * run) - i / groups * run;
+        for (int c = 0; c < n; c += GN_RUN) {
+            if (!EARLY || i != tid || c) fetch(i, c);
 #pragma unroll
             for (int k = 0; k < GN_RUN; ++k)
-                if (c + k < c1) { a1 += q[k].x; a2 += q[k].y; }
+                if (c + k < n) { a1 += q[k].x; a2 += q[k].y; }
         }
         sub[i] = make_float2(a1, a2);
     }
     __syncthreads();
-    float2* stat = sub + parts * groups;
+    float2* stat = sub + sums;
     for (int g = tid; g < groups; g += blockDim.x) {
         float a1 = 0.f, a2 = 0.f;
 #pragma unroll 4
@@ -332,12 +346,15 @@ __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_apply_kernel(const u
         const float n = (float)T * (float)cpg;
         const float m1 = a1 / n;
         const float var = fmaxf(a2 / n - m1 * m1, 0.f);
-        stat[g] = make_float2(bf16_to_f32(xb[g * cpg]) + m1, rsqrtf(var + eps));
+        stat[g] = make_float2((EARLY && g == tid ? shift : bf16_to_f32(xb[g * cpg])) + m1, rsqrtf(var + eps));
     }
     __syncthreads();
     if (!mine) return;
     float mean[NP], g0[NP], g1[NP], b0[NP], b1[NP];
-    const vec gv = reinterpret_cast<const vec*>(gamma)[cv], bv = reinterpret_cast<const vec*>(beta)[cv];
+    if (!EARLY) {
+        gv = reinterpret_cast<const vec*>(gamma)[cv];
+        bv = reinterpret_cast<const vec*>(beta)[cv];
+    }
     int g = cv * VEC / cpg;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
@@ -547,10 +564,15 @@ static int launch_gn(const uint16_t* x, uint16_t* y, const uint16_t* gamma, cons
     const int64_t slabs = (int64_t)Bn * ((T + rows - 1) / rows);
     const int iters = (int)std::min<int64_t>(GN_ITERS, std::max<int64_t>(1, slabs / GN_APPLY_WGS));
     const dim3 grid((T + rows * iters - 1) / (rows * iters), Bn);
-    if (silu)
-        hipLaunchKernelGGL((groupnorm_apply_kernel<VEC, true>), grid, dim3(athreads), lds, stream, x, y, gamma, beta, partials, T, C, groups, nchunks, parts, rows, iters, eps);
-    else
-        hipLaunchKernelGGL((groupnorm_apply_kernel<VEC, false>), grid, dim3(athreads), lds, stream, x, y, gamma, beta, partials, T, C, groups, nchunks, parts, rows, iters, eps);
+    auto apply = [&](auto with_silu, auto early) {
+        hipLaunchKernelGGL((groupnorm_apply_kernel<VEC, decltype(with_silu)::value, decltype(early)::value>), grid, dim3(athreads), lds, stream, x, y, gamma, beta, partials, T, C, groups,
+                           nchunks, parts, rows, iters, eps);
+    };
+    const bool early = iters == GN_ITERS;
+    if (silu && early) apply(std::true_type(), std::true_type());
+    else if (silu) apply(std::true_type(), std::false_type());
+    else if (early) apply(std::false_type(), std::true_type());
+    else apply(std::false_type(), std::false_type());
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }

@@ -812,6 +812,17 @@ def test_groupnorm_partial_batches_match_oracle(B, Bn, T, C, groups):
     assert np.abs(got - ref).mean() <= 2e-3 * np.abs(ref).mean() * 2       # bf16 rounds by 2^-9 at most, a wrong statistic moves everything
 
 
+# inputs of as many slabs as take all six to a workgroup, where the statistics and the affine are requested ahead of the rows: more groups than
+# threads, fewer channels than a 16-byte piece to a group, channels off eight, the last slab cut off, and one row short of that many slabs
+@pytest.mark.parametrize("Bn,T,C,groups", [(1, 2043, 2048, 1024), (2, 1201, 1280, 32), (1, 12000, 100, 10), (4, 3100, 320, 32), (2, 12239, 320, 160), (1, 12228, 320, 32)])
+def test_groupnorm_large_matches_oracle(B, Bn, T, C, groups):
+    r = rng(T + C)
+    x = G.bf16_round((r.standard_normal((Bn, T, C)) + 3.0 * r.standard_normal((Bn, 1, C))).astype(np.float32))
+    g, b = G.bf16_round((1 + 0.1 * r.standard_normal(C)).astype(np.float32)), G.bf16_round((0.1 * r.standard_normal(C)).astype(np.float32))
+    for call, ref in ((B.groupnorm_fwd, O.groupnorm), (B.groupnorm_silu_fwd, O.groupnorm_silu)):
+        assert rel_err(host(call(dev(x, B), dev(g, B), dev(b, B), groups=groups)), ref(x, g, b, groups=groups)) <= BF16_TOL
+
+
 # samples of one launch: a thread holds one row, two, three, four and, one token later, two launches; units of one group, two and
 # four; pieces of a row of 64 bytes and of a whole row; a batch just too large
 @pytest.mark.parametrize("Bn,T,C,groups,unit", [(1, 1, 320, 32, 1), (2, 204, 320, 32, 1), (2, 205, 640, 32, 1), (1, 408, 1280, 32, 1), (3, 409, 320, 32, 1), (1, 816, 640, 32, 1),
