@@ -418,7 +418,8 @@ __global__ __launch_bounds__(64 * HEADS, 3) void chain_kernel(const ChainArgs g,
                     for (int e = 0; e < 4; ++e) qf[mi][ni >> 1][(ni & 1) * 4 + e] = (__bf16)(acc[mi][ni][e] + b[e]);
                 }
             {
-                // scores: lane lr is the row, its keys are kt * 16 + qd * 4 + e.  Keys past the last one start far below any score
+                // scores: lane lr is the row, its keys are kt * 16 + qd * 4 + e.  Keys past the last one, which are that one again, start at
+                // -inf and stay there (a finite start is lost in the rounding of scores of 1e37 and above; where the product is inf or NaN, so is a real key's)
                 f32x4 s[2][5];
                 auto key_frag = [&](const u32x4* rows, int kk) {     // 16 keys, rows of 128 bytes
                     const u32x2* const k8 = reinterpret_cast<const u32x2*>(rows + lr * 8);
@@ -438,7 +439,7 @@ __global__ __launch_bounds__(64 * HEADS, 3) void chain_kernel(const ChainArgs g,
 #pragma unroll
                     for (int kt = 0; kt < 5; ++kt)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) s[0][kt][e] = s[1][kt][e] = kt * 16 + e < g.Tc - qd * 4 ? 0.f : -1.0e30f;
+                        for (int e = 0; e < 4; ++e) s[0][kt][e] = s[1][kt][e] = kt * 16 + e < g.Tc - qd * 4 ? 0.f : -INFINITY;
 #pragma unroll
                     for (int kk = 0; kk < 2; ++kk)
 #pragma unroll

@@ -1009,6 +1009,33 @@ def test_stack_chain(B, Bn, T, C, Tc, rank, bias):
     assert torch.equal(last[0], y[-1]) and torch.equal(last[-1], y[-1])
 
 
+# scores beside which any finite mask is lost in rounding (6e37), equal for all text tokens: keys that are no tokens must not count.  The keys' scale
+# applied ahead, or to the scores (keys with a bias)
+@pytest.mark.parametrize("Tc", [1, 9])
+@pytest.mark.parametrize("bias", [False, True])
+def test_stack_chain_large_scores(B, Tc, bias):
+    Bn, T, C = 39, 32, 320
+    cfg = small_cfg(Bn=Bn, T=T, Tc=Tc, C=C, heads=C // 64, r=0, depth=1, w_std=0.03, ctx_std=1.0)
+    p = G.make_stack_inputs(cfg, seed=Tc)
+    q2, k2 = p["blocks"][0]["q2"], p["blocks"][0]["k2"]
+    q2["W"][:] = 0
+    q2["b"] = G.bf16_round(np.full(C, 1e18, np.float32))
+    k2["W"][:] = 0
+    if bias:
+        k2["b"] = q2["b"].copy()
+    else:
+        k2["W"][:, 0] = G.bf16_round(np.full(C, 5e18, np.float32))
+        p["ctx"][:, :, 0] = 1
+    sp = B.StackParams(p)
+    x, ctx = dev(p["x"], B), dev(p["ctx"], B)
+    with B.dry_run() as names:
+        B.spatial_transformer_fwd(x, ctx, sp, cfg.heads)
+    assert "attention of the chain" in names
+    got = host(B.spatial_transformer_fwd(x, ctx, sp, cfg.heads))[:4]
+    ref = O.spatial_transformer(p["x"][:4], p["ctx"][:4], p, cfg.heads)
+    assert rel_err(got - p["x"][:4], ref - p["x"][:4]) <= 2 * BF16_TOL
+
+
 def test_stack_with_biased_q_k_v(B):
     """SDXL's q, k, v carry no bias, but a projection record may: the stack takes them too (the
     text keys / values projected ahead inside the self-attention launches included)."""
