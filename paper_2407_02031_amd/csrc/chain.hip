@@ -571,13 +571,23 @@ __global__ __launch_bounds__(64 * HEADS, 3) void chain_kernel(const ChainArgs g,
 // One workgroup of 640 channels fills a CU and takes 47 us (52 with adapters of rank 64) whatever the others do; the launches it stands for take
 // their time by the row.  us of a one-block stack, launches / chain, by blocks of rows: 32 113 / 123, 63 141 / 147, 94 190 / 188 (+ 64 200 / 194),
 // 126 196 / 192 (208 / 198), 164 250 / 238, 208 293 / 277 (310 / 287), 256 333 / 315 (348 / 325); in a second round, 288 351 / 364 (379 / 387),
-// 512 653 / 646 (686 / 670).  So: one round that is a third full, or several whose last is nearly full.  Of 320 channels two workgroups
-// share a CU; 16 + 8 69.0 / 71.0, 26 + 8 74.7 / 78.6, 38 + 8 88.1 / 88.9, + 64 96 / 92, 64 + 8 104 / 99, 126 + 8 134 / 125, 256 205 / 187, 376 263 / 257,
-// 512 + 64 309 / 304.
+// 512 653 / 646 (686 / 670).  So: one round that is a third full, or several whose last is nearly full.
+//   Of 320 channels two workgroups share a CU, which is a round of 512, and alone on a CU one is faster: up to 256 blocks 16 + 8 69.0 / 71.0,
+// 26 + 8 74.7 / 78.6, 38 + 8 88.1 / 88.9, + 64 96 / 92, 64 + 8 104 / 99, 126 + 8 134 / 125, 256 205 / 187.  Beyond that, without adapter, + 16, + 64, + 128:
+// 264 194 / 196, 216 / 215, 220 / 222, 233 / 234; 304 207 / 205, 232 / 227, 228 / 232, 242 / 240; 344 229 / 216, 246 / 242, 256 / 245, 258 / 262;
+// 368 235 / 219, 252 / 257, 258 / 249, 267 / 266; 440 267 / 249, 283 / 284, 285 / 275, 299 / 291; 480 278 / 261, 296 / 287, 300 / 282, 315 / 301; in a
+// second round 516 281 / 288, 304 / 321, 304 / 320, 330 / 350; 564 325 / 319, 359 / 349, 354 / 353, 369 / 380; 600 341 / 332, 374 / 361,
+// 369 / 364, 388 / 391; 750 474 / 447, 518 / 482, 517 / 493, 537 / 526; 880 520 / 508, 567 / 552, 546 / 543, 575 / 581 (+ 96 593 / 588); in a third,
+// 1030 581 / 586, 636 / 627, 617 / 626, 652 / 674; 1352 833 / 825, 885 / 875, 862 / 875, 907 / 931.
 bool chain_takes(int Bn, int T, int C, int Tc, const sd_proj& o1, const sd_proj& q2, const sd_proj& o2) {
-    if (Tc > CHAIN_KEYS || o1.r > CHAIN_RANK || q2.r > CHAIN_RANK || o2.r > CHAIN_RANK || Bn > 65535) return false;
+    const int rank = std::max(o1.r, std::max(q2.r, o2.r));
+    if (Tc > CHAIN_KEYS || rank > CHAIN_RANK || Bn > 65535) return false;
     const long blocks = (long)Bn * ((T + CHAIN_ROWS - 1) / CHAIN_ROWS), rounds = (blocks + 255) / 256;
-    if (C == 320) return blocks >= 38;
+    if (C == 320) {
+        if (blocks <= 256) return blocks >= 38;
+        if (blocks <= 512) return blocks >= (rank == 0 ? 304 : rank <= 32 ? 448 : 360);
+        return blocks >= 600 && blocks <= 1024 && rank <= 96;
+    }
     return C == 640 && (rounds == 1 ? blocks >= 90 : blocks >= 256 * rounds - 24);
 }
 

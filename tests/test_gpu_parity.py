@@ -979,9 +979,11 @@ def test_attn_block_few_rows(B):
 
 # from self-attention's output to the feed-forward's input in one launch: blocks of 32 rows cut off at each row count, text keys about the ends
 # of the 64 and 16 that are fetched together and of groups of eight, ranks about those of the tiles of A and of the steps of B (none, less than a
-# tile, beside each other), biased projections (keys that are not scaled ahead).  320 channels take it from 38 blocks on, 640 from 90, and in several rounds whose last is full.
+# tile, beside each other), biased projections (keys that are not scaled ahead).  Of 320 channels in
+# one workgroup a CU, two, and a second round; of 640 in one round and in two.
 @pytest.mark.parametrize("Bn,T,C,Tc,rank,bias", [(38, 1, 320, 1, 0, False), (40, 31, 320, 7, 8, False), (39, 32, 320, 64, 40, True), (20, 33, 320, 65, 128, False), (13, 70, 320, 80, 72, False),
-                                                 (90, 5, 640, 77, 64, False), (45, 33, 640, 63, 16, True), (30, 95, 640, 72, 128, False), (500, 33, 640, 77, 0, False), (257, 1, 320, 16, 24, False)])
+                                                 (90, 5, 640, 77, 64, False), (45, 33, 640, 63, 16, True), (30, 95, 640, 72, 128, False), (500, 33, 640, 77, 0, False), (150, 95, 320, 16, 24, False),
+                                                 (208, 95, 320, 7, 8, False)])
 def test_stack_chain(B, Bn, T, C, Tc, rank, bias):
     import torch
     cfg = small_cfg(Bn=Bn, T=T, Tc=Tc, C=C, heads=C // 64, r=rank, alpha=rank / 8, depth=1, w_std=0.03, ctx_std=1.0)
