@@ -982,7 +982,7 @@ def test_attn_block_few_rows(B):
 # tile, beside each other), biased projections (keys that are not scaled ahead).  Of 320 channels in
 # one workgroup a CU, two, and a second round; of 640 in one round and in two.
 @pytest.mark.parametrize("Bn,T,C,Tc,rank,bias", [(38, 1, 320, 1, 0, False), (40, 31, 320, 7, 8, False), (39, 32, 320, 64, 40, True), (20, 33, 320, 65, 128, False), (13, 70, 320, 80, 72, False),
-                                                 (90, 5, 640, 77, 64, False), (45, 33, 640, 63, 16, True), (30, 95, 640, 72, 128, False), (500, 33, 640, 77, 0, False), (150, 95, 320, 16, 24, False),
+                                                 (41, 71, 640, 77, 64, False), (45, 65, 640, 63, 16, True), (31, 95, 640, 72, 128, False), (167, 95, 640, 77, 0, False), (150, 95, 320, 16, 24, False),
                                                  (208, 95, 320, 7, 8, False)])
 def test_stack_chain(B, Bn, T, C, Tc, rank, bias):
     import torch

@@ -151,6 +151,15 @@ def test_chain_of_320_channels_by_rounds(B, Bn, T, none, r16, r64, r128):  # noq
     assert [chain(B, Bn, T, 320, r) for r in (0, 16, 64, 128)] == [bool(none), bool(r16), bool(r64), bool(r128)]
 
 
+# samples whose last blocks are partly empty: by their rows, except where 320 channels have a CU to a workgroup
+@pytest.mark.parametrize("Bn,T,Cc,taken", [
+    (90, 31, 640, 0), (91, 32, 640, 1), (45, 33, 640, 0), (60, 33, 640, 0), (41, 71, 640, 1), (88, 33, 640, 1), (245, 33, 640, 0), (250, 40, 640, 0), (167, 95, 640, 1), (244, 64, 640, 1),
+    (256, 1, 320, 1), (128, 33, 320, 1), (300, 1, 320, 0), (240, 33, 320, 0), (150, 95, 320, 1), (300, 75, 320, 0), (208, 95, 320, 1),
+])
+def test_chain_by_rows(B, Bn, T, Cc, taken):  # noqa: F811
+    assert chain(B, Bn, T, Cc, 16) == bool(taken)
+
+
 # ---- weights read ahead
 def ranges(name):
     return [(int(p, 16), int(n)) for p, n in re.findall(r" ([0-9a-f]+)\+(\d+)", name.split("ahead", 1)[1])] if ", ahead" in name else []
