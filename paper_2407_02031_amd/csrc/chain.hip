@@ -573,7 +573,8 @@ __global__ __launch_bounds__(64 * HEADS, 3) void chain_kernel(const ChainArgs g,
 // 126 196 / 192 (208 / 198), 164 250 / 238, 208 293 / 277 (310 / 287), 256 333 / 315 (348 / 325); in a second round, 288 351 / 364 (379 / 387),
 // 512 653 / 646 (686 / 670).  So: one round that is a third full, or several whose last is nearly full, counted in rows: blocks that samples of odd lengths
 // leave partly empty take as long as full ones (45 x 33 tokens + 16 278 / 286, 60 x 33 222 / 227; two rounds, 245 x 33 + 16 1191 / 1213, 250 x 40 + 128
-// 1326 / 1336, 250 x 57 + 64 1402 / 1380; of 320 channels 180 x 33 + 64 725 / 728, 300 x 8 + 64 1061 / 1072, 300 x 75 + 128 1474 / 1501).
+// 1326 / 1336, 250 x 57 + 64 1402 / 1380; of 320 channels 180 x 33 + 64 725 / 728, 300 x 8 + 64 1061 / 1072, 300 x 75 + 128 1474 / 1501).  Without adapters
+// the launches are in-tile projections of one round, and the line is later: 1 x 2880 183 / 187, 30 x 75 185 / 188, 60 x 48 253 / 255, 1 x 3264 208 / 204.
 //   Of 320 channels two workgroups share a CU, which is a round of 512, and alone on a CU one is faster: up to 256 blocks 16 + 8 69.0 / 71.0,
 // 26 + 8 74.7 / 78.6, 38 + 8 88.1 / 88.9, + 64 96 / 92, 64 + 8 104 / 99, 126 + 8 134 / 125, 256 205 / 187.  Beyond that, without adapter, + 16, + 64, + 128:
 // 264 194 / 196, 216 / 215, 220 / 222, 233 / 234; 304 207 / 205, 232 / 227, 228 / 232, 242 / 240; 344 229 / 216, 246 / 242, 256 / 245, 258 / 262;
@@ -592,7 +593,7 @@ bool chain_takes(int Bn, int T, int C, int Tc, const sd_proj& o1, const sd_proj&
         if (blocks <= 512) return blocks >= (rank == 0 ? 304 : rank <= 32 ? 448 : 360);
         return blocks >= 600 && blocks <= 1024 && rank <= 96;
     }
-    return C == 640 && (rounds == 1 ? rows >= 2880 : full && blocks >= 256 * rounds - 24);
+    return C == 640 && (rounds == 1 ? rows >= (rank == 0 ? 3264 : 2880) : full && blocks >= 256 * rounds - 24);
 }
 
 int launch_chain(const ChainCall& c, hipStream_t stream, ReadAhead* ahead) {

@@ -160,6 +160,12 @@ def test_chain_by_rows(B, Bn, T, Cc, taken):  # noqa: F811
     assert chain(B, Bn, T, Cc, 16) == bool(taken)
 
 
+# 640 channels: from 2880 rows on with adapters on any of the three projections, without from 3264
+@pytest.mark.parametrize("Bn,T,r,taken", [(1, 2879, 8, 0), (1, 2880, 8, 1), (1, 2880, 0, 0), (30, 97, 0, 0), (60, 48, 0, 0), (1, 3263, 0, 0), (1, 3264, 0, 1), (2, 3952, 0, 1)])
+def test_chain_of_640_channels_from(B, Bn, T, r, taken):  # noqa: F811
+    assert chain(B, Bn, T, 640, r) == bool(taken)
+
+
 # ---- weights read ahead
 def ranges(name):
     return [(int(p, 16), int(n)) for p, n in re.findall(r" ([0-9a-f]+)\+(\d+)", name.split("ahead", 1)[1])] if ", ahead" in name else []
