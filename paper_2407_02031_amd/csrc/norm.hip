@@ -199,6 +199,7 @@ constexpr int GN_TARGET_WGS = 256;   // partial-sum workgroups of a launch, one 
 constexpr int GN_MAX_PCHUNKS = 128;  // ... of a sample at most this many, ...
 constexpr int GN_PSLABS = 4;         // ... and fewer rather than with fewer slabs
 constexpr int GN_APPLY_WGS = 170;    // apply workgroups take more than one slab while this many are left (256: up to 8 % slower at 1 to 6 M elements)
+constexpr int GN_EARLY_WGS = 600;    // second pass without SiLU: statistics requested ahead of the rows up to so many workgroups (groupnorm_apply_kernel)
 constexpr int GN_RUN = 8;            // partials that a thread fetches together
 
 template <int VEC>
@@ -283,6 +284,9 @@ __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_partial_kernel(const
 // EARLY: what the statistics and the affine need is requested ahead of the rows.  Loads come back in the order they are issued in: behind the rows of
 // large inputs they take as long as those do (us with SiLU, inputs in turn from HBM, behind / ahead: 4 x 16384 x 320 30.9 / 28.7, 1 x 16384 x 1280 33.8 /
 // 31.9, 2 x 16384 x 320 19.3 / 18.8, 4 x 1200 x 960 12.2 / 11.9; where a workgroup has few slabs the rows want to be first: 2 x 4096 x 320 10.2 / 10.4).
+// Not without SiLU's arithmetic between loads and stores where workgroups follow each other on a CU (2 x 16384 x 320, 456 of them, 16.0 / 15.5; 1 x 43000 x 320,
+// 598, 20.9 / 19.5; 9 x 1200 x 1280, 603, 19.7 / 19.8; 4 x 6200 x 640, 692, 20.3 / 20.8; 4 x 16384 x 320, 911, 24.3 / 25.3; 16 x 1024 x 1280, 912, 25.0 / 26.5),
+// nor where a thread has 4 bytes of a row, six requests for eight or more ahead of them (1 x 12000 x 100 8.1 / 8.3, 8 x 3000 x 1220 45.2 / 48.0, with SiLU 8.5 / 8.6, 50.6 / 53.3).
 template <int VEC, bool SILU, bool EARLY>
 __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_apply_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ y,
                                                                            const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
@@ -546,15 +550,11 @@ static int launch_gn(const uint16_t* x, uint16_t* y, const uint16_t* gamma, cons
     // partial sums
     int want = (GN_TARGET_WGS + Bn - 1) / Bn;
     if (want > GN_MAX_PCHUNKS) want = GN_MAX_PCHUNKS;
-    int rows;
+    int prows, rows;
     const int most = nv > GN_THREADS ? GN_MAX_THREADS : GN_THREADS;
     const int pchunk = std::max((T + want - 1) / want, GN_PSLABS * (most / nv));   // short samples: a few slabs rather than more partials
-    const int pthreads = shape(most, pchunk, &rows);
+    const int pthreads = shape(most, pchunk, &prows);
     const int nchunks = (T + pchunk - 1) / pchunk;
-    SD_REQUIRE(pthreads <= GN_MAX_THREADS, SD_EUNSUPPORTED, "groupnorm: C=%d", C);
-    hipLaunchKernelGGL((groupnorm_partial_kernel<VEC>), dim3(nchunks, Bn), dim3(pthreads), (size_t)rows * C * sizeof(float), stream, x, partials, T, C,
-                       groups, nchunks, pchunk, rows);
-    SD_HIP_CHECK(hipGetLastError());
     const int athreads = shape(most, T, &rows);
     int parts = athreads / groups;
     if (parts > (nchunks + GN_RUN - 1) / GN_RUN) parts = (nchunks + GN_RUN - 1) / GN_RUN;
@@ -564,14 +564,20 @@ static int launch_gn(const uint16_t* x, uint16_t* y, const uint16_t* gamma, cons
     const int64_t slabs = (int64_t)Bn * ((T + rows - 1) / rows);
     const int iters = (int)std::min<int64_t>(GN_ITERS, std::max<int64_t>(1, slabs / GN_APPLY_WGS));
     const dim3 grid((T + rows * iters - 1) / (rows * iters), Bn);
+    const bool early = VEC == 8 && iters == GN_ITERS && (silu || (int64_t)grid.x * Bn <= GN_EARLY_WGS);
+    if (SD_DRY_RUN("groupnorm%s; ", dry_detail(early ? ", statistics first" : ""))) return SD_OK;
+    SD_REQUIRE(pthreads <= GN_MAX_THREADS, SD_EUNSUPPORTED, "groupnorm: C=%d", C);
+    hipLaunchKernelGGL((groupnorm_partial_kernel<VEC>), dim3(nchunks, Bn), dim3(pthreads), (size_t)prows * C * sizeof(float), stream, x, partials, T, C,
+                       groups, nchunks, pchunk, prows);
+    SD_HIP_CHECK(hipGetLastError());
     auto apply = [&](auto with_silu, auto early) {
         hipLaunchKernelGGL((groupnorm_apply_kernel<VEC, decltype(with_silu)::value, decltype(early)::value>), grid, dim3(athreads), lds, stream, x, y, gamma, beta, partials, T, C, groups,
                            nchunks, parts, rows, iters, eps);
     };
-    const bool early = iters == GN_ITERS;
-    if (silu && early) apply(std::true_type(), std::true_type());
+    constexpr std::bool_constant<VEC == 8> ahead;
+    if (silu && early) apply(std::true_type(), ahead);
     else if (silu) apply(std::true_type(), std::false_type());
-    else if (early) apply(std::false_type(), std::true_type());
+    else if (early) apply(std::false_type(), ahead);
     else apply(std::false_type(), std::false_type());
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
@@ -585,7 +591,7 @@ int launch_groupnorm(const uint16_t* x, uint16_t* y, const uint16_t* gamma, cons
     if (Bn <= 0 || T <= 0) return SD_OK;
     int iters = 0;
     const int unit = gn_unit(Bn, T, C, groups, &iters);
-    if (SD_DRY_RUN(unit ? "groupnorm unit; " : "groupnorm; ")) return SD_OK;
+    if (unit && SD_DRY_RUN("groupnorm unit; ")) return SD_OK;
     if (unit && iters <= 2) return launch_gn_unit<2>(x, y, gamma, beta, Bn, T, C, groups, unit, eps, stream, silu);
     if (unit) return launch_gn_unit<GN1_MAX_ITERS>(x, y, gamma, beta, Bn, T, C, groups, unit, eps, stream, silu);
     return C % 8 == 0 ? launch_gn<8>(x, y, gamma, beta, Bn, T, C, groups, eps, partials, stream, silu)

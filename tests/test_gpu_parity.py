@@ -812,8 +812,9 @@ def test_groupnorm_partial_batches_match_oracle(B, Bn, T, C, groups):
     assert np.abs(got - ref).mean() <= 2e-3 * np.abs(ref).mean() * 2       # bf16 rounds by 2^-9 at most, a wrong statistic moves everything
 
 
-# inputs of as many slabs as take all six to a workgroup, where the statistics and the affine are requested ahead of the rows: more groups than
-# threads, fewer channels than a 16-byte piece to a group, channels off eight, the last slab cut off, and one row short of that many slabs
+# inputs of as many slabs as take all six to a workgroup, where the statistics and the affine are requested ahead of the rows (with SiLU; without, in as many
+# workgroups as a round and less): more groups than threads, less than a 16-byte piece to a group, the last slab cut off, one row short of that many slabs; and
+# channels off eight, where they are not
 @pytest.mark.parametrize("Bn,T,C,groups", [(1, 2043, 2048, 1024), (2, 1201, 1280, 32), (1, 12000, 100, 10), (4, 3100, 320, 32), (2, 12239, 320, 160), (1, 12228, 320, 32)])
 def test_groupnorm_large_matches_oracle(B, Bn, T, C, groups):
     r = rng(T + C)

@@ -98,3 +98,17 @@ def test_feed_forward_in_projection(B, M, K, F, r, kernel):
 def test_projection_in_tile_or_not(B, M, K, N, r, kernel, ln):
     names = linear(B, M, K, N, r, ln=ln)
     assert names[-1] == (kernel.replace("records", "flags") if ln else kernel)
+
+
+# GroupNorm's second pass asks for statistics and affine ahead of its rows where a workgroup has six slabs of 16-byte pieces; without SiLU only while
+# workgroups do not follow each other on a CU for long
+@pytest.mark.parametrize("Bn,T,Cc,groups,plain,silu", [
+    (2, 16384, 320, 32, True, True), (1, 43000, 320, 32, True, True), (9, 1200, 1280, 32, False, True), (4, 16384, 320, 32, False, True), (16, 1024, 1280, 32, False, True),
+    (1, 12000, 100, 10, False, False), (8, 3000, 1220, 10, False, False), (2, 4096, 320, 32, False, False),
+])
+def test_groupnorm_second_pass(B, Bn, T, Cc, groups, plain, silu):
+    L = B.lib()
+    with B.dry_run(detail=True) as names:
+        for call in (L.sd_groupnorm_fwd, L.sd_groupnorm_silu_fwd):
+            assert call(0x10000, 0x20000, 0x30000, 0x40000, Bn, T, Cc, groups, 1e-6, 0x100000, L.sd_groupnorm_workspace_bytes(Bn, T, Cc, groups), None) == 0
+    assert names == ["groupnorm" + (", statistics first" if first else "") for first in (plain, silu)]
