@@ -287,6 +287,9 @@ __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_partial_kernel(const
 // Not without SiLU's arithmetic between loads and stores where workgroups follow each other on a CU (2 x 16384 x 320, 456 of them, 16.0 / 15.5; 1 x 43000 x 320,
 // 598, 20.9 / 19.5; 9 x 1200 x 1280, 603, 19.7 / 19.8; 4 x 6200 x 640, 692, 20.3 / 20.8; 4 x 16384 x 320, 911, 24.3 / 25.3; 16 x 1024 x 1280, 912, 25.0 / 26.5),
 // nor where a thread has 4 bytes of a row, six requests for eight or more ahead of them (1 x 12000 x 100 8.1 / 8.3, 8 x 3000 x 1220 45.2 / 48.0, with SiLU 8.5 / 8.6, 50.6 / 53.3).
+// Batches of five samples and more have fewer partials to wait for, and a CU's first workgroup then waits longer for its rows than it did for those (20 x 900 x 320, 13
+// partials, 260 workgroups, 12.1 / 12.8, with SiLU 14.6 / 14.9; 40 x 500 x 320 12.7 / 13.4, 15.0 / 15.4; 16 x 1600 x 320, 368, 13.9 / 14.1, 16.3 / 16.0; 90 x 300 x 320,
+// 450, 14.9 / 14.7, 17.3 / 16.7; up to four samples all of 250 to 360 gain, 4 x 4610 x 320 13.1 / 12.7, 15.2 / 14.6).
 template <int VEC, bool SILU, bool EARLY>
 __global__ __launch_bounds__(GN_MAX_THREADS) void groupnorm_apply_kernel(const uint16_t* __restrict__ x, uint16_t* __restrict__ y,
                                                                            const uint16_t* __restrict__ gamma, const uint16_t* __restrict__ beta,
@@ -564,7 +567,8 @@ static int launch_gn(const uint16_t* x, uint16_t* y, const uint16_t* gamma, cons
     const int64_t slabs = (int64_t)Bn * ((T + rows - 1) / rows);
     const int iters = (int)std::min<int64_t>(GN_ITERS, std::max<int64_t>(1, slabs / GN_APPLY_WGS));
     const dim3 grid((T + rows * iters - 1) / (rows * iters), Bn);
-    const bool early = VEC == 8 && iters == GN_ITERS && (silu || (int64_t)grid.x * Bn <= GN_EARLY_WGS);
+    const int64_t wgs = (int64_t)grid.x * Bn;
+    const bool early = VEC == 8 && iters == GN_ITERS && (silu || wgs <= GN_EARLY_WGS) && (nchunks >= 60 || wgs > (silu ? 300 : 400));
     if (SD_DRY_RUN("groupnorm%s; ", dry_detail(early ? ", statistics first" : ""))) return SD_OK;
     SD_REQUIRE(pthreads <= GN_MAX_THREADS, SD_EUNSUPPORTED, "groupnorm: C=%d", C);
     hipLaunchKernelGGL((groupnorm_partial_kernel<VEC>), dim3(nchunks, Bn), dim3(pthreads), (size_t)prows * C * sizeof(float), stream, x, partials, T, C,

@@ -101,10 +101,11 @@ def test_projection_in_tile_or_not(B, M, K, N, r, kernel, ln):
 
 
 # GroupNorm's second pass asks for statistics and affine ahead of its rows where a workgroup has six slabs of 16-byte pieces; without SiLU only while
-# workgroups do not follow each other on a CU for long
+# workgroups do not follow each other on a CU for long, of five samples and more not in a round that has hardly more than a workgroup a CU
 @pytest.mark.parametrize("Bn,T,Cc,groups,plain,silu", [
     (2, 16384, 320, 32, True, True), (1, 43000, 320, 32, True, True), (9, 1200, 1280, 32, False, True), (4, 16384, 320, 32, False, True), (16, 1024, 1280, 32, False, True),
     (1, 12000, 100, 10, False, False), (8, 3000, 1220, 10, False, False), (2, 4096, 320, 32, False, False),
+    (20, 900, 320, 32, False, False), (16, 1600, 320, 32, False, True), (90, 300, 320, 32, True, True), (4, 4610, 320, 32, True, True), (6, 1000, 960, 32, False, False),
 ])
 def test_groupnorm_second_pass(B, Bn, T, Cc, groups, plain, silu):
     L = B.lib()
