@@ -936,6 +936,27 @@ def test_deep_stack_reads_weights_ahead(B, Bn, T, C, depth):
         assert torch.equal(B.spatial_transformer_fwd(x, ctx, sp, cfg.heads), y)
 
 
+# several blocks of one launch each from self-attention to the feed-forward, one after the other in the same buffers; and stacks whose weights it reads ahead too
+@pytest.mark.parametrize("Bn,T,C,depth,ahead", [(10, 300, 640, 3, 0), (40, 100, 320, 2, 0), (10, 300, 640, 11, 10), (46, 350, 320, 18, 10)])
+def test_deep_stack_chain(B, Bn, T, C, depth, ahead):
+    import torch
+    cfg = small_cfg(Bn=Bn, T=T, Tc=77, C=C, heads=C // 64, Dc=2048, r=16, alpha=2.0, depth=depth, w_std=0.02)
+    p = G.make_stack_inputs(cfg, seed=T + depth)
+    sp = B.StackParams(p)
+    x, ctx = dev(p["x"], B), dev(p["ctx"], B)
+    with B.dry_run(detail=True) as names:
+        B.spatial_transformer_fwd(x, ctx, sp, cfg.heads)
+    assert sum(n.startswith("attention of the chain") for n in names) == depth
+    assert sum(n.startswith("layernorm of the chain, ahead") for n in names) >= ahead and ("ahead" in " ".join(names)) == (ahead > 0)
+    ws = torch.full((B.spatial_transformer_workspace_bytes(Bn, T, C, 77, cfg.Dc, sp.r_max),), 0xFF, dtype=torch.uint8, device="cuda")   # (what no launch wrote is NaN)
+    y = B.spatial_transformer_fwd(x, ctx, sp, cfg.heads, ws=ws).clone()
+    some = [0, Bn - 1]
+    ref = O.spatial_transformer(p["x"][some], p["ctx"][some], p, cfg.heads)
+    assert rel_err(host(y)[some], ref) <= BF16_TOL
+    for _ in range(3):
+        assert torch.equal(B.spatial_transformer_fwd(x, ctx, sp, cfg.heads, ws=ws), y)
+
+
 # few rows: K split over eight wavefronts (fewer slices than wavefronts, uneven shares, one and two stages in flight), tiles of 32x32, 32x64, 64x64
 # and 64x32, rows cut off, ranks that fill one block of A, two, four and none whole; no bias, or one with a residual
 @pytest.mark.parametrize("M,K,N,rank,res,kernel", [
