@@ -911,7 +911,7 @@ extern "C" int sd_spatial_transformer_fwd(const uint16_t* x, const uint16_t* ctx
         sw = StackWs();
         return carve_stack(w, sw, Bn, T, C, Tc, rmax, small);
     };
-    const bool room = ws && carve(false);     // (a smaller workspace keeps the launches it was sized for)
+    const bool room = ws && carve(false);     // (the chain needs nothing that a smaller one lacks; its callers keep the launches that they had)
     SD_REQUIRE(room || (ws && carve(true)), SD_EWORKSPACE, "spatial_transformer: workspace of %zu bytes, need %zu (%zu at the least, with attention tiles uncut)", ws_bytes,
                stack_bytes(Bn, T, C, Tc, rmax, false), stack_bytes(Bn, T, C, Tc, rmax, true));
     hipStream_t s = static_cast<hipStream_t>(stream);

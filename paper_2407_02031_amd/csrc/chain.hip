@@ -2,13 +2,14 @@
 // and residual, LayerNorm, cross-attention query, cross-attention over the text keys, its output projection and
 // residual, LayerNorm.  A workgroup takes 32 rows through all of it; the rows never leave the CU, the residual stays in registers.
 //
-// What bounds it: the weights.  Every workgroup reads all of them, and 256 CUs take one and the same matrix out of L2 at
-// 107-116 GB/s each (whole 128-byte lines straight into LDS; 16 rows of 64 bytes a load come in at 65, and fragments loaded
-// straight into registers at 37, because an instruction's adjacent lanes then lie in different lines): 7.1 us for 640 x 640, and their way
-// through LDS (written, read, and 40 KB of operand rows read by ten wavefronts) takes the port as long.  A step's clocks at 7904
-// rows: half in the three products, 13 % in cross-attention, 12 % in the LayerNorms, the rest first operands, residual and stores.
-// 52 us at 8192 rows with adapters of rank 64, 47 at 7904 without; as six launches 81 (out 20, LayerNorm 6.7, query 16.7,
-// attention 11, out 20, LayerNorm 6.7) and 68.
+// What bounds it: the weights, and the phases between them.  Every workgroup reads all of them, and 256 CUs take one and the same matrix out of L2
+// at 107-116 GB/s each (whole 128-byte lines straight into LDS; 16 rows of 64 bytes a load come in at 65, and fragments loaded
+// straight into registers at 37, because an instruction's adjacent lanes then lie in different lines): 7.1 us for 640 x 640.  A step's clocks at 7904
+// rows: half in the three products, 13 % in cross-attention, 12 % in the LayerNorms, the rest first operands, residual and stores.  Over the whole
+// launch, at 8192 rows + 64, the matrix cores are busy for 18 % of the time, the vector ALU for 21, LDS reads for 25, of which bank conflicts are 27.
+// us a launch, kernel traces of the same stacks one behind the other, the six launches that it stands for (output projection, LayerNorm, query,
+// attention, output projection, LayerNorm) / here: 8192 rows of 640 channels + 64 80.1 (19.8, 6.7, 16.3, 10.7, 19.8, 6.7) / 56.5 (58.6 where weights come from
+// HBM), 7904 without adapter 69.7 / 51.0; 8192 rows of 320 + 16 49.5 / 31.4, 2688 34.4 / 28.0.
 //
 // Wavefront w owns columns 64 w .. 64 w + 63 of every product, which are also attention head w: the query it computes is the one
 // it needs, and the output it computes is its part of the next operand.  What it needs of the weights nobody else does, so
@@ -568,7 +569,7 @@ __global__ __launch_bounds__(64 * HEADS, 3) void chain_kernel(const ChainArgs g,
         if (tid < 256) read_ahead<8>(ra, (int)(blockIdx.y * gridDim.x + blockIdx.x), tid);
 }
 
-// One workgroup of 640 channels fills a CU and takes 47 us (52 with adapters of rank 64) whatever the others do; the launches it stands for take
+// One workgroup of 640 channels fills a CU and takes 51 us (57 with adapters of rank 64) whatever the others do; the launches it stands for take
 // their time by the row.  us of a one-block stack, launches / chain, by blocks of rows: 32 113 / 123, 63 141 / 147, 94 190 / 188 (+ 64 200 / 194),
 // 126 196 / 192 (208 / 198), 164 250 / 238, 208 293 / 277 (310 / 287), 256 333 / 315 (348 / 325); in a second round, 288 351 / 364 (379 / 387),
 // 512 653 / 646 (686 / 670).  So: one round that is a third full, or several whose last is nearly full, counted in rows: blocks that samples of odd lengths
@@ -576,12 +577,13 @@ __global__ __launch_bounds__(64 * HEADS, 3) void chain_kernel(const ChainArgs g,
 // 1326 / 1336, 250 x 57 + 64 1402 / 1380; of 320 channels 180 x 33 + 64 725 / 728, 300 x 8 + 64 1061 / 1072, 300 x 75 + 128 1474 / 1501).  Without adapters
 // the launches are in-tile projections of one round, and the line is later: 1 x 2880 183 / 187, 30 x 75 185 / 188, 60 x 48 253 / 255, 1 x 3264 208 / 204.
 //   Of 320 channels two workgroups share a CU, which is a round of 512, and alone on a CU one is faster: up to 256 blocks 16 + 8 69.0 / 71.0,
-// 26 + 8 74.7 / 78.6, 38 + 8 88.1 / 88.9, + 64 96 / 92, 64 + 8 104 / 99, 126 + 8 134 / 125, 256 205 / 187.  Beyond that, without adapter, + 16, + 64, + 128:
-// 264 194 / 196, 216 / 215, 220 / 222, 233 / 234; 304 207 / 205, 232 / 227, 228 / 232, 242 / 240; 344 229 / 216, 246 / 242, 256 / 245, 258 / 262;
-// 368 235 / 219, 252 / 257, 258 / 249, 267 / 266; 440 267 / 249, 283 / 284, 285 / 275, 299 / 291; 480 278 / 261, 296 / 287, 300 / 282, 315 / 301; in a
-// second round 516 281 / 288, 304 / 321, 304 / 320, 330 / 350; 564 325 / 319, 359 / 349, 354 / 353, 369 / 380; 600 341 / 332, 374 / 361,
-// 369 / 364, 388 / 391; 750 474 / 447, 518 / 482, 517 / 493, 537 / 526; 880 520 / 508, 567 / 552, 546 / 543, 575 / 581 (+ 96 593 / 588); in a third,
-// 1030 581 / 586, 636 / 627, 617 / 626, 652 / 674; 1352 833 / 825, 885 / 875, 862 / 875, 907 / 931.
+// 26 + 8 74.7 / 78.6, 38 + 8 88.1 / 88.9, + 64 96 / 92, 64 + 8 104 / 99, 126 + 8 134 / 125, 256 205 / 187.  Past that without adapter, + 16, + 64, + 128, another
+// machine: 268 199 / 199, 223 / 223, 223 / 225, 243 / 241; 308 219 / 218, 245 / 243, 244 / 247, 261 / 260; 348 234 / 228, 257 / 256, 258 / 256, 273 / 270; 444 271 / 262,
+// 298 / 288, 298 / 291, 316 / 308; 496 291 / 278, 312 / 303, 310 / 304, 332 / 323 (the first machine's up to 440 blocks lay 1 % either way of these); in a
+// second round 516 344 / 341, 376 / 370, 369 / 373, 385 / 399; 564 332 / 329, 369 / 360, 363 / 363, 383 / 392; 600 342 / 337, 379 / 367, 373 / 370, 389 / 398; 750
+// 475 / 454, 524 / 489, 517 / 498, 541 / 528; 880 533 / 529, 585 / 567, 563 / 561, 587 / 600; in a third 1030 591 / 595, 643 / 635, 620 / 635, 658 / 682;
+// 1352 834 / 840, 896 / 892, 876 / 891, 920 / 948 (+ 40 as + 16; + 96 380 / 386 at 516, in between elsewhere).  Not where the rows past a multiple of 8192 are not there, so that
+// the launches need a round less: 86 x 95 tokens, 258 blocks, 266 / 271, 452 / 460, 435 / 444, 475 / 476; 6 x 2730, 516 blocks, 287 / 295, 311 / 327, 310 / 330, 339 / 359.
 bool chain_takes(int Bn, int T, int C, int Tc, const sd_proj& o1, const sd_proj& q2, const sd_proj& o2) {
     const int rank = std::max(o1.r, std::max(q2.r, o2.r));
     if (Tc > CHAIN_KEYS || rank > CHAIN_RANK || Bn > 65535) return false;
@@ -589,9 +591,8 @@ bool chain_takes(int Bn, int T, int C, int Tc, const sd_proj& o1, const sd_proj&
     const bool full = rows >= blocks * 28;
     if (C == 320) {
         if (blocks <= 256) return blocks >= 38;
-        if (!full) return false;
-        if (blocks <= 512) return blocks >= (rank == 0 ? 304 : rank <= 32 ? 448 : 360);
-        return blocks >= 600 && blocks <= 1024 && rank <= 96;
+        if (!full || rows <= 8192 * (rounds - 1)) return false;
+        return blocks <= 512 || rank <= 40 || (rank <= 96 && blocks >= 600 && blocks <= 1024);
     }
     return C == 640 && (rounds == 1 ? rows >= (rank == 0 ? 3264 : 2880) : full && blocks >= 256 * rounds - 24);
 }

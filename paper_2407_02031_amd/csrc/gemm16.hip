@@ -469,8 +469,11 @@ static int launch16r(GemmGroup& g, int rmax, hipStream_t stream) {
 // group of 988 tokens of 1280 channels + 16 37.6 / 27.6, of 2 x 256 of 320 + 8 20.4 / 13.9 (values stored transposed).
 //   Fewer rows than that: gemm_thin's tiles, the smallest that are one round.  us, here (or the general kernel) / there: 154x1280x2048 9.6 / 5.2, + 8 11.3 / 6.2,
 // + 64 14.2 / 8.9; 77x1280x1280 + 32 10.0 / 5.5; 512x320x320 + 8 5.6 / 4.1, x1280 7.5 / 4.4; 32x64: 308x1280x2048 9.8 / 6.9, 1000x320x320 + 8 5.7 / 4.6;
-// 64x64, where the K loop is long: 500x1280x5120 21.4 / 19.5, 1000x640x2560 + 16 13.7 / 13.1, 2000x320x1280 7.8 / 7.2 (1000x640x640 + 16 6.9 / 7.0).
-// They have whole tiles of columns only, and a bias only with a residual or an fp32 result, as the layers of a stack do.
+// 64x64, where the K loop is long: 500x1280x5120 21.4 / 19.5, 1000x640x2560 + 16 13.7 / 13.1, 2000x320x1280 7.8 / 7.2 (1000x640x640 + 16 6.9 / 7.0);
+// 64x32, for ranks above 32 at any K from 320 on: 736x640x320 + 64 6.9 / 6.5, 602x640x640 + 64 8.3 / 7.6, 405x640x1024 + 64 10.6 / 8.3, 667x640x1280 + 40
+// 13.1 / 9.2, 582x640x2048 + 64 13.2 / 12.1, 452x640x5120 + 40 28.5 / 22.1 (120 projections, 0.65 to 0.97).
+// They have whole tiles of columns only.  Results with a bias, bf16 and without residual, no layer of a stack asks for: those keep the kernels that they
+// had, which is not the faster side (here / there: 154x1280x2048 + 64 14.2 / 8.9, 512x320x320 + 16 5.7 / 4.2, 988x640x2560 + 64 17.7 / 17.7).
 constexpr int THIN_32x32 = 4, THIN_32x64 = 5, THIN_64x64 = 6;
 static int tile16(const GemmGroup& g) {
     long big = 0, mid = 0, small = 0, general = 0, lead = 0;   // tiles; of the general kernel: 128x128, and its producers'
