@@ -120,7 +120,8 @@ __global__ __launch_bounds__(512, 2) void gemm_thin_kernel(const GemmGroup g) {
     const u32x4* const ring = lds + wave * (STAGES * SLICE) + l16 * 8;
     // The loads of slice s have landed when no more are in flight than the other slice's, issued behind them (loads retire in order).  The epilogue's
     // lie between the first slice's and the second's and are counted nowhere: however many the compiler makes of them, and wherever it puts them, a
-    // wait is for slice s at the least.  (As fast as behind both slices, and counted: 0.95 to 1.02 of the time over 1250 calls, at the median 0.99.)
+    // wait is for slice s at the least.  (Against behind both slices, and counted: 0.95 to 1.02 of the time over
+    // 1250 calls, at the median 0.99; with all operands from HBM 0.95 to 1.03, 1.00, where the first product waits for an adapter's rows of B too.)
     int st = 0;
 #pragma unroll 1
     for (int s = wave; s < nk; s += NW) {
