@@ -4,29 +4,36 @@
 // What bounds it: the MFMAs of the most loaded CU.  The block's widths (2F = 5120 and 10240) are
 // whole multiples of 320 columns, and its token counts make a whole number of rounds over 256 CUs
 // of such tiles (8192x5120: two, 2048x10240: one) where 256x256 tiles need 2.5 and 1.25, that is
-// three and two.  One workgroup per CU, eight wavefronts of 64x160 (or 32x160): seven operand
-// fragments per ten MFMAs, 142 (or 91) FLOP per byte from L2.
+// three and two.  One workgroup per CU, eight wavefronts of 64x160 (or 32x160): 14 operand
+// fragments per 40 MFMAs (12 per 20), 142 (or 91) FLOP per byte from L2.
 //
 // Two stages of 64 deep operand tiles fill the LDS, so a stage is refilled as soon as the last
-// fragments of its tile are in registers, one load behind each of the next MFMAs, and has the
+// fragments of its tile are in registers, one load behind each of the next slots' MFMAs, and has the
 // rest of the step to arrive.
 //
-// The MFMA takes the rows of W first: a lane holds one row of x and 16 rows of W.  The rows of a
-// 32-row block of W in LDS are dealt so that these are the value and the gate rows of eight
-// consecutive output columns: GEGLU is done in the lane, and it stores 16 bytes.
+// The chip lowers its clock under MFMAs (2.4 GHz idle, 1.75 in this main loop, whose matrix cores are then 83 % busy), so what
+// an MFMA costs in energy is what it costs in time.  16x16x32 MFMAs take less of it than 32x32x16: the same
+// 64x160 products on normal operands out of registers 2100 TFLOP/s against 1850, out of LDS 1860 against 1680.  In this kernel: 8192x5120x640 + 64 68.5 -> 64.5 us,
+// 2048x10240x1280 + 64 54.0 -> 48.4, 988x10240x1280 30.1 -> 28.4 (with the weights from the last-level cache or HBM).
+//
+// The MFMA takes the rows of W first: a lane holds one row of x and four rows of W in a block of 16.  Blocks of value rows and of
+// the gate rows of the same output columns take turns: GEGLU is done in the lane, and it stores four columns.
 #include "gemm_dma.hpp"
 
 namespace sd {
 
-constexpr int GG_BN = 320, GG_OUT = 160, GG_NI = 5, GG_NW = 8;
+constexpr int GG_BN = 320, GG_OUT = 160, GG_WB = 10, GG_NW = 8;
 
-// MI: 32-row blocks of x per wavefront; four wavefronts by rows, two by columns
+// MI: 32 rows of x per wavefront times this; four wavefronts by rows, two by columns
 template <int MI>
 __global__ __launch_bounds__(512, 2) void gemm_geglu_kernel(const GemmGroup g) {
-    constexpr int BM = MI * 128, NI = GG_NI, NW = GG_NW;
+    constexpr int BM = MI * 128, XB = MI * 2, WB = GG_WB, NW = GG_NW;   // 16-row blocks of x and of W per wavefront
     constexpr int ROWS = BM + GG_BN, STAGE = ROWS * 8;         // 16-byte chunks of a stage
     constexpr int LPT = ROWS / 8 / NW, JP = BM / 8 / NW;       // loads per wavefront and stage, and those of x among them
+    constexpr int SLOTS = 2 * WB;                              // a tile is two 32 deep k-steps of WB blocks of W; a slot multiplies one block by the x blocks
+    constexpr int RING = MI == 2 ? 4 : 10;                     // blocks of W in registers (five where the accumulators are 160 registers: spills)
     static_assert(ROWS % (8 * NW) == 0 && BM % (8 * NW) == 0, "whole loads");
+    static_assert(SLOTS % RING == 0 && RING <= WB && LPT <= SLOTS, "slots");
     __shared__ u32x4 lds[2 * STAGE];
 
     GemmProblem P;
@@ -44,21 +51,16 @@ __global__ __launch_bounds__(512, 2) void gemm_geglu_kernel(const GemmGroup g) {
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, hi = lane >> 5;
+    const int l16 = lane & 15, quad = lane >> 4;
     const int wm = (wave >> 1) * (MI * 32), wn = (wave & 1) * (GG_BN / 2);
 
-    // row of W behind row j of the tile: in a block of 32 rows, row 16 a + 8 g + 4 h + e is the value
-    // (g = 0) or gate row of output column 8 h + 4 a + e
-    auto wrow = [&](int j) {
-        const int col = min(n0 + (j >> 5) * 16 + ((j >> 2) & 1) * 8 + ((j >> 4) & 1) * 4 + (j & 3), F - 1);
-        return col + ((j >> 3) & 1) * F;
-    };
+    // row of W behind row j of the tile: blocks of 16 value rows and the 16 gate rows of the same output columns take turns
+    auto wrow = [&](int j) { return min(n0 + (j >> 5) * 16 + (j & 15), F - 1) + ((j >> 4) & 1) * F; };
     // load j of wavefront w fills block j * NW + w of a stage: the rows of x first, then those of W
-    auto row_of = [&](int j) { return (j * NW + wave) * 8 + (lane >> 3); };
     uint32_t off[LPT];
 #pragma unroll
     for (int j = 0; j < LPT; ++j) {
-        const int row = row_of(j), c = swz<8>(row, lane & 7);
+        const int row = (j * NW + wave) * 8 + (lane >> 3), c = swz<8>(row, lane & 7);
         if (j < JP) off[j] = (uint32_t)(((min(m0 + row, Mp - 1) - m0) * P.ldp0 + c * 8) * 2);
         else off[j] = (uint32_t)((wrow(row - BM) * P.ldq0 + c * 8) * 2);
     }
@@ -67,9 +69,10 @@ __global__ __launch_bounds__(512, 2) void gemm_geglu_kernel(const GemmGroup g) {
     auto load = [&](int t, int stg, int j) {
         dma16_so<false>((j < JP ? pb0 : P.q0) + t * 64, off[j], wave_base + (uint32_t)(stg * (STAGE * 16) + j * (NW * 1024)));
     };
-    // tile of the adapter's segment: t [M, r] and B [2F, r]; chunks past r read zeros
-    auto load1 = [&](int t, int stg, int j) {
-        const int row = row_of(j), c = swz<8>(row, lane & 7), k = (t - nk0) * 64 + c * 8;
+    // tile of the adapter's segment: t [M, r] and B [2F, r]; chunks past r read zeros.  (From a lane number that the compiler
+    // does not know: it would form the addresses ahead of the main loop and spill there.)
+    auto load1 = [&](int t, int stg, int j, int ln) {
+        const int row = (j * NW + wave) * 8 + (ln >> 3), c = swz<8>(row, ln & 7), k = (t - nk0) * 64 + c * 8;
         const uint16_t* src = j < JP ? P.p1 + (int64_t)min(m0 + row, Mp - 1) * P.ldp1 : P.q1 + (int64_t)wrow(row - BM) * P.ldq1;
         dma16<false>(k < r ? reinterpret_cast<const void*>(src + k) : reinterpret_cast<const void*>(g_gemm_zeros),
                      wave_base + (uint32_t)(stg * (STAGE * 16) + j * (NW * 1024)));
@@ -79,51 +82,55 @@ __global__ __launch_bounds__(512, 2) void gemm_geglu_kernel(const GemmGroup g) {
 #pragma unroll
             for (int j = 0; j < LPT; ++j) load(t, stg, j);
         } else {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
 #pragma unroll
-            for (int j = 0; j < LPT; ++j) load1(t, stg, j);
+            for (int j = 0; j < LPT; ++j) load1(t, stg, j, ln);
         }
     };
 
-    f32x16 acc[MI][NI];
+    f32x4 acc[XB][WB];
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi)
+    for (int mi = 0; mi < XB; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
+        for (int ni = 0; ni < WB; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // the x blocks of both k-steps, and a ring of W blocks: slot s multiplies W block s % WB in k-step s / WB out of wf[s % RING],
+    // which is then refilled for slot s + RING, over the edge of two tiles too
+    bf16x8 xf[2][XB], wf[RING];
+    const int lrow = l16 * 8, lsw = (l16 >> 1) & 7;
+    auto frag = [&](int st, int ks) { return lds + (st * STAGE + lrow + ((ks * 4 + quad) ^ lsw)); };
+    auto fetch_x = [&](int st, int ks) {
+        const u32x4* const sx = frag(st, ks) + wm * 8;
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
-    bf16x8 xf[2][MI], wf[2][NI];
-    const int lrow = l32 * 8, lsw = (l32 >> 1) & 7;
-    auto fetch = [&](int st, int kk, int fs) {
-        const u32x4* const s = lds + (st * STAGE + lrow + ((kk * 2 + hi) ^ lsw));
-        const u32x4* const sx = s + wm * 8;
-        const u32x4* const sw = s + (BM + wn) * 8;
-#pragma unroll
-        for (int mi = 0; mi < MI; ++mi) xf[fs][mi] = __builtin_bit_cast(bf16x8, sx[mi * 256]);
-#pragma unroll
-        for (int ni = 0; ni < NI; ++ni) wf[fs][ni] = __builtin_bit_cast(bf16x8, sw[ni * 256]);
+        for (int mi = 0; mi < XB; ++mi) xf[ks][mi] = __builtin_bit_cast(bf16x8, sx[mi * 128]);
     };
-    auto multiply = [&](int fs, auto ld, int j0, int j1) {
+    auto fetch_w = [&](int st, int s) { wf[s % RING] = __builtin_bit_cast(bf16x8, (frag(st, s / WB) + (BM + wn) * 8)[(s % WB) * 128]); };
+    auto multiply = [&](int s) {
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < MI * NI; ++i) {
-            const int mi = i % MI, ni = i / MI;
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[fs][ni], xf[fs][mi], acc[mi][ni], 0, 0, 0);
-            const int a = j0 + (j1 - j0) * i / (MI * NI), b = j0 + (j1 - j0) * (i + 1) / (MI * NI);
-            if (a < b) {
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int j = a; j < b; ++j) ld(j);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
+        for (int mi = 0; mi < XB; ++mi)
+            acc[mi][s % WB] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[s % RING], xf[s / WB][mi], acc[mi][s % WB], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
     auto no_load = [](int) {};
-    auto head = [&](int st) {       // all k-steps of a tile but the last
+    // all slots of a tile but the last RING, loads [j0, LPT) of another dealt behind them
+    auto head = [&](int st, auto ld, int j0) {
 #pragma unroll
-        for (int kk = 0; kk < 3; ++kk) {
-            fetch(st, kk + 1, (kk + 1) & 1);
-            multiply(kk & 1, no_load, 0, 0);
+        for (int s = 0; s < SLOTS - RING; ++s) {
+            if (s == 0) fetch_x(st, 1);
+            multiply(s);
+            if (j0 + s < LPT) ld(j0 + s);
+            fetch_w(st, s + RING);
+        }
+    };
+    // the last RING slots of a tile, whose operands are in registers, while the first of the next are read
+    auto edge = [&](int sn, auto ld) {
+        fetch_x(sn, 0);
+#pragma unroll
+        for (int i = 0; i < RING; ++i) {
+            multiply(SLOTS - RING + i);
+            if (i < LPT) ld(i);
+            fetch_w(sn, i);
         }
     };
 
@@ -132,11 +139,13 @@ __global__ __launch_bounds__(512, 2) void gemm_geglu_kernel(const GemmGroup g) {
     if (nkt > 1) wait_vmcnt<LPT>();
     else wait_vmcnt<0>();
     __syncthreads();
-    fetch(0, 0, 0);
-    head(0);
+    fetch_x(0, 0);
+#pragma unroll
+    for (int s = 0; s < RING; ++s) fetch_w(0, s);
+    head(0, no_load, LPT);
 
-    // a step: the edge between tiles t and t+1, before the MFMAs of tile t's last k-step (whose
-    // fragments are in registers); the stage of tile t takes tile t+2
+    // a step: the edge between tiles t and t+1, before tile t's last slots (whose operands are in
+    // registers); the stage of tile t takes tile t+2
     int t = 0;
 #pragma unroll 1
     for (; t + 2 < nk0; ++t) {
@@ -144,55 +153,44 @@ __global__ __launch_bounds__(512, 2) void gemm_geglu_kernel(const GemmGroup g) {
         wait_vmcnt<0>();
         __syncthreads();
         auto ld = [&](int j) { load(t + 2, st, j); };
-        fetch(sn, 0, 0);
-        multiply(1, ld, 0, MI == 2 ? LPT : 5);
-        fetch(sn, 1, 1);
-        multiply(0, ld, MI == 2 ? LPT : 5, LPT);
-        fetch(sn, 2, 0);
-        multiply(1, no_load, 0, 0);
-        fetch(sn, 3, 1);
-        multiply(0, no_load, 0, 0);
+        edge(sn, ld);
+        head(sn, ld, RING);
     }
 #pragma unroll 1
     for (; t + 1 < nkt; ++t) {
         const int st = t & 1, sn = st ^ 1;
         wait_vmcnt<0>();
         __syncthreads();
-        fetch(sn, 0, 0);
         if (t + 2 < nkt) issue(t + 2, st);
-        multiply(1, no_load, 0, 0);
-        head(sn);
+        edge(sn, no_load);
+        head(sn, no_load, LPT);
     }
-    multiply(1, no_load, 0, 0);
+#pragma unroll
+    for (int s = SLOTS - RING; s < SLOTS; ++s) multiply(s);
 
     // ---- bias, GEGLU, store
     const float alpha = P.alpha;
     const uint16_t* const bias = P.bias;
 #pragma unroll
-    for (int ni = 0; ni < NI; ++ni) {
-        const int n = n0 + (wn >> 1) + ni * 16 + hi * 8;
+    for (int p = 0; p < WB / 2; ++p) {
+        const int n = n0 + (wn >> 1) + p * 16 + quad * 4;
         if (n >= F) continue;       // F is a multiple of 8
-        float bv[8], bg[8];
-        u32x4 b0 = {0u, 0u, 0u, 0u}, b1 = {0u, 0u, 0u, 0u};
+        u32x2 b0 = {0u, 0u}, b1 = {0u, 0u};
         if (bias) {
-            b0 = *reinterpret_cast<const u32x4*>(bias + n);
-            b1 = *reinterpret_cast<const u32x4*>(bias + F + n);
+            b0 = *reinterpret_cast<const u32x2*>(bias + n);
+            b1 = *reinterpret_cast<const u32x2*>(bias + F + n);
         }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            bv[e] = e & 1 ? bf16hi_to_f32(b0[e >> 1]) : bf16lo_to_f32(b0[e >> 1]);
-            bg[e] = e & 1 ? bf16hi_to_f32(b1[e >> 1]) : bf16lo_to_f32(b1[e >> 1]);
-        }
+        for (int mi = 0; mi < XB; ++mi) {
+            const int m = m0 + wm + mi * 16 + l16;
+            bf16x4 o;
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) {
-            const int m = m0 + wm + mi * 32 + l32;
-            bf16x8 o;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const int v = (e >> 2) * 8 + (e & 3);
-                o[e] = (__bf16)((alpha * acc[mi][ni][v] + bv[e]) * gelu_erf(alpha * acc[mi][ni][v + 4] + bg[e]));
+            for (int e = 0; e < 4; ++e) {
+                const float bv = e & 1 ? bf16hi_to_f32(b0[e >> 1]) : bf16lo_to_f32(b0[e >> 1]);
+                const float bg = e & 1 ? bf16hi_to_f32(b1[e >> 1]) : bf16lo_to_f32(b1[e >> 1]);
+                o[e] = (__bf16)((alpha * acc[mi][2 * p][e] + bv) * gelu_erf(alpha * acc[mi][2 * p + 1][e] + bg));
             }
-            if (m < Mp) *reinterpret_cast<bf16x8*>(static_cast<uint16_t*>(P.y) + (int64_t)m * P.ldy + n) = o;
+            if (m < Mp) *reinterpret_cast<bf16x4*>(static_cast<uint16_t*>(P.y) + (int64_t)m * P.ldy + n) = o;
         }
     }
 }
