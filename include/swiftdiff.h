@@ -134,7 +134,8 @@ int32_t sd_set_projection_fusion(int32_t on);
  * they write the names of what they would launch to sd_dry_run_text, in order, and need no device.  For tests that
  * are meant for one kernel, and for reading a dispatch rule at a size.  A launch that runs several steps names them one by one, "of the chain" behind each.  sd_dry_run(2) also writes, behind a comma, how many
  * problems a projection launch holds, the in-tile kernel's ring stages and residual, whether GroupNorm's second pass asks for its
- * statistics first, and the ranges of weights that an attention, LayerNorm or chain launch reads ahead (address+bytes, in hex and decimal).  Returns the previous setting. */
+ * statistics first, and the ranges of weights that an attention, LayerNorm or chain launch reads ahead (address+bytes, in hex and decimal); sd_dry_run(3) also how many queries an attention workgroup takes and how many groups of wavefronts share its
+ * key range.  Returns the previous setting. */
 int32_t sd_dry_run(int32_t on);
 const char* sd_dry_run_text(void);
 

@@ -154,9 +154,9 @@ def set_projection_fusion(on: bool) -> bool:
 @contextlib.contextmanager
 def dry_run(detail: bool = False):
     """Forward calls inside launch nothing; the list that this yields holds the kernels they would launch afterwards, with
-    `detail` also what they hold and read ahead."""
+    `detail` also what they hold and read ahead, with detail=3 also the tiles of attention launches."""
     names: list = []
-    _lib.sd_dry_run(2 if detail else 1)
+    _lib.sd_dry_run((3 if detail == 3 else 2) if detail else 1)
     try:
         yield names
     finally:

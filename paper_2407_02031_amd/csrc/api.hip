@@ -26,7 +26,7 @@ int hip_fail(hipError_t e, const char* what) {
 }
 
 thread_local bool g_dry_run = false;
-static thread_local bool g_dry_detail = false;
+static thread_local int g_dry_detail = 0;         // levels of detail
 static thread_local char g_dry_text[32768] = "";   // (twenty blocks and more, ten with the details)
 bool dry_note(const char* fmt, ...) {
     const size_t n = strlen(g_dry_text);
@@ -44,6 +44,12 @@ const char* dry_detail(const char* fmt, ...) {
     va_start(ap, fmt);
     vsnprintf(text, sizeof(text), fmt, ap);
     va_end(ap);
+    return text;
+}
+const char* dry_tiles(int queries, int groups) {
+    static thread_local char text[48];
+    text[0] = 0;
+    if (g_dry_detail > 1) snprintf(text, sizeof(text), ", %d queries, %d groups", queries, groups);
     return text;
 }
 const char* dry_ranges(const ReadRanges& ra) {
@@ -549,10 +555,10 @@ extern "C" int32_t sd_set_projection_fusion(int32_t on) {
     return was;
 }
 extern "C" int32_t sd_dry_run(int32_t on) {
-    const int32_t was = g_dry_run ? (g_dry_detail ? 2 : 1) : 0;
+    const int32_t was = g_dry_run ? 1 + g_dry_detail : 0;
     if (on) g_dry_text[0] = 0;
     g_dry_run = on != 0;
-    g_dry_detail = on == 2;
+    g_dry_detail = on > 1 ? (on > 2 ? 2 : 1) : 0;
     return was;
 }
 extern "C" const char* sd_dry_run_text(void) { return g_dry_text; }

@@ -2,22 +2,29 @@
 // (sample, head) without ever writing the scores (the transformer block's self-attention
 // over the latent tokens and cross-attention to the text tokens).
 //
-// The kernel works on the TRANSPOSED score tile S^T = K Q^T: with the 32x32x16 bf16 MFMA
-// the accumulator of lane l then holds one query (column l % 32) and 16 of the tile's keys
-// (rows), so the softmax row maximum and row sum are in-register reductions plus a single
-// exchange between the two half-wavefronts, the running rescale factor is a per-lane
-// scalar, and the exponentials, packed to bf16, are already laid out as the B operand of
+// The kernel works on the TRANSPOSED score tile S^T = K Q^T: with the 16x16x32 bf16 MFMA
+// the accumulator of lane l then holds one query (column l % 16) and four of the block's keys
+// (rows), so the softmax row maximum is an in-register reduction plus exchanges between the four
+// quads of 16 lanes, the running rescale factor is a per-lane
+// scalar, and the exponentials of two key blocks, packed to bf16, are already laid out as the B operand of
 // the second MFMA, O^T += V^T P^T.  V is consumed transposed ([C, keys]), which is how the
 // v-projection GEMM writes it, so both K and V^T tiles are staged with 16-byte rows.
 //
-// Workgroup: 4 wavefronts, each owning 32 queries; K / V^T tiles of 64 keys go from
+// What bounds it: vector-ALU issue, at a clock that the chip lowers under load (1.8 to 1.95 GHz of 2.4).  Per 32 queries x 64 keys a SIMD
+// issues 32 exponentials (8 clocks each), 16 packings (4.5), 36 MFMAs (8.5) and some 20 others (4), with plain keys 32 FMAs: 734 and 862
+// clocks, and 816 were measured with three wavefronts to a SIMD and plain keys; the matrix core needs 576, LDS gives 256 bytes a clock and is asked for
+// a sixth of it.  16x16x32 MFMAs, although two issues for one, because the 32x32x16 ones cost more energy and
+// leave the row sums to instructions that do not run beside MFMAs: 12 x 4096 x 8 heads 426 -> 386 us, in a block of
+// 2 x 4096 tokens of 640 channels 94 -> 86, 8 x 988 x 20 heads 58.6 -> 53.1.
+//
+// Workgroup: one group of 4 wavefronts, each owning 32 (or 64) queries, or two groups that share the key range; K / V^T tiles of 64 keys go from
 // global memory straight into LDS rings (wave-wide 1 KB loads of XOR-swizzled 16-byte
 // chunks), one tile ahead of the one being used.  K rows are placed in LDS with the keys
-// of every 16-key group in the order [0-3, 8-11, 4-7, 12-15]: the score accumulator of a
-// lane then holds 8 consecutive keys per 16-key group, and the matching V^T operand is a
+// of every 32-key group in the order [0-3, 8-11, 16-19, 24-27, 4-7, 12-15, 20-23, 28-31]: a lane's scores of two
+// key blocks are then 8 consecutive keys, and the matching V^T operand is a
 // single 16-byte LDS read of the plain [C, keys] layout.
 //
-// Work split.  A (sample, head, 128-query tile) is a tile; a workgroup normally takes one.
+// Work split.  A (sample, head, 128-query or 256-query tile) is a tile; a workgroup normally takes one (attention_plan).
 // When the tile count lies between two and three per CU (640 tiles on 256 CUs leaves half
 // the CUs with three tiles and half with two), the launch is padded to exactly three
 // workgroups per CU by cutting the key range of the surplus tiles in half: every CU then
@@ -32,6 +39,8 @@
 namespace sd {
 
 __device__ __forceinline__ int aswz(int row, int chunk) { return chunk ^ ((row >> 1) & 7); }
+// which of a tile's 64 keys K row r of LDS holds: bits 4, 3, 2 of the key are bits 3, 2, 4 of the row
+__device__ __forceinline__ int key_of_row(int r) { return (r & 35) | ((r & 12) << 1) | ((r & 16) >> 2); }
 
 constexpr float RESCALE_LOG2 = 8.0f;
 
@@ -54,41 +63,52 @@ __device__ __forceinline__ void attn_wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-constexpr int PART_FLOATS = 34 * 256;   // one half of a cut tile: 32 accumulator values, max, sum per thread
+// One half of a cut tile of 128 queries: 32 accumulator values a thread, then its queries' reference maxima and row sums.  A tile of
+// 256 takes two.
+constexpr int PART_FLOATS = 34 * 256;
 
-// normalise and store one 32-query block of a tile: lane holds query l32, d = db*32 + 8*(v/4) + 4*hi + v%4
-__device__ __forceinline__ void store_queries(const f32x16 (&o)[2], float l, uint16_t* __restrict__ out, int64_t ldo,
-                                              int b, int Tq, int row, int head, int hi) {
-    float l_lo, l_hi;
-    both_halves(l, l_lo, l_hi);   // the two half-wavefronts summed different keys of the same query
-    const float inv = 1.0f / (l_lo + l_hi);
-    if (row < Tq) {
-        uint16_t* op = out + ((int64_t)b * Tq + row) * ldo + head * 64 + 4 * hi;
+// Largest of what the four quads of a wavefront (16 lanes each) hold for the same query, in every lane: exchanges of rows
+// of 16 lanes and of half-wavefronts
+__device__ __forceinline__ float quads_max(float x) {
+    float a = x, b = x, lo, hi;
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    both_halves(fmaxf(a, b), lo, hi);
+    return fmaxf(lo, hi);
+}
+
+// normalise and store: lane holds queries row + qb*16, d = (d0 + db)*16 + 4*quad + v; l: row sums, whole
+template <int QB, int KD>
+__device__ __forceinline__ void store_queries(const f32x4 (&o)[KD][QB], const float (&l)[QB], uint16_t* __restrict__ out, int64_t ldo,
+                                              int b, int Tq, int row, int head, int d0, int quad) {
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
+    for (int qb = 0; qb < QB; ++qb) {
+        const float inv = 1.0f / l[qb];
+        if (row + qb * 16 < Tq) {
+            uint16_t* op = out + ((int64_t)b * Tq + row + qb * 16) * ldo + head * 64 + d0 * 16 + 4 * quad;
 #pragma unroll
-            for (int v4 = 0; v4 < 4; ++v4) {
+            for (int db = 0; db < KD; ++db) {
                 bf16x4 w;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[db][4 * v4 + e] * inv);
-                *reinterpret_cast<bf16x4*>(op + db * 32 + 8 * v4) = w;
+                for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[db][qb][e] * inv);
+                *reinterpret_cast<bf16x4*>(op + db * 16) = w;
             }
+        }
     }
 }
 
 // PRE: the keys arrive multiplied by 1/8 * log2(e) (the K projection's epilogue does it before
 // rounding to bf16), so a score is already the exponent of 2, and the running reference maximum
-// is subtracted by the matrix core: a fifth, half-depth k-step multiplies a fragment of ones (K side) with
-// (-m split into three bf16 terms, exact to fp32) on the query side, so the accumulator holds
+// is subtracted by the matrix core: all rows of a lane's accumulator belong to its query, so they start at
+// -m (one register, four times over) instead of 0, the accumulator holds
 // s - m and the vector ALU only exponentiates.  Without PRE one FMA per score does both.
-// MEASURE: the maximum of every key tile is measured before its exponentials are formed and the
-// reference moves whenever a tile's maximum exceeds it by 2^8.  With TRY (prescaled keys, and long
+// The maximum of every half tile is measured and the
+// reference moves whenever it is exceeded by 2^8.  With TRY (prescaled keys, and long
 // ranges of plain ones) the kernel tries without first.  What
 // the reference maximum is for is range, not accuracy: p = 2^(s - m) is formed, rounded and
 // accumulated in floating point, whose relative precision does not depend on magnitude, so any m
 // gives the same result as long as nothing overflows and the row sum does not vanish.  The first
-// attempt therefore measures only a segment's first tile (m becomes a score that occurs: the row
-// sum is >= 1 from then on) and its last (which may be masked); in between the exponentials are
+// attempt therefore measures only a segment's first half tile (m becomes a score that occurs: the row
+// sum is >= 1 from then on); after it the exponentials are
 // formed against that fixed reference with no maximum pass at all.  At the end every lane looks at
 // its row sum and accumulator: if anything is not finite or close to it, some score lay 2^100 or more
 // above the first tile's; a workgroup in which any wavefront saw that returns true without storing
@@ -101,17 +121,25 @@ typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 typedef __attribute__((address_space(3))) int32_t lds_i32;
 typedef __attribute__((address_space(3))) uint16_t lds_u16;
 
-// ldsK: [2][64 keys (permuted within 16)][8 chunks of 8 d], 2-deep ring;  ldsV: [3][64 d][8 chunks of 8 keys], 3-deep ring
-template <bool PRE, bool MEASURE>
+typedef __attribute__((address_space(3))) float lds_f32;
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
+
+// QB: 16-query blocks of a wavefront.  GR: groups of four wavefronts; each takes an equal share of the key range for all of the
+// workgroup's 64 * QB queries, and their states meet in LDS at the end.
+// lds, per group: K [2][64 keys (permuted within 32)][8 chunks of 8 d], then V [2][64 d][8 chunks of 8 keys];  ml: [GR][2][64 * QB]
+constexpr int ATTN_GROUP_CH = 4 * 512;   // 16-byte chunks
+template <int QB, int GR, bool PRE, bool TRY>
 __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, int64_t ldq,
                                                const uint16_t* __restrict__ k, int64_t ldk,
                                                const uint16_t* __restrict__ vt, int64_t ldvt,
                                                uint16_t* __restrict__ out, int64_t ldo,
                                                int Tq, int Tk, int Tkp, int heads, int qtiles, float c,
                                                int nfull, int nsplit, int total, float* __restrict__ parts, int32_t* __restrict__ arrived,
-                                               lds_u32x4* const ldsK, lds_u32x4* const ldsV, lds_i32* const wg_redo, const int tid, const int bid) {
-    constexpr int QB = 1;             // 32-query blocks per wavefront
-    constexpr int BQ = 4 * 32 * QB;
+                                               lds_u32x4* const lds, lds_f32* const ml, lds_i32* const wg_redo, const int tid, const int bid, const bool again) {
+    constexpr int BQ = 64 * QB, KD = 4 / GR;
+    constexpr int THREADS = 256 * GR;
+    constexpr int PART = KD * QB * 4 * THREADS + 2 * BQ;     // floats of a part
+    static_assert(2 * PART <= QB * PART_FLOATS, "a part fits its share of the scratch memory");
 
     // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous range of
     // (sample, head, query tile) so that one head's K and V stay in one XCD's L2.
@@ -138,52 +166,55 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     const int qt = tile % qtiles;
     const int head = (tile / qtiles) % heads, b = tile / (qtiles * heads);
     const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, hi = lane >> 5;
-    const int q0 = qt * BQ + wave * 32 * QB;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) & 3, grp = GR == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 8);
+    const int l16 = lane & 15, quad = lane >> 4;
+    const int q0 = qt * BQ + wave * 16 * QB;
+    // this group's tiles are [g0, g0 + n), its keys end at kend: of an odd number of tiles the one in the middle is masked for the
+    // first group, which sits out where it is the only one
+    const int n = (s1 - s0 + GR - 1) / GR, g0 = GR > 1 && grp ? s1 - n : s0;
+    const int kend = GR > 1 && grp == 0 ? (s1 - n) * 64 : min(Tk, s1 * 64);
+    const bool live = g0 * 64 < kend;
 
-    // ---- Q fragments (B operand of S^T = K Q^T): lane holds q[row l32][d = kk*16 + hi*8 ..+8]
-    bf16x8 qf[QB][4];
+    // ---- Q fragments (B operand of S^T = K Q^T): lane holds q[row l16][d = kk*32 + quad*8 ..+8]
+    bf16x8 qf[QB][2];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        int row = q0 + qb * 32 + l32;
+        int row = q0 + qb * 16 + l16;
         row = row < Tq ? row : Tq - 1;
-        const uint16_t* qp = q + ((int64_t)b * Tq + row) * ldq + head * 64 + hi * 8;
+        const uint16_t* qp = q + ((int64_t)b * Tq + row) * ldq + head * 64 + quad * 8;
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk) qf[qb][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + kk * 16));
+        for (int kk = 0; kk < 2; ++kk) qf[qb][kk] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(qp + kk * 32));
     }
 
     // ---- tile loaders.  A tile is 8 blocks of 1 KB (8 rows x 8 chunks); load j of wave w
     // fills block j*4 + w: lane l lands at chunk position l % 8 of row l / 8 and fetches the
-    // logical chunk the XOR swizzle places there.  K row r holds key (r with bits 2 and 3
-    // exchanged); keys past Tk re-read the last key (masked later), V^T chunks past the
-    // padded key count read zeros.
-    const uint32_t ldsK_base = (uint32_t)(uintptr_t)ldsK;
-    const uint32_t ldsV_base = (uint32_t)(uintptr_t)ldsV;
+    // logical chunk the XOR swizzle places there.  K row r holds key key_of_row(r); keys past Tk
+    // re-read the last key (masked later), V^T chunks past the padded key count read zeros.
+    lds_u32x4* const ring = lds + grp * ATTN_GROUP_CH;
+    const uint32_t ring_base = (uint32_t)(uintptr_t)ring;
     const uint16_t* kbase = k + (int64_t)b * Tk * ldk + head * 64;
     // rows of the two loads of a lane are 32 apart: same swizzled chunk for both
     const int r0 = wave * 8 + (lane >> 3);
     const int kc8 = aswz(r0, lane & 7) * 8;
-    const int kkey0 = (r0 & ~12) | ((r0 & 4) << 1) | ((r0 & 8) >> 1);
+    const int kkey0 = key_of_row(r0);
     // full tiles: byte offset of this lane's first K row and first V^T row from the tile's base; the
     // second row of each lies 32 rows further, a wave-uniform distance that goes into the scalar base
     const uint32_t koff = (uint32_t)(((int64_t)kkey0 * ldk + kc8) * 2);
     const uint32_t voff = (uint32_t)(((int64_t)r0 * ldvt + kc8) * 2);
     const int64_t krow32 = 64 * ldk, vrow32 = 64 * ldvt;     // bytes
     const char* vbase = reinterpret_cast<const char*>(vt + (int64_t)(head * 64) * ldvt + (int64_t)b * Tkp);
-    const bool ragged = (Tk & 63) != 0;
-    auto issue_kv = [&](int t, int kslot, int vslot) {
+    auto issue_kv = [&](int t, int slot) {
         const int key0 = t * 64;
-        const uint32_t kdst = ldsK_base + (uint32_t)(kslot * 8192 + wave * 1024);
-        const uint32_t vdst = ldsV_base + (uint32_t)(vslot * 8192 + wave * 1024);
-        if (ragged && t == nt - 1) {
+        const uint32_t kdst = ring_base + (uint32_t)(slot * 8192 + wave * 1024);
+        const uint32_t vdst = kdst + 16384;
+        if (key0 + 64 > Tk) {
             // (the lane's row and chunk are derived afresh from a laundered lane index, so that
             // nothing of this rare path is kept in registers through the key loop)
             int ln = lane;
             asm volatile("" : "+v"(ln));
             const int rr = wave * 8 + (ln >> 3);
             const int cc8 = aswz(rr, ln & 7) * 8;
-            const int kk0 = (rr & ~12) | ((rr & 4) << 1) | ((rr & 8) >> 1);
+            const int kk0 = key_of_row(rr);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 int key = key0 + kk0 + j * 32;
@@ -205,339 +236,371 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
             for (int j = 0; j < 2; ++j) attn_dma16_so(vb + j * vrow32, voff, vdst + j * 4096);
         }
     };
-    // padding keys [Tk, Tkp) of the last tile hold whatever the caller's buffer held: zero
-    // them in LDS so that 0 * garbage stays 0 (thread: row tid / 4, keys Tk + tid % 4 (+ 4))
-    auto zero_pad_keys = [&](int t, int vslot) {
-        lds_u16* lv = reinterpret_cast<lds_u16*>(ldsV + vslot * 512);
-        const int d = tid >> 2;
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int key = Tk + (tid & 3) + 4 * i;
-            const int kl = key - t * 64;
-            if (key < Tkp && kl < 64) lv[(d * 8 + aswz(d, kl >> 3)) * 8 + (kl & 7)] = 0;
-        }
-    };
 
-    f32x16 o[QB][2];
-    float m[QB], l[QB];
+    constexpr bool KEEP_M = PRE && QB == 2;      // -m ready as the start of the scores (registers)
+    f32x4 o[4][QB], ls[QB], mneg[KEEP_M ? QB : 1];
+    float m[QB];
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        m[qb] = PRE ? 0.f : -INFINITY;
-        l[qb] = 0.f;
+        if (KEEP_M) mneg[KEEP_M ? qb : 0] = f32x4{0.f, 0.f, 0.f, 0.f};
+        m[qb] = PRE && live ? 0.f : -INFINITY;
+        ls[qb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[qb][db][v] = 0.f;
+        for (int db = 0; db < 4; ++db) o[db][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 
-    // S^T tile of key tile t: 64 keys x (32*QB) queries.  The K fragments of the first two
-    // k-steps are fetched by the caller ahead of time (their LDS latency hides behind the
-    // running-maximum update), the other two are read here.
-    auto load_kfrags = [&](int t, int kk0, bf16x8 (&kf)[2][2]) {
-        const lds_u32x4* lk = ldsK + (t & 1) * 512;
+    // A key tile is worked through in halves of 32 keys: scores of one half while the half before is exponentiated.
+    // Rows that are 16 apart share the swizzle.
+    const int lrow8 = l16 * 8, lsw = (l16 >> 1) & 7;
+    // K fragments of half h: kf[kb][kk], key block kb, d = kk*32 ..
+    auto load_kfrags = [&](int slot, int h, bf16x8 (&kf)[2][2]) {
 #pragma unroll
-        for (int kk = 0; kk < 2; ++kk)
+        for (int kk = 0; kk < 2; ++kk) {
+            const lds_u32x4* lk = ring + slot * 512 + h * 256 + lrow8 + ((kk * 4 + quad) ^ lsw);
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const int r = kb * 32 + l32;
-                kf[kk][kb] = __builtin_bit_cast(bf16x8, lk[r * 8 + aswz(r, (kk0 + kk) * 2 + hi)]);
-            }
-    };
-    // PRE: operands of the extra k-step, a 32x32x8 MFMA (half the cost of a 16-deep one; a lane
-    // supplies k-slots 4*hi .. 4*hi+3).  K side: 1.0 in k-slots 0..2 of every key row; query side:
-    // -m as three bf16 terms in those slots; the upper half-wavefront supplies zeros.
-    const u32x2 ones_bits = {hi ? 0u : 0x3F803F80u, hi ? 0u : 0x00003F80u};
-    const bf16x4 ones_frag = __builtin_bit_cast(bf16x4, ones_bits);
-    bf16x4 mfrag[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) mfrag[qb] = __builtin_bit_cast(bf16x4, u32x2{0u, 0u});
-    auto set_mfrag = [&](int qb) {
-        const float x = -m[qb];
-        const __bf16 h = (__bf16)x;
-        const float r1 = x - (float)h;
-        const __bf16 md = (__bf16)r1;
-        const __bf16 lo = (__bf16)(r1 - (float)md);
-        const uint32_t w0 = (uint32_t)__builtin_bit_cast(uint16_t, h) | ((uint32_t)__builtin_bit_cast(uint16_t, md) << 16);
-        const uint32_t w1 = (uint32_t)__builtin_bit_cast(uint16_t, lo);
-        mfrag[qb] = __builtin_bit_cast(bf16x4, u32x2{hi ? 0u : w0, hi ? 0u : w1});
-    };
-    auto compute_s = [&](int t, f32x16 (&s)[QB][2], bf16x8 (&kf0)[2][2]) {
-        bf16x8 kf1[2][2];
-        load_kfrags(t, 2, kf1);
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) s[qb][kb][v] = 0.f;
-        if (PRE) {
-#pragma unroll
-            for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-                for (int kb = 0; kb < 2; ++kb) s[qb][kb] = __builtin_amdgcn_mfma_f32_32x32x8bf16_1k(ones_frag, mfrag[qb], s[qb][kb], 0, 0, 0);
+            for (int kb = 0; kb < 2; ++kb) kf[kb][kk] = __builtin_bit_cast(bf16x8, lk[kb * 128]);
         }
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-#pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                const bf16x8 a = kk < 2 ? kf0[kk][kb] : kf1[kk - 2][kb];
-#pragma unroll
-                for (int qb = 0; qb < QB; ++qb)
-                    s[qb][kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[qb][kk], s[qb][kb], 0, 0, 0);
-            }
     };
-    // keys past Tk (last tile only) get a score of -inf
-    auto mask_tail = [&](int t, f32x16 (&s)[QB][2]) {
+    // With the K row order above, a lane's scores of a half are its keys quad*8 ..+8, the 16-byte chunk h*4 + quad of a V^T row
+    auto load_vfrags = [&](int slot, int h, bf16x8 (&vf)[4]) {
+        const lds_u32x4* lv = ring + 1024 + slot * 512 + lrow8 + ((h * 4 + quad) ^ lsw);
+#pragma unroll
+        for (int db = 0; db < 4; ++db) vf[db] = __builtin_bit_cast(bf16x8, lv[db * 128]);
+    };
+    // scores of a half; all of a lane's accumulator values belong to its query, so they can start at -m
+    auto compute_s = [&](f32x4 (&s)[2][QB], bf16x8 (&kf)[2][2]) {
 #pragma unroll
         for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int key = t * 64 + kb * 32 + 16 * (v >> 3) + 8 * hi + (v & 7);
-                if (key >= Tk) {
-#pragma unroll
-                    for (int qb = 0; qb < QB; ++qb) s[qb][kb][v] = -INFINITY;
-                }
+            for (int qb = 0; qb < QB; ++qb) {
+                const float x = PRE ? -m[qb] : 0.f;
+                s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][0], qf[qb][0], KEEP_M ? mneg[KEEP_M ? qb : 0] : f32x4{x, x, x, x}, 0, 0, 0);
             }
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) s[kb][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[kb][1], qf[qb][1], s[kb][qb], 0, 0, 0);
     };
-    // running-maximum bookkeeping of one tile: the reference maximum m only moves when the
-    // tile maximum exceeds it by more than RESCALE_LOG2 in the exponent (p <= 2^RESCALE_LOG2
-    // stays far inside fp32 / bf16 range), so the O and l rescale runs on the first tiles and
-    // almost never afterwards.  This lane's query is column l32, its keys are its registers.
-    // PRE: the scores arrive already shifted by m, so the tile maximum is the excess over it; the
-    // segment's first tile always re-references (m starts at 0, not at the scores' level).
-    auto update_max = [&](f32x16 (&s)[QB][2], bool first) {
+    // a group's last tile: keys from kend on get a score of -inf, and their values (padding holds whatever the
+    // caller's buffer held) become zeros, so that 0 * garbage stays 0
+    auto mask_scores = [&](int t, int h, f32x4 (&s)[2][QB]) {
+        const int left = kend - (t * 64 + h * 32 + quad * 8);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (kb * 4 + v >= left) {
+#pragma unroll
+                    for (int qb = 0; qb < QB; ++qb) s[kb][qb][v] = -INFINITY;
+                }
+    };
+    auto mask_values = [&](int t, int h, bf16x8 (&vf)[4]) {
+        const int left = kend - (t * 64 + h * 32 + quad * 8);
+        u32x4 keep;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) keep[i] = 2 * i + 1 < left ? 0xffffffffu : 2 * i < left ? 0xffffu : 0u;
+#pragma unroll
+        for (int db = 0; db < 4; ++db) vf[db] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vf[db]) & keep);
+    };
+    // Running-maximum bookkeeping of a half: the reference maximum m only moves when a
+    // score exceeds it by more than RESCALE_LOG2 in the exponent (p <= 2^RESCALE_LOG2
+    // stays far inside fp32 / bf16 range), so the O and row sum rescale runs on the first tiles and
+    // almost never afterwards.  This lane's queries are column l16 of each block, its keys are its registers; it looks at those alone
+    // (`over`), and any lane over the limit has all quads look together.
+    // PRE: the scores arrive already shifted by m, so their maximum is the excess over it; those of the half after it, where
+    // they have been formed (next), move along.  The first half always sets the reference (m starts at 0, not at the scores' level).
+    auto lane_max = [&](f32x4 (&s)[2][QB], int qb) {
+        float mx = fmaxf(s[0][qb][0], s[1][qb][0]);
+#pragma unroll
+        for (int v = 1; v < 4; ++v) mx = fmaxf(fmaxf(mx, s[0][qb][v]), s[1][qb][v]);
+        return mx;
+    };
+    auto over = [&](float mx, int qb) { return PRE ? mx > RESCALE_LOG2 : (mx - m[qb]) * c > RESCALE_LOG2; };
+    auto move_max = [&](int qb, float lane_mx, f32x4 (&s)[2][QB], f32x4 (*next)[QB], bool first) {
+        // the other quads hold the other keys of this query: lane swaps (vector-ALU operations, no LDS round trip)
+        const float mx = quads_max(lane_mx);
+        float alpha;
+        if (PRE) {
+            const float delta = first || mx > RESCALE_LOG2 ? mx : 0.f;
+            alpha = __builtin_amdgcn_exp2f(-delta);
+            m[qb] += delta;
+            if (KEEP_M) mneg[KEEP_M ? qb : 0] = f32x4{-m[qb], -m[qb], -m[qb], -m[qb]};
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb) {
+                s[kb][qb] -= delta;
+                if (next) next[kb][qb] -= delta;
+            }
+        } else {
+            const float mnew = over(mx, qb) ? mx : m[qb];
+            alpha = __builtin_amdgcn_exp2f((m[qb] - mnew) * c);
+            m[qb] = mnew;
+        }
+        ls[qb] *= alpha;
+#pragma unroll
+        for (int db = 0; db < 4; ++db) o[db][qb] *= alpha;
+    };
+    // The second attempt looks before it forms the probabilities.
+    auto look_first = [&](f32x4 (&s)[2][QB]) {
+        if (!TRY || !again) return;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-            float mx = fmaxf(s[qb][0][0], s[qb][1][0]);
-#pragma unroll
-            for (int v = 1; v < 16; ++v) mx = fmaxf(fmaxf(mx, s[qb][0][v]), s[qb][1][v]);
-            // the other half-wavefront holds the other 32 keys of this query: exchange the
-            // two halves with a lane swap (a vector-ALU operation, no LDS round trip)
-            float mx_lo, mx_hi;
-            both_halves(mx, mx_lo, mx_hi);
-            mx = fmaxf(mx_lo, mx_hi);
-            if (PRE) {
-                const bool need = first || mx > RESCALE_LOG2;
-                if (__builtin_amdgcn_ballot_w64(need) != 0ull) {
-                    const float delta = need ? mx : 0.f;
-                    const float alpha = __builtin_amdgcn_exp2f(-delta);
-                    m[qb] += delta;
-                    l[qb] *= alpha;
-#pragma unroll
-                    for (int db = 0; db < 2; ++db)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) o[qb][db][v] *= alpha;
-#pragma unroll
-                    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-                        for (int v = 0; v < 16; ++v) s[qb][kb][v] -= delta;
-                    set_mfrag(qb);
-                }
-                continue;
-            }
-            const bool need = (mx - m[qb]) * c > RESCALE_LOG2;
-            if (__builtin_amdgcn_ballot_w64(need) != 0ull) {
-                const float mnew = need ? mx : m[qb];
-                const float alpha = __builtin_amdgcn_exp2f((m[qb] - mnew) * c);
-                m[qb] = mnew;
-                l[qb] *= alpha;
-#pragma unroll
-                for (int db = 0; db < 2; ++db)
-#pragma unroll
-                    for (int v = 0; v < 16; ++v) o[qb][db][v] *= alpha;
-            }
+            const float mx = lane_max(s, qb);
+            if (__builtin_amdgcn_ballot_w64(over(mx, qb)) != 0ull) move_max(qb, mx, s, nullptr, false);
         }
     };
-    // p = exp2((s - m) * c) packed to bf16 in MFMA operand order; the row sum adds up the
-    // packed (rounded) values with a bf16 dot-product against ones, two per instruction, so
-    // the normaliser matches exactly what the second MFMA multiplies
-    auto exponentials = [&](f32x16 (&s)[QB][2], bf16x8 (&pf)[QB][2][2]) {
-        const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+    // p = exp2((s - m) * c) packed to bf16 in MFMA operand order
+    auto exponentials = [&](f32x4 (&s)[2][QB], bf16x8 (&pf)[QB]) {
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             const float mc = m[qb] * c;
-            float ls0 = 0.f, ls1 = 0.f;
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-                for (int g2 = 0; g2 < 2; ++g2) {
-                    bf16x8 pk;
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float p0 = __builtin_amdgcn_exp2f(PRE ? s[qb][kb][g2 * 8 + 2 * e] : s[qb][kb][g2 * 8 + 2 * e] * c - mc);
-                        const float p1 = __builtin_amdgcn_exp2f(PRE ? s[qb][kb][g2 * 8 + 2 * e + 1] : s[qb][kb][g2 * 8 + 2 * e + 1] * c - mc);
-                        const bf16x2 pp = {(__bf16)p0, (__bf16)p1};
-                        pk[2 * e] = pp[0];
-                        pk[2 * e + 1] = pp[1];
-                        if (e & 1) ls1 = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, ls1, false);
-                        else ls0 = __builtin_amdgcn_fdot2_f32_bf16(pp, ones, ls0, false);
-                    }
-                    pf[qb][kb][g2] = pk;
-                }
-            l[qb] += ls0 + ls1;
+                for (int v = 0; v < 4; ++v) pf[qb][kb * 4 + v] = (__bf16)__builtin_amdgcn_exp2f(PRE ? s[kb][qb][v] : s[kb][qb][v] * c - mc);
         }
     };
-    // O^T += V^T P^T.  With the K row order above, accumulator register v of block kb is key
-    // kb*32 + 16*(v/8) + 8*hi + v%8: sub-step (kb, g2) multiplies keys kb*32 + 16*g2 + 8*hi ..+8,
-    // the 16-byte chunk kb*4 + g2*2 + hi of a V^T row
-    auto accumulate_o = [&](int vslot, bf16x8 (&pf)[QB][2][2]) {
-        const lds_u32x4* lv = ldsV + vslot * 512;
-        // (row index laundered: the four swizzled chunk addresses are formed here, a few vector
-        // operations per tile, instead of living in registers through the whole key loop)
-        int lrow = l32;
-        asm volatile("" : "+v"(lrow));
+    // Kernels that measure every tile look afterwards, beside the exponentials, and form the probabilities once more where a
+    // score lies too far above the reference: 8 x 988 x 20 heads 54.4 -> 53.6 us, 8 x 512 x 10 14.5 -> 14.0.
+    auto look_after = [&](f32x4 (&s)[2][QB], f32x4 (&next)[2][QB], bf16x8 (&pf)[QB]) {
+        if (TRY) return;
+        float mx[QB];
+        bool need = false;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int qb = 0; qb < QB; ++qb) {
+            mx[qb] = lane_max(s, qb);
+            need = need || over(mx[qb], qb);
+        }
+        if (__builtin_amdgcn_ballot_w64(need) == 0ull) return;
 #pragma unroll
-            for (int g2 = 0; g2 < 2; ++g2)
+        for (int qb = 0; qb < QB; ++qb) move_max(qb, mx[qb], s, next, false);
+        exponentials(s, pf);
+    };
+    // O^T += V^T P^T.  The row sums are one more block of rows, of ones: the normaliser matches exactly what is multiplied,
+    // every lane has its queries' whole sums, and the vector ALU does nothing for them.  (v_dot2c_f32_bf16, which adds up two
+    // a lane, does not run beside MFMAs: 32 exponentials, 16 packings and 32 MFMAs take 593 clocks of a SIMD, 786 with 16 of those among them.)
+    u32x4 ones_bits = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+    asm volatile("" : "+v"(ones_bits));
+    const bf16x8 ones = __builtin_bit_cast(bf16x8, ones_bits);
+    auto accumulate_o = [&](bf16x8 (&vf)[4], bf16x8 (&pf)[QB]) {
 #pragma unroll
-                for (int db = 0; db < 2; ++db) {
-                    const int r = db * 32 + lrow;
-                    const bf16x8 a = __builtin_bit_cast(bf16x8, lv[r * 8 + aswz(r, kb * 4 + g2 * 2 + hi)]);
+        for (int db = 0; db < 4; ++db)
 #pragma unroll
-                    for (int qb = 0; qb < QB; ++qb)
-                        o[qb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[qb][kb][g2], o[qb][db], 0, 0, 0);
-                }
+            for (int qb = 0; qb < QB; ++qb) o[db][qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[db], pf[qb], o[db][qb], 0, 0, 0);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) ls[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qb], ls[qb], 0, 0, 0);
     };
 
-    // ---- prologue: the first two key tiles in flight, S of the first
-    issue_kv(s0, s0 & 1, 0);
-    if (s0 + 1 < s1) {
-        issue_kv(s0 + 1, (s0 + 1) & 1, 1);
-        attn_wait_vmcnt<4>();
-    } else {
-        attn_wait_vmcnt<0>();
+    // ---- prologue: the first two key tiles in flight, scores of the first half
+    if (live) {
+        issue_kv(g0, 0);
+        if (n > 1) {
+            issue_kv(g0 + 1, 1);
+            attn_wait_vmcnt<4>();
+        } else {
+            attn_wait_vmcnt<0>();
+        }
     }
     __syncthreads();
-    f32x16 sa[QB][2], sb[QB][2];
-    {
-        bf16x8 kf0[2][2];
-        load_kfrags(s0, 0, kf0);
-        compute_s(s0, sa, kf0);
+    const int last = g0 + n - 1;
+    const bool masked = last * 64 + 64 > kend;
+    f32x4 sa[2][QB], sb[2][QB];
+    bf16x8 kf[2][2], vf[4], pf[QB];
+    if (live) {
+        load_kfrags(0, 0, kf);
+        compute_s(sa, kf);
+        if (n == 1 && masked) mask_scores(last, 0, sa);
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) move_max(qb, lane_max(sa, qb), sa, nullptr, true);       // the first half sets the reference
     }
-    // unmeasured form: the segment's first tile sets the reference (a one-tile segment masks its tail first, below)
-    if (!MEASURE && s1 - s0 > 1) update_max(sa, true);
 
-    // ---- main loop, software-pipelined: the score MFMAs of tile t+1 are independent of the
-    // exponentials of tile t and sit in the same basic block, so the matrix pipe and the
-    // vector ALU overlap inside one wavefront.  Two tiles per trip (the score buffers swap
-    // roles), the last tile is peeled: nothing to prefetch, and only it may need masking.
-    int vslot = 0;
-    bf16x8 pf[QB][2][2];
-    // One pipelined step: finish tile t (scores in `cur`), start tile t+1 (scores into `nxt`).
-    // On entry tile t+1 is the only load in flight: wait for this wave's part, barrier (all
-    // of tile t+1 is in LDS, every wave is done with step t-1), then refill the slots step
-    // t-1 read last (K slot t%2 held K(t), V slot (t+2)%3 held V(t-1)) with tile t+2.
-    auto step = [&](int t, f32x16 (&cur)[QB][2], f32x16 (&nxt)[QB][2]) {
+    // ---- main loop, software-pipelined: the score MFMAs of one half are independent of the exponentials of the half before
+    // and sit in the same basic block, so the matrix pipe and the vector ALU overlap inside one wavefront.
+    // At the edge between two tiles the last of the old one's operands are in registers: when this wavefront's loads of the new
+    // one have landed, one barrier says that it is whole and the slot of the old one free, which takes the tile after next.
+#pragma unroll 1
+    for (int i = 0; i + 1 < n; ++i) {
+        const int slot = i & 1;
+        load_kfrags(slot, 1, kf);
+        load_vfrags(slot, 0, vf);
+        __builtin_amdgcn_sched_barrier(0);
+        look_first(sa);
+        compute_s(sb, kf);
+        exponentials(sa, pf);
+        look_after(sa, sb, pf);
+        accumulate_o(vf, pf);
+        load_vfrags(slot, 1, vf);
         attn_wait_vmcnt<0>();
         __syncthreads();
-        const int vnext2 = vslot == 0 ? 2 : vslot - 1;   // (vslot + 2) % 3
-        if (t + 2 < s1) issue_kv(t + 2, t & 1, vnext2);
-        bf16x8 kf0[2][2];
-        load_kfrags(t + 1, 0, kf0);
+        if (i + 2 < n) issue_kv(g0 + i + 2, slot);
+        load_kfrags(slot ^ 1, 0, kf);
         __builtin_amdgcn_sched_barrier(0);
-        if (MEASURE) update_max(cur, t == s0);
-        compute_s(t + 1, nxt, kf0);
-        exponentials(cur, pf);
-        accumulate_o(vslot, pf);
-        vslot = vslot == 2 ? 0 : vslot + 1;
-    };
-    const bool mask_last = ragged && s1 == nt;
-    int t = s0;
-#pragma unroll 1
-    for (; t + 2 < s1; t += 2) {
-        step(t, sa, sb);
-        step(t + 1, sb, sa);
-    }
-    if (t + 1 < s1) {            // one more pipelined step, last tile's scores end up in sb
-        step(t, sa, sb);
-        if (mask_last) mask_tail(nt - 1, sb);
-        update_max(sb, s1 - s0 == 1);
+        look_first(sb);
+        compute_s(sa, kf);
         exponentials(sb, pf);
-    } else {                     // last tile's scores are in sa
-        if (mask_last) mask_tail(nt - 1, sa);
-        update_max(sa, s1 - s0 == 1);
+        look_after(sb, sa, pf);
+        accumulate_o(vf, pf);
+    }
+    if (live) {
+        const int slot = (n - 1) & 1;
+        if (n > 1 && masked) mask_scores(last, 0, sa);
+        load_kfrags(slot, 1, kf);
+        load_vfrags(slot, 0, vf);
+        look_first(sa);
+        compute_s(sb, kf);
+        if (masked) {
+            mask_values(last, 0, vf);
+            mask_scores(last, 1, sb);
+        }
         exponentials(sa, pf);
+        look_after(sa, sb, pf);
+        accumulate_o(vf, pf);
+        look_first(sb);
+        load_vfrags(slot, 1, vf);
+        if (masked) mask_values(last, 1, vf);
+        exponentials(sb, pf);
+        look_after(sb, sa, pf);
+        accumulate_o(vf, pf);
     }
-    // the last tile's V^T landed before the barrier of the step before (or of the prologue)
-    if ((Tk & 7) && s1 == nt) {
-        zero_pad_keys(nt - 1, vslot);
-        __syncthreads();
-    }
-    accumulate_o(vslot, pf);
 
-    if (!MEASURE) {
+    if (TRY && !again) {
         // did the attempt stay in range?  (a row sum of +inf, or NaN anywhere, says no.)  The limit leaves room for
-        // what the tail adds up: two half-wavefronts' sums, of two halves of a cut tile, must stay finite, and the
-        // reciprocal of their sum a normal number.
-        float mag = l[0];
+        // what the tail adds up: the sums of two groups of two halves of a cut tile must stay finite, and the
+        // reciprocal of theirs a normal number.
+        float mag = 0.f;
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
+        for (int qb = 0; qb < QB; ++qb) {
+            mag += ls[qb][0];
 #pragma unroll
-            for (int v = 0; v < 16; ++v) mag += fabsf(o[0][db][v]);
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) mag += fabsf(o[db][qb][v]);
+        }
         const bool bad = __builtin_amdgcn_ballot_w64(!(mag <= 1.0e37f)) != 0ull;
         if (bad && lane == 0) *wg_redo = 1;
-        __syncthreads();             // (which also ends every wavefront's LDS reads of this attempt)
-        if (__builtin_expect(*wg_redo != 0, 0)) return true;
+    }
+    if ((TRY && !again) || GR > 1) __syncthreads();     // (which also ends every wavefront's reads of the tiles)
+    if (TRY && !again && __builtin_expect(__builtin_amdgcn_readfirstlane(*wg_redo) != 0, 0)) return true;
+
+    // the scores are in score units, or already in exponent units when the keys were prescaled
+    const float cm = PRE ? 1.0f : c;
+    float l[QB];
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) l[qb] = ls[qb][0];
+    // ---- the groups' states about their common maximum: each finishes KD of the four d blocks
+    f32x4 fin[KD][QB];
+    if constexpr (GR == 1) {
+#pragma unroll
+        for (int db = 0; db < KD; ++db)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) fin[db][qb] = o[db][qb];
+    } else {
+        lds_f32x4* const ex = reinterpret_cast<lds_f32x4*>(lds) + (tid & 255);
+#pragma unroll
+        for (int db = 0; db < KD; ++db)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                ex[grp * ATTN_GROUP_CH + (db * QB + qb) * 256] = grp ? o[db][qb] : o[KD + db][qb];
+                fin[db][qb] = grp ? o[KD + db][qb] : o[db][qb];
+            }
+        lds_f32* const mq = ml + wave * 16 * QB + l16;
+        if (quad == 0) {
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                mq[grp * 2 * BQ + qb * 16] = m[qb];
+                mq[(grp * 2 + 1) * BQ + qb * 16] = l[qb];
+            }
+        }
+        __syncthreads();
+        const int og = grp ^ 1;
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const float mo = mq[og * 2 * BQ + qb * 16], lo = mq[(og * 2 + 1) * BQ + qb * 16];
+            const float mm = fmaxf(m[qb], mo);
+            const float fs = __builtin_amdgcn_exp2f((m[qb] - mm) * cm), fo = __builtin_amdgcn_exp2f((mo - mm) * cm);
+            const float f0 = grp ? fo : fs, f1 = grp ? fs : fo;      // the first group's term, then the second's, in both
+            l[qb] = (grp ? lo : l[qb]) * f0 + (grp ? l[qb] : lo) * f1;
+            m[qb] = mm;
+#pragma unroll
+            for (int db = 0; db < KD; ++db) {
+                const f32x4 ov = ex[og * ATTN_GROUP_CH + (db * QB + qb) * 256];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) fin[db][qb][v] = (grp ? ov[v] : fin[db][qb][v]) * f0 + (grp ? fin[db][qb][v] : ov[v]) * f1;
+            }
+        }
     }
 
     // ---- a whole tile is normalised and stored; half of a cut tile leaves its state behind
     if (part < 0) {
-        store_queries(o[0], l[0], out, ldo, b, Tq, q0 + l32, head, hi);
-    } else if (!arrived) {
-        float* pp = parts + ((size_t)(tile - nfull) * 2 + part) * PART_FLOATS + tid;
+        store_queries(fin, l, out, ldo, b, Tq, q0 + l16, head, grp * KD, quad);
+        return false;
+    }
+    float* const pp = parts + ((size_t)(tile - nfull) * 2 + part) * PART;
+    float* const pm = pp + KD * QB * 4 * THREADS + wave * 16 * QB + l16;    // maxima, sums BQ further: one quad of the first group writes them
+    if (!arrived) {
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
+        for (int db = 0; db < KD; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) pp[(db * 16 + v) * 256] = o[0][db][v];
-        pp[32 * 256] = m[0];
-        pp[33 * 256] = l[0];
-    } else {
-        // Merge inside the launch: both halves leave their state (device-scope stores: the other
-        // half may run on another XCD), then count themselves in; the one that arrives second
-        // reads the first one's state and finishes the tile.  Nobody waits.  The counter is
-        // zero before the launch and the second arrival puts it back.
-        const int cut = tile - nfull;
-        float* pp = parts + ((size_t)cut * 2 + part) * PART_FLOATS + tid;
+            for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
-        for (int db = 0; db < 2; ++db)
+                for (int v = 0; v < 4; ++v) pp[((db * QB + qb) * 4 + v) * THREADS + tid] = fin[db][qb][v];
+        if (grp == 0 && quad == 0) {
 #pragma unroll
-            for (int v = 0; v < 16; ++v) __hip_atomic_store(pp + (db * 16 + v) * 256, o[0][db][v], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(pp + 32 * 256, m[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(pp + 33 * 256, l[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a device-scope store counts until it is visible at that scope
-        __syncthreads();                                    // ... for every wave of this half; LDS is free from here on
-        lds_i32* const first = reinterpret_cast<lds_i32*>(ldsK);
-        if (tid == 0) *first = __hip_atomic_fetch_add(arrived + cut, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __syncthreads();
-        if (*first == 1) {
-            if (tid == 0) __hip_atomic_store(arrived + cut, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const float* po = parts + ((size_t)cut * 2 + (1 - part)) * PART_FLOATS + tid;
-            const float mo = __hip_atomic_load(po + 32 * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const float lo = __hip_atomic_load(po + 33 * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            // the halves' maxima are in score units, or already in exponent units when the keys were prescaled
-            const float cm = PRE ? 1.0f : c;
-            const float mm = fmaxf(m[0], mo);
-            const float fs = __builtin_amdgcn_exp2f((m[0] - mm) * cm), fo = __builtin_amdgcn_exp2f((mo - mm) * cm);
-            // same expression, operand for operand, whichever half arrives second: first half's term, then second's
-            const float f0 = part == 0 ? fs : fo, f1 = part == 0 ? fo : fs;
-#pragma unroll
-            for (int db = 0; db < 2; ++db)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float ov = __hip_atomic_load(po + (db * 16 + v) * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    const float a0 = part == 0 ? o[0][db][v] : ov, a1 = part == 0 ? ov : o[0][db][v];
-                    o[0][db][v] = a0 * f0 + a1 * f1;
-                }
-            const float lsum = (part == 0 ? l[0] : lo) * f0 + (part == 0 ? lo : l[0]) * f1;
-            store_queries(o[0], lsum, out, ldo, b, Tq, q0 + l32, head, hi);
+            for (int qb = 0; qb < QB; ++qb) pm[qb * 16] = m[qb], pm[BQ + qb * 16] = l[qb];
         }
+        return false;
+    }
+    // Merge inside the launch: both halves leave their state (device-scope stores: the other
+    // half may run on another XCD), then count themselves in; the one that arrives second
+    // reads the first one's state and finishes the tile.  Nobody waits.  The counter is
+    // zero before the launch and the second arrival puts it back.
+    const int cut = tile - nfull;
+    auto put = [](float* p, float x) { __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    auto get = [](const float* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+#pragma unroll
+    for (int db = 0; db < KD; ++db)
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) put(pp + ((db * QB + qb) * 4 + v) * THREADS + tid, fin[db][qb][v]);
+    if (grp == 0 && quad == 0) {
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) put(pm + qb * 16, m[qb]), put(pm + BQ + qb * 16, l[qb]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a device-scope store counts until it is visible at that scope
+    __syncthreads();                                    // ... for every wave of this half; LDS is free from here on
+    lds_i32* const first = reinterpret_cast<lds_i32*>(lds);
+    if (tid == 0) *first = __hip_atomic_fetch_add(arrived + cut, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    if (*first == 1) {
+        if (tid == 0) __hip_atomic_store(arrived + cut, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const ptrdiff_t other = (part ? -1 : 1) * (ptrdiff_t)PART;
+        float f0[QB], f1[QB], lsum[QB];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            const float mo = get(pm + other + qb * 16), lo = get(pm + other + BQ + qb * 16);
+            const float mm = fmaxf(m[qb], mo);
+            const float fs = __builtin_amdgcn_exp2f((m[qb] - mm) * cm), fo = __builtin_amdgcn_exp2f((mo - mm) * cm);
+            // same expression, operand for operand, whichever half arrives second: first half's term, then second's
+            f0[qb] = part == 0 ? fs : fo, f1[qb] = part == 0 ? fo : fs;
+            lsum[qb] = (part == 0 ? l[qb] : lo) * f0[qb] + (part == 0 ? lo : l[qb]) * f1[qb];
+        }
+#pragma unroll
+        for (int db = 0; db < KD; ++db)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const float ov = get(pp + other + ((db * QB + qb) * 4 + v) * THREADS + tid);
+                    const float a0 = part == 0 ? fin[db][qb][v] : ov, a1 = part == 0 ? ov : fin[db][qb][v];
+                    fin[db][qb][v] = a0 * f0[qb] + a1 * f1[qb];
+                }
+        store_queries(fin, lsum, out, ldo, b, Tq, q0 + l16, head, grp * KD, quad);
     }
     return false;
 }
 
-template <bool PRE, bool TRY, bool AHEAD>
-__global__ __launch_bounds__(256, 3) void attention_kernel(const uint16_t* __restrict__ q, int64_t ldq,
+template <int QB, int GR, bool PRE, bool TRY, bool AHEAD>
+__global__ __launch_bounds__(256 * GR, GR == 1 && QB == 2 ? 3 : 2) void attention_kernel(const uint16_t* __restrict__ q, int64_t ldq,
                                                         const uint16_t* __restrict__ k, int64_t ldk,
                                                         const uint16_t* __restrict__ vt, int64_t ldvt,
                                                         uint16_t* __restrict__ out, int64_t ldo,
@@ -549,56 +612,54 @@ __global__ __launch_bounds__(256, 3) void attention_kernel(const uint16_t* __res
         // (the arguments in one batch, not a second one behind the branch)
         asm volatile("" ::"s"(q), "s"(ldq), "s"(k), "s"(ldk), "s"(vt), "s"(ldvt), "s"(Tq), "s"(Tk), "s"(Tkp), "s"(heads), "s"(qtiles));
         if ((int)blockIdx.x >= total) {
-            read_ahead<16>(ra, (int)blockIdx.x - total, (int)threadIdx.x);
+            read_ahead<16>(ra, ((int)blockIdx.x - total) * GR + (int)(threadIdx.x >> 8), (int)threadIdx.x & 255);
             return;
         }
     }
-    __shared__ u32x4 ldsK[2 * 64 * 8];
-    __shared__ u32x4 ldsV[3 * 64 * 8];
+    __shared__ u32x4 tiles[GR * ATTN_GROUP_CH];
+    __shared__ float maxima[GR == 1 ? 1 : GR * 2 * 64 * QB];
     __shared__ int32_t wg_redo;         // some wavefront's unmeasured attempt overflowed
-    lds_u32x4* const lk = (lds_u32x4*)ldsK;
-    lds_u32x4* const lv = (lds_u32x4*)ldsV;
+    lds_u32x4* const lk = (lds_u32x4*)tiles;
+    lds_f32* const ml = (lds_f32*)maxima;
     lds_i32* const redo = (lds_i32*)&wg_redo;
     if (TRY && threadIdx.x == 0) *redo = 0;    // (ordered before its first use by the key loop's barriers)
-    if (!TRY) {
-        (void)attention_body<PRE, true>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, total, parts, arrived, lk, lv, redo,
-                                        (int)threadIdx.x, (int)blockIdx.x);
-    } else if (attention_body<PRE, false>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, total, parts, arrived, lk, lv, redo,
-                                   (int)threadIdx.x, (int)blockIdx.x)) {
-        // Second attempt, in the measured form, for inputs whose scores climb by more than 2^100
-        // over a key range.  Its inputs pass through empty assembly statements so that it shares
-        // no value with the first attempt: nothing of it may stay in registers through the first
-        // attempt's key loop and tail.
-        int tid2 = threadIdx.x, bid2 = blockIdx.x;
-        const uint16_t *q2 = q, *k2 = k, *vt2 = vt;
-        uint16_t* out2 = out;
-        lds_u32x4 *lk2 = lk, *lv2 = lv;
-        asm volatile("" : "+v"(tid2), "+s"(bid2), "+s"(q2), "+s"(k2), "+s"(vt2), "+s"(out2), "+s"(lk2), "+s"(lv2));
-        (void)attention_body<PRE, true>(q2, ldq, k2, ldk, vt2, ldvt, out2, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, total, parts, arrived, lk2, lv2,
-                                        redo, tid2, bid2);
-    }
+    // (One body for both attempts: as two, the second one's values took registers from the first, 65 to 150 of them spilled.)
+    bool again = false;
+    while (attention_body<QB, GR, PRE, TRY>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, total, parts, arrived, lk, ml, redo,
+                                            (int)threadIdx.x, (int)blockIdx.x, again))
+        again = true;
 }
 
-// One workgroup per cut tile: combine the two halves about their common maximum.
-__global__ __launch_bounds__(256) void attention_merge_kernel(const float* __restrict__ parts, uint16_t* __restrict__ out, int64_t ldo,
+// One workgroup per cut tile: combine the two halves about their common maximum.  Threads as in the kernel that left them.
+template <int QB, int GR>
+__global__ __launch_bounds__(256 * GR) void attention_merge_kernel(const float* __restrict__ parts, uint16_t* __restrict__ out, int64_t ldo,
                                                               int Tq, int heads, int qtiles, int nfull, float c) {
+    constexpr int BQ = 64 * QB, KD = 4 / GR, THREADS = 256 * GR, PART = KD * QB * 4 * THREADS + 2 * BQ;
     const int tile = nfull + blockIdx.x;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int l32 = lane & 31, hi = lane >> 5;
-    const float* pa = parts + ((size_t)blockIdx.x * 2) * PART_FLOATS + tid;
-    const float* pb = pa + PART_FLOATS;
-    const float ma = pa[32 * 256], mb = pb[32 * 256];
-    const float mm = fmaxf(ma, mb);
-    const float fa = __builtin_amdgcn_exp2f((ma - mm) * c), fb = __builtin_amdgcn_exp2f((mb - mm) * c);
-    f32x16 o[2];
+    const int tid = threadIdx.x, lane = tid & 63, wave = (tid >> 6) & 3, grp = tid >> 8;
+    const int l16 = lane & 15, quad = lane >> 4;
+    const float* pa = parts + ((size_t)blockIdx.x * 2) * PART;
+    const float* pb = pa + PART;
+    const int at = KD * QB * 4 * THREADS + wave * 16 * QB + l16;
+    f32x4 o[KD][QB];
+    float l[QB];
 #pragma unroll
-    for (int db = 0; db < 2; ++db)
+    for (int qb = 0; qb < QB; ++qb) {
+        const float ma = pa[at + qb * 16], mb = pb[at + qb * 16];
+        const float mm = fmaxf(ma, mb);
+        const float fa = __builtin_amdgcn_exp2f((ma - mm) * c), fb = __builtin_amdgcn_exp2f((mb - mm) * c);
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[db][v] = pa[(db * 16 + v) * 256] * fa + pb[(db * 16 + v) * 256] * fb;
-    const float l = pa[33 * 256] * fa + pb[33 * 256] * fb;
+        for (int db = 0; db < KD; ++db)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int i = ((db * QB + qb) * 4 + v) * THREADS + tid;
+                o[db][qb][v] = pa[i] * fa + pb[i] * fb;
+            }
+        l[qb] = pa[at + BQ + qb * 16] * fa + pb[at + BQ + qb * 16] * fb;
+    }
     const int qt = tile % qtiles;
     const int head = (tile / qtiles) % heads, b = tile / (qtiles * heads);
-    store_queries(o, l, out, ldo, b, Tq, qt * 128 + wave * 32 + l32, head, hi);
+    store_queries(o, l, out, ldo, b, Tq, qt * BQ + wave * 16 * QB + l16, head, grp * KD, quad);
 }
 
 // CUs of the current device (cached; the query allocates nothing)
@@ -637,6 +698,28 @@ size_t attention_scratch_bytes(int Bn, int Tq, int Tk, int heads, bool block) {
     return (size_t)attention_nsplit(Bn, Tq, Tk, heads, block) * 2 * PART_FLOATS * sizeof(float);
 }
 
+// Which kernel, and its tiles: whole ones, and ones whose key range is cut in half (nsplit of them; 128 queries each, as the scratch
+// memory is laid out for).
+//   Up to one tile of 128 queries per CU the workgroup's key range goes to two groups of wavefronts, from eight key tiles on (us,
+// standalone, one group / two: 1 x 1024 x 20 heads 17.5 / 15.4, 1 x 4096 x 5 50.5 / 41.0, 1 x 512 x 5 10.2 / 9.6, 2 x 256 x 10 8.4 / 8.5); cut tiles
+// too, where their halves are one per CU.
+//   Tiles of 256 queries, 64 to a wavefront, read K and V^T half as often, but few of them load the CUs unevenly, and two wavefronts
+// to a SIMD is all that the registers hold.  With two groups of wavefronts where they are one round (128 / 256 queries: 1 x 4096 x 10 71.3 / 65.9,
+// 2 x 2500 x 10 47.5 / 44.9, 2 x 1500 x 20 31.6 / 31.0, 2 x 1024 x 20 23.9 / 25.6), with one where rounds of them come out ahead (4 x 3000 x 10 105 / 98,
+// 4 x 4096 x 20 331 / 311, 8 x 1500 x 20 106 / 102; 2 x 4096 x 20, three rounds for five of the small ones, 171 / 189).
+struct AttnPlan { int qb, gr, qtiles, nfull; };
+static AttnPlan attention_plan(int Bn, int Tq, int nt, int heads, int nsplit) {
+    AttnPlan p;
+    const long cus = device_cus(), tiles = (long)((Tq + 127) / 128) * heads * Bn, wide = (long)((Tq + 255) / 256) * heads * Bn;
+    p.qb = 2;
+    p.gr = (nsplit > 0 ? tiles <= cus / 2 : tiles <= cus && nt >= 8) ? 2 : 1;
+    if (nsplit == 0 && tiles > cus && wide <= cus && nt >= 24) p.qb = 4, p.gr = 2;
+    if (nsplit == 0 && wide > cus && nt >= 20 && (double)((wide + cus - 1) / cus) * 1.85 < (double)((tiles + cus - 1) / cus)) p.qb = 4;
+    p.qtiles = (Tq + 64 * p.qb - 1) / (64 * p.qb);
+    p.nfull = p.qtiles * heads * Bn - nsplit;
+    return p;
+}
+
 int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t ldk,
                      const uint16_t* vt, int64_t ldvt, uint16_t* out, int64_t ldo,
                      int Bn, int Tq, int Tk, int Tkp, int heads, bool k_prescaled, void* scratch, size_t scratch_bytes, int* cut_tiles,
@@ -648,32 +731,39 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     *cut_tiles = 0;
     if (Bn <= 0 || Tq <= 0 || heads <= 0) return SD_OK;
     const float c = 0.125f * 1.44269504088896340736f;   // 1/sqrt(64) * log2(e)
-    const int qtiles = (Tq + 127) / 128;
-    const long tiles = (long)qtiles * heads * Bn;
-    SD_REQUIRE(tiles < (1l << 30), SD_EINVAL, "attention: problem too large");
+    SD_REQUIRE((long)((Tq + 127) / 128) * heads * Bn < (1l << 30), SD_EINVAL, "attention: problem too large");
     int nsplit = attention_nsplit(Bn, Tq, Tk, heads, k_prescaled);
     const size_t need = (size_t)nsplit * 2 * PART_FLOATS * sizeof(float);
     if (nsplit > 0 && !(scratch && scratch_bytes >= need && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0)) nsplit = 0;
-    const int nfull = (int)tiles - nsplit;
-    if (nsplit > arrived_n) arrived = nullptr;   // not enough counters: the halves are merged by the second kernel
-    // The unmeasured attempt saves a maximum per score tile and costs its check and the registers that the second
-    // attempt's code takes from it.  Against measuring every tile: prescaled keys 84 us for 90 at 4096 keys, and
-    // ahead at 77 too (a 32 x 32 stack 2690 for 2760); plain keys 355 for 372 at 8 x 3929 x 10 heads, 116 for 123 at
-    // 8 x 1434 x 20, 22.7 for 22.9 at 2 x 1330 x 10, but 59.7 for 57.6 at 8 x 988 x 20.
     const int nt = (Tk + 63) / 64;
+    const AttnPlan plan = attention_plan(Bn, Tq, nt, heads, nsplit);
+    if (nsplit > arrived_n) arrived = nullptr;   // not enough counters: the halves are merged by the second kernel
+    // The unmeasured attempt saves a maximum per half tile and costs its check: from 20 tiles of plain keys on, always with prescaled ones.
     *cut_tiles = arrived ? 0 : nsplit;
     // Read-ahead in the room that three workgroups to a CU leave: 8 MB and 2 MB per key tile, which the launch is long
     // enough for.  (With 1 MB per key tile the queue falls behind at 32 x 32 tokens: 2540 us per stack for 2500, 2658 without any.)
-    const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, 3l * device_cus() - attention_grid(nfull, nsplit), 16) : ReadRanges{};
-    if (SD_DRY_RUN("attention%s%s%s%s; ", k_prescaled ? " prescaled" : "", k_prescaled || nt >= 20 ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "", dry_ranges(ra))) return SD_OK;
+    // Workgroups of two groups have a CU each; what reads ahead runs beside them and behind.
+    const int grid = attention_grid(plan.nfull, nsplit);
+    const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, plan.gr == 1 ? 3l * device_cus() - grid : 448, 16) : ReadRanges{};
+    if (SD_DRY_RUN("attention%s%s%s%s%s; ", k_prescaled ? " prescaled" : "", k_prescaled || nt >= 20 ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "", dry_ranges(ra), dry_tiles(64 * plan.qb, plan.gr))) return SD_OK;
     auto go = [&](auto kernel, const auto& ranges) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(attention_grid(nfull, nsplit) + ra.wgs)), dim3(256), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
-                           qtiles, c, nfull, nsplit, static_cast<float*>(scratch), arrived, ranges);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(grid + (ra.wgs + plan.gr - 1) / plan.gr)), dim3(256 * plan.gr), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
+                           plan.qtiles, c, plan.nfull, nsplit, static_cast<float*>(scratch), arrived, ranges);
     };
-    if (k_prescaled && ra.wgs) go(attention_kernel<true, true, true>, ra);
-    else if (k_prescaled) go(attention_kernel<true, true, false>, NoRanges{});
-    else if (nt >= 20) go(attention_kernel<false, true, false>, NoRanges{});
-    else go(attention_kernel<false, false, false>, NoRanges{});
+    auto kind = [&](auto qb, auto gr) {
+        constexpr int QB = decltype(qb)::value, GR = decltype(gr)::value;
+        if (k_prescaled && ra.wgs) go(attention_kernel<QB, GR, true, true, true>, ra);
+        else if (k_prescaled) go(attention_kernel<QB, GR, true, true, false>, NoRanges{});
+        else if (nt >= 20) go(attention_kernel<QB, GR, false, true, false>, NoRanges{});
+        else go(attention_kernel<QB, GR, false, false, false>, NoRanges{});
+    };
+    using I1 = std::integral_constant<int, 1>;
+    using I2 = std::integral_constant<int, 2>;
+    using I4 = std::integral_constant<int, 4>;
+    if (plan.qb == 4 && plan.gr == 2) kind(I4{}, I2{});
+    else if (plan.qb == 4) kind(I4{}, I1{});
+    else if (plan.gr == 2) kind(I2{}, I2{});
+    else kind(I2{}, I1{});
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }
@@ -683,10 +773,12 @@ int launch_attention_merge(const void* scratch, uint16_t* out, int64_t ldo, int 
     if (cut_tiles <= 0 || SD_DRY_RUN("merge; ")) return SD_OK;
     // the halves' maxima are in score units, or already in exponent units when the keys were prescaled
     const float c = k_prescaled ? 1.0f : 0.125f * 1.44269504088896340736f;
-    const int qtiles = (Tq + 127) / 128;
-    const int nfull = qtiles * heads * Bn - cut_tiles;
-    hipLaunchKernelGGL(attention_merge_kernel, dim3((unsigned)cut_tiles), dim3(256), 0, stream, static_cast<const float*>(scratch), out, ldo,
-                       Tq, heads, qtiles, nfull, c);
+    const AttnPlan p = attention_plan(Bn, Tq, 0, heads, cut_tiles);
+        auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)cut_tiles), dim3(256 * p.gr), 0, stream, static_cast<const float*>(scratch), out, ldo, Tq, heads, p.qtiles, p.nfull, c);
+    };
+    if (p.gr == 2) go(attention_merge_kernel<2, 2>);
+    else go(attention_merge_kernel<2, 1>);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }

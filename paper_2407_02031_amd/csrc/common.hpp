@@ -88,6 +88,8 @@ bool dry_note(const char* fmt, ...);   // true
 // what a note adds where details are asked for (sd_dry_run(2)), empty elsewhere
 const char* dry_detail(const char* fmt, ...);
 const char* dry_ranges(const ReadRanges& ra);
+// sd_dry_run(3): an attention workgroup
+const char* dry_tiles(int queries, int groups);
 #define SD_DRY_RUN(...) (__builtin_expect(::sd::g_dry_run, 0) && ::sd::dry_note(__VA_ARGS__))
 
 #define SD_HIP_CHECK(expr)                                         \

@@ -542,6 +542,55 @@ def test_attention_plain_scores_that_climb(B, boost, Tq, Tk, heads):
     assert max(per_tile) <= BF16_TOL
 
 
+# The kernels that a launch's tile count chooses (queries of a workgroup, groups of wavefronts that share its key range), each with a key range of an odd number
+# of tiles and a ragged last one: ordinary scores, and scores that climb by more than 2^128 in a middle tile (where the first attempt, if
+# any, overflows).
+@pytest.mark.parametrize("climb", [False, True])
+@pytest.mark.parametrize("Bn,Tq,Tk,heads,queries,groups", [(1, 130, 64 * 8 + 3, 3, 128, 2), (1, 200, 64 * 20 + 9, 2, 128, 2), (1, 1100, 64 * 24 + 61, 30, 256, 2),
+                                                           (1, 1000, 64 * 20 + 10, 100, 256, 1), (1, 300, 64 * 6 + 40, 2, 128, 1)])
+def test_attention_kernels_by_tile_count(B, Bn, Tq, Tk, heads, queries, groups, climb):
+    r = rng(Tq + Tk)
+    C = heads * 64
+    nt = (Tk + 63) // 64
+    level = np.zeros(nt, np.float32)
+    level[nt // 2], level[nt - 1] = 150.0, 60.0
+    n0 = r.choice([-1.0, 1.0], 64).astype(np.float32)
+    sign = np.where(r.random((Bn, Tq, heads, 1)) < 0.5, 1.0, -1.0).astype(np.float32)
+    q = (0.3 * r.standard_normal((Bn, Tq, heads, 64), dtype=np.float32) + (sign * n0 if climb else 0)).astype(np.float32)
+    k = r.standard_normal((Bn, Tk, heads, 64), dtype=np.float32) * (0.3 if climb else 3.0) + (level[np.arange(Tk) // 64][None, :, None, None] * n0 / 8.0 if climb else 0)
+    q, k = G.bf16_round(q).reshape(Bn, Tq, C), G.bf16_round(k.astype(np.float32)).reshape(Bn, Tk, C)
+    v = G.bf16_round(r.standard_normal((Bn, Tk, C), dtype=np.float32))
+    args = (dev(q, B), dev(k, B), vt_layout(v, B), heads)
+    with B.dry_run(detail=3) as names:
+        B.attention_fwd(*args)
+    assert names[0] == "attention%s, %d queries, %d groups" % (" try" if nt >= 20 else "", queries, groups)
+    got = host(B.attention_fwd(*args))
+    assert np.isfinite(got).all()
+    h = np.array(sorted({0, heads // 2, heads - 1}))
+    cols = (h[:, None] * 64 + np.arange(64)).ravel()
+    ref = O.attention(q[..., cols], k[..., cols], v[..., cols], len(h), dtype=np.float32 if Tq >= 1000 else np.float64)
+    per_tile = [rel_err(got[:, i:i + 128][..., cols], ref[:, i:i + 128]) for i in range(0, Tq, 128)]
+    assert max(per_tile) <= BF16_TOL
+
+
+# ... and inside a block, with prescaled keys: 256 queries and one group
+def test_attn_block_of_many_tiles(B):
+    import torch
+    Bn, T, C = 8, 1290, 640
+    r = rng(T)
+    ps = [mkproj(r, C, C, 0, bias=i == 3, scale=1.0) for i in range(4)]
+    g, b = G.bf16_round((1 + 0.02 * r.standard_normal(C)).astype(np.float32)), G.bf16_round((0.02 * r.standard_normal(C)).astype(np.float32))
+    x = r.standard_normal((Bn, T, C), dtype=np.float32)
+    args = (torch.from_numpy(x).cuda(), None, dev(g, B), dev(b, B), *[B.Proj.from_numpy(p) for p in ps], C // 64)
+    with B.dry_run(detail=3) as names:
+        B.attn_block_fwd(*args)
+    assert "attention prescaled try, 256 queries, 1 groups" in names
+    y = host(B.attn_block_fwd(*args))
+    for s in (0, Bn - 1):        # (samples do not meet)
+        ref = O.attn_sublayer(x[s:s + 1], None, g, b, *ps, C // 64)
+        assert rel_err(y[s:s + 1] - x[s:s + 1], ref - x[s:s + 1]) <= BF16_TOL
+
+
 # Row sums just under the top of the fp32 range: one key of each half-wavefront's octets scores 2^127.3 above the first key
 # tile, so either half's sum is finite and their sum is not.  (1217 keys and more take the attempt without maxima; the values
 # are small, so that the accumulators stay in range.)  Whole tiles, and tiles whose halves are merged.
