@@ -10,12 +10,14 @@
 // store.
 //
 // Tiling: BM x BN output tile per workgroup, BK = 64, WGM x WGN wavefronts, each owning
-// (BM/WGM) x (BN/WGN) as 32x32x16 bf16 MFMA tiles with fp32 accumulators.
+// (BM/WGM) x (BN/WGN) as 16x16x32 bf16 MFMA tiles with fp32 accumulators (32x32x16 ones cost more
+// energy, and the chip lowers its clock under them: 8192x4096x4096 223 -> 211 us, 16384x1280x5120 + 64 249 -> 240, 8 x 4096 rows of
+// 640 channels with four adapters 43.4 -> 42.6, 5000x640x2560 + 64 28.4 -> 26.8; same bits; 3000x1280x5120 + 64 54.4 -> 57.3).
 // Pipeline: operand tiles go global -> LDS directly (wave-wide 1 KB loads of 16-byte
-// chunks, XOR-swizzled so the 32 rows one MFMA operand read touches fall in distinct
+// chunks, XOR-swizzled so the 16 rows one MFMA operand read touches fall in distinct
 // banks) into a ring of STAGES tiles, STAGES-1 of them in flight ahead of the one being
-// multiplied; the operand fragments of k-step kk+1 are read from LDS while the MFMAs of k-step
-// kk run, across the edge of two tiles too, and a tile's loads are dealt between the MFMAs of a
+// multiplied; operand blocks are read from LDS a few MFMAs ahead of their use,
+// across the edge of two tiles too, and a tile's loads are dealt between the MFMAs of a
 // step.  What bounds it: the L2 -> LDS operand stream, 100-125 GB/s per CU with all of them at it
 // (a stream alone: 145 with few CUs), then the MFMAs, whose rate under load is 1.6 PFLOP/s; the
 // two overlap only as far as no wavefront waits to issue a load.  8192x4096x4096, 128x128 tiles,
@@ -26,7 +28,7 @@
 
 namespace sd {
 
-constexpr int EPI_STRIDE = 72;   // floats per staged row: 4 rows apart differ by 128 B mod 256 (no bank overlap)
+constexpr int EPI_STRIDE = 68;   // floats per staged row: 16 rows apart by 4 banks, 16 bytes of each
 
 // Tiles that gave up waiting for a producer's flag (never, unless the dependency protocol is
 // broken): the wait is bounded so that every wavefront exits whatever happens.
@@ -70,14 +72,15 @@ template <int BM, int BN, int BK, int WGM, int WGN, int STAGES, bool GEGLU, bool
 __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, u32x4* const lds) {
     constexpr int NW = WGM * WGN;
     constexpr int WM = BM / WGM, WN = BN / WGN;
-    constexpr int MI = WM / 32, NI = WN / 32;
+    constexpr int MI = WM / 16, NI = WN / 16;  // 16x16 blocks of a wavefront
     constexpr int CPR = BK / 8;                // 16-byte chunks per LDS row
     constexpr int RPB = 64 / CPR;              // tile rows per 1 KB block (one wave-wide load)
-    constexpr int KK = BK / 16;                // MFMA k-steps per tile
+    constexpr int SLOTS = 2 * NI;              // a tile is two 32 deep k-steps of NI blocks of Q; a slot multiplies one of them by the MI blocks of P
+    constexpr int RING = NI < 4 ? NI : 4;      // blocks of Q in registers
     constexpr int NBLK = (BM + BN) / RPB;      // 1 KB blocks per stage
     constexpr int LPT = NBLK / NW;             // direct-to-LDS loads per wave (= per lane) per tile
     constexpr int STAGE = (BM + BN) * CPR;     // 16-byte chunks per stage
-    static_assert(BK == 64 || BK == 32, "BK");
+    static_assert(BK == 64 && SLOTS % RING == 0, "BK");
     static_assert(NBLK % NW == 0, "tile/waves mismatch");
     static_assert(!GEGLU || (NI % 2 == 0), "GEGLU needs value/gate column-block pairs per wave");
     static_assert(STAGES >= 2 && STAGES <= 5, "ring depth");
@@ -95,7 +98,7 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int l32 = lane & 31, hi = lane >> 5;
+    const int l16 = lane & 15, quad = lane >> 4;
     const int wm = (wave / WGN) * WM, wn = (wave % WGN) * WN;
 
     // ---- dependency on a producer problem of this launch.  The flags are read once now (the
@@ -118,12 +121,12 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
         f_early = __hip_atomic_load(fptr, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= P.wait_need;
     }
 
-    // Q-operand (weight) row of tile row j.  GEGLU: 32-row blocks alternate value / gate
-    // rows of the same 32 output columns, so one lane ends up holding both halves.
+    // Q-operand (weight) row of tile row j.  GEGLU: 16-row blocks alternate value / gate
+    // rows of the same 16 output columns, so one lane ends up holding both halves.
     auto qrow = [&](int j) -> int {
         if (GEGLU) {
-            int blk = j >> 5;
-            int col = n0 + (blk >> 1) * 32 + (j & 31);
+            int blk = j >> 4;
+            int col = n0 + (blk >> 1) * 16 + (j & 15);
             col = col < N ? col : N - 1;
             return col + ((blk & 1) ? P.geglu_F : 0);
         } else {
@@ -224,50 +227,56 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
         }
     };
 
-    f32x16 acc[MI][NI];
+    f32x4 acc[MI][NI];
 #pragma unroll
     for (int mi = 0; mi < MI; ++mi)
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mi][ni][v] = 0.f;
+        for (int ni = 0; ni < NI; ++ni) acc[mi][ni] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // operand fragments of two k-steps: the one being multiplied and the next, which is read
-    // from LDS meanwhile, also across the edge between two tiles (KK is even: the first k-step
-    // of every tile uses set 0)
-    bf16x8 af[2][MI], bfr[2][NI];
-    auto fetch = [&](int st, int kk, int fs) {
-        const u32x4* la = lds + st * STAGE;
-        const u32x4* lb = la + BM * CPR;
+    // operands in registers: the P blocks of both k-steps, and a ring of Q blocks.  Slot s multiplies Q block s % NI in k-step
+    // s / NI out of bfr[s % RING], which is then refilled for slot s + RING, over the edge between two tiles too.
+    // The MFMA takes the Q rows first: a lane holds four consecutive columns of one row of the result.
+    bf16x8 af[2][MI], bfr[RING];
+    const int lrow = l16 * CPR, lsw = (l16 >> 1) & 7;       // (rows 16 apart share the swizzle)
+    auto frag = [&](int st, int ks) { return lds + (st * STAGE + lrow + ((ks * 4 + quad) ^ lsw)); };
+    auto fetch_p = [&](int st, int ks) {
+        const u32x4* const la = frag(st, ks) + wm * CPR;
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi) {
-            const int r = wm + mi * 32 + l32;
-            af[fs][mi] = __builtin_bit_cast(bf16x8, la[r * CPR + swz<CPR>(r, kk * 2 + hi)]);
-        }
+        for (int mi = 0; mi < MI; ++mi) af[ks][mi] = __builtin_bit_cast(bf16x8, la[mi * 16 * CPR]);
+    };
+    auto fetch_q = [&](int st, int s) { bfr[s % RING] = __builtin_bit_cast(bf16x8, (frag(st, s / NI) + (BM + wn) * CPR)[(s % NI) * 16 * CPR]); };
+    auto multiply = [&](int s) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) {
-            const int r = wn + ni * 32 + l32;
-            bfr[fs][ni] = __builtin_bit_cast(bf16x8, lb[r * CPR + swz<CPR>(r, kk * 2 + hi)]);
+        for (int mi = 0; mi < MI; ++mi)
+            acc[mi][s % NI] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[s % RING], af[s / NI][mi], acc[mi][s % NI], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // A step: the last RING slots of a tile, whose operands are in registers, while the first of the next (in stage sn) are read
+    // (`edge`); then the others of that one (`head`).  The loads of another tile are dealt over it, a few behind each
+    // slot's MFMAs (`load(j)` issues one): a wavefront issues in order, and a burst of loads would hold up its
+    // MFMAs until the address unit has taken the last one, at 16 clocks apiece for the whole CU.
+    auto deal = [&](auto load, int i) {
+#pragma unroll
+        for (int j = i * LPT / SLOTS; j < (i + 1) * LPT / SLOTS; ++j) load(j);
+    };
+    auto edge = [&](int sn, auto load) {
+        fetch_p(sn, 0);
+#pragma unroll
+        for (int i = 0; i < RING; ++i) {
+            multiply(SLOTS - RING + i);
+            deal(load, i);
+            fetch_q(sn, i);
         }
     };
-    // MFMAs of one k-step out of fragment set `fs`, with loads [j0, j1) of a tile dealt between them
-    // (`load(j)` issues one): a wavefront issues in order, and a burst of loads would hold up its
-    // MFMAs until the address unit has taken the last one, at 16 clocks apiece for the whole CU
-    auto multiply = [&](int fs, auto load, int j0, int j1) {
-        // keep the reads of the next k-step ahead of the MFMAs of this one: left alone, the
-        // scheduler sinks them to just before their use and exposes the LDS latency
-        __builtin_amdgcn_sched_barrier(0);
+    auto head = [&](int st, auto load) {
 #pragma unroll
-        for (int i = 0; i < MI * NI; ++i) {
-            const int mi = i / NI, ni = i % NI;
-            acc[mi][ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[fs][mi], bfr[fs][ni], acc[mi][ni], 0, 0, 0);
-            const int a = j0 + (j1 - j0) * i / (MI * NI), b = j0 + (j1 - j0) * (i + 1) / (MI * NI);
-            if (a < b) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int j = a; j < b; ++j) load(j);
-            if (a < b) __builtin_amdgcn_sched_barrier(0);
+        for (int s = 0; s < SLOTS - RING; ++s) {
+            if (s == 0) fetch_p(st, 1);
+            multiply(s);
+            deal(load, RING + s);
+            fetch_q(st, s + RING);
         }
-        __builtin_amdgcn_sched_barrier(0);
     };
     auto no_load = [](int) {};
 
@@ -285,18 +294,16 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
     };
     wait_tiles(nkt - 1 < STAGES - 1 ? nkt - 1 : STAGES - 1);
     __syncthreads();
-    fetch(0, 0, 0);
+    fetch_p(0, 0);
 #pragma unroll
-    for (int kk = 0; kk + 1 < KK; ++kk) {
-        fetch(0, kk + 1, (kk + 1) & 1);
-        multiply(kk & 1, no_load, 0, 0);
-    }
+    for (int s = 0; s < RING; ++s) fetch_q(0, s);
+    head(0, no_load);
 
     // ---- main loop.  A step starts at the edge between tile t and tile t+1, before the MFMAs of
-    // tile t's last k-step: its fragments are in registers, so once this wave's loads of tile t+1
+    // tile t's last slots: their operands are in registers, so once this wave's loads of tile t+1
     // have landed (newer ones may stay in flight) one barrier says both that tile t+1 is whole and
     // that the stage of tile t is free.  That stage is refilled with tile t+STAGES, its loads dealt
-    // over the step, while the last k-step of tile t and all but the last of tile t+1 are multiplied.
+    // over the step.
     int st = 0;                         // stage of tile t
     int t = 0;
     const int nfull = GUARD ? K0 / BK : nk0;   // whole tiles of K segment 0
@@ -309,13 +316,8 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
         const uint16_t* const qb = qb0 + (t + STAGES) * BK;
         const uint32_t sbase = wave_base + (uint32_t)st * (STAGE * 16);
         auto load = [&](int j) { dma16_so<false>(j < JP ? pb : qb, off0[j], sbase + (uint32_t)j * (NW * 1024)); };
-        fetch(sn, 0, 0);
-        multiply(1, load, 0, LPT / KK);
-#pragma unroll
-        for (int kk = 0; kk + 1 < KK; ++kk) {
-            fetch(sn, kk + 1, (kk + 1) & 1);
-            multiply(kk & 1, load, (kk + 1) * LPT / KK, (kk + 2) * LPT / KK);
-        }
+        edge(sn, load);
+        head(sn, load);
         st = sn;
     }
     // the same for the tiles around and behind the end of segment 0, and for the last ones, which
@@ -325,41 +327,40 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
         wait_tiles(nkt - 2 - t < STAGES - 2 ? nkt - 2 - t : STAGES - 2);
         __syncthreads();
         const int sn = st + 1 == STAGES ? 0 : st + 1;
-        fetch(sn, 0, 0);
         if (t + STAGES < nkt) issue_tile(t + STAGES, st);
-        multiply(1, no_load, 0, 0);
-#pragma unroll
-        for (int kk = 0; kk + 1 < KK; ++kk) {
-            fetch(sn, kk + 1, (kk + 1) & 1);
-            multiply(kk & 1, no_load, 0, 0);
-        }
+        edge(sn, no_load);
+        head(sn, no_load);
         st = sn;
     }
 
-    // ---- epilogue geometry.  Accumulator layout of the 32x32 MFMA: lane holds column l32 and
-    // rows 8*(v/4) + 4*hi + (v%4), v = 0..15.  Each wave stages a 32-row x CCOLS-column piece at
-    // a time in its own LDS region (fp32, padded rows) and writes it out as 16-byte row pieces:
-    // lane handles 4 consecutive columns (lcol) of row lr, lr + RPP, ... of the piece.
-    constexpr int NOUT = GEGLU ? NI / 2 : NI;   // 32-column output blocks per wave
-    constexpr int CB = (NOUT % 2 == 0) ? 2 : 1; // 32-column blocks staged per pass (<= 64 columns)
-    constexpr int CCOLS = CB * 32;              // staged columns
+    // ---- epilogue geometry.  A lane holds columns 4*quad .. +4 of each of its 16-column blocks, in row l16 of each 16-row block.
+    // Each wave stages a 32-row x CCOLS-column piece at a time in its own LDS region (fp32, padded rows) and writes it out as
+    // whole row pieces: lane handles 4 consecutive columns (lcol) of row lr, lr + RPP, ... of the piece.  (Stored from where they are, 32 or 64 bytes
+    // of a row at a time: 8192x1920x640 + 64 39 -> 44 us, 2048x1280x1280 + 64 with an fp32 residual 20.1 -> 21.9.)
+    constexpr int NOUT = GEGLU ? NI / 2 : NI;   // 16-column output blocks per wave
+    constexpr int CB = (NOUT % 4 == 0) ? 4 : 2; // ... staged per pass (<= 64 columns)
+    constexpr int CCOLS = CB * 16;              // staged columns
     constexpr int LPR = CCOLS / 4;              // lanes per staged row (4 columns each)
     constexpr int RPP = 64 / LPR;               // rows per pass
     constexpr int NPASS = 32 / RPP;
-    static_assert(NOUT % CB == 0, "column chunking");
+    static_assert(NOUT % CB == 0 && MI % 2 == 0, "pieces");
     const int wn_out = GEGLU ? (wn >> 1) : wn;
     const bool y_f32 = P.y_f32 != 0;
     const int lr = lane / LPR, lcol = (lane % LPR) * 4;
     const bool ld_ok = ((P.ldy & 3) == 0) && (!P.res || (P.ldr & 3) == 0);
+    // a tile that lies inside the output with 16-byte-aligned rows takes straight-line code: all
+    // staged pieces read, then all residual pieces, then all stores (no per-lane bounds)
+    const bool full = ld_ok && m0 + BM <= Mp && n0 + BN_OUT <= N;
+    const int qcol = n0 + wn_out + quad * 4;
 
     // fp32 residual: fetch this lane's pieces of the whole wave tile now, so that the loads
     // fly during the last tile's MFMAs and the epilogue never waits piece by piece
-    f32x4 rpre[RES32 ? MI : 1][RES32 ? NOUT / CB : 1][RES32 ? NPASS : 1];
+    f32x4 rpre[RES32 ? MI / 2 : 1][RES32 ? NOUT / CB : 1][RES32 ? NPASS : 1];
     const bool res_pre = RES32 && P.res && P.res_f32 && ld_ok;
     if (RES32 && res_pre) {
         const float* rp = static_cast<const float*>(P.res);
 #pragma unroll
-        for (int mi = 0; mi < MI; ++mi)
+        for (int mi = 0; mi < MI / 2; ++mi)
 #pragma unroll
             for (int cc = 0; cc < NOUT / CB; ++cc) {
                 const int q4 = n0 + wn_out + cc * CCOLS + lcol;
@@ -375,18 +376,30 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
     // per-column bias of this lane's output columns: fetched now as well (raw bits, widened after
     // the last MFMAs; a column past N reads the last valid one and is never stored)
     const uint16_t* bias = P.bias;
-    uint32_t bv_raw[NOUT], bg_raw[NOUT];
+    u32x2 bv_raw[NOUT], bg_raw[GEGLU ? NOUT : 1];
 #pragma unroll
-    for (int nj = 0; nj < NOUT; ++nj) bv_raw[nj] = bg_raw[nj] = 0u;
+    for (int nj = 0; nj < NOUT; ++nj) {
+        bv_raw[nj] = u32x2{0u, 0u};
+        if (GEGLU) bg_raw[GEGLU ? nj : 0] = u32x2{0u, 0u};
+    }
     if (bias && !P.bias_on_rows) {
+        // (a record's bias need not be aligned; whole pieces of four where it is)
+        const bool pieces = n0 + BN_OUT <= N && ((reinterpret_cast<uintptr_t>(bias) & 7) == 0) && (!GEGLU || (P.geglu_F & 3) == 0);
+        auto four = [&](const uint16_t* b, int q4) {
+            if (pieces) return *as_global(reinterpret_cast<const u32x2*>(b + q4));
+            uint32_t w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = *as_global(b + min(q4 + e, N - 1));
+            return u32x2{w[0] | (w[1] << 16), w[2] | (w[3] << 16)};
+        };
 #pragma unroll
         for (int nj = 0; nj < NOUT; ++nj) {
-            const int q = min(n0 + wn_out + nj * 32 + l32, N - 1);
-            bv_raw[nj] = bias[q];
-            if (GEGLU) bg_raw[nj] = bias[q + P.geglu_F];
+            bv_raw[nj] = four(bias, qcol + nj * 16);
+            if (GEGLU) bg_raw[GEGLU ? nj : 0] = four(bias + P.geglu_F, qcol + nj * 16);
         }
     }
-    multiply(1, no_load, 0, 0);
+#pragma unroll
+    for (int s = SLOTS - RING; s < SLOTS; ++s) multiply(s);
     __syncthreads();   // ring reads done before the epilogue reuses LDS
     // a record's last reader takes the nonce out again.  (Every wavefront of the tile has seen the words by
     // now, or has given up; the count was zeroed before the first of them was written.)
@@ -399,40 +412,33 @@ __device__ __forceinline__ void gemm_tile(const GemmProblem& P, const int tile, 
     // computed from a stale or half-written down-projection must not look like a result
     const float alpha = timed_out ? __builtin_nanf("") : P.alpha;
     int32_t* const sig = P.signal;
-    // a tile that lies inside the output with 16-byte-aligned rows takes straight-line code: all
-    // staged pieces read, then all residual pieces, then all stores (no per-lane bounds)
-    const bool full = ld_ok && m0 + BM <= Mp && n0 + BN_OUT <= N;
-    float bv[NOUT], bg[NOUT];
+    // (opaque to the optimiser, which would otherwise widen right after the loads and wait for them there)
 #pragma unroll
     for (int nj = 0; nj < NOUT; ++nj) {
-        // (opaque to the optimiser, which would otherwise widen right after the loads and wait for them there)
-        asm volatile("" : "+v"(bv_raw[nj]), "+v"(bg_raw[nj]));
-        bv[nj] = __uint_as_float(bv_raw[nj] << 16);
-        bg[nj] = __uint_as_float(bg_raw[nj] << 16);
+        asm volatile("" : "+v"(bv_raw[nj]));
+        if (GEGLU) asm volatile("" : "+v"(bg_raw[GEGLU ? nj : 0]));
     }
-
+    auto widen = [](const u32x2& w, int e) { return e & 1 ? bf16hi_to_f32(w[e >> 1]) : bf16lo_to_f32(w[e >> 1]); };
+    // block (mi, nj) as it is staged
+    auto value = [&](int mi, int nj) {
+        f32x4 v;
 #pragma unroll
-    for (int mi = 0; mi < MI; ++mi) {
+        for (int e = 0; e < 4; ++e) {
+            if (GEGLU) v[e] = (alpha * acc[mi][GEGLU ? 2 * nj : 0][e] + widen(bv_raw[nj], e)) * gelu_erf(alpha * acc[mi][GEGLU ? 2 * nj + 1 : 0][e] + widen(bg_raw[GEGLU ? nj : 0], e));
+            else v[e] = alpha * acc[mi][nj][e] + widen(bv_raw[nj], e);
+        }
+        return v;
+    };
+#pragma unroll
+    for (int mi = 0; mi < MI / 2; ++mi) {
 #pragma unroll
         for (int cc = 0; cc < NOUT / CB; ++cc) {
             // 1) registers -> staging (value after alpha, bias, GEGLU)
 #pragma unroll
-            for (int cj = 0; cj < CB; ++cj) {
-                const int nj = cc * CB + cj;
+            for (int m2 = 0; m2 < 2; ++m2)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int rr = 8 * (v >> 2) + 4 * hi + (v & 3);
-                    float val;
-                    if (GEGLU) {
-                        const float a = alpha * acc[mi][2 * nj][v] + bv[nj];
-                        const float gt = alpha * acc[mi][2 * nj + 1][v] + bg[nj];
-                        val = a * gelu_erf(gt);
-                    } else {
-                        val = alpha * acc[mi][nj][v] + bv[nj];
-                    }
-                    stage[rr * EPI_STRIDE + cj * 32 + l32] = val;
-                }
-            }
+                for (int cj = 0; cj < CB; ++cj)
+                    *reinterpret_cast<f32x4*>(stage + (m2 * 16 + l16) * EPI_STRIDE + cj * 16 + quad * 4) = value(mi * 2 + m2, cc * CB + cj);
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
             __builtin_amdgcn_wave_barrier();
             // 2) staging -> global: lane handles 4 consecutive columns of one row per pass
@@ -696,7 +702,7 @@ GemmChoice gemm_choice(const GemmGroup& g) {
         if (t128 > 256 && meanK < 1024) return take(GEMM_64x128);
     }
     // One large plain projection with a long K loop (no launch of the transformer block: the
-    // 8192 x 4096 x 4096 yardstick takes 224, 248 at 128x128).  Not for grouped
+    // 8192 x 4096 x 4096 yardstick takes 211, 248 at 128x128 before both had 16x16x32 MFMAs).  Not for grouped
     // launches: the q/k/v group with its short text-context problems loses a third.
     if (!res32 && n_main == 1 && t256 >= 512 && meanK >= 2048) return take(GEMM_256x256);
     // 128x128 tiles, two workgroups per CU.  Of eight 32x64 wavefronts where problems of different sizes share the launch (q, k,
