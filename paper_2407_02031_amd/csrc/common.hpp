@@ -159,7 +159,7 @@ constexpr int GEMM_MAX_PROBLEMS = 16;
 struct GemmGroup {
     int32_t n;
     int32_t total_tiles;
-    int32_t n_lead;                          // tiles of the signalling problems (first in the group), filled by the launcher
+    int32_t n_lead;                          // tiles dealt round-robin over the XCDs: the signalling problems', and a few long ones; first in the group, filled by the launcher
     int32_t zero_n;                          // the launch also clears zero_ptr[0 .. zero_n): the flags of the next launch
     int32_t* zero_ptr;
     int32_t first_tile[GEMM_MAX_PROBLEMS];   // copy of p[i].tile_begin, read by every workgroup in one scalar load

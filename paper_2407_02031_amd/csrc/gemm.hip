@@ -619,6 +619,11 @@ static int launch_cfg(GemmGroup& g, bool guard, hipStream_t stream) {
     }
     g.total_tiles = total;
     if (total == 0) return SD_OK;
+    // A few tiles of longer K loops behind the producers' (text keys / values in a q, k, v launch) are dealt round-robin like those: in
+    // one XCD's range they held up its other tiles (7904x1920x640 with 20 text tiles: every XCD was done after 26 us, that one after 34).
+    int front = 0;
+    for (int i = 0; i < g.n && (g.p[i].signal || g.p[i].K0 > g.p[g.n - 1].K0); ++i) front = g.p[i].tile_begin + g.p[i].tiles_m * g.p[i].tiles_n;
+    if (front - g.n_lead <= total / 8) g.n_lead = front;
     if (SD_DRY_RUN("gemm %dx%d/%d waves/%d stages%s%s%s%s%s; ", BM, BN, WGM * WGN, STAGES, GEGLU ? " geglu" : "", RES32 ? " res32" : "", guard ? " guard" : "",
                    !g.p[0].signal ? "" : g.p[0].nonce ? " records" : " flags", dry_detail(", %d problems", g.n)))
         return SD_OK;

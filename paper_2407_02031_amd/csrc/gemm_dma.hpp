@@ -86,7 +86,8 @@ static_assert(sizeof(GemmProblem) == sizeof(ProblemWords), "problem record size"
 // of activation rows and weight rows.
 // The tiles of signalling problems (down-projections that tiles of this same launch wait
 // for) come first and are dealt round-robin: they are the first workgroups dispatched on
-// every XCD, so all of them are running, or done, before any tile can wait for them.
+// every XCD, so all of them are running, or done, before any tile can wait for them.  A few tiles of
+// longer K loops may follow in the same manner (launch_cfg).
 // Kernel arguments arrive through scalar loads, and the compiler issues a load next to its first
 // use: left alone, a workgroup pays six or seven such rounds one after the other before its
 // first operand load.  One round is forced instead, 0.4 us: the header and the first problem's record
