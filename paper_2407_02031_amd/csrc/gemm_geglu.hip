@@ -261,9 +261,98 @@ __global__ __launch_bounds__(512, 2) void down_kernel(const uint16_t* __restrict
         }
     }
 }
+
+// ---- the same for few rows or ranks: BM rows x 16 columns per workgroup.  Bound by latency: a wavefront loads 64 deep
+// blocks of both operands, every eighth, into LDS of its own, all of them at once up to K = 1536 (2048 with 16 rows), and the workgroup
+// meets once, to add up eight partial sums.
+template <int BM>
+__global__ __launch_bounds__(512, 2) void down16_kernel(const uint16_t* __restrict__ x, int64_t ldx, const uint16_t* __restrict__ A, float scale,
+                                                        uint16_t* __restrict__ t, int M, int K, int r) {
+    constexpr int ROWS = BM + 16, BLK = ROWS * 8, NL = ROWS / 8;    // 16-byte chunks of a block, its 1 KB loads
+    constexpr int DEPTH = BM == 32 ? 3 : 4, MI = BM / 16;           // blocks of a wavefront in flight
+    __shared__ u32x4 lds[8 * DEPTH * BLK];
+    static_assert(sizeof(lds) <= 160 * 1024 && MI * 64 <= DEPTH * BLK, "LDS");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l16 = lane & 15, quad = lane >> 4;
+    const int m0 = blockIdx.x * BM, c0 = blockIdx.y * 16;
+    const int mine = (K / 64 - wave + 7) / 8;
+    u32x4* const own = lds + wave * (DEPTH * BLK);
+    const uint32_t base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds + (uint32_t)wave * (DEPTH * BLK * 16);
+    const uint16_t* src[NL];
+#pragma unroll
+    for (int j = 0; j < NL; ++j) {
+        const int row = j * 8 + (lane >> 3);
+        src[j] = (row < BM ? x + (int64_t)min(m0 + row, M - 1) * ldx : A + (int64_t)min(c0 + row - BM, r - 1) * K) + wave * 64 + swz<8>(row, lane & 7) * 8;
+    }
+    auto issue = [&](int i, int slot) {
+#pragma unroll
+        for (int j = 0; j < NL; ++j) dma16<false>(src[j] + i * 512, base + (uint32_t)(slot * (BLK * 16) + j * 1024));
+    };
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+        if (d < mine) issue(d, d);
+    f32x4 acc[MI];
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) acc[mi] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int lsw = (l16 >> 1) & 7;
+    int slot = 0;
+#pragma unroll 1
+    for (int i = 0; i < mine; ++i) {
+        const int newer = mine - 1 - i;         // blocks that may stay in flight
+        if (DEPTH >= 4 && newer >= 3) wait_vmcnt<3 * NL>();
+        else if (newer >= 2) wait_vmcnt<2 * NL>();
+        else if (newer == 1) wait_vmcnt<NL>();
+        else wait_vmcnt<0>();
+        bf16x8 a[2], xf[2][MI];
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const u32x4* const b = own + slot * BLK + l16 * 8 + ((kk * 4 + quad) ^ lsw);
+            a[kk] = __builtin_bit_cast(bf16x8, b[BM * 8]);
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) xf[kk][mi] = __builtin_bit_cast(bf16x8, b[mi * 128]);
+        }
+        // the block is in registers: its place takes another
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + DEPTH < mine) issue(i + DEPTH, slot);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi) acc[mi] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[kk], xf[kk][mi], acc[mi], 0, 0, 0);
+        slot = slot + 1 == DEPTH ? 0 : slot + 1;
+    }
+    f32x4* const part = reinterpret_cast<f32x4*>(own);
+#pragma unroll
+    for (int mi = 0; mi < MI; ++mi) part[mi * 64 + lane] = acc[mi];
+    __syncthreads();
+    if (wave < MI) {
+        const f32x4* const p = reinterpret_cast<const f32x4*>(lds) + wave * 64 + lane;
+        f32x4 v = p[0];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) v += p[w * (DEPTH * BLK)];
+        const int m = m0 + wave * 16 + l16, c = c0 + quad * 4;
+        bf16x4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = (__bf16)(v[e] * scale);
+        if (m < M && c < r) *reinterpret_cast<bf16x4*>(t + (int64_t)m * r + c) = o;    // r is a multiple of 8
+    }
+}
+// 16 columns a workgroup while all of them are one round, and 16 rows where that still holds.  us a launch in the stacks, 32x64 / here:
+// 2048x1280 + 64 6.62 / 4.86 (64 workgroups and 256).  With the wide tiles behind it, weights in L2: 2048x2560x640 + 64 24.0 / 22.3, 2048x5120x1280 + 64 54.0 / 52.0,
+// 3952x2560x640 + 16 35.5 / 33.9, 8192x1280x320 + 16 26.1 / 25.5 (32x64: three quarters of the columns are not there).  In more than a
+// round every column tile would read the rows again: 8192x640 + 64 stays with 32x64, 5.84.
 int launch_down(const uint16_t* x, int64_t ldx, const uint16_t* A, float scale, uint16_t* t, int M, int K, int r, hipStream_t stream) {
-    if (SD_DRY_RUN("down; ")) return SD_OK;
-    hipLaunchKernelGGL(down_kernel, dim3((M + DN_BM - 1) / DN_BM, (r + DN_BN - 1) / DN_BN), dim3(512), 0, stream, x, ldx, A, scale, t, M, K, r);
+    const int n16 = (r + 15) / 16;
+    const bool narrow = (M + 31) / 32 * n16 <= 256, low = narrow && (M + 15) / 16 * n16 <= 256;
+    const int rows = low ? 16 : DN_BM, cols = narrow ? 16 : DN_BN;
+    if (SD_DRY_RUN("down%s; ", dry_detail(narrow ? ", %d rows by 16" : ", %d rows by 64", rows))) return SD_OK;
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((M + rows - 1) / rows, (r + cols - 1) / cols), dim3(512), 0, stream, x, ldx, A, scale, t, M, K, r);
+    };
+    if (low) launch(down16_kernel<16>);
+    else if (narrow) launch(down16_kernel<32>);
+    else launch(down_kernel);
     SD_HIP_CHECK(hipGetLastError());
     return SD_OK;
 }

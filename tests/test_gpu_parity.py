@@ -322,6 +322,28 @@ def test_lora_linear_geglu_wide_tiles(B, M, C, F, rank):
     assert rel_err(host(y)[rows], ref) <= BF16_TOL
 
 
+# the down-projection in front of the wide tiles, about the ends of its three tilings, by what depends on it alone (no base weights): ranks off
+# 16, K of fewer 64 deep blocks than wavefronts, of more than they have in flight, odd numbers.  t, B's products and y are rounded to bf16
+@pytest.mark.parametrize("M,K,F,rank,tile", [
+    (1024, 1280, 5120, 64, "16 rows by 16"), (1540, 1280, 5120, 64, "32 rows by 16"), (2048, 1280, 5120, 64, "32 rows by 16"), (3206, 640, 2560, 64, "32 rows by 64"),
+    (990, 1280, 5120, 8, "16 rows by 16"), (1000, 640, 5120, 72, "32 rows by 16"), (4096, 640, 2560, 16, "16 rows by 16"), (6531, 448, 2560, 16, "32 rows by 16"),
+    (6200, 192, 1288, 16, "32 rows by 16"), (8192, 640, 2560, 16, "32 rows by 16"), (1000, 2112, 5120, 24, "16 rows by 16"), (2040, 1664, 5120, 40, "32 rows by 16"),
+])
+def test_down_projection_tiles(B, M, K, F, rank, tile):
+    r = rng(M + K + rank)
+    p = mkproj(r, 2 * F, K, rank, bias=False, scale=1.0)
+    p["W"] = np.zeros_like(p["W"])
+    p["A"] = G.bf16_round(r.standard_normal((rank, K)).astype(np.float32) / np.sqrt(K).astype(np.float32))
+    p["B"] = G.bf16_round(r.standard_normal((2 * F, rank)).astype(np.float32) / np.sqrt(rank).astype(np.float32))
+    x = G.bf16_round(r.standard_normal((M, K)).astype(np.float32))
+    call = lambda: B.lora_linear_fwd(dev(x, B), B.Proj.from_numpy(p), epilogue=B.SD_EPI_GEGLU)
+    with B.dry_run(detail=True) as names:
+        call()
+    assert [n for n in names if n.startswith("down")] == ["down, " + tile]
+    ref = O.geglu(O.lora_linear(x, p["W"], None, p["A"], p["B"], p["scale"]))
+    assert rel_err(host(call()), ref) <= BF16_TOL
+
+
 # each body of the plain projection, asserted to be the one that runs: in-tile adapters with every number of A columns, the
 # general kernel's tiles with dependency flags (a LayerNorm in front has cleared them), with records, and without an adapter, with an
 # fp32 residual, with K or the rank off 64, two column tiles of producers, ragged rows and columns.  mode: plain, res (fp32 residual), ln
