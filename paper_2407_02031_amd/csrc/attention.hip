@@ -107,7 +107,7 @@ __device__ __forceinline__ void store_queries(const f32x4 (&o)[KD][QB], const fl
 // the reference maximum is for is range, not accuracy: p = 2^(s - m) is formed, rounded and
 // accumulated in floating point, whose relative precision does not depend on magnitude, so any m
 // gives the same result as long as nothing overflows and the row sum does not vanish.  The first
-// attempt therefore measures only a segment's first half tile (m becomes a score that occurs: the row
+// attempt therefore measures only a segment's first tile (m becomes a score that occurs: the row
 // sum is >= 1 from then on); after it the exponentials are
 // formed against that fixed reference with no maximum pass at all.  At the end every lane looks at
 // its row sum and accumulator: if anything is not finite or close to it, some score lay 2^100 or more
@@ -308,7 +308,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     // almost never afterwards.  This lane's queries are column l16 of each block, its keys are its registers; it looks at those alone
     // (`over`), and any lane over the limit has all quads look together.
     // PRE: the scores arrive already shifted by m, so their maximum is the excess over it; those of the half after it, where
-    // they have been formed (next), move along.  The first half always sets the reference (m starts at 0, not at the scores' level).
+    // they have been formed (next), move along.  The first tile always sets the reference (m starts at 0, not at the scores' level).
     auto lane_max = [&](f32x4 (&s)[2][QB], int qb) {
         float mx = fmaxf(s[0][qb][0], s[1][qb][0]);
 #pragma unroll
@@ -390,7 +390,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         for (int qb = 0; qb < QB; ++qb) ls[qb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[qb], ls[qb], 0, 0, 0);
     };
 
-    // ---- prologue: the first two key tiles in flight, scores of the first half
+    // ---- prologue: the first two key tiles in flight, scores of the first tile
     if (live) {
         issue_kv(g0, 0);
         if (n > 1) {
@@ -406,11 +406,19 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     f32x4 sa[2][QB], sb[2][QB];
     bf16x8 kf[2][2], vf[4], pf[QB];
     if (live) {
+        // The first tile sets the reference, its second half too (formed once more in its turn): a query's largest weight is then mostly
+        // 1, which bf16 holds exactly.  Set by the first half alone, 2 x 4096 x 10 heads on 77 keys were 2.6 % further from float64.
+        load_kfrags(0, 1, kf);
+        compute_s(sb, kf);
+        if (n == 1 && masked) mask_scores(last, 1, sb);
+        float mx[QB];
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) mx[qb] = lane_max(sb, qb);
         load_kfrags(0, 0, kf);
         compute_s(sa, kf);
         if (n == 1 && masked) mask_scores(last, 0, sa);
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) move_max(qb, lane_max(sa, qb), sa, nullptr, true);       // the first half sets the reference
+        for (int qb = 0; qb < QB; ++qb) move_max(qb, fmaxf(mx[qb], lane_max(sa, qb)), sa, nullptr, true);
     }
 
     // ---- main loop, software-pipelined: the score MFMAs of one half are independent of the exponentials of the half before
