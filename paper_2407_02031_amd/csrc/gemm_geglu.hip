@@ -377,7 +377,8 @@ static int launch_geglu_mi(GemmGroup& g, hipStream_t stream) {
 // where the general kernel hides it.  Measured over those launches: 0.8 % slower than the best of the six in the mean, one in ten by
 // more than 3 %, none by more than 14.  (us with the LayerNorm in front, 64x64 with three stages / 64x64 / 128x64 / 256x128 / wide 256 /
 // wide 128: 2048x1280x320 15.1 13.2 14.3 19.8 21.9 16.1; 988x5120x1280 44.3 45.2 47.5 47.8 46.8 36.6; 7904x2560x640 88.3 85.7 76.4 85.4
-// 69.0 79.4; 7904x4096x2048 327 331 283 257 272 286.)
+// 69.0 79.4; 7904x4096x2048 327 331 283 257 272 286;
+// all before 16x16x32 MFMAs, which took 6 to 10 % off the wide tiles; the others moved by 5 % at most either way.)
 GegluTiles geglu_tiles(int M, int F, int K, int r, bool wide_ok) {
     const int k_steps = K / 64, steps = k_steps + (r + 63) / 64;
     auto tiles = [&](int rows, int cols) { return (long)((M + rows - 1) / rows) * ((F + cols - 1) / cols); };
