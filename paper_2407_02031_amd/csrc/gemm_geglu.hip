@@ -338,13 +338,14 @@ __global__ __launch_bounds__(512, 2) void down16_kernel(const uint16_t* __restri
         if (m < M && c < r) *reinterpret_cast<bf16x4*>(t + (int64_t)m * r + c) = o;    // r is a multiple of 8
     }
 }
-// 16 columns a workgroup while all of them are one round, and 16 rows where that still holds.  us a launch in the stacks, 32x64 / here:
-// 2048x1280 + 64 6.62 / 4.86 (64 workgroups and 256).  With the wide tiles behind it, weights in L2: 2048x2560x640 + 64 24.0 / 22.3, 2048x5120x1280 + 64 54.0 / 52.0,
-// 3952x2560x640 + 16 35.5 / 33.9, 8192x1280x320 + 16 26.1 / 25.5 (32x64: three quarters of the columns are not there).  In more than a
-// round every column tile would read the rows again: 8192x640 + 64 stays with 32x64, 5.84.
+// 16 columns a workgroup while all of them are one round, and at rank 16 and less, where 32x64 loads rows of A that it has no use for; 16 rows
+// where that is one round, too.  us a launch in the stacks, 32x64 / here: 2048x1280 + 64 6.62 / 4.86 (64 workgroups and 256).  With the wide tiles behind it,
+// weights in L2, 32x64 / 32x16 / 16x16: 988x5120x1280 + 64 35.3 / 32.8 / 32.6, 1800x2560x640 + 32 22.9 / 21.4 / 21.1; 32x64 / 32x16: 2048x5120x1280 + 64
+// 53.1 / 50.6, 8192x1280x320 + 16 26.1 / 25.5, 16384x2560x640 + 16 124.5 / 122.9.  In more than a round every column tile reads the rows
+// again: 3952x2560x640 + 64 35.4 / 36.0, 8192x2560x640 + 32 64.8 / 65.7, + 64 65.9 / 69.6.
 int launch_down(const uint16_t* x, int64_t ldx, const uint16_t* A, float scale, uint16_t* t, int M, int K, int r, hipStream_t stream) {
     const int n16 = (r + 15) / 16;
-    const bool narrow = (M + 31) / 32 * n16 <= 256, low = narrow && (M + 15) / 16 * n16 <= 256;
+    const bool narrow = n16 == 1 || (M + 31) / 32 * n16 <= 256, low = narrow && (M + 15) / 16 * n16 <= 256;
     const int rows = low ? 16 : DN_BM, cols = narrow ? 16 : DN_BN;
     if (SD_DRY_RUN("down%s; ", dry_detail(narrow ? ", %d rows by 16" : ", %d rows by 64", rows))) return SD_OK;
     auto launch = [&](auto kernel) {

@@ -327,7 +327,7 @@ def test_lora_linear_geglu_wide_tiles(B, M, C, F, rank):
 @pytest.mark.parametrize("M,K,F,rank,tile", [
     (1024, 1280, 5120, 64, "16 rows by 16"), (1540, 1280, 5120, 64, "32 rows by 16"), (2048, 1280, 5120, 64, "32 rows by 16"), (3206, 640, 2560, 64, "32 rows by 64"),
     (990, 1280, 5120, 8, "16 rows by 16"), (1000, 640, 5120, 72, "32 rows by 16"), (4096, 640, 2560, 16, "16 rows by 16"), (6531, 448, 2560, 16, "32 rows by 16"),
-    (6200, 192, 1288, 16, "32 rows by 16"), (8192, 640, 2560, 16, "32 rows by 16"), (1000, 2112, 5120, 24, "16 rows by 16"), (2040, 1664, 5120, 40, "32 rows by 16"),
+    (6200, 192, 1288, 16, "32 rows by 16"), (8192, 640, 2560, 16, "32 rows by 16"), (16384, 640, 2560, 16, "32 rows by 16"), (1000, 2112, 5120, 24, "16 rows by 16"), (2040, 1664, 5120, 40, "32 rows by 16"),
 ])
 def test_down_projection_tiles(B, M, K, F, rank, tile):
     r = rng(M + K + rank)
