@@ -319,9 +319,19 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     auto move_max = [&](int qb, float lane_mx, f32x4 (&s)[2][QB], f32x4 (*next)[QB], bool first) {
         // the other quads hold the other keys of this query: lane swaps (vector-ALU operations, no LDS round trip)
         const float mx = quads_max(lane_mx);
+        // Nothing has been summed up when the reference is first set, so nothing is rescaled: for scores below -128 the factor would be
+        // infinite, and infinity times the sums' zeros NaN.
+        if (first) {
+            m[qb] = mx;
+            if (KEEP_M) mneg[KEEP_M ? qb : 0] = f32x4{-mx, -mx, -mx, -mx};
+#pragma unroll
+            for (int kb = 0; kb < 2; ++kb)
+                if (PRE) s[kb][qb] -= mx;
+            return;
+        }
         float alpha;
         if (PRE) {
-            const float delta = first || mx > RESCALE_LOG2 ? mx : 0.f;
+            const float delta = mx > RESCALE_LOG2 ? mx : 0.f;
             alpha = __builtin_amdgcn_exp2f(-delta);
             m[qb] += delta;
             if (KEEP_M) mneg[KEEP_M ? qb : 0] = f32x4{-m[qb], -m[qb], -m[qb], -m[qb]};

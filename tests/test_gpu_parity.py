@@ -1741,3 +1741,54 @@ def test_attn_block_scores_that_climb_from_key_tile_to_key_tile(B, boost):
     # negative control: the output depends on which keys win (attention to the first tile only is far away)
     ref_first = O.attn_sublayer(h, ctx[:, :64], g, b, pq, pk, pv, po, 1)
     assert rel_err(ref_first - h, ref - h) > 10 * BF16_TOL
+
+
+# Prescaled keys (inside a block) through every kernel that a launch's tile count chooses, with scores that climb to 2^150 above the first tile
+# inside each range that keeps a reference of its own (the first attempt overflows, the measured form takes over), and with first tiles of
+# those ranges 2^150 below the others (the reference starts there; nothing has been summed up that it could rescale).
+# Half of the queries see the mirrored scores, so both kinds share wavefronts.
+@pytest.mark.parametrize("where", ["climb", "low"])
+@pytest.mark.parametrize("Bn,T,Tc,heads,cut,queries,groups", [
+    (2, 200, 64 * 6 + 23, 1, False, 128, 1), (2, 200, 64 * 7 + 23, 2, False, 128, 2), (2, 200, 64 * 8 + 23, 2, False, 128, 2), (2, 200, 64 * 26 + 23, 2, True, 128, 2),
+    (4, 1800, 64 * 24 + 5, 5, True, 128, 1), (4, 1200, 64 * 24 + 9, 10, False, 256, 2), (8, 1290, 64 * 20 + 10, 10, False, 256, 1),
+])
+def test_attn_block_references_of_every_kernel(B, Bn, T, Tc, heads, cut, queries, groups, where):
+    import torch
+    C = heads * 64
+    r = rng(T + Tc)
+    n0 = r.standard_normal((heads, 64)).astype(np.float32)
+    n0 = ((n0 - n0.mean(1, keepdims=True)) / n0.std(1, keepdims=True)).reshape(C)       # what LayerNorm makes of a row along n0
+    sign = np.where(r.random((Bn, T, 1)) < 0.5, 1.0, -1.0).astype(np.float32)
+    h = (sign * n0 * (1.0 + 0.05 * r.standard_normal((Bn, T, 1))) + 0.15 * r.standard_normal((Bn, T, C))).astype(np.float32)
+    # the key tiles [lo, hi) of each range with a reference of its own: halves of a cut tile, and in them (or in the whole) groups of wavefronts
+    nt = (Tc + 63) // 64
+    ranges = [(0, (nt + 1) // 2), ((nt + 1) // 2, nt)] if cut else [(0, nt)]
+    if groups == 2:
+        ranges = [s for lo, hi in ranges for s in ((lo, lo + (hi - lo) // 2), (hi - (hi - lo + 1) // 2, hi))]
+    level = np.zeros(nt, np.float32)                     # natural-log score of a key tile for a query along +n0
+    for lo, hi in ranges:
+        level[(lo + hi) // 2 if where == "climb" else lo] = 105.0
+    a = level[np.arange(Tc) // 64] + 0.5 * r.standard_normal(Tc).astype(np.float32)
+    ctx = G.bf16_round((a[None, :, None] * n0[None, None, :] / 8.0 + 0.05 * r.standard_normal((Bn, Tc, C))).astype(np.float32))
+    eye = {"W": np.eye(C, dtype=np.float32), "b": None, "A": None, "B": None, "scale": 0.0}
+    pv = mkproj(r, C, C, 0, bias=False)
+    po = mkproj(r, C, C, 0, bias=True)
+    g, b = np.ones(C, np.float32), np.zeros(C, np.float32)
+    # the test is what it says
+    q0 = O.layernorm(h[0], g, b)[:, :64]
+    scores = {up: (q0[int(np.argmax(sign[0, :, 0] == up))] @ ctx[0, :, :64].T.astype(np.float64)) / 8.0 * 1.4426950408889634 for up in (1.0, -1.0)}
+    for lo, hi in ranges:
+        first, rest = slice(64 * lo, 64 * lo + 64), slice(64 * lo + 64, 64 * hi)
+        if where == "climb":
+            assert scores[1.0][rest].max() - scores[1.0][first].max() > 135
+        else:
+            assert scores[-1.0][first].max() < -135 and scores[-1.0][rest].max() > -30 and scores[1.0][first].max() > 135
+    args = (torch.from_numpy(h).cuda(), dev(ctx, B), dev(g, B), dev(b, B), B.Proj.from_numpy(eye), B.Proj.from_numpy(eye), B.Proj.from_numpy(pv), B.Proj.from_numpy(po), heads)
+    with B.dry_run(detail=3) as names:
+        B.attn_block_fwd(*args)
+    assert "attention prescaled try%s, %d queries, %d groups" % (" cut" if cut else "", queries, groups) in names
+    got = host(B.attn_block_fwd(*args))
+    assert np.isfinite(got).all()
+    for s in (0, Bn - 1):        # (samples do not meet)
+        ref = O.attn_sublayer(h[s:s + 1], ctx[s:s + 1], g, b, eye, eye, pv, po, heads)
+        assert rel_err(got[s:s + 1] - h[s:s + 1], ref - h[s:s + 1]) <= BF16_TOL
