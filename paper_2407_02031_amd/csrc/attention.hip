@@ -321,12 +321,14 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         const float mx = quads_max(lane_mx);
         // Nothing has been summed up when the reference is first set, so nothing is rescaled: for scores below -128 the factor would be
         // infinite, and infinity times the sums' zeros NaN.
+        // A tile of nothing but -inf weighs nothing; its reference is one that any score exceeds.  (PRE: 0, because the scores start at -m, and a
+        // huge one would swallow them.)
         if (first) {
-            m[qb] = mx;
-            if (KEEP_M) mneg[KEEP_M ? qb : 0] = f32x4{-mx, -mx, -mx, -mx};
+            m[qb] = PRE ? (mx == -INFINITY ? 0.f : mx) : fmaxf(mx, -3.4028234663852886e38f);
+            if (KEEP_M) mneg[KEEP_M ? qb : 0] = f32x4{-m[qb], -m[qb], -m[qb], -m[qb]};
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
-                if (PRE) s[kb][qb] -= mx;
+                if (PRE) s[kb][qb] -= m[qb];
             return;
         }
         float alpha;
@@ -503,7 +505,10 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     const float cm = PRE ? 1.0f : c;
     float l[QB];
 #pragma unroll
-    for (int qb = 0; qb < QB; ++qb) l[qb] = ls[qb][0];
+    for (int qb = 0; qb < QB; ++qb) {
+        l[qb] = ls[qb][0];
+        if (PRE) m[qb] = l[qb] == 0.f ? -INFINITY : m[qb];     // (no key of weight in this range: the reference was none)
+    }
     // ---- the groups' states about their common maximum: each finishes KD of the four d blocks
     f32x4 fin[KD][QB];
     if constexpr (GR == 1) {

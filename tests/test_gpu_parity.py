@@ -1792,3 +1792,58 @@ def test_attn_block_references_of_every_kernel(B, Bn, T, Tc, heads, cut, queries
     for s in (0, Bn - 1):        # (samples do not meet)
         ref = O.attn_sublayer(h[s:s + 1], ctx[s:s + 1], g, b, eye, eye, pv, po, heads)
         assert rel_err(got[s:s + 1] - h[s:s + 1], ref - h[s:s + 1]) <= BF16_TOL
+
+
+# Whole key tiles with scores of -inf (weights of exactly zero): where a range of keys with a reference of its own begins, and the whole of the last
+# such range.  Plain keys, and keys of a block whose projection overflows there
+@pytest.mark.parametrize("where", ["first", "all"])
+@pytest.mark.parametrize("block,Bn,Tq,Tk,heads,kernel", [
+    (False, 1, 130, 64 * 8 + 3, 3, ", 128 queries, 2 groups"), (False, 1, 200, 64 * 20 + 9, 2, " try, 128 queries, 2 groups"), (False, 1, 1100, 64 * 24 + 61, 30, " try, 256 queries, 2 groups"),
+    (False, 1, 4096, 64 * 21, 20, " try cut merge, 128 queries, 1 groups"), (True, 2, 200, 64 * 8 + 23, 2, " prescaled try, 128 queries, 2 groups"),
+    (True, 2, 200, 64 * 26 + 23, 2, " prescaled try cut, 128 queries, 2 groups"), (True, 4, 1200, 64 * 24 + 9, 10, " prescaled try, 256 queries, 2 groups"),
+])
+def test_attention_key_tiles_at_minus_infinity(B, block, Bn, Tq, Tk, heads, kernel, where):
+    import torch
+    C = heads * 64
+    r = rng(Tq + Tk + heads)
+    nt = (Tk + 63) // 64
+    ranges = [(0, (nt + 1) // 2), ((nt + 1) // 2, nt)] if " cut" in kernel else [(0, nt)]
+    if kernel.endswith("2 groups"):
+        ranges = [s for lo, hi in ranges for s in ((lo, lo + (hi - lo) // 2), (hi - (hi - lo + 1) // 2, hi))]
+    out = np.zeros(nt, bool)
+    for lo, hi in ranges if where == "first" else ranges[-1:]:
+        out[lo:hi if where == "all" else lo + 1] = True
+    out = out[np.arange(Tk) // 64]
+    q = r.standard_normal((Bn, Tq, heads, 64), dtype=np.float32)
+    q[..., 0] = 2.0 + np.abs(q[..., 0])                  # (positive after LayerNorm, too)
+    q = G.bf16_round(q).reshape(Bn, Tq, C)
+    k = r.standard_normal((Bn, Tk, heads, 64), dtype=np.float32)
+    k[..., 0] = 0.0
+    k = G.bf16_round(k).reshape(Bn, Tk, C)
+    if block:
+        eye, pk, pv, po = (mkproj(r, C, C, 0, bias=i == 3) for i in range(4))
+        eye["W"] = np.eye(C, dtype=np.float32)
+        pk["W"] = np.diag(np.where(np.arange(C) % 64 == 0, 64.0, 1.0)).astype(np.float32)
+        pv["W"][:, ::64] = 0.0
+        k[:, out, ::64] = -2.0 ** 127
+        g, b = np.ones(C, np.float32), np.zeros(C, np.float32)
+        args = (torch.from_numpy(q).cuda(), dev(k, B), dev(g, B), dev(b, B), *[B.Proj.from_numpy(p) for p in (eye, pk, pv, po)], heads)
+        call = lambda: B.attn_block_fwd(*args)
+        want = lambda s: O.attn_sublayer(q[s:s + 1], k[s:s + 1][:, ~out], g, b, eye, pk, pv, po, heads) - q[s:s + 1]
+        got_of = lambda y, s: y[s:s + 1] - q[s:s + 1]
+    else:
+        k[:, out, ::64] = -np.inf
+        v = G.bf16_round(r.standard_normal((Bn, Tk, C), dtype=np.float32))
+        args = (dev(q, B), dev(k, B), vt_layout(v, B), heads)
+        call = lambda: B.attention_fwd(*args)
+        h = np.array(sorted({0, heads // 2, heads - 1}))
+        cols = (h[:, None] * 64 + np.arange(64)).ravel()
+        want = lambda s: O.attention(q[..., cols], k[..., cols][:, ~out], v[..., cols][:, ~out], len(h), dtype=np.float32 if Tq > 1000 else np.float64)
+        got_of = lambda y, s: y[..., cols]
+    with B.dry_run(detail=3) as names:
+        call()
+    assert "attention" + kernel in names
+    y = host(call())
+    assert np.isfinite(y).all()
+    for s in sorted({0, Bn - 1}):
+        assert rel_err(got_of(y, s), want(s)) <= BF16_TOL
