@@ -63,8 +63,7 @@ __device__ __forceinline__ void attn_wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// One half of a cut tile of 128 queries: 32 accumulator values a thread, then its queries' reference maxima and row sums.  A tile of
-// 256 takes two.
+// One half of a cut tile: 32 accumulator values a thread, then its queries' reference maxima and row sums.  Cut tiles have 128 queries.
 constexpr int PART_FLOATS = 34 * 256;
 
 // Largest of what the four quads of a wavefront (16 lanes each) hold for the same query, in every lane: exchanges of rows
@@ -139,13 +138,14 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     constexpr int BQ = 64 * QB, KD = 4 / GR;
     constexpr int THREADS = 256 * GR;
     constexpr int PART = KD * QB * 4 * THREADS + 2 * BQ;     // floats of a part
-    static_assert(2 * PART <= QB * PART_FLOATS, "a part fits its share of the scratch memory");
+    constexpr bool CUT = QB == 2;
+    static_assert(!CUT || PART <= PART_FLOATS, "a part fits its share of the scratch memory");
 
     // Workgroups are dealt round-robin to the 8 XCDs; give each XCD a contiguous range of
     // (sample, head, query tile) so that one head's K and V stay in one XCD's L2.
     const int nt = (Tk + 63) >> 6;
     int tile, s0 = 0, s1 = nt, part = -1;   // steps [s0, s1) of the tile; part >= 0: a half tile
-    if (nsplit == 0) {
+    if (!CUT || nsplit == 0) {
         tile = bid;
         if ((total & 7) == 0) tile = (tile & 7) * (total >> 3) + (tile >> 3);
     } else {
@@ -553,7 +553,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     }
 
     // ---- a whole tile is normalised and stored; half of a cut tile leaves its state behind
-    if (part < 0) {
+    if (!CUT || part < 0) {
         store_queries(fin, l, out, ldo, b, Tq, q0 + l16, head, grp * KD, quad);
         return false;
     }
@@ -646,11 +646,15 @@ __global__ __launch_bounds__(256 * GR, GR == 1 && QB == 2 ? 3 : 2) void attentio
     lds_f32* const ml = (lds_f32*)maxima;
     lds_i32* const redo = (lds_i32*)&wg_redo;
     if (TRY && threadIdx.x == 0) *redo = 0;    // (ordered before its first use by the key loop's barriers)
-    // (One body for both attempts: as two, the second one's values took registers from the first, 65 to 150 of them spilled.)
+    // (One body for both attempts: as two, the second one's values took registers from the first, 65 to 150 of them spilled.  The second trip's
+    // indexes are opaque: what both trips form of them would be formed ahead of the loop and kept, 64 queries to a wavefront spilled 44 registers.)
     bool again = false;
+    int tid = threadIdx.x, bid = blockIdx.x;
     while (attention_body<QB, GR, PRE, TRY>(q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads, qtiles, c, nfull, nsplit, total, parts, arrived, lk, ml, redo,
-                                            (int)threadIdx.x, (int)blockIdx.x, again))
+                                            tid, bid, again)) {
         again = true;
+        asm volatile("" : "+v"(tid), "+s"(bid));
+    }
 }
 
 // One workgroup per cut tile: combine the two halves about their common maximum.  Threads as in the kernel that left them.
@@ -760,6 +764,7 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     if (nsplit > 0 && !(scratch && scratch_bytes >= need && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0)) nsplit = 0;
     const int nt = (Tk + 63) / 64;
     const AttnPlan plan = attention_plan(Bn, Tq, nt, heads, nsplit);
+    SD_REQUIRE(nsplit == 0 || plan.qb == 2, SD_EINVAL, "attention: cut tiles have 128 queries");     // what the kernels and the scratch memory are made for
     if (nsplit > arrived_n) arrived = nullptr;   // not enough counters: the halves are merged by the second kernel
     // The unmeasured attempt saves a maximum per half tile and costs its check: from 20 tiles of plain keys on, always with prescaled ones.
     *cut_tiles = arrived ? 0 : nsplit;

@@ -113,3 +113,30 @@ def test_groupnorm_second_pass(B, Bn, T, Cc, groups, plain, silu):
         for call in (L.sd_groupnorm_fwd, L.sd_groupnorm_silu_fwd):
             assert call(0x10000, 0x20000, 0x30000, 0x40000, Bn, T, Cc, groups, 1e-6, 0x100000, L.sd_groupnorm_workspace_bytes(Bn, T, Cc, groups), None) == 0
     assert names == ["groupnorm" + (", statistics first" if first else "") for first in (plain, silu)]
+
+
+# Cut attention tiles have 128 queries, and their halves fit the scratch memory that the call asks for: over token and key counts, heads and samples, on its
+# own and inside a block
+def test_cut_attention_tiles(B):
+    L = B.lib()
+    p = B.sd_proj(0x10000, None, None, None, 0, 0.0)
+    seen = set()
+    for Tq in (64, 200, 800, 1000, 1290, 1500, 1800, 2048, 3000, 3952, 4096):
+        for Tk in (77, 500, 800, 1300, 1500, 2000, 3952, 4096):
+            for Bn, heads in ((1, 5), (1, 10), (2, 5), (1, 20), (2, 10), (2, 20), (4, 20), (8, 20)):
+                tiles = (Tq + 127) // 128 * heads * Bn
+                with B.dry_run(detail=3) as names:
+                    need = L.sd_attention_workspace_bytes(Bn, Tq, Tk, heads)
+                    assert L.sd_attention_fwd(0x1000, 0x2000, 0x3000, 0x4000, Bn, Tq, Tk, 64 * heads, heads, 0x100000, need, None) == 0
+                    rc = L.sd_attn_block_fwd(0x1000, 0x2000, BF16, 0x3000, Tk, 128, 0x4000, 0x5000, 1e-5, C.byref(p), C.byref(p), C.byref(p), C.byref(p), Bn, Tq, 64 * heads, heads,
+                                             0x100000, L.sd_attn_block_workspace_bytes(Bn, Tq, 64 * heads, Tk, 128, 0), None)
+                    assert rc == 0, L.sd_last_error()
+                launches = [n for n in names if n.startswith("attention")]
+                assert len(launches) == 2
+                for n in launches:
+                    seen.add(n)
+                    assert " cut" not in n or n.endswith((", 128 queries, 1 groups", ", 128 queries, 2 groups")), (n, Bn, Tq, Tk, heads)
+                if " cut" in launches[0]:        # a half: 128 x 64 values, 128 maxima, 128 sums
+                    assert need >= (768 - tiles) * 2 * 128 * 66 * 4
+    assert {n.split(",", 1)[1] for n in seen} == {" 128 queries, 1 groups", " 128 queries, 2 groups", " 256 queries, 1 groups", " 256 queries, 2 groups"}
+    assert {n.split(",")[0] for n in seen} >= {"attention try cut merge", "attention prescaled try cut", "attention prescaled try", "attention try", "attention"}
