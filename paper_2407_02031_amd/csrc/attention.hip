@@ -135,6 +135,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
                                                int Tq, int Tk, int Tkp, int heads, int qtiles, float c,
                                                int nfull, int nsplit, int total, float* __restrict__ parts, int32_t* __restrict__ arrived,
                                                lds_u32x4* const lds, lds_f32* const ml, lds_i32* const wg_redo, const int tid, const int bid, const bool again) {
+    static_assert(TRY || !PRE, "scores formed with -m are not moved once the half before them has been looked at");
     constexpr int BQ = 64 * QB, KD = 4 / GR;
     constexpr int THREADS = 256 * GR;
     constexpr int PART = KD * QB * 4 * THREADS + 2 * BQ;     // floats of a part
@@ -307,8 +308,8 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     // stays far inside fp32 / bf16 range), so the O and row sum rescale runs on the first tiles and
     // almost never afterwards.  This lane's queries are column l16 of each block, its keys are its registers; it looks at those alone
     // (`over`), and any lane over the limit has all quads look together.
-    // PRE: the scores arrive already shifted by m, so their maximum is the excess over it; those of the half after it, where
-    // they have been formed (next), move along.  The first tile always sets the reference (m starts at 0, not at the scores' level).
+    // PRE: the scores arrive already shifted by m, so their maximum is the excess over it.  The first tile always sets the reference (m starts at 0,
+    // not at the scores' level).
     auto lane_max = [&](f32x4 (&s)[2][QB], int qb) {
         float mx = fmaxf(s[0][qb][0], s[1][qb][0]);
 #pragma unroll
@@ -316,7 +317,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         return mx;
     };
     auto over = [&](float mx, int qb) { return PRE ? mx > RESCALE_LOG2 : (mx - m[qb]) * c > RESCALE_LOG2; };
-    auto move_max = [&](int qb, float lane_mx, f32x4 (&s)[2][QB], f32x4 (*next)[QB], bool first) {
+    auto move_max = [&](int qb, float lane_mx, f32x4 (&s)[2][QB], bool first) {
         // the other quads hold the other keys of this query: lane swaps (vector-ALU operations, no LDS round trip)
         const float mx = quads_max(lane_mx);
         // Nothing has been summed up when the reference is first set, so nothing is rescaled: for scores below -128 the factor would be
@@ -338,10 +339,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
             m[qb] += delta;
             if (KEEP_M) mneg[KEEP_M ? qb : 0] = f32x4{-m[qb], -m[qb], -m[qb], -m[qb]};
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb) {
-                s[kb][qb] -= delta;
-                if (next) next[kb][qb] -= delta;
-            }
+            for (int kb = 0; kb < 2; ++kb) s[kb][qb] -= delta;
         } else {
             const float mnew = over(mx, qb) ? mx : m[qb];
             alpha = __builtin_amdgcn_exp2f((m[qb] - mnew) * c);
@@ -357,7 +355,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             const float mx = lane_max(s, qb);
-            if (__builtin_amdgcn_ballot_w64(over(mx, qb)) != 0ull) move_max(qb, mx, s, nullptr, false);
+            if (__builtin_amdgcn_ballot_w64(over(mx, qb)) != 0ull) move_max(qb, mx, s, false);
         }
     };
     // p = exp2((s - m) * c) packed to bf16 in MFMA operand order
@@ -373,7 +371,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
     };
     // Kernels that measure every tile look afterwards, beside the exponentials, and form the probabilities once more where a
     // score lies too far above the reference: 8 x 988 x 20 heads 54.4 -> 53.6 us, 8 x 512 x 10 14.5 -> 14.0.
-    auto look_after = [&](f32x4 (&s)[2][QB], f32x4 (&next)[2][QB], bf16x8 (&pf)[QB]) {
+    auto look_after = [&](f32x4 (&s)[2][QB], bf16x8 (&pf)[QB]) {
         if (TRY) return;
         float mx[QB];
         bool need = false;
@@ -384,7 +382,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         }
         if (__builtin_amdgcn_ballot_w64(need) == 0ull) return;
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) move_max(qb, mx[qb], s, next, false);
+        for (int qb = 0; qb < QB; ++qb) move_max(qb, mx[qb], s, false);
         exponentials(s, pf);
     };
     // O^T += V^T P^T.  The row sums are one more block of rows, of ones: the normaliser matches exactly what is multiplied,
@@ -430,7 +428,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         compute_s(sa, kf);
         if (n == 1 && masked) mask_scores(last, 0, sa);
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) move_max(qb, fmaxf(mx[qb], lane_max(sa, qb)), sa, nullptr, true);
+        for (int qb = 0; qb < QB; ++qb) move_max(qb, fmaxf(mx[qb], lane_max(sa, qb)), sa, true);
     }
 
     // ---- main loop, software-pipelined: the score MFMAs of one half are independent of the exponentials of the half before
@@ -446,7 +444,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         look_first(sa);
         compute_s(sb, kf);
         exponentials(sa, pf);
-        look_after(sa, sb, pf);
+        look_after(sa, pf);
         accumulate_o(vf, pf);
         load_vfrags(slot, 1, vf);
         attn_wait_vmcnt<0>();
@@ -457,7 +455,7 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         look_first(sb);
         compute_s(sa, kf);
         exponentials(sb, pf);
-        look_after(sb, sa, pf);
+        look_after(sb, pf);
         accumulate_o(vf, pf);
     }
     if (live) {
@@ -472,13 +470,13 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
             mask_scores(last, 1, sb);
         }
         exponentials(sa, pf);
-        look_after(sa, sb, pf);
+        look_after(sa, pf);
         accumulate_o(vf, pf);
         look_first(sb);
         load_vfrags(slot, 1, vf);
         if (masked) mask_values(last, 1, vf);
         exponentials(sb, pf);
-        look_after(sb, sa, pf);
+        look_after(sb, pf);
         accumulate_o(vf, pf);
     }
 
@@ -764,16 +762,17 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     if (nsplit > 0 && !(scratch && scratch_bytes >= need && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0)) nsplit = 0;
     const int nt = (Tk + 63) / 64;
     const AttnPlan plan = attention_plan(Bn, Tq, nt, heads, nsplit);
-    SD_REQUIRE(nsplit == 0 || plan.qb == 2, SD_EINVAL, "attention: cut tiles have 128 queries");     // what the kernels and the scratch memory are made for
-    if (nsplit > arrived_n) arrived = nullptr;   // not enough counters: the halves are merged by the second kernel
     // The unmeasured attempt saves a maximum per half tile and costs its check: from 20 tiles of plain keys on, always with prescaled ones.
+    const bool tries = k_prescaled || nt >= 20;
+    SD_REQUIRE(plan.qb == 2 || (nsplit == 0 && tries), SD_EINVAL, "attention: 256 queries, but cut or measured");     // no such kernel, and scratch memory for 128
+    if (nsplit > arrived_n) arrived = nullptr;   // not enough counters: the halves are merged by the second kernel
     *cut_tiles = arrived ? 0 : nsplit;
     // Read-ahead in the room that three workgroups to a CU leave: 8 MB and 2 MB per key tile, which the launch is long
     // enough for.  (With 1 MB per key tile the queue falls behind at 32 x 32 tokens: 2540 us per stack for 2500, 2658 without any.)
     // Workgroups of two groups have a CU each; what reads ahead runs beside them and behind.
     const int grid = attention_grid(plan.nfull, nsplit);
     const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, plan.gr == 1 ? 3l * device_cus() - grid : 448, 16) : ReadRanges{};
-    if (SD_DRY_RUN("attention%s%s%s%s%s; ", k_prescaled ? " prescaled" : "", k_prescaled || nt >= 20 ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "", dry_ranges(ra), dry_tiles(64 * plan.qb, plan.gr))) return SD_OK;
+    if (SD_DRY_RUN("attention%s%s%s%s%s; ", k_prescaled ? " prescaled" : "", tries ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "", dry_ranges(ra), dry_tiles(64 * plan.qb, plan.gr))) return SD_OK;
     auto go = [&](auto kernel, const auto& ranges) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(grid + (ra.wgs + plan.gr - 1) / plan.gr)), dim3(256 * plan.gr), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
                            plan.qtiles, c, plan.nfull, nsplit, static_cast<float*>(scratch), arrived, ranges);
@@ -782,8 +781,8 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
         constexpr int QB = decltype(qb)::value, GR = decltype(gr)::value;
         if (k_prescaled && ra.wgs) go(attention_kernel<QB, GR, true, true, true>, ra);
         else if (k_prescaled) go(attention_kernel<QB, GR, true, true, false>, NoRanges{});
-        else if (nt >= 20) go(attention_kernel<QB, GR, false, true, false>, NoRanges{});
-        else go(attention_kernel<QB, GR, false, false, false>, NoRanges{});
+        else if (tries) go(attention_kernel<QB, GR, false, true, false>, NoRanges{});
+        else if constexpr (QB == 2) go(attention_kernel<QB, GR, false, false, false>, NoRanges{});
     };
     using I1 = std::integral_constant<int, 1>;
     using I2 = std::integral_constant<int, 2>;
