@@ -322,10 +322,11 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         const float mx = quads_max(lane_mx);
         // Nothing has been summed up when the reference is first set, so nothing is rescaled: for scores below -128 the factor would be
         // infinite, and infinity times the sums' zeros NaN.
-        // A tile of nothing but -inf weighs nothing; its reference is one that any score exceeds.  (PRE: 0, because the scores start at -m, and a
-        // huge one would swallow them.)
+        // A tile of nothing but -inf weighs nothing; its reference is one that any score exceeds.  (PRE: the scores start at -m, and a huge one would
+        // swallow them.  So it is 0, and where everything behind that tile lies so far below that the row sum vanishes, the second attempt starts at -2^13, from
+        // where fp32 still resolves 2^-10.  What lies 2^126 and more below that counts for nothing.)
         if (first) {
-            m[qb] = PRE ? (mx == -INFINITY ? 0.f : mx) : fmaxf(mx, -3.4028234663852886e38f);
+            m[qb] = PRE ? (mx == -INFINITY ? (again ? -8192.f : 0.f) : mx) : fmaxf(mx, -3.4028234663852886e38f);
             if (KEEP_M) mneg[KEEP_M ? qb : 0] = f32x4{-m[qb], -m[qb], -m[qb], -m[qb]};
 #pragma unroll
             for (int kb = 0; kb < 2; ++kb)
@@ -484,16 +485,19 @@ __device__ __forceinline__ bool attention_body(const uint16_t* __restrict__ q, i
         // did the attempt stay in range?  (a row sum of +inf, or NaN anywhere, says no.)  The limit leaves room for
         // what the tail adds up: the sums of two groups of two halves of a cut tile must stay finite, and the
         // reciprocal of theirs a normal number.
+        // Prescaled keys: a row sum below 1 says that the reference was not a score (a first tile of -inf).
         float mag = 0.f;
+        bool low = false;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
             mag += ls[qb][0];
+            if (PRE && live) low = low || ls[qb][0] < 0x1p-60f;
 #pragma unroll
             for (int db = 0; db < 4; ++db)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) mag += fabsf(o[db][qb][v]);
         }
-        const bool bad = __builtin_amdgcn_ballot_w64(!(mag <= 1.0e37f)) != 0ull;
+        const bool bad = __builtin_amdgcn_ballot_w64(low || !(mag <= 1.0e37f)) != 0ull;
         if (bad && lane == 0) *wg_redo = 1;
     }
     if ((TRY && !again) || GR > 1) __syncthreads();     // (which also ends every wavefront's reads of the tiles)

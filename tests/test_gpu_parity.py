@@ -1847,3 +1847,43 @@ def test_attention_key_tiles_at_minus_infinity(B, block, Bn, Tq, Tk, heads, kern
     assert np.isfinite(y).all()
     for s in sorted({0, Bn - 1}):
         assert rel_err(got_of(y, s), want(s)) <= BF16_TOL
+
+
+# ... and what lies behind such a tile far below 0, but above everything before it: it has all the weight.  (A range of prescaled keys that begins with
+# -inf starts from the reference 0, to which these scores, 2^-200 and less, are nothing.)
+@pytest.mark.parametrize("Bn,T,Tc,heads,cut,queries,groups", [
+    (2, 200, 64 * 8 + 23, 2, False, 128, 2), (2, 200, 64 * 26 + 23, 2, True, 128, 2), (4, 1200, 64 * 24 + 9, 10, False, 256, 2),
+])
+def test_attn_block_low_scores_behind_a_tile_at_minus_infinity(B, Bn, T, Tc, heads, cut, queries, groups):
+    import torch
+    C = heads * 64
+    r = rng(T + Tc + heads)
+    nt = (Tc + 63) // 64
+    lo, hi = ((nt + 1) // 2, nt) if cut else (0, nt)
+    begin = hi - (hi - lo + 1) // 2                      # first tile of the last group's keys (an odd tile count: the shared one)
+    tile = np.arange(Tc) // 64
+    out = tile == begin
+    q = r.standard_normal((Bn, T, heads, 64), dtype=np.float32)
+    q[..., 0] = 4.0 + np.abs(q[..., 0])                  # (2.4 to 5 after LayerNorm)
+    q = q.reshape(Bn, T, C)
+    k = r.standard_normal((Bn, Tc, heads, 64), dtype=np.float32)
+    k[..., 0] = np.where(tile > begin, -8.0, -10.0)[None, :, None]
+    k[:, out, :, 0] = -2.0 ** 127                        # times 64: -inf
+    k = G.bf16_round(k).reshape(Bn, Tc, C)
+    eye, pk, pv, po = (mkproj(r, C, C, 0, bias=i == 3) for i in range(4))
+    eye["W"] = np.eye(C, dtype=np.float32)
+    pk["W"] = np.diag(np.where(np.arange(C) % 64 == 0, 64.0, 1.0)).astype(np.float32)
+    pv["W"][:, ::64] = 0.0
+    g, b = np.ones(C, np.float32), np.zeros(C, np.float32)
+    # the test is what it says (scores as exponents of 2)
+    q0 = O.layernorm(q, g, b).reshape(Bn, T, heads, 64)[..., 0]
+    assert q0.min() * 8.0 * 8.0 * 1.44 > 150 and q0.min() * 2.0 * 8.0 * 1.44 > 30 and q0.max() * 10.0 * 8.0 * 1.45 < 4000
+    args = (torch.from_numpy(q).cuda(), dev(k, B), dev(g, B), dev(b, B), *[B.Proj.from_numpy(p) for p in (eye, pk, pv, po)], heads)
+    with B.dry_run(detail=3) as names:
+        B.attn_block_fwd(*args)
+    assert "attention prescaled try%s, %d queries, %d groups" % (" cut" if cut else "", queries, groups) in names
+    y = host(B.attn_block_fwd(*args))
+    assert np.isfinite(y).all()
+    for s in (0, Bn - 1):
+        want = O.attn_sublayer(q[s:s + 1], k[s:s + 1][:, ~out], g, b, eye, pk, pv, po, heads) - q[s:s + 1]
+        assert rel_err(y[s:s + 1] - q[s:s + 1], want) <= BF16_TOL
