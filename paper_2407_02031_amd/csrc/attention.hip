@@ -10,10 +10,10 @@
 // the second MFMA, O^T += V^T P^T.  V is consumed transposed ([C, keys]), which is how the
 // v-projection GEMM writes it, so both K and V^T tiles are staged with 16-byte rows.
 //
-// What bounds it: vector-ALU issue, at a clock that the chip lowers under load (1.8 to 1.95 GHz of 2.4).  Per 32 queries x 64 keys a SIMD
-// issues 32 exponentials (8 clocks each), 16 packings (4.5), 36 MFMAs (8.5) and some 20 others (4), with plain keys 32 FMAs: 734 and 862
-// clocks, and 816 were measured with three wavefronts to a SIMD and plain keys; the matrix core needs 576, LDS gives 256 bytes a clock and is asked for
-// a sixth of it.  16x16x32 MFMAs, although two issues for one, because the 32x32x16 ones cost more energy and
+// What limits it: vector-ALU issue, at a clock that the chip lowers under load (1.8 to 1.95 GHz of 2.4).  Per 32 queries x 64 keys a SIMD
+// issues 32 exponentials (8 clocks each, measured alone), 16 packings (4.5), 36 MFMAs (8.5), 16 LDS reads and four others (4), with plain keys 32 FMAs (4): 714
+// and 842 clocks if none of it overlapped.  816 were measured with three wavefronts to a SIMD and plain keys, so little does, and the sum is no
+// lower bound; that is the matrix core's 576.  LDS gives 256 bytes a clock and is asked for a sixth of it.  16x16x32 MFMAs, although two issues for one, because the 32x32x16 ones cost more energy and
 // leave the row sums to instructions that do not run beside MFMAs: 12 x 4096 x 8 heads 426 -> 386 us, in a block of
 // 2 x 4096 tokens of 640 channels 94 -> 86, 8 x 988 x 20 heads 58.6 -> 53.1.
 //
@@ -706,10 +706,12 @@ static int device_cus() {
 
 // number of tiles to cut in half (0: one workgroup per tile)
 // block: inside an attention block, where the halves are merged in the launch.  Up to two tiles per CU and from 24 key tiles on, all
-// are cut there if the most loaded CU then has less to do, and from 48 on also one per CU: more wavefronts cover latencies better.  (us, a
-// whole self-attention block, whole / cut: 1 x 1500 x 640 channels 43.6 / 39.6, 1 x 2048 x 1280 84.5 / 82.3, 1 x 3952 x 320 60.9 / 58.6,
-// 1 x 4096 x 320 63.3 / 57.3, 1 x 3952 x 640 103.4 / 97.2, 2 x 4096 x 320 103.6 / 92.0; with as much on a CU as before 1 x 1500 x 1280
-// 62.4 / 64.2, 1 x 2048 x 640 47.6 / 47.6, 1 x 3840 x 512 68.5 / 65.0, 1 x 4096 x 960 129.1 / 132.5; at 16 key tiles the merge costs what that gives or more: 2 x 988 x 640 38.8 / 39.1,
+// are cut there if the most loaded CU then has less to do, and from 48 on also one per CU.  (us, a whole self-attention block without adapters, whole tiles of
+// whatever kernel attention_plan has for them / cut: 1 x 1500 x 640 channels 39.6 / 36.7, 1 x 2048 x 1280 83.2 / 77.7, 1 x 3952 x 640 102.9 / 89.9, 1 x 4096 x 640
+// 102.1 / 88.8, 2 x 4096 x 320 102.1 / 87.0, 1 x 3000 x 320 46.8 / 39.5, 2 x 2048 x 640 73.6 / 67.7; with as much on a CU as before 1 x 1500 x 1280
+// 59.7 / 62.9, 1 x 2048 x 640 43.9 / 46.1, 1 x 2500 x 640 51.6 / 54.5, 1 x 4096 x 960 132.6 / 132.6, 2 x 3000 x 320 56.7 / 59.3.
+// One per CU: 1 x 3952 x 320 51.4 / 55.0, 1 x 4096 x 320 52.8 / 55.4, 1 x 3840 x 512 61.5 / 64.6.  That line was drawn when a whole tile had one
+// group of wavefronts, 63.3 / 57.3 at 4096 x 320; with two it no longer pays.  At 16 key tiles, before there were two groups: 2 x 988 x 640 38.8 / 39.1,
 // 1 x 1024 x 1280 44.0 / 45.6.)
 static int attention_nsplit(int Bn, int Tq, int Tk, int heads, bool block) {
     const long tiles = (long)((Tq + 127) / 128) * heads * Bn;
@@ -731,7 +733,8 @@ size_t attention_scratch_bytes(int Bn, int Tq, int Tk, int heads, bool block) {
 // memory is laid out for).
 //   Up to one tile of 128 queries per CU the workgroup's key range goes to two groups of wavefronts, from eight key tiles on (us,
 // standalone, one group / two: 1 x 1024 x 20 heads 17.5 / 15.4, 1 x 4096 x 5 50.5 / 41.0, 1 x 512 x 5 10.2 / 9.6, 2 x 256 x 10 8.4 / 8.5); cut tiles
-// too, where their halves are one per CU.
+// too, where their halves are one per CU.  Each group takes half of the tiles, rounded up, so few and odd ones gain least: 2 x 10 heads, both with the
+// attempt without maxima, 576 keys 10.1 / 10.9, 640 10.8 / 10.6, 704 11.5 / 11.9, 768 12.2 / 11.8, 832 13.3 / 13.7, 896 14.1 / 13.6.
 //   Tiles of 256 queries, 64 to a wavefront, read K and V^T half as often, but few of them load the CUs unevenly, and two wavefronts
 // to a SIMD is all that the registers hold.  With two groups of wavefronts where they are one round (128 / 256 queries: 1 x 4096 x 10 71.3 / 65.9,
 // 2 x 2500 x 10 47.5 / 44.9, 2 x 1500 x 20 31.6 / 31.0, 2 x 1024 x 20 23.9 / 25.6), with one where rounds of them come out ahead (4 x 3000 x 10 105 / 98,
@@ -766,16 +769,19 @@ int launch_attention(const uint16_t* q, int64_t ldq, const uint16_t* k, int64_t 
     if (nsplit > 0 && !(scratch && scratch_bytes >= need && (reinterpret_cast<uintptr_t>(scratch) & 15) == 0)) nsplit = 0;
     const int nt = (Tk + 63) / 64;
     const AttnPlan plan = attention_plan(Bn, Tq, nt, heads, nsplit);
-    // The unmeasured attempt saves a maximum per half tile and costs its check: from 20 tiles of plain keys on, always with prescaled ones.
+    // The unmeasured attempt saves a maximum per half tile and costs its check: from 20 tiles of plain keys on, always with prescaled ones.  (The line is as old
+    // as a second attempt that spilled.  Now, us, measured / tried first: 2 x 4096 on 77 keys x 10 heads 9.66 / 9.79, 1 x 512 x 5 9.20 / 9.35, 4 x 400 x 20 13.2 / 12.7,
+    // 8 x 512 x 10 13.8 / 13.1, 8 x 988 x 20 52.5 / 50.2, 8 x 1100 x 20 66.8 / 62.9, 4 x 1216 x 10 26.6 / 25.1.)
     const bool tries = k_prescaled || nt >= 20;
     SD_REQUIRE(plan.qb == 2 || (nsplit == 0 && tries), SD_EINVAL, "attention: 256 queries, but cut or measured");     // no such kernel, and scratch memory for 128
     if (nsplit > arrived_n) arrived = nullptr;   // not enough counters: the halves are merged by the second kernel
     *cut_tiles = arrived ? 0 : nsplit;
     // Read-ahead in the room that three workgroups to a CU leave: 8 MB and 2 MB per key tile, which the launch is long
     // enough for.  (With 1 MB per key tile the queue falls behind at 32 x 32 tokens: 2540 us per stack for 2500, 2658 without any.)
-    // Workgroups of two groups have a CU each; what reads ahead runs beside them and behind.
+    // Workgroups of two groups have a CU each; what reads ahead runs beside them and behind.  (256 threads to each of the 448; ten blocks, with none of them / 128 / 256 /
+    // 448 / 768 / 1024: 1 x 988 x 1280 + 16 1628 1563 1567 1492 1490 1487, 1 x 620 x 1280 + 64 1748 1699 1725 1598 1599 1598.)
     const int grid = attention_grid(plan.nfull, nsplit);
-    const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, plan.gr == 1 ? 3l * device_cus() - grid : 448, 16) : ReadRanges{};
+    const ReadRanges ra = ahead && k_prescaled ? ahead->take((8ull + 2 * nt) << 20, plan.gr == 1 ? 3l * device_cus() - grid : 7l * device_cus() / 4, 16) : ReadRanges{};
     if (SD_DRY_RUN("attention%s%s%s%s%s; ", k_prescaled ? " prescaled" : "", tries ? " try" : "", nsplit > 0 ? (arrived ? " cut" : " cut merge") : "", dry_ranges(ra), dry_tiles(64 * plan.qb, plan.gr))) return SD_OK;
     auto go = [&](auto kernel, const auto& ranges) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(grid + (ra.wgs + plan.gr - 1) / plan.gr)), dim3(256 * plan.gr), 0, stream, q, ldq, k, ldk, vt, ldvt, out, ldo, Tq, Tk, Tkp, heads,
@@ -805,7 +811,7 @@ int launch_attention_merge(const void* scratch, uint16_t* out, int64_t ldo, int 
     // the halves' maxima are in score units, or already in exponent units when the keys were prescaled
     const float c = k_prescaled ? 1.0f : 0.125f * 1.44269504088896340736f;
     const AttnPlan p = attention_plan(Bn, Tq, 0, heads, cut_tiles);
-        auto go = [&](auto kernel) {
+    auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)cut_tiles), dim3(256 * p.gr), 0, stream, static_cast<const float*>(scratch), out, ldo, Tq, heads, p.qtiles, p.nfull, c);
     };
     if (p.gr == 2) go(attention_merge_kernel<2, 2>);

@@ -12,7 +12,8 @@
 // Tiling: BM x BN output tile per workgroup, BK = 64, WGM x WGN wavefronts, each owning
 // (BM/WGM) x (BN/WGN) as 16x16x32 bf16 MFMA tiles with fp32 accumulators (32x32x16 ones cost more
 // energy, and the chip lowers its clock under them: 8192x4096x4096 223 -> 211 us, 16384x1280x5120 + 64 249 -> 240, 8 x 4096 rows of
-// 640 channels with four adapters 43.4 -> 42.6, 5000x640x2560 + 64 28.4 -> 26.8; same bits; 3000x1280x5120 + 64 54.4 -> 57.3).
+// 640 channels with four adapters 43.4 -> 42.6, 5000x640x2560 + 64 28.4 -> 26.8; same bits.  Some of the launches with one tile per CU are slower, and why is not known:
+// 3000x1280x5120 + 64 55.5 -> 57.7, 6000x640x1280 + 64 21.0 -> 21.6, 4120x640x320 + 64 10.7 -> 10.9).
 // Pipeline: operand tiles go global -> LDS directly (wave-wide 1 KB loads of 16-byte
 // chunks, XOR-swizzled so the 16 rows one MFMA operand read touches fall in distinct
 // banks) into a ring of STAGES tiles, STAGES-1 of them in flight ahead of the one being
@@ -620,7 +621,9 @@ static int launch_cfg(GemmGroup& g, bool guard, hipStream_t stream) {
     g.total_tiles = total;
     if (total == 0) return SD_OK;
     // A few tiles of longer K loops behind the producers' (text keys / values in a q, k, v launch) are dealt round-robin like those: in
-    // one XCD's range they held up its other tiles (7904x1920x640 with 20 text tiles: every XCD was done after 26 us, that one after 34).
+    // one XCD's range they held up its other tiles (7904x1920x640 with 20 text tiles: every XCD was done after 26 us, that one after 34).  How few makes
+    // no difference that could be measured (two blocks, none / up to 6 / 12.5 / 25 / 50 % of the tiles: 2 x 3952 x 640 589 581 582 582 583, 2 x 1024 x 1280 + 64
+    // 519 518 514 512 514, 4 x 1200 x 640 + 32 422 418 418 420 417).
     int front = 0;
     for (int i = 0; i < g.n && (g.p[i].signal || g.p[i].K0 > g.p[g.n - 1].K0); ++i) front = g.p[i].tile_begin + g.p[i].tiles_m * g.p[i].tiles_n;
     if (front - g.n_lead <= total / 8) g.n_lead = front;
@@ -707,7 +710,8 @@ GemmChoice gemm_choice(const GemmGroup& g) {
         if (t128 > 256 && meanK < 1024) return take(GEMM_64x128);
     }
     // One large plain projection with a long K loop (no launch of the transformer block: the
-    // 8192 x 4096 x 4096 yardstick takes 211, 248 at 128x128 before both had 16x16x32 MFMAs).  Not for grouped
+    // 8192 x 4096 x 4096 yardstick takes 220, 245 at 256x128, 260 at 128x128; 8192x8192x2048 + 64 256, 284, 290; but
+    // 16384x1280x5120 + 64, five of these tiles wide, 254, 217, 236).  Not for grouped
     // launches: the q/k/v group with its short text-context problems loses a third.
     if (!res32 && n_main == 1 && t256 >= 512 && meanK >= 2048) return take(GEMM_256x256);
     // 128x128 tiles, two workgroups per CU.  Of eight 32x64 wavefronts where problems of different sizes share the launch (q, k,

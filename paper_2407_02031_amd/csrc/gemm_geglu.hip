@@ -373,13 +373,13 @@ static int launch_geglu_mi(GemmGroup& g, hipStream_t stream) {
 }
 // Which tiles.  Up to four 64x64 tiles per CU, that many workgroups of the general kernel in one round: 64x64 (three
 // ring stages while there are at most two per CU and the K loop is not short), 128x64 from three on.  Beyond that the
-// estimate, us, that fits 600 launches of 154 to 16384 rows and C = 320 to 2048: rounds of workgroups over 256 CUs (128x64:
-// over two per CU), each with a fixed part and one per 64 deep step; the wide tiles' down-projection is a launch of its own
-// where the general kernel hides it.  Measured over those launches: 0.8 % slower than the best of the six in the mean, one in ten by
-// more than 3 %, none by more than 14.  (us with the LayerNorm in front, 64x64 with three stages / 64x64 / 128x64 / 256x128 / wide 256 /
-// wide 128: 2048x1280x320 15.1 13.2 14.3 19.8 21.9 16.1; 988x5120x1280 44.3 45.2 47.5 47.8 46.8 36.6; 7904x2560x640 88.3 85.7 76.4 85.4
-// 69.0 79.4; 7904x4096x2048 327 331 283 257 272 286;
-// all before 16x16x32 MFMAs, which took 6 to 10 % off the wide tiles; the others moved by 5 % at most either way.)
+// estimate, us, fitted to 600 launches of 154 to 16384 rows and C = 320 to 2048 before 16x16x32 MFMAs and 16 columns a workgroup in the
+// down-projection: rounds of workgroups over 256 CUs (128x64: over two per CU), each with a fixed part and one per 64 deep step; the wide tiles' down-projection is a
+// launch of its own where the general kernel hides it.  With the kernels as they are, over 120 launches of 154 to 16384 rows, C = 320 to 1280 and ranks 0 to 128 behind a LayerNorm: 0.4 %
+// slower than the best of the six in the mean, one in thirty by more than 3 %, none by more than 8.  Without a LayerNorm in front (no launch of the transformer block), 50 launches: 4 % in the mean,
+// one in four by more than 3 %, the worst by 35 (1032x2560x640 + 64 23.3, 17.3 with 128x64).  us with the LayerNorm, 64x64 with three stages / 64x64 / 128x64 / 256x128 / wide 256 /
+// wide 128: 2048x1280x320 + 8 21.2 17.1 17.6 21.7 24.5 17.4; 988x5120x1280 39.7 40.0 43.1 42.0 41.1 32.4; 7904x2560x640 80.7 79.2 71.3 79.0 63.4 71.4; 7904x4096x2048 316 315 270
+// 241 252 268; 8192x2560x640 + 64 89.3 88.0 83.0 82.2 73.0 82.3.
 GegluTiles geglu_tiles(int M, int F, int K, int r, bool wide_ok) {
     const int k_steps = K / 64, steps = k_steps + (r + 63) / 64;
     auto tiles = [&](int rows, int cols) { return (long)((M + rows - 1) / rows) * ((F + cols - 1) / cols); };
